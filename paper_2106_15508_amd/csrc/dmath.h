@@ -92,6 +92,33 @@ constexpr double kF0 = 1.0, kF1 = 1.0, kF2 = 1.0 / 2.0, kF3 = 1.0 / 6.0, kF4 = 1
                  kF16 = 1.0 / 20922789888000.0, kF17 = 1.0 / 355687428096000.0,
                  kF18 = 1.0 / 6402373705728000.0;
 
+// ---------------------------------------------------------------- division, square root
+
+// a / b and sqrt(x), correctly rounded, for operands and results that stay
+// well inside the normal range (x > 0): the Newton steps of the general
+// sequences without their scaling, range tests and fix-up (a third of the
+// instructions).  Callers name the range.
+__device__ __forceinline__ double div_n(double a, double b)
+{
+    double y = __builtin_amdgcn_rcp(b);
+    y = __builtin_fma(y, __builtin_fma(-b, y, 1.0), y);
+    y = __builtin_fma(y, __builtin_fma(-b, y, 1.0), y);
+    const double q = a * y;
+    return __builtin_fma(__builtin_fma(-b, q, a), y, q);
+}
+
+__device__ __forceinline__ double sqrt_n(double x)
+{
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y;
+    double h = 0.5 * y;
+    const double r = __builtin_fma(-h, g, 0.5);
+    g = __builtin_fma(g, r, g);
+    h = __builtin_fma(h, r, h);
+    g = __builtin_fma(__builtin_fma(-g, g, x), h, g);
+    return __builtin_fma(__builtin_fma(-g, g, x), h, g);
+}
+
 // ---------------------------------------------------------------- exp family
 
 // e^r for |r| <= ln2/2 + tiny: degree-13 Taylor polynomial.
@@ -114,6 +141,16 @@ __device__ __forceinline__ double exp_poly(double r)
     return p;
 }
 
+// k as an int32, saturating: v_cvt_i32_f64 clamps an input outside the int32
+// range (NaN: 0) by its definition, where a C++ conversion would be
+// undefined.  One instruction, as the plain conversion compiles to.
+__device__ __forceinline__ int cvt_i32_sat(double x)
+{
+    int r;
+    asm("v_cvt_i32_f64 %0, %1" : "=v"(r) : "v"(x));
+    return r;
+}
+
 // exp(x) for x already known to lie in [kExpLo, kExpHi].
 __device__ __forceinline__ double exp_core(double x)
 {
@@ -129,6 +166,47 @@ __device__ __forceinline__ double exp(double x)
     if (x > kExpHi) return __builtin_inf();
     if (x < kExpLo) return 0.0;
     return exp_core(x);
+}
+
+// exp(x) for any x, the range tests by selection (no branch).
+__device__ __forceinline__ double exp_select(double x)
+{
+    const double k = __builtin_rint(x * kLog2e);
+    const double t = x - k * kLn2Hi;
+    const double r = __builtin_fma(-k, kLn2Lo, t);
+    double e = __builtin_ldexp(exp_poly(r), cvt_i32_sat(k));
+    e = x > kExpHi ? __builtin_inf() : e;
+    return x < kExpLo ? 0.0 : e;
+}
+
+// expm1(x) for any x without a branch: the Taylor polynomial of the small
+// arguments and the exponential's polynomial share their coefficients
+// 1/13! .. 1/2!, so one Horner chain runs on x or on the reduced argument
+// (its first step adds 0 or 1/14!), the same operations as the two branches.
+__device__ __forceinline__ double expm1_select(double x)
+{
+    const bool small = __builtin_fabs(x) <= 0.34657359027997264;
+    const double k = __builtin_rint(x * kLog2e);
+    const double t = x - k * kLn2Hi;
+    const double r = __builtin_fma(-k, kLn2Lo, t);
+    const double v = small ? x : r;
+    double p = __builtin_fma(small ? kF14 : 0.0, v, kF13);
+    p = __builtin_fma(p, v, kF12);
+    p = __builtin_fma(p, v, kF11);
+    p = __builtin_fma(p, v, kF10);
+    p = __builtin_fma(p, v, kF9);
+    p = __builtin_fma(p, v, kF8);
+    p = __builtin_fma(p, v, kF7);
+    p = __builtin_fma(p, v, kF6);
+    p = __builtin_fma(p, v, kF5);
+    p = __builtin_fma(p, v, kF4);
+    p = __builtin_fma(p, v, kF3);
+    p = __builtin_fma(p, v, kF2);
+    double e = __builtin_fma(__builtin_fma(p, v, kF1), v, kF0);
+    e = __builtin_ldexp(e, cvt_i32_sat(k));
+    e = x > kExpHi ? __builtin_inf() : e;
+    e = x < kExpLo ? 0.0 : e;
+    return small ? __builtin_fma(x * x, p, x) : e - 1.0;
 }
 
 __device__ __forceinline__ double expm1(double x)
@@ -172,7 +250,8 @@ __device__ __forceinline__ double atanh_tail(double z)
     return z * q;
 }
 
-// log(x) for finite x > 0.
+// log(x) for finite x > 0 (NaN stays NaN); the division's operands lie in
+// [-0.3, 0.42] and [1.7, 2.42], exact zero included.
 __device__ __forceinline__ double log_pos(double x)
 {
     int e;
@@ -182,7 +261,7 @@ __device__ __forceinline__ double log_pos(double x)
         e = e - 1;
     }
     const double a = f - 1.0;
-    const double s = a / (2.0 + a);
+    const double s = div_n(a, 2.0 + a);
     const double R = atanh_tail(s * s);
     const double lf = 2.0 * (s + s * R);
     const double de = (double)e;
@@ -244,22 +323,15 @@ __device__ __forceinline__ void sincos2pi(double t, double& c, double& s)
     pc = __builtin_fma(pc, ny2, kF4);
     pc = __builtin_fma(pc, ny2, kF2);
     pc = __builtin_fma(pc, ny2, kF0);
-    const double cf = fold ? sy : pc;
-    const double sf = fold ? pc : sy;
-    const int iq = (int)q;
-    if (iq == 0) {
-        c = cf;
-        s = sf;
-    } else if (iq == 1) {
-        c = -sf;
-        s = cf;
-    } else if (iq == 2) {
-        c = -cf;
-        s = -sf;
-    } else {
-        c = sf;
-        s = -cf;
-    }
+    // quadrant 0: (cf, sf), 1: (-sf, cf), 2: (-cf, -sf), 3: (sf, -cf) with
+    // (cf, sf) = (pc, sy), exchanged by the fold; by selection, so that the
+    // lanes' quadrants do not split the wave
+    const unsigned iq = (unsigned)(int)q;
+    const bool swap = fold != ((iq & 1u) != 0);
+    const double cc = swap ? sy : pc;
+    const double ss = swap ? pc : sy;
+    c = (iq + 1u) & 2u ? -cc : cc;
+    s = iq & 2u ? -ss : ss;
 }
 
 // Box-Muller pair from one word: u1 = low half, u2 = high half.
@@ -267,7 +339,7 @@ __device__ __forceinline__ void normal_pair(uint64_t w, double& z0, double& z1)
 {
     const double u1 = ((double)(uint32_t)w + 0.5) * 0x1p-32;
     const double u2 = ((double)(uint32_t)(w >> 32) + 0.5) * 0x1p-32;
-    const double rho = __builtin_sqrt(-2.0 * log_pos(u1));
+    const double rho = sqrt_n(-2.0 * log_pos(u1));  // in [2^-32, 45]
     double c, s;
     sincos2pi(u2, c, s);
     z0 = rho * c;
@@ -332,76 +404,135 @@ __device__ __forceinline__ double beta_general(double a, double b, uint64_t seed
 
 constexpr double kTSwitch = 10.0;
 constexpr int kBinvCap = 128;
+constexpr int kBinvStep = 4;  // search steps between two looks at the wave
 
-// 1/j, j = 1..kBinvCap, rounded to nearest at compile time.  The inversion
-// loop's step counter is the same in every lane still searching, so the
-// entry is a wave-uniform (scalar) load.
+// 1/j, j = 1..kBinvCap, rounded to nearest at compile time.  The search's
+// step counter is wave-uniform, so an entry is a scalar load; kBinvStep more
+// entries let the loop request the next group while it works on this one.
 struct RecipTab {
-    double v[kBinvCap + 1];
+    double v[kBinvCap + kBinvStep];
     constexpr RecipTab() : v{}
     {
-        for (int j = 1; j <= kBinvCap; ++j) v[j] = 1.0 / (double)j;
+        for (int j = 0; j < kBinvCap + kBinvStep; ++j) v[j] = 1.0 / (double)(j + 1);
     }
 };
 __device__ constexpr RecipTab kRecip{};
 
-// Bin(n, p) with the inversion uniform from word wu and, in the normal
-// branch, the deviate of the Box-Muller pair of word wz (half 0: cosine,
-// half 1: sine), formed on first use and kept in (have, z0, z1) for the
-// draw that shares the pair; n is an exact integer held in a double.
-__device__ __forceinline__ double binomial_pair(double n, double p, uint64_t wu, uint64_t wz, int half, bool& have,
-                                                double& z0, double& z1)
+// A success probability as the samplers use it: q = min(p, 1 - p) (0 for
+// p <= 0 or p = 1; NaN stays NaN) and whether the draw counts failures.
+struct Prob {
+    double q;
+    bool flip;
+};
+
+__device__ __forceinline__ Prob make_prob(double p)
 {
-    if (n <= 0.0 || p <= 0.0) return 0.0;
-    if (p >= 1.0) return n;
-    const bool flip = p > 0.5;
-    const double q = flip ? 1.0 - p : p;
-    const double m = n * q;
-    double x;
-    if (m < kTSwitch) {
-        const double u = u01(wu);
-        double f = exp(n * log1p(-q));
-        double F = f;
-        const double r = q / (1.0 - q);
-        double k = 0.0;
-        for (int it = 0; it < kBinvCap && u > F && k < n; ++it) {
-            f = f * (((n - k) * r) * kRecip.v[it + 1]);  // (n - k) r / (k + 1), k = it
-            k = k + 1.0;
-            F = F + f;
-        }
-        x = k;
-    } else {
-        if (!have) {
-            normal_pair(wz, z0, z1);
-            have = true;
-        }
-        const double z = half ? z1 : z0;
-        const double sd = __builtin_sqrt(m * (1.0 - q));
-        const double y = (m + 0.5) + sd * z;
-        x = __builtin_floor(y);
-        if (x < 0.0) x = 0.0;
-        if (x > n) x = n;
+    Prob r;
+    r.flip = p > 0.5;
+    r.q = r.flip ? 1.0 - p : p;
+    r.q = p <= 0.0 ? 0.0 : r.q;
+    return r;
+}
+
+// log1p(-q) and q / (1 - q) for 0 < q <= 1/2: what the inversion of Bin(n, q)
+// needs of q.  (Quotients of a subnormal q may round differently from IEEE
+// division; there n log1p(-q) vanishes against 1 and the draw is 0.)
+__device__ __forceinline__ double log1p_neg(double q)
+{
+    if (-q >= kSqrt1_2 - 1.0) {
+        const double s = div_n(-q, 2.0 - q);
+        const double R = atanh_tail(s * s);
+        return 2.0 * (s + s * R);
     }
-    return flip ? n - x : x;
+    const double u = 1.0 - q;
+    return log_pos(u) + div_n(-q - (u - 1.0), u);
+}
+
+__device__ __forceinline__ double odds(double q) { return div_n(q, 1.0 - q); }
+
+// Bin(n, q) by sequential search, 0 < n q < kTSwitch, l1 = log1p(-q),
+// r = q / (1 - q): the number of k with u > F(k), k < min(n, kBinvCap), where
+// f(0) = exp(n l1), f(k + 1) = f(k) ((n - k) r) (1/(k + 1)) and F sums f.  F
+// never falls, so the draw is a count and lanes that are done need no mask:
+// the wave takes kBinvStep steps, then looks whether any lane still searches.
+// (Past k = n the terms are zeros: F stays.)  The factors of f(k + 1) do not
+// depend on f, and the next reciprocals are requested a group ahead: what is
+// left of a step's latency is one product and one sum, where a loop that
+// stopped lane by lane waited for its scalar load in every step.
+__device__ __forceinline__ double binomial_search(double n, double l1, double r, uint64_t wu)
+{
+    const double u = u01(wu);
+    double f = exp_core(n * l1);  // n l1 in [-14, 0]
+    double F = f;
+    double nk = n;
+    unsigned count = 0;
+    double c[kBinvStep];
+#pragma unroll
+    for (int s = 0; s < kBinvStep; ++s) c[s] = kRecip.v[s];
+    for (int it = 0; it < kBinvCap; it += kBinvStep) {
+        double d[kBinvStep];
+#pragma unroll
+        for (int s = 0; s < kBinvStep; ++s) d[s] = kRecip.v[it + kBinvStep + s];
+#pragma unroll
+        for (int s = 0; s < kBinvStep; ++s) {
+            count += u > F ? 1u : 0u;
+            f = f * ((nk * r) * c[s]);
+            F = F + f;
+            nk = nk - 1.0;
+        }
+        if (__ballot(u > F) == 0ull) break;
+#pragma unroll
+        for (int s = 0; s < kBinvStep; ++s) c[s] = d[s];
+    }
+    const double x = (double)count;
+    return x < n ? x : n;
+}
+
+// Bin(n, p) with p as q (Prob) from a uniform word and a standard normal; n
+// is an exact integer >= 0 held in a double.  n q < kTSwitch searches, the
+// rest rounds the normal.  The normal branch is taken by nearly every wave
+// and runs unmasked; inv() supplies (l1, r) where a lane searches.
+template <class Inv>
+__device__ __forceinline__ double binomial_draw(double n, const Prob& p, double z, uint64_t wu, Inv inv)
+{
+    const double m = n * p.q;
+    const bool small = m < kTSwitch;           // false for NaN
+    const double sd = sqrt_n(m * (1.0 - p.q));  // used for m >= kTSwitch: in [2, 2^27]
+    double x = __builtin_floor((m + 0.5) + sd * z);
+    x = x < 0.0 ? 0.0 : x;
+    x = x > n ? n : x;
+    x = small ? 0.0 : x;
+    if (small && m > 0.0) {
+        double l1, r;
+        inv(l1, r);
+        x = binomial_search(n, l1, r, wu);
+    }
+    return p.flip ? n - x : x;
 }
 
 // Bin(n, p) from one word: its uniform and its cosine deviate.
 __device__ __forceinline__ double binomial(double n, double p, uint64_t w)
 {
-    bool have = false;
-    double z0, z1;
-    return binomial_pair(n, p, w, w, 0, have, z0, z1);
+    if (n <= 0.0) return 0.0;
+    const Prob P = make_prob(p);
+    return binomial_draw(n, P, normal_one(w), w, [&](double& l1, double& r) {
+        l1 = log1p_neg(P.q);
+        r = odds(P.q);
+    });
 }
 
 // floor(N(h, sqrt h)) clamped to [0, n] (the paper's own transition sampler).
+__device__ __forceinline__ double normal_floor_z(double n, double h, double z)
+{
+    double x = __builtin_floor(h + __builtin_sqrt(h) * z);
+    x = x < 0.0 ? 0.0 : x;
+    x = x > n ? n : x;
+    return (n <= 0.0 || !(h > 0.0)) ? 0.0 : x;
+}
+
 __device__ __forceinline__ double normal_floor(double n, double h, uint64_t w)
 {
-    if (n <= 0.0 || !(h > 0.0)) return 0.0;
-    const double z = normal_one(w);
-    double x = __builtin_floor(h + __builtin_sqrt(h) * z);
-    if (x < 0.0) x = 0.0;
-    if (x > n) x = n;
-    return x;
+    return normal_floor_z(n, h, normal_one(w));
 }
 
 }  // namespace dm

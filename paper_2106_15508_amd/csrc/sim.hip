@@ -13,7 +13,7 @@ namespace {
 // Proposal kernel of one batch: lane p makes proposal j = base + p and
 // publishes the wave's acceptance ballot for the ordered compaction.
 // ---------------------------------------------------------------------------
-// Waves per SIMD the register allocation aims for.  The kernel needs 156
+// Waves per SIMD the register allocation aims for.  The kernel needs 144
 // VGPRs, so three waves per SIMD are resident whether two or three are asked
 // for; asking for two gave a slightly different instruction schedule that ran
 // 1.8% faster, and asking for four (128 VGPRs) was 6% slower.

@@ -45,17 +45,6 @@ __device__ __forceinline__ Col load_col(const_col_ptr cols, int k)
     return c;
 }
 
-// k = rint(t) as an int32, saturating: v_cvt_i32_f64 clamps an input outside
-// the int32 range to INT32_MIN / INT32_MAX by its definition, where a C++
-// conversion of such a value would be undefined.  One instruction, as the
-// plain conversion compiles to.
-__device__ __forceinline__ int cvt_i32_sat(double x)
-{
-    int r;
-    asm("v_cvt_i32_f64 %0, %1" : "=v"(r) : "v"(x));
-    return r;
-}
-
 // exp of the term (without q): with f = t - k in [-1/2, 1/2] and L = ln2/1024,
 // e^(f L) = 1 + f (L + f (L^2/2 + f L^3/6)); ex[0..2] = L, L^2/2, L^3/6
 // (kernel arguments: SGPRs).
@@ -71,7 +60,7 @@ __device__ __forceinline__ double term_exp(const double* uj, double cj, const Co
     const double t = D * cj;
     const double kk = __builtin_rint(t);
     const double f = t - kk;
-    const int ik = cvt_i32_sat(kk);
+    const int ik = dm::cvt_i32_sat(kk);
     double p = __builtin_fma(f, ex[2], ex[1]);
     p = __builtin_fma(p, f, ex[0]);
     p = __builtin_fma(p, f, 1.0);

@@ -1,0 +1,59 @@
+"""GPU parity at the sizes and values where a kernel changes its path: ends of
+a search, of a tile, of a dispatch range.  Against the oracle, bit for bit
+unless a test states its tolerance."""
+import itertools
+
+import numpy as np
+import pytest
+
+from paper_2106_15508_amd import abcsmc as A
+from paper_2106_15508_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def test_binomial_search_edges(oracle):
+    """The sequential search's ends: n inside and past the four-step groups,
+    the 128-step cap, uniforms at both ends, n p on both sides of the switch at
+    10, p where log1p changes form, p of 0, 1, 1/2 and next to them."""
+    ns = [0, 1, 2, 3, 4, 5, 7, 8, 9, 12, 16, 33, 34, 127, 128, 129, 1000, 10**9, 2**52]
+    words = [0, 1 << 12, 2**63, 2**64 - 1, 2**64 - (1 << 12), 0xFFFFFFFF00000000, 0x123456789ABCDEF0]
+    recs = []
+    for n, w in itertools.product(ns, words):
+        ps = [0.0, 1e-310, 1e-17, 1.0 / (n + 1), 0.29289321881345237, 0.2928932188134524, 0.2928932188134525, 0.3,
+              0.5, np.nextafter(0.5, 1), 0.75, np.nextafter(1, 0), 1.0, -0.25, -1e300]
+        if n:
+            ps += [10.0 / n, np.nextafter(10.0 / n, 0), np.nextafter(10.0 / n, 1), 9.0 / n, 1.0 - 9.0 / n]
+        recs += [(n, p, w) for p in ps if p <= 1.0]
+    n = np.array([r[0] for r in recs], dtype=np.int64)
+    p = np.array([r[1] for r in recs])
+    w = np.array([r[2] for r in recs], dtype=np.uint64)
+    rec = np.stack([n.view(np.uint64), p.view(np.uint64), w], 1)
+    out = np.zeros(n.size, np.int64)
+    got = A.debug_eval(10, np.ascontiguousarray(rec), n.size, out)
+    want = oracle.binomial(n, p, w)
+    bad = np.flatnonzero(got != want)
+    assert bad.size == 0, (n[bad[:5]], p[bad[:5]], w[bad[:5]], got[bad[:5]], want[bad[:5]])
+
+
+#: rates the prior box may hold but never meets in earnest: negative, huge,
+#: probabilities that round to 1, powers that over- and underflow
+EXTREME = [(0.0, 1.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0), (1.0, 100.0, 700.0, 1.0, 50.0, 50.0, 0.5, 2.0),
+           (1e300, 1.0, -800.0, 1e-300, 1e-310, 0.3, 0.2, 5.0), (0.3, 2.0, 1e306, 800.0, 1e-9, 1e-9, 1.0, 1e9),
+           (-5.0, 1.0, 0.5, -0.3, -2.0, -900.0, 0.5, 1.0), (0.5, 1e308, 0.1, 0.05, 0.1, 0.7, -3.0, 0.5),
+           (0.2, 3.0, 0.4, 40.0, 0.7, 0.6931471805599453, 0.01, -1.0), (2.0, 1.0, 0.0, 0.35, 0.34657359027997264, 0.3, 1.0, 1.0)]
+
+
+@pytest.mark.parametrize("sampler", [W.SAMPLER_BINOMIAL, W.SAMPLER_NORMAL_FLOOR])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 64, 65, 300])
+def test_trajectories_extreme_rates(oracle, sampler, n):
+    w = W.tiny(sampler=sampler)
+    theta = np.array([EXTREME[k % len(EXTREME)] for k in range(n)])
+    got = A.simulate(w, theta, seed=3, rnd=2, index0=11)
+    for k in range(min(n, 24)):
+        want = oracle.simulate(w, theta[k], 3, 2, 11 + k)
+        # an infinite hazard's floor-normal draw is NaN (inf - inf): from that
+        # day on the counts have no integer value to compare
+        days = int(np.argmax(np.append((want < 0).any(1), True)))
+        assert days >= 1
+        assert np.array_equal(got[k][:days], want[:days]), k
