@@ -12,7 +12,8 @@
 
 namespace abcsmc {
 
-constexpr int kChunkP = kBlock;  // proposals per work item of the persistent kernel
+constexpr int kChunkP = kBlock;          // proposals per work item of the persistent kernel, one lane each
+constexpr int kChunkQuad = kBlock / 4;   // and with four lanes per proposal
 constexpr int kMaxWChunks = 32;  // column chunks per run in the weight kernel
 
 // Read-only description of one run.
@@ -20,7 +21,7 @@ struct BRun {
     Model m;
     const double* obs;
     int32_t N;
-    int32_t cap_chunks;        // staging capacity in work items
+    int32_t cap_chunks;        // staging capacity in work items of BatchArgs::chunk proposals
     int32_t step_schedule;
     int32_t beta_b_fixed;
     int32_t step_is_variance;
@@ -89,7 +90,8 @@ struct BatchArgs {
     const int4* w_tab;         // weight grid: (run, row block, chunk, -)
     const int2* fin_tab;       // weight finalize grid: (run, row block)
     int32_t n_runs;
-    int32_t max_cap_chunks;
+    int32_t chunk;             // proposals per work item: kChunkP or kChunkQuad
+    int32_t max_cap_blocks;    // largest staging capacity of a run in blocks of kBlock proposals
     int32_t n_res_blocks, n_w_blocks, n_fin_blocks;
     int32_t propose_blocks;
     double ex[7];              // table-exp constants (as WeightArgs::ex)

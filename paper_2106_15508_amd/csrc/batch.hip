@@ -87,8 +87,8 @@ __global__ __launch_bounds__(kBlock) void begin_kernel(BatchArgs a)
         S.invalid = S.attempts = S.days = S.survivors = S.fallback = S.terms = S.window_terms = 0;
         const double rate = S.rate > 0.01 ? S.rate : 0.01;
         unsigned long long lim = stage == 0
-                                     ? (unsigned long long)((R.N + kChunkP - 1) / kChunkP)
-                                     : (unsigned long long)__builtin_ceil((double)R.N / (rate * kChunkP) * a.g->margin);
+                                     ? (unsigned long long)((R.N + a.chunk - 1) / a.chunk)
+                                     : (unsigned long long)__builtin_ceil((double)R.N / (rate * a.chunk) * a.g->margin);
         if (lim < 1) lim = 1;
         S.limit = lim;
     }
@@ -280,7 +280,7 @@ __device__ int pick(const BatchArgs& a, int start, bool exact, int* chunk)
             } else {
                 const unsigned long long inflight = issued - ld_relaxed(&S.completed);
                 const double rate = S.rate > 0.01 ? S.rate : 0.01;
-                const double need = __builtin_ceil((double)(Rr.N - done) / (rate * kChunkP)) * a.g->margin;
+                const double need = __builtin_ceil((double)(Rr.N - done) / (rate * a.chunk)) * a.g->margin;
                 const unsigned long long bound = need > 1.0 ? (unsigned long long)need : 1ull;
                 if (inflight >= bound) continue;
             }
@@ -294,7 +294,8 @@ __device__ int pick(const BatchArgs& a, int start, bool exact, int* chunk)
     return -1;
 }
 
-template <bool kRound0>
+// kQuad: four lanes per proposal, kChunkQuad proposals per work item.
+template <bool kRound0, bool kQuad>
 __global__ __launch_bounds__(kBlock) void propose_persistent_kernel(BatchArgs a)
 {
     __shared__ int s_run, s_chunk;
@@ -315,7 +316,9 @@ __global__ __launch_bounds__(kBlock) void propose_persistent_kernel(BatchArgs a)
         ++iter;
         const BRun& R = a.runs[r];
         const BState& S = a.st[r];
-        const uint32_t p = (uint32_t)k * kChunkP + threadIdx.x;  // proposal index within the stage
+        // proposal index within the stage
+        const uint32_t p = kQuad ? (uint32_t)k * kChunkQuad + threadIdx.x / 4 : (uint32_t)k * kChunkP + threadIdx.x;
+        const bool lead = !kQuad || (threadIdx.x & 3u) == 0;
         const int cur = S.cur;
         const lane::ProposalIn in{R.obs,
                                   (uint32_t)stage,
@@ -331,22 +334,26 @@ __global__ __launch_bounds__(kBlock) void propose_persistent_kernel(BatchArgs a)
                                   -1.0,
                                   0.0};
         lane::ProposalOut o;
-        if (R.m.sampler == 0) lane::propose_one<kRound0, 0>(R.m, in, p, o);
-        else lane::propose_one<kRound0, 1>(R.m, in, p, o);
-        double* su = R.st_u + (size_t)p * kNP;
+        if (R.m.sampler == 0) lane::propose_one<kRound0, 0, kQuad>(R.m, in, p, o);
+        else lane::propose_one<kRound0, 1, kQuad>(R.m, in, p, o);
+        if (lead) {
+            double* su = R.st_u + (size_t)p * kNP;
 #pragma unroll
-        for (int q = 0; q < kNP; ++q) su[q] = o.u[q];
-        R.st_d[p] = o.d;
-        R.st_sigma[p] = o.sigma;
-        R.st_parent[p] = o.parent;
-        R.st_att[p] = o.att;
-        const unsigned long long mask = __ballot(o.acc);
-        const unsigned long long inv = lane::wave_sum_u64(o.valid ? 0ull : 1ull);
-        const unsigned long long natt = lane::wave_sum_u64((unsigned long long)(o.att < 0 ? -o.att : o.att));
-        const unsigned long long ndays = lane::wave_sum_u64((unsigned long long)o.days);
+            for (int q = 0; q < kNP; ++q) su[q] = o.u[q];
+            R.st_d[p] = o.d;
+            R.st_sigma[p] = o.sigma;
+            R.st_parent[p] = o.parent;
+            R.st_att[p] = o.att;
+        }
+        unsigned long long mask = __ballot(o.acc && lead);
+        if (kQuad) mask = lane::quad_ballot(mask);
+        const unsigned long long inv = lane::wave_sum_u64(lead && !o.valid ? 1ull : 0ull);
+        const unsigned long long natt = lane::wave_sum_u64(lead ? (unsigned long long)(o.att < 0 ? -o.att : o.att) : 0ull);
+        const unsigned long long ndays = lane::wave_sum_u64(lead ? (unsigned long long)o.days : 0ull);
         const int w = threadIdx.x / kWave;
         if ((threadIdx.x & (kWave - 1)) == 0) {
-            R.wave_mask[p / kWave] = mask;
+            if (kQuad) reinterpret_cast<unsigned short*>(R.wave_mask)[p / 16] = (unsigned short)mask;
+            else R.wave_mask[p / kWave] = mask;
             s_cnt[w][0] = (unsigned long long)__popcll(mask);
             s_cnt[w][1] = inv;
             s_cnt[w][2] = natt;
@@ -380,7 +387,7 @@ __global__ __launch_bounds__(kBlock) void bcompact_scan_kernel(BatchArgs a)
     BState& S = a.st[r];
     if (S.failed) return;
     const unsigned long long issued = S.issued < (unsigned long long)R.cap_chunks ? S.issued : (unsigned long long)R.cap_chunks;
-    const int nW = (int)issued * (kChunkP / kWave);
+    const int nW = (int)issued * (a.chunk / kWave);
     const int per = (nW + kBlock - 1) / kBlock;
     const int w0 = threadIdx.x * per, w1 = min(nW, w0 + per);
     unsigned long long s = 0;
@@ -404,8 +411,8 @@ __global__ __launch_bounds__(kBlock) void bcompact_scatter_kernel(BatchArgs a)
     BState& S = a.st[r];
     if (S.failed) return;
     const unsigned long long issued = S.issued < (unsigned long long)R.cap_chunks ? S.issued : (unsigned long long)R.cap_chunks;
-    if ((unsigned long long)k >= issued) return;
-    const uint32_t p = (uint32_t)k * kChunkP + threadIdx.x;
+    const uint32_t p = (uint32_t)k * kBlock + threadIdx.x;
+    if ((unsigned long long)p >= issued * (unsigned)a.chunk) return;
     const unsigned long long mask = R.wave_mask[p / kWave];
     const uint32_t lane = p % kWave;
     if (!((mask >> lane) & 1ull)) return;
@@ -695,12 +702,18 @@ void batch_launch_stage(const BatchArgs& a, bool stage0, hipStream_t s)
         hipLaunchKernelGGL(res_stats_kernel, dim3(a.n_res_blocks), b, 0, s, a);
         hipLaunchKernelGGL(res_count_kernel, dim3(a.n_res_blocks), b, 0, s, a);
         hipLaunchKernelGGL(res_write_kernel, dim3(a.n_res_blocks), b, 0, s, a);
-        hipLaunchKernelGGL(propose_persistent_kernel<false>, dim3(a.propose_blocks), b, 0, s, a);
+        if (a.chunk == kChunkQuad)
+            hipLaunchKernelGGL((propose_persistent_kernel<false, true>), dim3(a.propose_blocks), b, 0, s, a);
+        else
+            hipLaunchKernelGGL((propose_persistent_kernel<false, false>), dim3(a.propose_blocks), b, 0, s, a);
     } else {
-        hipLaunchKernelGGL(propose_persistent_kernel<true>, dim3(a.propose_blocks), b, 0, s, a);
+        if (a.chunk == kChunkQuad)
+            hipLaunchKernelGGL((propose_persistent_kernel<true, true>), dim3(a.propose_blocks), b, 0, s, a);
+        else
+            hipLaunchKernelGGL((propose_persistent_kernel<true, false>), dim3(a.propose_blocks), b, 0, s, a);
     }
     hipLaunchKernelGGL(bcompact_scan_kernel, dim3(a.n_runs), b, 0, s, a);
-    hipLaunchKernelGGL(bcompact_scatter_kernel, dim3(a.max_cap_chunks, a.n_runs), b, 0, s, a);
+    hipLaunchKernelGGL(bcompact_scatter_kernel, dim3(a.max_cap_blocks, a.n_runs), b, 0, s, a);
     if (!stage0) {
         hipLaunchKernelGGL(bwdim_kernel, dim3(a.n_runs), b, 0, s, a);
         hipLaunchKernelGGL(bkeys_kernel, dim3(a.n_key_blocks), b, 0, s, a);

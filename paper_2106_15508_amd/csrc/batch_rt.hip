@@ -33,7 +33,8 @@ int bfail(std::string* e, int code, const std::string& m)
     return code;
 }
 
-int run_cap_chunks(const abcsmc_config& c)
+// staging capacity of a run in blocks of kChunkP proposals
+int run_cap_blocks(const abcsmc_config& c)
 {
     int64_t cap = c.max_proposals > 0 ? c.max_proposals : std::max<int64_t>(4 * c.n_particles, 16384);
     if (cap > ((int64_t)1 << 24)) cap = (int64_t)1 << 24;
@@ -57,7 +58,7 @@ RunLayout run_layout(const abcsmc_config& c, size_t o)
 {
     RunLayout L{};
     const size_t N = (size_t)c.n_particles, T = (size_t)c.n_days;
-    const size_t B = (size_t)run_cap_chunks(c) * kChunkP;
+    const size_t B = (size_t)run_cap_blocks(c) * kChunkP;
     const size_t nres = (N + 1023) / 1024;
     auto take = [&](size_t bytes) {
         const size_t at = o;
@@ -162,7 +163,7 @@ struct abcsmc_batch {
     size_t ws_bytes = 0;
     bool own_ws = false;
     size_t off_runs = 0, off_st = 0, off_g = 0, off_order = 0, off_res = 0, off_w = 0, off_fin = 0;
-    int n_res = 0, max_w_blocks = 0, n_fin = 0, max_cap_chunks = 0;
+    int n_res = 0, max_w_blocks = 0, n_fin = 0, max_cap_blocks = 0;
     abcsmc_schedule sched{};
     BatchArgs args{};
     hipGraphExec_t exec[2] = {nullptr, nullptr};  // stage 0, later stages
@@ -402,6 +403,19 @@ int abcsmc_batch_init(const abcsmc_config* cfgs, int32_t n_runs, const int64_t* 
         return bail(ABCSMC_EDEVICE, "hipEventCreate failed");
     // per-run regions and descriptors
     size_t o = 0, n_total = 0;
+    // Few particles in all: four lanes per proposal (propose.h).  A stage is one
+    // launch, so the whole batch's proposals (0.8 accepted at first) count
+    // against the chip, and the runs' uneven horizons leave most of it to the
+    // longest: the quads win up to twice the single launch's limit (12-48 runs,
+    // 6 stages: sum of N 21000, 43000, 66000, 82000: 5.8, 7.7, 9.8, 10.1 ms
+    // against 7.4, 8.9, 10.8, 10.7; 115000: 12.7 against 12.1).
+    int64_t expected = 0;
+    int sampler = 0;
+    for (int r = 0; r < n_runs; ++r) {
+        expected += cfgs[r].n_particles * 5 / 4;
+        sampler = std::max(sampler, cfgs[r].sampler);
+    }
+    const int chunk = propose_by_quads(expected / 2, sampler) ? kChunkQuad : kChunkP;
     std::vector<int2> res_tab, fin_tab;
     b->runs.resize(n_runs);
     for (int r = 0; r < n_runs; ++r) {
@@ -426,7 +440,7 @@ int abcsmc_batch_init(const abcsmc_config* cfgs, int32_t n_runs, const int64_t* 
         char* w = b->ws;
         R.obs = (const double*)(w + L.obs);
         R.N = (int32_t)c.n_particles;
-        R.cap_chunks = run_cap_chunks(c);
+        R.cap_chunks = run_cap_blocks(c) * (kChunkP / chunk);
         R.step_schedule = c.step_schedule;
         R.beta_b_fixed = c.beta_b;
         R.beta_a_fixed = c.beta_a;
@@ -466,7 +480,7 @@ int abcsmc_batch_init(const abcsmc_config* cfgs, int32_t n_runs, const int64_t* 
         const int rb = (int)((c.n_particles + kWeightRows - 1) / kWeightRows);
         for (int y = 0; y < rb; ++y) fin_tab.push_back(make_int2(r, y));
         b->max_w_blocks += rb * wchunks_max(c.n_particles);
-        b->max_cap_chunks = std::max(b->max_cap_chunks, R.cap_chunks);
+        b->max_cap_blocks = std::max(b->max_cap_blocks, run_cap_blocks(c));
         std::vector<double> od(obs[r], obs[r] + (size_t)(c.n_days + 1) * 3);
         b->obs.emplace_back(obs[r], obs[r] + (size_t)(c.n_days + 1) * 3);
         if (hipMemcpy(w + L.obs, od.data(), od.size() * 8, hipMemcpyHostToDevice) != hipSuccess)
@@ -503,7 +517,8 @@ int abcsmc_batch_init(const abcsmc_config* cfgs, int32_t n_runs, const int64_t* 
     A.w_tab = (const int4*)(b->ws + b->off_w);
     A.fin_tab = (const int2*)(b->ws + b->off_fin);
     A.n_runs = n_runs;
-    A.max_cap_chunks = b->max_cap_chunks;
+    A.chunk = chunk;
+    A.max_cap_blocks = b->max_cap_blocks;
     A.n_res_blocks = b->n_res;
     A.n_fin_blocks = b->n_fin;
     A.colkeys = (unsigned long long*)(b->ws + WL.colkeys);
@@ -591,7 +606,7 @@ int abcsmc_batch_round(abcsmc_batch* b, abcsmc_round_info* infos)
             I.ess = S.ess;
             I.proposals = (int64_t)S.proposals;
             const unsigned long long cap = (unsigned long long)b->runs[r].cap_chunks;
-            I.simulated = (int64_t)std::min<unsigned long long>(S.issued, cap) * kChunkP;
+            I.simulated = (int64_t)std::min<unsigned long long>(S.issued, cap) * b->args.chunk;
             I.invalid = (int64_t)S.invalid;
             I.attempts = (int64_t)S.attempts;
             I.survivors = (int64_t)S.survivors;

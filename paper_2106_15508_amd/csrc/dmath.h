@@ -334,16 +334,22 @@ __device__ __forceinline__ void sincos2pi(double t, double& c, double& s)
     s = iq & 2u ? -ss : ss;
 }
 
-// Box-Muller pair from one word: u1 = low half, u2 = high half.
-__device__ __forceinline__ void normal_pair(uint64_t w, double& z0, double& z1)
+// Box-Muller pair from one word: u1 = low half, u2 = high half; lu = log u1.
+__device__ __forceinline__ double u1_of(uint64_t w) { return ((double)(uint32_t)w + 0.5) * 0x1p-32; }
+
+__device__ __forceinline__ void normal_from_log(double lu, uint64_t w, double& z0, double& z1)
 {
-    const double u1 = ((double)(uint32_t)w + 0.5) * 0x1p-32;
     const double u2 = ((double)(uint32_t)(w >> 32) + 0.5) * 0x1p-32;
-    const double rho = sqrt_n(-2.0 * log_pos(u1));  // in [2^-32, 45]
+    const double rho = sqrt_n(-2.0 * lu);  // of [2^-32, 45]
     double c, s;
     sincos2pi(u2, c, s);
     z0 = rho * c;
     z1 = rho * s;
+}
+
+__device__ __forceinline__ void normal_pair(uint64_t w, double& z0, double& z1)
+{
+    normal_from_log(log_pos(u1_of(w)), w, z0, z1);
 }
 
 // Cosine half of the pair only (the floor-normal and gamma samplers).

@@ -206,6 +206,8 @@ void launch_propose(const ProposeArgs& a, bool round0, hipStream_t s);
 // occupancy in workgroups per compute unit x the compute units), so a first
 // batch never leaves lanes of a second round to run on a mostly idle chip.
 int64_t propose_first_batch_lanes();
+// Whether n trajectories of one launch are made by four lanes each.
+bool propose_by_quads(int64_t n, int sampler);
 void launch_compact(const CompactArgs& a, hipStream_t s);
 void launch_resample(const ResampleArgs& a, hipStream_t s);
 // The weight pass in three parts, so that the caller can time the sum kernel

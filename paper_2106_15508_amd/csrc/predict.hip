@@ -12,17 +12,23 @@ namespace {
 
 // Lane per particle j: theta = lo + u width, trajectory of the stream
 // (seed, j, round) written as series[(3 t + c) N + j].
-template <int kSampler>
+// (kQuad: a quad per particle).
+template <int kSampler, bool kQuad>
 __global__ __launch_bounds__(kBlock) void predict_series_kernel(PredictArgs a)
 {
-    const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t j = kQuad ? t / 4 : t;
     if (j >= a.n) return;
     double th[kNP];
 #pragma unroll
     for (int q = 0; q < kNP; ++q) th[q] = a.m.lo[q] + a.u[j * kNP + q] * a.m.width[q];
     int32_t days = 0;
-    lane::simulate_distance<kSampler, true>(a.m, th, nullptr, a.round, (uint32_t)j, __builtin_inf(), nullptr, days,
-                                            nullptr, a.series + j, a.n);
+    if (kQuad)
+        lane::simulate_distance_quad<kSampler, true>(a.m, th, nullptr, a.round, (uint32_t)j, __builtin_inf(), nullptr,
+                                                     days, nullptr, a.series + j, a.n);
+    else
+        lane::simulate_distance<kSampler, true>(a.m, th, nullptr, a.round, (uint32_t)j, __builtin_inf(), nullptr, days,
+                                                nullptr, a.series + j, a.n);
 }
 
 // One block per (day, series) row: its n_quant quantiles.
@@ -41,11 +47,15 @@ __global__ __launch_bounds__(kBlock) void predict_band_kernel(PredictArgs a)
 
 void launch_predict(const PredictArgs& a, hipStream_t s)
 {
-    const dim3 grid((unsigned)((a.n + kBlock - 1) / kBlock));
-    if (a.m.sampler == 0)
-        hipLaunchKernelGGL((predict_series_kernel<0>), grid, dim3(kBlock), 0, s, a);
-    else
-        hipLaunchKernelGGL((predict_series_kernel<1>), grid, dim3(kBlock), 0, s, a);
+    const bool quad = propose_by_quads(a.n, a.m.sampler);
+    const dim3 grid((unsigned)(((quad ? 4 * a.n : a.n) + kBlock - 1) / kBlock));
+    if (a.m.sampler == 0) {
+        if (quad) hipLaunchKernelGGL((predict_series_kernel<0, true>), grid, dim3(kBlock), 0, s, a);
+        else hipLaunchKernelGGL((predict_series_kernel<0, false>), grid, dim3(kBlock), 0, s, a);
+    } else {
+        if (quad) hipLaunchKernelGGL((predict_series_kernel<1, true>), grid, dim3(kBlock), 0, s, a);
+        else hipLaunchKernelGGL((predict_series_kernel<1, false>), grid, dim3(kBlock), 0, s, a);
+    }
     hipLaunchKernelGGL(predict_band_kernel, dim3((unsigned)(3 * (a.m.T + 1))), dim3(kBlock), 0, s, a);
 }
 

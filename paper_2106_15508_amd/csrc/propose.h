@@ -160,6 +160,192 @@ __device__ __forceinline__ double simulate_distance(const Model& m, const double
     return __builtin_sqrt(acc);
 }
 
+// ---------------------------------------------------------------------------
+// Four lanes per trajectory.  A small batch leaves most of the chip idle and
+// takes as long as one wave's instruction stream, so its parallelism is spent
+// inside the trajectory: lane q of a quad makes Philox block q of the day,
+// lanes 1-3 one Box-Muller pair each while lane 0 takes log C, lanes 0-2 draw
+// S->I, I->A and A->R at once, then lanes 3 and 0 draw A->D and I->Ru.  The
+// state is kept by all four lanes; values change hands by quad permutes.
+// Every value is the one-lane form's, bit for bit.
+// ---------------------------------------------------------------------------
+template <int kCtrl>
+__device__ __forceinline__ uint32_t quad_perm(uint32_t v)
+{
+    return (uint32_t)__builtin_amdgcn_mov_dpp((int)v, kCtrl, 0xF, 0xF, true);
+}
+template <int kCtrl>
+__device__ __forceinline__ uint64_t quad_perm(uint64_t v)
+{
+    return ((uint64_t)quad_perm<kCtrl>((uint32_t)(v >> 32)) << 32) | quad_perm<kCtrl>((uint32_t)v);
+}
+template <int kCtrl>
+__device__ __forceinline__ double quad_perm(double v)
+{
+    return __longlong_as_double((long long)quad_perm<kCtrl>((uint64_t)__double_as_longlong(v)));
+}
+// the value lane k of the quad holds, in all four lanes
+template <int k, class T>
+__device__ __forceinline__ T quad_lane(T v)
+{
+    return quad_perm<k * 0x55>(v);
+}
+
+// every fourth bit of a wave's ballot, closed up to the wave's 16 quads
+__device__ __forceinline__ unsigned long long quad_ballot(unsigned long long m)
+{
+    m &= 0x1111111111111111ull;
+    m = (m | (m >> 3)) & 0x0303030303030303ull;
+    m = (m | (m >> 6)) & 0x000F000F000F000Full;
+    m = (m | (m >> 12)) & 0x000000FF000000FFull;
+    return (m | (m >> 24)) & 0xFFFFull;
+}
+
+template <int kSampler, bool kTraj, bool kSplit = false>
+__device__ __forceinline__ double simulate_distance_quad(const Model& m, const double* th,
+                                                         const double* __restrict__ obs, uint32_t round,
+                                                         uint32_t index, double exit_thr, int64_t* traj,
+                                                         int32_t& days, double* split = nullptr,
+                                                         double* series = nullptr, int64_t sstride = 0)
+{
+    const uint32_t q = threadIdx.x & 3u;
+    const double alpha0 = th[0], alpha_c = th[1], n_exp = th[2], beta = th[3];
+    const double gamma = th[4], delta = th[5], eta = th[6], kappa = th[7];
+    double A = m.A0, R = m.R0, D = m.D0;
+    double I = __builtin_floor(kappa * A);
+    const double room = m.P - (A + R + D);
+    if (I > room) I = room;
+    if (I < 0.0) I = 0.0;
+    double S = m.P - (A + R + D + I);
+    double Ru = 0.0;
+    // the lane's fixed transition probability: I->Ru, I->A, A->R, A->D
+    dm::Prob own{};
+    double l1 = 0.0, od = 0.0;
+    if (kSampler == 0) {
+        own = dm::make_prob(-dm::expm1_select(q == 0 ? -(beta * eta) : q == 1 ? -gamma : q == 2 ? -beta : -delta));
+        l1 = dm::log1p_neg(own.q);
+        od = dm::odds(own.q);
+    }
+    auto record = [&](int32_t t) {
+        if (!kTraj || q != 0) return;
+        if (series) {
+            double* col = series + (size_t)(3 * t) * sstride;
+            col[0] = A;
+            col[sstride] = R;
+            col[2 * sstride] = D;
+        } else {
+            int64_t* row = traj + (size_t)t * 6;
+            row[0] = (int64_t)S; row[1] = (int64_t)I; row[2] = (int64_t)A;
+            row[3] = (int64_t)R; row[4] = (int64_t)D; row[5] = (int64_t)Ru;
+        }
+    };
+    record(0);
+    double acc = 0.0;
+    for (int32_t t = 0; t < m.T; ++t) {
+        const dm::w2 b = dm::block_words(m.seed, index, round, dm::kSim, (uint32_t)t, q);
+        const double C = A + R + D;
+        // the lane's Box-Muller word and, in lane 0 (binomial: words 5, 6, 7 in lanes
+        // 2, 3, 1) or 1 (floor-normal: words 0-3 in lanes 0-3), the logarithm of C
+        // (permutes stand outside every selection: all four lanes take part)
+        uint64_t wn;
+        if (kSampler == 0) {
+            const uint64_t w7 = quad_lane<3>(b.b);
+            wn = q == 1 ? w7 : q == 2 ? b.b : b.a;
+        } else {
+            const uint64_t w1 = quad_lane<0>(b.b), w2 = quad_lane<1>(b.a), w3 = quad_lane<1>(b.b);
+            wn = q == 0 ? b.a : q == 1 ? w1 : q == 2 ? w2 : w3;
+        }
+        double u1 = dm::u1_of(wn);
+        if (kSampler == 0) u1 = q == 0 ? C : u1;
+        const double lg = dm::log_pos(u1);
+        double zc, zs, logC;
+        dm::normal_from_log(lg, wn, zc, zs);
+        double z4 = 0.0;
+        if (kSampler == 0) {
+            logC = quad_lane<0>(lg);
+        } else {
+            const uint64_t w4 = quad_lane<2>(b.a);
+            const double l4 = dm::log_pos(q == 1 ? C : dm::u1_of(w4));
+            double unused;
+            dm::normal_from_log(quad_lane<0>(l4), w4, z4, unused);
+            logC = quad_lane<1>(l4);
+        }
+        double pw = dm::exp_select(n_exp * logC);
+        pw = C == 0.0 ? (n_exp == 0.0 ? 1.0 : 0.0) : pw;
+        const double g = alpha0 + alpha_c / (1.0 + pw);
+        const double rate = (g * I) * m.invP;
+        double n1, n2, n3, n4, n5;
+        if (kSampler == 0) {
+            const dm::Prob pSI = dm::make_prob(-dm::expm1_select(-rate));
+            // S->I, I->A, A->R in lanes 0, 1, 2 (lane 3: a draw from nothing)
+            const dm::Prob pa{q == 0 ? pSI.q : own.q, q == 0 ? pSI.flip : own.flip};
+            const double na = q == 0 ? S : q == 1 ? I : q == 2 ? A : 0.0;
+            const double zs2 = quad_lane<2>(zs), zc23 = quad_perm<0x32>(zc);  // lane 0 <- 2, lane 2 <- 3
+            const uint64_t ub = quad_lane<0>(b.b), ua = quad_lane<1>(b.a);
+            const double x = dm::binomial_draw(na, pa, q == 1 ? zs2 : zc23, q == 0 ? b.a : q == 1 ? ub : ua,
+                                               [&](double& a, double& r) {
+                                                   a = l1;
+                                                   r = od;
+                                                   if (q == 0) {
+                                                       a = dm::log1p_neg(pSI.q);
+                                                       r = dm::odds(pSI.q);
+                                                   }
+                                               });
+            n1 = quad_lane<0>(x);
+            n2 = quad_lane<1>(x);
+            n3 = quad_lane<2>(x);
+            // A->D in lane 3, I->Ru in lane 0
+            const double nb = q == 3 ? A - n3 : q == 0 ? I - n2 : 0.0;
+            const double zc1 = quad_lane<1>(zc);
+            const uint64_t u3 = quad_lane<1>(b.b), u4 = quad_lane<2>(b.a);
+            const double y = dm::binomial_draw(nb, own, q == 0 ? zc1 : zs, q == 0 ? u4 : u3,
+                                               [&](double& a, double& r) {
+                                                   a = l1;
+                                                   r = od;
+                                               });
+            n4 = quad_lane<3>(y);
+            n5 = quad_lane<0>(y);
+        } else {
+            const double x = dm::normal_floor_z(q == 0 ? S : q == 1 ? I : A, q == 0 ? rate * S : q == 1 ? gamma * I : beta * A,
+                                                zc);
+            n1 = quad_lane<0>(x);
+            n2 = quad_lane<1>(x);
+            n3 = quad_lane<2>(x);
+            const double y = dm::normal_floor_z(q == 3 ? A - n3 : I - n2, q == 3 ? delta * A : (beta * eta) * I,
+                                                q == 3 ? zc : z4);
+            n4 = quad_lane<3>(y);
+            n5 = quad_lane<0>(y);
+        }
+        S = S - n1;
+        I = I + n1 - n2 - n5;
+        A = A + n2 - n3 - n4;
+        R = R + n3;
+        D = D + n4;
+        Ru = Ru + n5;
+        record(t + 1);
+        if (kSplit || !kTraj) {
+            const double* o = obs + (size_t)(t + 1) * 3;
+            const double dA = A - o[0];
+            const double dR = R - o[1];
+            const double dD = D - o[2];
+            if (kSplit) {
+                split[0] = split[0] + dA * dA;
+                split[1] = split[1] + dR * dR;
+                split[2] = split[2] + dD * dD;
+            }
+            acc = acc + dA * dA;
+            acc = acc + dR * dR;
+            acc = acc + dD * dD;
+            if (!kSplit && acc > exit_thr) {
+                days = t + 1;
+                return __builtin_inf();
+            }
+        }
+    }
+    days = m.T;
+    return __builtin_sqrt(acc);
+}
+
 // First k with cdf[k] > r (cdf non-decreasing, cdf[n-1] > r).
 __device__ __forceinline__ int32_t upper_bound_u64(const uint64_t* __restrict__ cdf, int32_t n, uint64_t r)
 {
@@ -215,6 +401,56 @@ struct ProposalOut {
 // the Box-Muller pairs of words 1..4; u = u_k + sigma z (eq. 17); stop at the
 // first u inside [0,1]^8.  Then simulate, distance, accept iff d <= eps.
 // ---------------------------------------------------------------------------
+// Attempt att (1, 2, ...) of proposal j in stage >= 1: true when u lies in the cube.
+__device__ __forceinline__ bool attempt(const Model& m, const ProposalIn& a, uint32_t j, int32_t att, uint64_t Q,
+                                        double* u, double& sigma, int32_t& parent)
+{
+    const uint32_t sub = (uint32_t)(att - 1);
+    const dm::w2 b0 = dm::block_words(m.seed, j, a.round, dm::kPerturb, sub, 0);
+    const dm::w2 b1 = dm::block_words(m.seed, j, a.round, dm::kPerturb, sub, 1);
+    const dm::w2 b2 = dm::block_words(m.seed, j, a.round, dm::kPerturb, sub, 2);
+    const uint64_t r = __umul64hi(b0.a, Q);
+    const int32_t k = upper_bound_u64(a.cdf, a.n_prev, r);
+    // Beta(a, b), b integer: exp( sum_m log U_m / (a + m) )
+    double L = 0.0;
+    uint64_t hold = 0;
+    const int32_t nb = (a.s_fixed >= 0.0 || a.beta_b_real > 0.0) ? 0 : a.beta_b;
+    for (int32_t mm = 0; mm < nb; ++mm) {
+        uint64_t w;
+        if (mm == 0) {
+            w = b2.b;
+        } else if (mm & 1) {
+            const dm::w2 nb = dm::block_words(m.seed, j, a.round, dm::kPerturb, sub, 2u + (uint32_t)((mm + 1) >> 1));
+            w = nb.a;
+            hold = nb.b;
+        } else {
+            w = hold;
+        }
+        L = L + dm::log_pos(dm::u01(w)) / (a.beta_a + (double)mm);
+    }
+    const double s = a.s_fixed >= 0.0       ? a.s_fixed
+                     : a.beta_b_real > 0.0 ? dm::beta_general(a.beta_a, a.beta_b_real, m.seed, j, a.round, sub)
+                                           : dm::exp(L);
+    double sg = a.step_is_variance ? __builtin_sqrt(s) : s;
+    if (sg < 1e-8) sg = 1e-8;
+    double z[kNP];
+    dm::normal_pair(b0.b, z[0], z[1]);
+    dm::normal_pair(b1.a, z[2], z[3]);
+    dm::normal_pair(b1.b, z[4], z[5]);
+    dm::normal_pair(b2.a, z[6], z[7]);
+    const double* up = a.u_prev + (size_t)k * kNP;
+    bool inside = true;
+#pragma unroll
+    for (int d = 0; d < kNP; ++d) {
+        const double v = up[d] + sg * z[d];
+        u[d] = v;
+        inside = inside && (v >= 0.0 && v <= 1.0);
+    }
+    sigma = sg;
+    parent = k;
+    return inside;
+}
+
 // Stage-0 prior draw (kRound0) or the perturbation attempts of stage >= 1:
 // fills o.u, o.sigma, o.parent, o.att and o.valid.
 template <bool kRound0>
@@ -237,52 +473,7 @@ __device__ __forceinline__ void perturb_one(const Model& m, const ProposalIn& a,
             const uint64_t Q = a.cdf[a.n_prev - 1];
             valid = false;
             for (att = 1; att <= a.max_attempts; ++att) {
-                const uint32_t sub = (uint32_t)(att - 1);
-                const dm::w2 b0 = dm::block_words(m.seed, j, a.round, dm::kPerturb, sub, 0);
-                const dm::w2 b1 = dm::block_words(m.seed, j, a.round, dm::kPerturb, sub, 1);
-                const dm::w2 b2 = dm::block_words(m.seed, j, a.round, dm::kPerturb, sub, 2);
-                const uint64_t r = __umul64hi(b0.a, Q);
-                const int32_t k = upper_bound_u64(a.cdf, a.n_prev, r);
-                // Beta(a, b), b integer: exp( sum_m log U_m / (a + m) )
-                double L = 0.0;
-                uint64_t hold = 0;
-                const int32_t nb = (a.s_fixed >= 0.0 || a.beta_b_real > 0.0) ? 0 : a.beta_b;
-                for (int32_t mm = 0; mm < nb; ++mm) {
-                    uint64_t w;
-                    if (mm == 0) {
-                        w = b2.b;
-                    } else if (mm & 1) {
-                        const dm::w2 nb = dm::block_words(m.seed, j, a.round, dm::kPerturb, sub,
-                                                          2u + (uint32_t)((mm + 1) >> 1));
-                        w = nb.a;
-                        hold = nb.b;
-                    } else {
-                        w = hold;
-                    }
-                    L = L + dm::log_pos(dm::u01(w)) / (a.beta_a + (double)mm);
-                }
-                const double s = a.s_fixed >= 0.0       ? a.s_fixed
-                                 : a.beta_b_real > 0.0 ? dm::beta_general(a.beta_a, a.beta_b_real, m.seed, j,
-                                                                          a.round, sub)
-                                                       : dm::exp(L);
-                double sg = a.step_is_variance ? __builtin_sqrt(s) : s;
-                if (sg < 1e-8) sg = 1e-8;
-                double z[kNP];
-                dm::normal_pair(b0.b, z[0], z[1]);
-                dm::normal_pair(b1.a, z[2], z[3]);
-                dm::normal_pair(b1.b, z[4], z[5]);
-                dm::normal_pair(b2.a, z[6], z[7]);
-                const double* up = a.u_prev + (size_t)k * kNP;
-                bool inside = true;
-#pragma unroll
-                for (int d = 0; d < kNP; ++d) {
-                    const double v = up[d] + sg * z[d];
-                    u[d] = v;
-                    inside = inside && (v >= 0.0 && v <= 1.0);
-                }
-                sigma = sg;
-                parent = k;
-                if (inside) {
+                if (attempt(m, a, j, att, Q, u, sigma, parent)) {
                     valid = true;
                     break;
                 }
@@ -296,10 +487,51 @@ __device__ __forceinline__ void perturb_one(const Model& m, const ProposalIn& a,
     o.valid = valid;
 }
 
-template <bool kRound0, int kSampler>
+// perturb_one by a quad: its lanes try four attempts at a time and the first
+// one inside the cube is kept (none: the last of max_attempts, as one lane
+// after another would leave it).
+template <bool kRound0>
+__device__ __forceinline__ void perturb_quad(const Model& m, const ProposalIn& a, uint32_t j, ProposalOut& o)
+{
+    if (kRound0) {
+        perturb_one<true>(m, a, j, o);
+        return;
+    }
+    const uint32_t q = threadIdx.x & 3u, quad0 = threadIdx.x & (kWave - 4);
+    const uint64_t Q = a.cdf[a.n_prev - 1];
+    o.valid = false;
+    int32_t base = 0;
+    for (;; base += 4) {
+        const int32_t att = base + 1 + (int32_t)q;
+        const bool in = att <= a.max_attempts && attempt(m, a, j, att, Q, o.u, o.sigma, o.parent);
+        const uint32_t hit = (uint32_t)(__ballot(in) >> quad0) & 15u;
+        uint32_t src;
+        if (hit) {
+            src = (uint32_t)__builtin_ctz(hit);
+            o.valid = true;
+            o.att = base + 1 + (int32_t)src;
+        } else if (base + 4 >= a.max_attempts) {
+            src = (uint32_t)(a.max_attempts - 1 - base);
+            o.att = -a.max_attempts;
+        } else {
+            continue;
+        }
+        const int from = (int)(quad0 + src);
+#pragma unroll
+        for (int d = 0; d < kNP; ++d) o.u[d] = __shfl(o.u[d], from, kWave);
+        o.sigma = __shfl(o.sigma, from, kWave);
+        o.parent = __shfl(o.parent, from, kWave);
+        return;
+    }
+}
+
+// kQuad: the four lanes of a quad make the proposal together (and all hold
+// the result).
+template <bool kRound0, int kSampler, bool kQuad = false>
 __device__ __forceinline__ void propose_one(const Model& m, const ProposalIn& a, uint32_t j, ProposalOut& o)
 {
-    perturb_one<kRound0>(m, a, j, o);
+    if (kQuad) perturb_quad<kRound0>(m, a, j, o);
+    else perturb_one<kRound0>(m, a, j, o);
     double d = __builtin_inf();
     bool acc = false;
     int32_t days = 0;
@@ -307,7 +539,8 @@ __device__ __forceinline__ void propose_one(const Model& m, const ProposalIn& a,
         double th[kNP];
 #pragma unroll
         for (int q = 0; q < kNP; ++q) th[q] = m.lo[q] + o.u[q] * m.width[q];
-        d = simulate_distance<kSampler, false>(m, th, a.obs, a.round, j, a.exit_thr, nullptr, days);
+        d = kQuad ? simulate_distance_quad<kSampler, false>(m, th, a.obs, a.round, j, a.exit_thr, nullptr, days)
+                  : simulate_distance<kSampler, false>(m, th, a.obs, a.round, j, a.exit_thr, nullptr, days);
         acc = d <= a.eps;
     }
     o.d = d;

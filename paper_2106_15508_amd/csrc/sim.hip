@@ -57,6 +57,45 @@ void propose_kernel(ProposeArgs a)
     }
 }
 
+// The same with four lanes per proposal (64 proposals per workgroup).
+template <bool kRound0, int kSampler>
+__global__ __launch_bounds__(kBlock) void propose_quad_kernel(ProposeArgs a)
+{
+    const uint32_t p = blockIdx.x * (kBlock / 4) + threadIdx.x / 4;
+    const bool active = p < a.count, lead = (threadIdx.x & 3u) == 0;
+    const uint32_t j = a.base + p;
+    const lane::ProposalIn in{a.obs,    a.round,  a.max_attempts, a.eps,   a.exit_thr,          a.u_prev,
+                              a.cdf,    a.n_prev, a.beta_a,       a.beta_b, a.step_is_variance, a.s_fixed, a.beta_b_real};
+    lane::ProposalOut o;
+    o.valid = false;
+    o.acc = false;
+    o.days = 0;
+    o.att = 0;
+    if (active) {
+        lane::propose_one<kRound0, kSampler, true>(a.m, in, j, o);
+        if (lead) {
+            double* su = a.st_u + (size_t)p * kNP;
+#pragma unroll
+            for (int q = 0; q < kNP; ++q) su[q] = o.u[q];
+            a.st_d[p] = o.d;
+            a.st_sigma[p] = o.sigma;
+            a.st_parent[p] = o.parent;
+            a.st_att[p] = o.att;
+        }
+    }
+    const unsigned long long mask = lane::quad_ballot(__ballot(o.acc && lead));
+    const bool count = active && lead;
+    const unsigned long long inv = lane::wave_sum_u64((count && !o.valid) ? 1ull : 0ull);
+    const unsigned long long natt = lane::wave_sum_u64(count ? (unsigned long long)(o.att < 0 ? -o.att : o.att) : 0ull);
+    const unsigned long long ndays = lane::wave_sum_u64(count ? (unsigned long long)o.days : 0ull);
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        reinterpret_cast<unsigned short*>(a.wave_mask)[p / 16] = (unsigned short)mask;
+        if (inv) atomicAdd(&a.ctr->invalid, inv);
+        if (natt) atomicAdd(&a.ctr->attempts, natt);
+        if (ndays) atomicAdd(&a.ctr->days, ndays);
+    }
+}
+
 // Exclusive prefix of the per-wave acceptance counts (one workgroup) and the
 // batch's starting rank.
 constexpr int kScanThreads = 1024;
@@ -115,10 +154,11 @@ __global__ __launch_bounds__(kBlock) void compact_scatter_kernel(CompactArgs a)
     if (gr == (unsigned long long)(a.N - 1)) a.ctr->proposals = (unsigned long long)a.base + p + 1ull;
 }
 
-template <int kSampler>
+template <int kSampler, bool kQuad>
 __global__ __launch_bounds__(kBlock) void simulate_traj_kernel(TrajArgs a)
 {
-    const int64_t k = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t t = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+    const int64_t k = kQuad ? t / 4 : t;
     if (k >= a.n) return;
     double th[kNP];
 #pragma unroll
@@ -126,8 +166,11 @@ __global__ __launch_bounds__(kBlock) void simulate_traj_kernel(TrajArgs a)
     int64_t* traj = a.traj + (size_t)k * (size_t)(a.m.T + 1) * 6;
     // a bare trajectory: no observations, no distance
     int32_t days = 0;
-    lane::simulate_distance<kSampler, true>(a.m, th, nullptr, a.round, a.index0 + (uint32_t)k,
-                                      __builtin_inf(), traj, days);
+    const uint32_t index = a.index0 + (uint32_t)k;
+    if (kQuad)
+        lane::simulate_distance_quad<kSampler, true>(a.m, th, nullptr, a.round, index, __builtin_inf(), traj, days);
+    else
+        lane::simulate_distance<kSampler, true>(a.m, th, nullptr, a.round, index, __builtin_inf(), traj, days);
 }
 
 __global__ __launch_bounds__(kBlock) void debug_eval_kernel(int32_t fn, int64_t n, const void* in,
@@ -195,9 +238,37 @@ int64_t propose_first_batch_lanes()
     return (int64_t)cus * blocks * kBlock;
 }
 
+// Four lanes a trajectory cut its time from 455 to 220 us (120 days) as long
+// as the quads' waves have a SIMD each, to 315-325 us at two waves a SIMD and
+// to 430 us at three, while one lane a trajectory takes 455 us up to 65536 of
+// them; at four (550 us) the quads' extra instructions show.  The floor-normal
+// day has no searches to share out: 145, 220-250 and 325-335 us at one, two
+// and three waves against 245-310 us.
+bool propose_by_quads(int64_t n, int sampler)
+{
+    int dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    const int64_t per_wave_round = (int64_t)cus * 4 * (kWave / 4);  // trajectories at one quad wave per SIMD
+    return n <= per_wave_round * (sampler == 0 ? 3 : 2);
+}
+
 void launch_propose(const ProposeArgs& a, bool round0, hipStream_t s)
 {
     const dim3 g(grid_for(a.count)), b(kBlock);
+    if (propose_by_quads(a.count, a.m.sampler)) {
+        const dim3 gq(grid_for((int64_t)a.count * 4));
+        if (round0) {
+            if (a.m.sampler == 0) hipLaunchKernelGGL((propose_quad_kernel<true, 0>), gq, b, 0, s, a);
+            else hipLaunchKernelGGL((propose_quad_kernel<true, 1>), gq, b, 0, s, a);
+        } else {
+            if (a.m.sampler == 0) hipLaunchKernelGGL((propose_quad_kernel<false, 0>), gq, b, 0, s, a);
+            else hipLaunchKernelGGL((propose_quad_kernel<false, 1>), gq, b, 0, s, a);
+        }
+        return;
+    }
     if (round0) {
         if (a.m.sampler == 0) hipLaunchKernelGGL((propose_kernel<true, 0>), g, b, 0, s, a);
         else hipLaunchKernelGGL((propose_kernel<true, 1>), g, b, 0, s, a);
@@ -215,10 +286,15 @@ void launch_compact(const CompactArgs& a, hipStream_t s)
 
 void launch_simulate_traj(const TrajArgs& a, hipStream_t s)
 {
-    if (a.m.sampler == 0)
-        hipLaunchKernelGGL((simulate_traj_kernel<0>), dim3(grid_for(a.n)), dim3(kBlock), 0, s, a);
-    else
-        hipLaunchKernelGGL((simulate_traj_kernel<1>), dim3(grid_for(a.n)), dim3(kBlock), 0, s, a);
+    const bool quad = propose_by_quads(a.n, a.m.sampler);
+    const dim3 g(grid_for(quad ? 4 * a.n : a.n)), b(kBlock);
+    if (a.m.sampler == 0) {
+        if (quad) hipLaunchKernelGGL((simulate_traj_kernel<0, true>), g, b, 0, s, a);
+        else hipLaunchKernelGGL((simulate_traj_kernel<0, false>), g, b, 0, s, a);
+    } else {
+        if (quad) hipLaunchKernelGGL((simulate_traj_kernel<1, true>), g, b, 0, s, a);
+        else hipLaunchKernelGGL((simulate_traj_kernel<1, false>), g, b, 0, s, a);
+    }
 }
 
 void launch_debug_eval(int32_t fn, int64_t n, const void* in, void* out, double pa, int32_t pb,

@@ -57,3 +57,38 @@ def test_trajectories_extreme_rates(oracle, sampler, n):
         days = int(np.argmax(np.append((want < 0).any(1), True)))
         assert days >= 1
         assert np.array_equal(got[k][:days], want[:days]), k
+
+
+@pytest.mark.parametrize("sampler", [W.SAMPLER_BINOMIAL, W.SAMPLER_NORMAL_FLOOR])
+def test_quad_and_lane_trajectories_agree(sampler):
+    """One large call (a lane per trajectory) equals its parts made in small
+    calls (four lanes per trajectory), every trajectory, ragged sizes."""
+    w = W.C1.with_(sampler=sampler, n_days=20)
+    n = 60_001
+    theta = np.asarray(w.lo) + np.random.default_rng(21).uniform(size=(n, 8)) * (np.asarray(w.hi) - np.asarray(w.lo))
+    whole = A.simulate(w, theta, seed=8, rnd=4, index0=3)
+    for a, b in ((0, 1), (1, 18), (18, 7000), (7000, 19_999), (19_999, 40_000), (40_000, n)):
+        assert np.array_equal(A.simulate(w, theta[a:b], seed=8, rnd=4, index0=3 + a), whole[a:b]), (a, b)
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(max_attempts=3), dict(step_schedule=W.STEP_MEANVAR, step_is_variance=True),
+                                dict(step_schedule=W.STEP_FIXED, beta_a=1.5, beta_b=6, sampler=W.SAMPLER_NORMAL_FLOOR,
+                                     max_attempts=5)])
+def test_quad_and_lane_runs_agree(kw):
+    """A stage made in one large batch (a lane per proposal) and in small ones
+    (four lanes per proposal) keeps the same particles, void proposals
+    included: the attempts run four at a time in the small ones."""
+    w = W.tiny(n_particles=53_000, n_days=12, surv_ratio=0.4, **kw)
+    obs = A.observations(w)
+    got = []
+    for batch in (200_000, 8000):
+        with A.Context(w, obs, batch=batch) as ctx:
+            infos = ctx.run(3)
+            got.append((infos, ctx.population(), ctx.weights()))
+    (ia, pa, wa), (ib, pb, wb) = got
+    for a, b in zip(ia, ib):
+        assert a["eps_next"] == b["eps_next"] and a["proposals"] == b["proposals"]
+    assert all(np.array_equal(pa[k], pb[k]) for k in pa)
+    assert all(np.array_equal(x, y) for x, y in zip(wa, wb))
+    if "max_attempts" in kw:
+        assert ia[1]["invalid"] > 0
