@@ -42,6 +42,7 @@ struct BRun {
     uint64_t* cdf;
     double* cols;
     double* wpart;             // wchunks x N
+    uint2* wcounts;            // wchunks x groups of 64 rows (WeightArgs::counts)
     double* st_u;
     double* st_d;
     double* st_sigma;
@@ -54,7 +55,8 @@ struct BRun {
     int32_t res_blk0;          // first block of this run in the segmented resample grid
     int32_t res_nblk;
     int32_t off;               // first slot of this run in the batch-wide sort arrays (sum of earlier N)
-    int32_t rb0;               // first 128-row block of this run in the finalize / window tables
+    WeightCols sc;             // this run's part of the sorted columns and rows
+    WeightRows sr;
 };
 
 // Mutable state of one run (device).
@@ -69,8 +71,7 @@ struct BState {
     int32_t failed;    // 1 once a stage ran out of proposals (run frozen)
     int32_t cur;       // population buffer of the last completed stage
     int32_t nxt;       // buffer the current stage writes
-    int32_t dstar;     // sort coordinate of the weight window (largest column variance)
-    int32_t pad_;
+    WeightGeom geom;   // sort code of the weight pass
     unsigned long long issued, completed, done_acc, accepted, proposals, invalid, attempts, days,
         survivors, fallback, limit, stages_done, terms, window_terms;
 };
@@ -98,10 +99,7 @@ struct BatchArgs {
     // weight window (batch-wide arrays; run r owns slots [off_r, off_r + N_r))
     unsigned long long* colkeys;  // npad: (run, column key, column) sorted
     unsigned long long* rowkeys;  // npad: (run, sigma half-octave, row key, row) sorted
-    double* scols;             // n_total x 9 sorted columns (u_k, q_k)
-    double* skey;              // n_total sorted sort-coordinate values
-    double* rwin;              // n_total per-row window half-widths (slot off_r + j)
-    int2* win;                 // per 128-row block: column window [x, y) within the run
+    double* rwin;              // n_total per-row window radii (slot off_r + j)
     const double* wtab;        // kWeightTab entries 2^(i/1024) of the table exponential
     size_t npad;               // power-of-two sort length >= n_total
     int32_t n_total;           // sum of N_r

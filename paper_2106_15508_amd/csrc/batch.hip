@@ -434,47 +434,49 @@ __global__ __launch_bounds__(kBlock) void bcompact_scatter_kernel(BatchArgs a)
 
 // ------------------------------------------------------------------ weights
 
-// Weight window, per run (as the single-run pass): the sort coordinate d* of
-// largest column variance; columns sorted by (run, u_{k,d*}); rows sorted by
-// (run, sigma half-octave descending, u_{j,d*}); each row's half-width comes from its parent's
-// term (wterm::window_halfwidth) and each 128-row block gets the union of its
-// rows' column ranges.  One batch-wide bitonic
-// sort per key set: the run index in the top 12 bits keeps every run's keys in
-// its own slot range [off_r, off_r + N_r).
-using wterm::coord_key32;
-using wterm::lower_index;
+// Weight pass, per run as the single-run one (smc.hip, wterm.h): column
+// statistics choose the run's sort code; columns sorted by (run, code), rows by
+// (run, sigma half-octave descending, code); gathered with what the pair test
+// needs; every wave evaluates the columns one of its rows needs.  One
+// batch-wide bitonic sort per key set: the run index in the top 12 bits keeps
+// every run's keys in its own slot range [off_r, off_r + N_r).
 using wterm::sigma_half_octave;
-using wterm::wave_max;
-using wterm::wave_min;
-using wterm::wave_sum_u64;
 
-// One block per run: variance of each coordinate over the run's columns.
-__global__ __launch_bounds__(kBlock) void bwdim_kernel(BatchArgs a)
+constexpr int kDimThreads = 1024;
+
+// One block per run: sum, sum of squares, minimum and maximum of each
+// coordinate over the run's columns (thread t: coordinate t % 8).
+__global__ __launch_bounds__(kDimThreads) void bwgeom_kernel(BatchArgs a)
 {
-    __shared__ double sh[kBlock];
+    __shared__ double sh[4][kDimThreads];
     const BRun& R = a.runs[blockIdx.x];
     BState& S = a.st[blockIdx.x];
     if (S.failed) return;
-    const int M = (int)S.survivors;
-    double best = -1.0;
-    int bd = 0;
-    for (int d = 0; d < kNP; ++d) {
-        double s1 = 0.0, s2 = 0.0;
-        for (int k = threadIdx.x; k < M; k += kBlock) {
-            const double v = R.cols[(size_t)k * 9 + d];
-            s1 += v;
-            s2 += v * v;
-        }
-        s1 = bsum(s1, sh);
-        s2 = bsum(s2, sh);
-        const double mean = s1 / (double)M;
-        const double var = s2 / (double)M - mean * mean;
-        if (var > best) {
-            best = var;
-            bd = d;
-        }
+    const int M = (int)S.survivors, t = threadIdx.x, d = t & 7;
+    double s1 = 0.0, s2 = 0.0, mn = __builtin_inf(), mx = -__builtin_inf();
+#pragma unroll 4
+    for (int k = t / 8; k < M; k += kDimThreads / 8) {
+        const double v = R.cols[(size_t)k * 9 + d];
+        s1 += v;
+        s2 += v * v;
+        mn = v < mn ? v : mn;
+        mx = v > mx ? v : mx;
     }
-    if (threadIdx.x == 0) S.dstar = bd;
+    sh[0][t] = s1;
+    sh[1][t] = s2;
+    sh[2][t] = mn;
+    sh[3][t] = mx;
+    __syncthreads();
+    for (int off = kDimThreads / 2; off >= 8; off >>= 1) {
+        if (t < off) {
+            sh[0][t] += sh[0][t + off];
+            sh[1][t] += sh[1][t + off];
+            sh[2][t] = sh[2][t] < sh[2][t + off] ? sh[2][t] : sh[2][t + off];
+            sh[3][t] = sh[3][t] > sh[3][t + off] ? sh[3][t] : sh[3][t + off];
+        }
+        __syncthreads();
+    }
+    if (t == 0) wterm::make_geom(sh[0], sh[1], sh[2], sh[3], (double)M, S.geom);
 }
 
 // run owning batch-wide slot i (i < n_total)
@@ -489,13 +491,16 @@ __device__ __forceinline__ int slot_run(const BatchArgs& a, int i)
     return lo;
 }
 
+// grid.y 0: columns, 1: rows.
 __global__ __launch_bounds__(kBlock) void bkeys_kernel(BatchArgs a)
 {
+    __shared__ uint32_t cells[kNP * kBlock];
     const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= a.npad) return;
+    if (i >= a.npad) return;  // each thread uses its own LDS column only
+    const bool row = blockIdx.y != 0;
+    unsigned long long* keys = row ? a.rowkeys : a.colkeys;
     if (i >= (size_t)a.n_total) {
-        a.colkeys[i] = ~0ull;
-        a.rowkeys[i] = ~0ull;
+        keys[i] = ~0ull;
         return;
     }
     const int r = slot_run(a, (int)i);
@@ -503,128 +508,82 @@ __global__ __launch_bounds__(kBlock) void bkeys_kernel(BatchArgs a)
     const BState& S = a.st[r];
     const unsigned long long k = (unsigned long long)((int)i - R.off);
     const unsigned long long run = (unsigned long long)r << 52;
-    if (S.failed) {
-        a.colkeys[i] = run | (0xFFFFFFFFull << 20) | k;
-        a.rowkeys[i] = run | k;
+    if (S.failed || (!row && k >= (unsigned long long)S.survivors)) {
+        keys[i] = run | (0xFFFFFFFFull << 20) | k;
         return;
     }
-    const int ds = S.dstar;
-    a.colkeys[i] = (k < (unsigned long long)S.survivors)
-                       ? run | (coord_key32(R.cols[k * 9 + ds]) << 20) | k
-                       : run | (0xFFFFFFFFull << 20) | k;
+    const WeightGeom& g = S.geom;
     const int nx = S.nxt;
-    // half-octaves in descending order: the widest windows are dispatched first
-    const unsigned long long oct = 127ull - sigma_half_octave(R.sigma[nx][k]);
-    a.rowkeys[i] = run | (oct << 45) | ((coord_key32(R.u[nx][k * kNP + ds]) >> 7) << 20) | k;
-    const double* uj = R.u[nx] + k * kNP;
-    const int32_t par = R.parent[nx][k];
-    const bool ok = par >= 0 && par < R.N;
-    a.rwin[i] = wterm::window_halfwidth(uj, R.sigma[nx][k], ok ? R.u[1 - nx] + (size_t)par * kNP : uj,
-                                        ok ? (double)R.q[par] : 0.0, (double)R.cdf[R.N - 1]);
-}
-
-__global__ __launch_bounds__(kBlock) void bcolgather_kernel(BatchArgs a)
-{
-    const int i = blockIdx.x * kBlock + threadIdx.x;
-    if (i >= a.n_total) return;
-    const int r = slot_run(a, i);
-    const BRun& R = a.runs[r];
-    const BState& S = a.st[r];
-    if (S.failed || i - R.off >= (int)S.survivors) return;
-    const size_t src = (size_t)(a.colkeys[i] & 0xFFFFFull);
-    const double* c = R.cols + src * 9;
-    double* o = a.scols + (size_t)i * 9;
+    double u[kNP];
 #pragma unroll
-    for (int d = 0; d < 9; ++d) o[d] = c[d];
-    a.skey[i] = c[S.dstar];
+    for (int d = 0; d < kNP; ++d) {
+        u[d] = row ? R.u[nx][k * kNP + d] : R.cols[k * 9 + d];
+        cells[d * kBlock + threadIdx.x] = wterm::cell20(u[d], g.lo[d], g.inv[d]);
+    }
+    uint32_t key = wterm::morton32(g, cells + threadIdx.x, kBlock);
+    if (row) {
+        const double sj = R.sigma[nx][k];
+        // half-octaves in descending order: the widest windows are dispatched first
+        key = ((127u - (uint32_t)sigma_half_octave(sj)) << 25) | (key >> 7);
+        const int32_t par = R.parent[nx][k];
+        const bool ok = par >= 0 && par < R.N;
+        a.rwin[i] = wterm::window_radius(u, sj, ok ? R.u[1 - nx] + (size_t)par * kNP : u, ok ? (double)R.q[par] : 0.0,
+                                         (double)R.cdf[R.N - 1]);
+    }
+    keys[i] = run | ((unsigned long long)key << 20) | k;
 }
 
-// One block per (run, 256 sorted rows): the block's column window.
-__global__ __launch_bounds__(kWeightRows) void bwindow_kernel(BatchArgs a)
+// grid = finalize table (run, row block): the block's slots of the run's
+// sorted columns and rows.
+__global__ __launch_bounds__(kWeightRows) void bgather_kernel(BatchArgs a)
 {
-    __shared__ double slo[kWeightRows / kWave], shi[kWeightRows / kWave];
     const int2 fb = a.fin_tab[blockIdx.x];
     const BRun& R = a.runs[fb.x];
     const BState& S = a.st[fb.x];
     if (S.failed) return;
-    const int nx = S.nxt;
-    const int rr = fb.y * kWeightRows + threadIdx.x;
-    const int M = (int)S.survivors;
-    const double* sk = a.skey + R.off;
-    double lo = __builtin_inf(), hi = -__builtin_inf();
-    unsigned long long own = 0;  // columns of this row's own window
-    if (rr < R.N) {
-        const size_t j = (size_t)(a.rowkeys[R.off + rr] & 0xFFFFFull);
-        const double W = a.rwin[R.off + j];
-        const double x = R.u[nx][j * kNP + S.dstar];
-        lo = x - W;
-        hi = x + W;
-        own = (unsigned long long)(lower_index(sk, M, hi, true) - lower_index(sk, M, lo, false));
-    }
-    own = wave_sum_u64(own);
-    if ((threadIdx.x & (kWave - 1)) == 0 && own) atomicAdd(&a.st[fb.x].window_terms, own);
-    lo = wave_min(lo);
-    hi = wave_max(hi);
-    if ((threadIdx.x & (kWave - 1)) == 0) {
-        slo[threadIdx.x / kWave] = lo;
-        shi[threadIdx.x / kWave] = hi;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int q = 0; q < kWeightRows / kWave; ++q) {
-            lo = slo[q] < lo ? slo[q] : lo;
-            hi = shi[q] > hi ? shi[q] : hi;
-        }
-        a.win[R.rb0 + fb.y] = make_int2(lower_index(sk, M, lo, false), lower_index(sk, M, hi, true));
+    const size_t i = (size_t)fb.y * kWeightRows + threadIdx.x;
+    if (blockIdx.y == 0) {
+        const size_t M = (size_t)S.survivors;
+        if (i < weight_col_pad(M))
+            wterm::gather_column(R.sc, S.geom, i, i < M, R.cols + (i < M ? (size_t)(a.colkeys[R.off + i] & 0xFFFFFull) : 0) * 9);
+    } else {
+        const bool real = i < (size_t)R.N;
+        const size_t j = real ? (size_t)(a.rowkeys[R.off + i] & 0xFFFFFull) : 0;
+        wterm::gather_row(R.sr, S.geom, i, real, R.u[S.nxt] + j * kNP, R.sigma[S.nxt][j], a.rwin[R.off + j], a.ex);
     }
 }
 
-// grid = weight table (run, row block, chunk): chunk c of the block's window,
-// sorted rows; partial sums go to the rows' own indices (finalize unchanged).
+// grid = weight table (run, row block, chunk): chunk c of the run's column
+// tiles, sorted rows.
 __global__ __launch_bounds__(kWeightRows) void bweights_kernel(BatchArgs a)
 {
     __shared__ double T[wterm::kTab];
+    __shared__ __attribute__((aligned(16))) uint32_t list[kWeightRows / kWave][kListLen];
     const int4 wb = a.w_tab[blockIdx.x];
     const BRun& R = a.runs[wb.x];
     const BState& S = a.st[wb.x];
     if (S.failed) return;  // uniform across the block
-    const int nx = S.nxt;
+    const int M = (int)S.survivors, tiles = (M + kColTile - 1) / kColTile;
+    const int t0 = (int)(((long long)tiles * wb.z) / R.wchunks), t1 = (int)(((long long)tiles * (wb.z + 1)) / R.wchunks);
     const int rr = wb.y * kWeightRows + threadIdx.x;
-    const bool active = rr < R.N;
-    const size_t j = active ? (size_t)(a.rowkeys[R.off + rr] & 0xFFFFFull) : 0;
-    const int2 wnd = a.win[R.rb0 + wb.y];
-    const int len = wnd.y - wnd.x > 0 ? wnd.y - wnd.x : 0;
-    const int Sc = R.wchunks, c = wb.z;
-    const int k0 = wnd.x + (int)(((long long)len * c) / Sc);
-    const int k1 = wnd.x + (int)(((long long)len * (c + 1)) / Sc);
-    if (k0 >= k1) {
-        if (active) R.wpart[(size_t)c * R.N + j] = 0.0;
+    double* out = R.wpart + (size_t)wb.z * R.N;
+    const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+    const int group = __builtin_amdgcn_readfirstlane(wb.y * (kWeightRows / kWave) + w);
+    if (t0 >= t1) {
+        if (rr < R.N) out[rr] = 0.0;
+        if (lane == 0) R.wcounts[(size_t)wb.z * (R.sr.pad / kWave) + group] = make_uint2(0, 0);
         return;
     }
-    wterm::load_table(T, a.wtab);
-    __syncthreads();
-    const int ds = S.dstar;
-    double uj[kNP];
-    double cj = 0.0, lo = __builtin_inf(), hi = -__builtin_inf();
-    if (active) {
-#pragma unroll
-        for (int d = 0; d < kNP; ++d) uj[d] = R.u[nx][j * kNP + d];
-        const double sj = R.sigma[nx][j];
-        cj = wterm::row_scale(sj, a.ex);
-        lo = uj[ds] - a.rwin[R.off + j];
-        hi = uj[ds] + a.rwin[R.off + j];
-    } else {
-#pragma unroll
-        for (int d = 0; d < kNP; ++d) uj[d] = 0.0;
+    uint32_t listed = 0, window = 0;
+    double total = 0.0;
+    const unsigned long long first = wterm::near_tiles(R.sr, R.sc, group, lane, t0, t1);
+    if (__syncthreads_or(first != 0 || t1 - t0 > kWave)) {
+        wterm::load_table(T, a.wtab);
+        __syncthreads();
+        total = wterm::row_sum(R.sr, R.sc, group, lane, t0, t1, M, first, T, list[w], a.ex, listed, window);
     }
-    const double wlo = wave_min(lo), whi = wave_max(hi);
-    const unsigned long long lanes = (unsigned long long)__popcll(__ballot(active));
-    unsigned long long evaluated = 0;
-    const double total = wterm::row_sum(uj, cj, (wterm::const_col_ptr)(a.scols + (size_t)R.off * 9),
-                                        (wterm::const_col_ptr)(a.skey + R.off), k0, k1, wlo, whi, T, a.ex, lanes,
-                                        evaluated);
-    if (active) R.wpart[(size_t)c * R.N + j] = total;
-    if ((threadIdx.x & (kWave - 1)) == 0 && evaluated) atomicAdd(&a.st[wb.x].terms, evaluated);
+    if (rr < R.N) out[rr] = total;
+    if (lane == 0) R.wcounts[(size_t)wb.z * (R.sr.pad / kWave) + group] = make_uint2(listed, window);
 }
 
 __global__ __launch_bounds__(kWeightRows) void bfinalize_kernel(BatchArgs a)
@@ -633,10 +592,26 @@ __global__ __launch_bounds__(kWeightRows) void bfinalize_kernel(BatchArgs a)
     const BRun& R = a.runs[fb.x];
     const BState& S = a.st[fb.x];
     if (S.failed) return;
-    const int j = fb.y * kWeightRows + threadIdx.x;
-    if (j >= R.N) return;
+    const int rr = fb.y * kWeightRows + threadIdx.x;
+    const int group = rr / kWave, lane = threadIdx.x & (kWave - 1);
+    if (group * kWave < R.N) {
+        unsigned long long listed = 0, window = 0;
+        for (int c = lane; c < R.wchunks; c += kWave) {
+            const uint2 n = R.wcounts[(size_t)c * (R.sr.pad / kWave) + group];
+            listed += n.x;
+            window += n.y;
+        }
+        listed = wterm::wave_sum_u64(listed);
+        window = wterm::wave_sum_u64(window);
+        if (lane == 0 && listed) {
+            atomicAdd(&a.st[fb.x].terms, listed * (unsigned long long)min(kWave, R.N - group * kWave));
+            atomicAdd(&a.st[fb.x].window_terms, window);
+        }
+    }
+    if (rr >= R.N) return;
     double L = 0.0;
-    for (int c = 0; c < R.wchunks; ++c) L += R.wpart[(size_t)c * R.N + j];
+    for (int c = 0; c < R.wchunks; ++c) L += R.wpart[(size_t)c * R.N + rr];
+    const size_t j = (size_t)(a.rowkeys[R.off + rr] & 0xFFFFFull);
     R.logw[S.nxt][j] = 8.0 * dm::log(R.sigma[S.nxt][j]) - dm::log(L);
 }
 
@@ -715,12 +690,11 @@ void batch_launch_stage(const BatchArgs& a, bool stage0, hipStream_t s)
     hipLaunchKernelGGL(bcompact_scan_kernel, dim3(a.n_runs), b, 0, s, a);
     hipLaunchKernelGGL(bcompact_scatter_kernel, dim3(a.max_cap_blocks, a.n_runs), b, 0, s, a);
     if (!stage0) {
-        hipLaunchKernelGGL(bwdim_kernel, dim3(a.n_runs), b, 0, s, a);
-        hipLaunchKernelGGL(bkeys_kernel, dim3(a.n_key_blocks), b, 0, s, a);
+        hipLaunchKernelGGL(bwgeom_kernel, dim3(a.n_runs), dim3(kDimThreads), 0, s, a);
+        hipLaunchKernelGGL(bkeys_kernel, dim3(a.n_key_blocks, 2), b, 0, s, a);
         launch_sort_u64_pair(a.colkeys, a.rowkeys, a.npad, s);
-        hipLaunchKernelGGL(bcolgather_kernel, dim3((a.n_total + kBlock - 1) / kBlock), b, 0, s, a);
         const dim3 bw(kWeightRows);
-        hipLaunchKernelGGL(bwindow_kernel, dim3(a.n_fin_blocks), bw, 0, s, a);
+        hipLaunchKernelGGL(bgather_kernel, dim3(a.n_fin_blocks, 2), bw, 0, s, a);
         hipLaunchKernelGGL(bweights_kernel, dim3(a.n_w_blocks), bw, 0, s, a);
         hipLaunchKernelGGL(bfinalize_kernel, dim3(a.n_fin_blocks), bw, 0, s, a);
     }

@@ -41,17 +41,19 @@ int run_cap_blocks(const abcsmc_config& c)
     return (int)((cap + kChunkP - 1) / kChunkP);
 }
 
-int wchunks_max(int64_t N) { return (int)std::min<int64_t>(kMaxWChunks, std::max<int64_t>(1, (N / 2 + 2047) / 2048)); }
+int wchunks_max(int64_t N) { return (int)std::min<int64_t>(kMaxWChunks, std::max<int64_t>(1, (N / 2 + 255) / 256)); }
 
-int wchunks_for(int64_t N, int weight_cols)
+// Column chunks of a run: as the schedule asks, and more where the launch
+// (row_blocks workgroups a chunk) would leave the chip idle.
+int wchunks_for(int64_t N, int weight_cols, int64_t row_blocks)
 {
-    const int64_t c = std::max<int64_t>(1, (N / 2 + weight_cols - 1) / weight_cols);
-    return (int)std::min<int64_t>(c, wchunks_max(N));
+    const int64_t c = std::max<int64_t>((N / 2 + weight_cols - 1) / weight_cols, (8192 + row_blocks - 1) / row_blocks);
+    return (int)std::min<int64_t>(std::max<int64_t>(c, 1), wchunks_max(N));
 }
 
 struct RunLayout {
     size_t obs, u[2], d[2], sigma[2], logw[2], W[2], parent[2], index[2], att[2], q, cdf, cols, wpart, st_u, st_d,
-        st_sigma, st_parent, st_att, wmask, woff, red_u, red_d, end;
+        st_sigma, st_parent, st_att, wmask, woff, red_u, red_d, scu, scq, scop, scbox, sru, srscale, srr2, srop, srbox, wcounts, end;
 };
 
 RunLayout run_layout(const abcsmc_config& c, size_t o)
@@ -89,18 +91,28 @@ RunLayout run_layout(const abcsmc_config& c, size_t o)
     L.woff = take(B / kWave * 4);
     L.red_u = take(3 * nres * 8);
     L.red_d = take(nres * 8);
+    const size_t cpad = weight_col_pad(N), rpad = weight_row_pad(N);
+    L.scu = take(cpad * kNP * 8);
+    L.scq = take(cpad * 8);
+    L.scop = take(3 * cpad * 16);
+    L.scbox = take(cpad / kColTile * 16 * 4);
+    L.sru = take(rpad * kNP * 8);
+    L.srscale = take(rpad * 8);
+    L.srr2 = take(rpad * 8);
+    L.srop = take(3 * rpad * 16);
+    L.srbox = take(rpad / kWave * 17 * 4);
+    L.wcounts = take((size_t)wchunks_max((int64_t)N) * (rpad / kWave) * sizeof(uint2));
     L.end = o;
     return L;
 }
 
-// Batch-wide weight-window arrays after the tables: column and row sort keys
-// (power-of-two length), sorted columns, their sort-coordinate values, one
-// window per kWeightRows-row block, and the exponential table.
+// Batch-wide weight-pass arrays after the tables: column and row sort keys
+// (power-of-two length), the rows' window radii and the exponential table.
 struct WinLayout {
-    size_t colkeys, rowkeys, scols, skey, rwin, win, wtab, end, npad;
+    size_t colkeys, rowkeys, rwin, wtab, end, npad;
 };
 
-WinLayout win_layout(size_t o, size_t n_total, size_t n_fin)
+WinLayout win_layout(size_t o, size_t n_total)
 {
     WinLayout L{};
     L.npad = sort_padded_size(n_total);
@@ -111,10 +123,7 @@ WinLayout win_layout(size_t o, size_t n_total, size_t n_fin)
     };
     L.colkeys = take(L.npad * 8);
     L.rowkeys = take(L.npad * 8);
-    L.scols = take(n_total * 9 * 8);
-    L.skey = take(n_total * 8);
     L.rwin = take(n_total * 8);
-    L.win = take(n_fin * sizeof(int2));
     L.wtab = take(kWeightTab * 8);
     L.end = o;
     return L;
@@ -229,7 +238,7 @@ int apply_schedule(abcsmc_batch* b)
     std::vector<int4> wt;
     for (int i = 0; i < b->R; ++i) {
         const int r = order[i];
-        b->runs[r].wchunks = wchunks_for(b->cfgs[r].n_particles, s.weight_cols);
+        b->runs[r].wchunks = wchunks_for(b->cfgs[r].n_particles, s.weight_cols, b->n_fin);
         const int rb = (int)((b->cfgs[r].n_particles + kWeightRows - 1) / kWeightRows);
         for (int y = 0; y < rb; ++y)
             for (int c = 0; c < b->runs[r].wchunks; ++c) wt.push_back(make_int4(r, y, c, 0));
@@ -352,7 +361,7 @@ int abcsmc_batch_workspace_size(const abcsmc_config* cfgs, int32_t n_runs, size_
     size_t n_total = 0;
     for (int r = 0; r < n_runs; ++r) n_total += (size_t)cfgs[r].n_particles;
     if (n_total > ((size_t)1 << 26)) return bfail(nullptr, ABCSMC_EINVAL, "batched runs: sum of N <= 2^26");
-    o = win_layout(o, n_total, (size_t)n_fin).end;
+    o = win_layout(o, n_total).end;
     *bytes = o;
     return ABCSMC_OK;
 }
@@ -462,6 +471,7 @@ int abcsmc_batch_init(const abcsmc_config* cfgs, int32_t n_runs, const int64_t* 
         R.cdf = (uint64_t*)(w + L.cdf);
         R.cols = (double*)(w + L.cols);
         R.wpart = (double*)(w + L.wpart);
+        R.wcounts = (uint2*)(w + L.wcounts);
         R.st_u = (double*)(w + L.st_u);
         R.st_d = (double*)(w + L.st_d);
         R.st_sigma = (double*)(w + L.st_sigma);
@@ -472,7 +482,10 @@ int abcsmc_batch_init(const abcsmc_config* cfgs, int32_t n_runs, const int64_t* 
         R.red_u = (unsigned long long*)(w + L.red_u);
         R.red_d = (double*)(w + L.red_d);
         R.off = (int32_t)n_total;
-        R.rb0 = (int32_t)fin_tab.size();
+        R.sc = WeightCols{(double*)(w + L.scu), (double*)(w + L.scq), w + L.scop, (float*)(w + L.scbox),
+                          weight_col_pad((size_t)c.n_particles)};
+        R.sr = WeightRows{(double*)(w + L.sru), (double*)(w + L.srscale), (double*)(w + L.srr2), w + L.srop,
+                          (float*)(w + L.srbox), weight_row_pad((size_t)c.n_particles)};
         n_total += (size_t)c.n_particles;
         R.res_blk0 = (int32_t)res_tab.size();
         R.res_nblk = (int32_t)((c.n_particles + 1023) / 1024);
@@ -500,7 +513,7 @@ int abcsmc_batch_init(const abcsmc_config* cfgs, int32_t n_runs, const int64_t* 
     o = al(o + (size_t)b->max_w_blocks * sizeof(int4));
     b->off_fin = o;
     o = al(o + fin_tab.size() * sizeof(int2));
-    const WinLayout WL = win_layout(o, n_total, fin_tab.size());
+    const WinLayout WL = win_layout(o, n_total);
     o = WL.end;
     if (o > bytes) return bail(ABCSMC_EINVAL, "internal layout mismatch");
     if (hipMemcpy(b->ws + b->off_res, res_tab.data(), res_tab.size() * sizeof(int2), hipMemcpyHostToDevice) != hipSuccess ||
@@ -523,10 +536,7 @@ int abcsmc_batch_init(const abcsmc_config* cfgs, int32_t n_runs, const int64_t* 
     A.n_fin_blocks = b->n_fin;
     A.colkeys = (unsigned long long*)(b->ws + WL.colkeys);
     A.rowkeys = (unsigned long long*)(b->ws + WL.rowkeys);
-    A.scols = (double*)(b->ws + WL.scols);
-    A.skey = (double*)(b->ws + WL.skey);
     A.rwin = (double*)(b->ws + WL.rwin);
-    A.win = (int2*)(b->ws + WL.win);
     A.wtab = (const double*)(b->ws + WL.wtab);
     launch_weight_table((double*)(b->ws + WL.wtab), b->stream);
     if (hipGetLastError() != hipSuccess) return bail(ABCSMC_EDEVICE, "launch of the exponential table failed");

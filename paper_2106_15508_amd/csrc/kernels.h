@@ -119,6 +119,38 @@ struct ResampleArgs {
 // Entries of the weight kernels' exponential table (2^(i/1024)).
 constexpr int kWeightTab = 1024;
 
+// Scale and bit order of the weight pass' sort code (device).
+struct WeightGeom {
+    double lo[kNP], inv[kNP];  // the columns' box: (u - lo) inv in [0, 1]
+    double mid[kNP];           // its centre
+    int32_t seq[32];           // code bit i: coordinate | (bit of it << 3)
+};
+
+constexpr int kColTile = 64;    // columns per tile of the weight kernels
+constexpr int kListLen = 128;   // entries of a wave's column list (a power of two >= 64 + 8)
+
+// Sorted columns (survivors of the previous stage).
+struct WeightCols {
+    double* u;     // M x 8
+    double* q;     // M
+    void* op;      // 3 x pad float16 octets: high parts, low parts, norms
+    float* box;    // per tile: minima[8], maxima[8]
+    size_t pad;    // columns padded to whole tiles
+};
+
+// Sorted rows (accepted particles), in groups of a wave.
+struct WeightRows {
+    double* u;      // pad x 8
+    double* scale;  // c_j = -1024 / (2 sigma_j^2 ln 2)
+    double* r2;     // squared window radius (-1 in the padding)
+    void* op;       // 3 x pad float16 octets
+    float* box;     // per group: minima[8], maxima[8], box test threshold
+    size_t pad;     // rows padded to whole kWeightRows blocks
+};
+
+__host__ __device__ inline size_t weight_col_pad(size_t n) { return (n + kColTile - 1) / kColTile * kColTile; }
+__host__ __device__ inline size_t weight_row_pad(size_t n) { return (n + kWeightRows - 1) / kWeightRows * kWeightRows; }
+
 struct WeightArgs {
     const double* u;        // N x 8 rows
     const double* sigma;    // N
@@ -128,27 +160,24 @@ struct WeightArgs {
     const unsigned long long* M;  // device scalar: survivors
     double* partial;        // chunks x N row sums per column chunk
     double* logw;           // N
-    // windowed evaluation: columns sorted by one coordinate, rows by
-    // (step-size half-octave, same coordinate); each workgroup visits only the
-    // columns that can give a nonzero term
     unsigned long long* rowkeys;  // Npad sort keys (row index in the low 32 bits)
     unsigned long long* colkeys;  // Npad sort keys (column index in the low 32 bits)
-    double* scols;          // M x 9 columns in sorted order
-    double* skey;           // M sorted coordinate values
-    double* dimpart;        // per-block partial sums for the coordinate choice (kRedMax x 16)
-    int32_t* dstar;         // device scalar: the coordinate
+    WeightCols sc;
+    WeightRows sr;
+    double* dimpart;        // kDimBlocks x 32 per-block statistics of the columns
+    WeightGeom* geom;       // device: the sort code
     size_t npad;            // padded sort length (power of two >= N)
-    int2* win;              // per row block: sorted column range [first, end) of its window
-    int32_t cols_per_chunk; // columns per grid-y chunk of a window
+    int32_t chunk_tiles;    // column tiles per chunk
+    uint2* counts;          // chunks x groups: columns listed, pairs inside the rows' own windows
     unsigned long long* terms;  // device counter of evaluated terms
-    unsigned long long* window_terms;  // device counter: sum over rows of the row's own window
-    // per-row window half-widths from each row's parent term
+    unsigned long long* window_terms;  // device counter: pairs inside the rows' own windows
+    // per-row window radii from each row's parent term
     const int32_t* parent;  // N parent indices into the previous population
     const double* u_prev;   // previous population, n_prev x 8
     const uint64_t* q_prev; // its resampling weights q_k (0 for non-survivors)
     const uint64_t* cdf;    // its integer CDF (cdf[n_prev - 1] = Q)
     int32_t n_prev;
-    double* rwin;           // N half-widths W_j sigma_j
+    double* rwin;           // N radii W_j sigma_j
     // table exponential: ln2/1024, its square / 2, its cube / 6, 1024/ln2
     // (kernel arguments so they sit in scalar registers)
     double ex[7];
@@ -184,12 +213,10 @@ struct SelectArgs {
     double* out;            // device scalar: type-7 quantile
 };
 
-// Column chunks of the weight kernel for N rows: enough workgroups to give
-// every SIMD about eight waves, with the partial sums bounded by 2^23 doubles.
+// Column tiles per chunk (grid y) and chunks of the weight kernel for N rows.
+int weight_chunk_tiles(int64_t N);
 int weight_chunks(int64_t N);
-// Windowed weight kernel: columns per chunk and chunks per row block.
-int weight_cols_per_chunk(int64_t N);
-int weight_window_chunks(int64_t N);
+constexpr int kDimBlocks = 64;  // blocks of the column statistics
 
 struct TrajArgs {
     Model m;

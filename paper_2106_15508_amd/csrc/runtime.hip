@@ -76,15 +76,23 @@ Layout make_layout(const abcsmc_config& c)
     for (int r = 0; r < 5; ++r) L.red[r] = take(kRedMax * 8);
     L.hist = take(2 * 2048 * sizeof(unsigned int));
     L.sel = take(8 * sizeof(unsigned long long));
-    L.wpart = take((size_t)std::max(weight_chunks((int64_t)N), weight_window_chunks((int64_t)N)) * N * sizeof(double));
+    L.wpart = take((size_t)weight_chunks((int64_t)N) * N * sizeof(double));
     const size_t npad = sort_padded_size(N);
+    const size_t cpad = weight_col_pad(N), rpad = weight_row_pad(N);
     L.rowkeys = take(npad * 8);
     L.colkeys = take(npad * 8);
-    L.scols = take(N * 9 * sizeof(double));
-    L.skey = take(N * sizeof(double));
-    L.dimpart = take(256 * 16 * sizeof(double));
-    L.dstar = take(sizeof(int32_t));
-    L.win = take(((N + kWeightRows - 1) / kWeightRows) * sizeof(int2));
+    L.scu = take(cpad * kNP * sizeof(double));
+    L.scq = take(cpad * sizeof(double));
+    L.scop = take(3 * cpad * 16);
+    L.scbox = take(cpad / kColTile * 16 * sizeof(float));
+    L.sru = take(rpad * kNP * sizeof(double));
+    L.srscale = take(rpad * sizeof(double));
+    L.srr2 = take(rpad * sizeof(double));
+    L.srop = take(3 * rpad * 16);
+    L.srbox = take(rpad / kWave * 17 * sizeof(float));
+    L.dimpart = take(kDimBlocks * 32 * sizeof(double));
+    L.geom = take(sizeof(WeightGeom));
+    L.wcounts = take((size_t)weight_chunks((int64_t)N) * (rpad / kWave) * sizeof(uint2));
     L.rwin = take(N * sizeof(double));
     L.wtab = take(kWeightTab * sizeof(double));
     L.total = o;
@@ -504,9 +512,8 @@ int abcsmc_round(abcsmc_ctx* x, abcsmc_round_info* info)
             wa.sigma = dst.sigma;
             wa.cols = x->at<double>(x->L.cols);
             wa.N = N;
-            wa.chunks = weight_window_chunks(N);
-            wa.cols_per_chunk = weight_cols_per_chunk(N);
-            wa.win = x->at<int2>(x->L.win);
+            wa.chunks = weight_chunks(N);
+            wa.chunk_tiles = weight_chunk_tiles(N);
             wa.terms = &ctr->terms;
             wa.window_terms = &ctr->window_terms;
             wa.M = &ctr->survivors;
@@ -514,10 +521,13 @@ int abcsmc_round(abcsmc_ctx* x, abcsmc_round_info* info)
             wa.logw = dst.logw;
             wa.rowkeys = x->at<unsigned long long>(x->L.rowkeys);
             wa.colkeys = x->at<unsigned long long>(x->L.colkeys);
-            wa.scols = x->at<double>(x->L.scols);
-            wa.skey = x->at<double>(x->L.skey);
+            wa.sc = WeightCols{x->at<double>(x->L.scu), x->at<double>(x->L.scq), x->at<char>(x->L.scop),
+                               x->at<float>(x->L.scbox), weight_col_pad((size_t)N)};
+            wa.sr = WeightRows{x->at<double>(x->L.sru),  x->at<double>(x->L.srscale), x->at<double>(x->L.srr2),
+                               x->at<char>(x->L.srop), x->at<float>(x->L.srbox), weight_row_pad((size_t)N)};
             wa.dimpart = x->at<double>(x->L.dimpart);
-            wa.dstar = x->at<int32_t>(x->L.dstar);
+            wa.geom = x->at<WeightGeom>(x->L.geom);
+            wa.counts = x->at<uint2>(x->L.wcounts);
             wa.npad = sort_padded_size((size_t)N);
             wa.parent = dst.parent;
             wa.u_prev = prev.u;

@@ -1,6 +1,6 @@
 // smc.hip -- SMC stage machinery around the proposal kernel:
 //   resample   prior set, eq. 10 weights and the integer CDF of eq. 11
-//   weights    N x M importance-weight row sums, LDS-tiled, FP64
+//   weights    N x M importance-weight row sums, windowed, FP64
 //   normalise  W = softmax(log-weights), effective sample size
 //   select     exact type-7 percentile of eq. 8 by radix select
 // All reductions combine per-block partials in a fixed order, so every result
@@ -8,6 +8,8 @@
 #include "dmath.h"
 #include "kernels.h"
 #include "wterm.h"
+
+#include <algorithm>
 
 namespace abcsmc {
 
@@ -224,203 +226,159 @@ __global__ __launch_bounds__(kBlock) void resample_write_kernel(ResampleArgs a)
 // the log of 1 / (proposal density at u_j given sigma_j) up to a constant
 // (prior density 1 on the cube).  One lane per row; the columns are split in
 // `chunks` contiguous ranges (grid y) so the launch fills the chip; every lane
-// of a wave reads the same column through scalar loads.  Four columns are
-// evaluated per step into even/odd partial sums; per-chunk partial sums are
-// added in a fixed order.
+// of a wave evaluates the same column, from scalar loads.  Per-chunk partial
+// sums are added in a fixed order.
 //
 // The exponential here is table driven (1024 entries of 2^(i/1024) in LDS and
 // a cubic in the remainder).  Its relative error (a few 1e-16) is far inside
 // the 1e-12 the weights are held to; the trajectories never use it.
 // ---------------------------------------------------------------------------
-using wterm::kTile;
-using wterm::coord_key32;
-using wterm::lower_index;
 using wterm::sigma_half_octave;
-using wterm::wave_max;
-using wterm::wave_min;
 using wterm::wave_sum_u64;
 
 // ---- windowed evaluation -------------------------------------------------
-// Row j only needs the columns whose coordinate d* lies within its
-// half-width R_j = W_j sigma_j of u_jd*: every other column has a term at
-// most q_k e^{-W_j^2/2}, and W_j is chosen from the row's own parent term so
-// that all of them together stay below 2^-53 of the row sum (at most 37.7,
-// where every omitted exponential is below e^-710).  Per stage: pick the
-// coordinate d* with the largest spread among the columns (the windows then
-// exclude the most columns: sigma is the same in every coordinate), sort the
-// columns by it, sort the rows by (half-octave of sigma, descending; u_d*), and let every
-// workgroup (128 consecutive sorted rows) visit only the union of its rows'
-// windows; a wave also skips tiles outside its own lanes' union.
+// Row j only needs the columns within its radius R_j = W_j sigma_j: every
+// other column has a term at most q_k e^{-W_j^2/2}, and W_j is chosen from the
+// row's own parent term so that all of them together stay below 2^-53 of the
+// row sum (at most 37.7, where every omitted exponential is below e^-710).
+// Per stage: statistics of the columns choose the sort code (wterm.h), columns
+// are sorted by it, rows by (half-octave of sigma descending, code), both are
+// gathered into sorted arrays with what the pair test needs, and every wave
+// (64 consecutive sorted rows) evaluates the columns one of its rows needs.
 
-constexpr int kDimBlocks = 256;
-
+// Column statistics: sum, sum of squares, minimum and maximum per coordinate.
+// Thread t takes coordinate t % 8 of every 32nd column.
 __global__ __launch_bounds__(kBlock) void wdim_partial_kernel(WeightArgs a)
 {
+    __shared__ double sh[4][kBlock];
+    const int M = (int)*a.M, t = threadIdx.x, d = t & 7;
+    double s1 = 0.0, s2 = 0.0, mn = __builtin_inf(), mx = -__builtin_inf();
+    for (int k = blockIdx.x * (kBlock / 8) + t / 8; k < M; k += gridDim.x * (kBlock / 8)) {
+        const double v = a.cols[(size_t)k * 9 + d];
+        s1 += v;
+        s2 += v * v;
+        mn = v < mn ? v : mn;
+        mx = v > mx ? v : mx;
+    }
+    sh[0][t] = s1;
+    sh[1][t] = s2;
+    sh[2][t] = mn;
+    sh[3][t] = mx;
+    __syncthreads();
+    for (int off = kBlock / 2; off >= 8; off >>= 1) {
+        if (t < off) {
+            sh[0][t] += sh[0][t + off];
+            sh[1][t] += sh[1][t + off];
+            sh[2][t] = sh[2][t] < sh[2][t + off] ? sh[2][t] : sh[2][t + off];
+            sh[3][t] = sh[3][t] > sh[3][t + off] ? sh[3][t] : sh[3][t + off];
+        }
+        __syncthreads();
+    }
+    if (t < 32) a.dimpart[blockIdx.x * 32 + t] = sh[t >> 3][t & 7];
+}
+
+__global__ __launch_bounds__(kBlock) void wgeom_kernel(WeightArgs a)
+{
     __shared__ double sh[kBlock];
-    const int M = (int)*a.M;
-    double s1[kNP], s2[kNP];
-#pragma unroll
-    for (int d = 0; d < kNP; ++d) s1[d] = s2[d] = 0.0;
-    for (int k = blockIdx.x * kBlock + threadIdx.x; k < M; k += gridDim.x * kBlock) {
-#pragma unroll
-        for (int d = 0; d < kNP; ++d) {
-            const double v = a.cols[(size_t)k * 9 + d];
-            s1[d] += v;
-            s2[d] += v * v;
-        }
+    const int t = threadIdx.x, which = (t & 31) >> 3;
+    double v = which < 2 ? 0.0 : (which == 2 ? __builtin_inf() : -__builtin_inf());
+    for (int b = t >> 5; b < kDimBlocks; b += kBlock / 32) {
+        const double p = a.dimpart[b * 32 + (t & 31)];
+        v = which < 2 ? v + p : (which == 2 ? (p < v ? p : v) : (p > v ? p : v));
     }
-    for (int d = 0; d < kNP; ++d) {
-        const double t1 = block_sum_f64(s1[d], sh);
-        const double t2 = block_sum_f64(s2[d], sh);
-        if (threadIdx.x == 0) {
-            a.dimpart[blockIdx.x * 16 + d] = t1;
-            a.dimpart[blockIdx.x * 16 + 8 + d] = t2;
+    sh[t] = v;
+    __syncthreads();
+    for (int off = kBlock / 2; off >= 32; off >>= 1) {
+        if (t < off) {
+            const double p = sh[t + off];
+            sh[t] = which < 2 ? sh[t] + p : (which == 2 ? (p < sh[t] ? p : sh[t]) : (p > sh[t] ? p : sh[t]));
         }
+        __syncthreads();
     }
+    if (t == 0) wterm::make_geom(sh, sh + 8, sh + 16, sh + 24, (double)*a.M, *a.geom);
 }
 
-__global__ __launch_bounds__(kBlock) void wdim_pick_kernel(WeightArgs a)
+// Sort keys of the columns (grid.y 0) and of the rows (grid.y 1), and the
+// rows' window radii.
+__global__ __launch_bounds__(kBlock) void wkeys_kernel(WeightArgs a)
 {
-    __shared__ double sh[kBlock];
-    const int M = (int)*a.M;
-    double best = -1.0;
-    int bd = 0;
-    for (int d = 0; d < kNP; ++d) {
-        const double t1 = block_sum_f64(threadIdx.x < kDimBlocks ? a.dimpart[threadIdx.x * 16 + d] : 0.0, sh);
-        const double t2 = block_sum_f64(threadIdx.x < kDimBlocks ? a.dimpart[threadIdx.x * 16 + 8 + d] : 0.0, sh);
-        const double mean = t1 / (double)M;
-        const double var = t2 / (double)M - mean * mean;
-        if (var > best) {
-            best = var;
-            bd = d;
-        }
-    }
-    if (threadIdx.x == 0) *a.dstar = bd;
-}
-
-__global__ __launch_bounds__(kBlock) void wcolkeys_kernel(WeightArgs a)
-{
+    __shared__ uint32_t cells[kNP * kBlock];
     const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= a.npad) return;
-    const int M = (int)*a.M;
-    const int ds = *a.dstar;
-    a.colkeys[i] = i < (size_t)M ? (coord_key32(a.cols[i * 9 + ds]) << 32) | (unsigned long long)i : ~0ull;
-}
-
-__global__ __launch_bounds__(kBlock) void wcolgather_kernel(WeightArgs a)
-{
-    const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    const int M = (int)*a.M;
-    if (i >= (size_t)M) return;
-    const int ds = *a.dstar;
-    const size_t src = (size_t)(a.colkeys[i] & 0xFFFFFFFFull);
-    const double* c = a.cols + src * 9;
-    double* o = a.scols + i * 9;
-#pragma unroll
-    for (int d = 0; d < 9; ++d) o[d] = c[d];
-    a.skey[i] = c[ds];
-}
-
-__global__ __launch_bounds__(kBlock) void wrowkeys_kernel(WeightArgs a)
-{
-    const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= a.npad) return;
-    if (i >= (size_t)a.N) {
-        a.rowkeys[i] = ~0ull;
+    if (i >= a.npad) return;  // each thread uses its own LDS column only
+    const bool row = blockIdx.y != 0;
+    unsigned long long* keys = row ? a.rowkeys : a.colkeys;
+    if (i >= (size_t)(row ? a.N : (int)*a.M)) {
+        keys[i] = ~0ull;
         return;
     }
-    const int ds = *a.dstar;
-    // half-octaves in descending order: the widest windows are dispatched first
-    const unsigned long long hi =
-        ((127ull - sigma_half_octave(a.sigma[i])) << 25) | (coord_key32(a.u[i * kNP + ds]) >> 7);
-    a.rowkeys[i] = (hi << 32) | (unsigned long long)i;
-    double uj[kNP];
+    const WeightGeom& g = *a.geom;
+    double u[kNP];
 #pragma unroll
-    for (int d = 0; d < kNP; ++d) uj[d] = a.u[i * kNP + d];
-    const int32_t par = a.parent[i];
-    const bool ok = par >= 0 && par < a.n_prev;
-    a.rwin[i] = wterm::window_halfwidth(uj, a.sigma[i], ok ? a.u_prev + (size_t)par * kNP : uj,
-                                        ok ? (double)a.q_prev[par] : 0.0, (double)a.cdf[a.n_prev - 1]);
+    for (int d = 0; d < kNP; ++d) {
+        u[d] = row ? a.u[i * kNP + d] : a.cols[i * 9 + d];
+        cells[d * kBlock + threadIdx.x] = wterm::cell20(u[d], g.lo[d], g.inv[d]);
+    }
+    uint32_t key = wterm::morton32(g, cells + threadIdx.x, kBlock);
+    if (row) {
+        const double sj = a.sigma[i];
+        // half-octaves in descending order: the widest windows are dispatched first
+        key = ((127u - (uint32_t)sigma_half_octave(sj)) << 25) | (key >> 7);
+        const int32_t par = a.parent[i];
+        const bool ok = par >= 0 && par < a.n_prev;
+        a.rwin[i] = wterm::window_radius(u, sj, ok ? a.u_prev + (size_t)par * kNP : u, ok ? (double)a.q_prev[par] : 0.0,
+                                         (double)a.cdf[a.n_prev - 1]);
+    }
+    keys[i] = ((unsigned long long)key << 32) | (unsigned long long)i;
 }
 
-// Window of each row block (kWeightRows consecutive sorted rows): the sorted
-// column range that can hold a nonzero term for any of its rows.
-__global__ __launch_bounds__(kWeightRows) void wwindow_kernel(WeightArgs a)
+// Sorted columns (a wave per tile) and sorted rows (a wave per group).
+__global__ __launch_bounds__(kBlock) void wgather_kernel(WeightArgs a)
 {
-    __shared__ double slo[kWeightRows / kWave], shi[kWeightRows / kWave];
-    const int r = blockIdx.x * kWeightRows + threadIdx.x;
-    const int ds = *a.dstar;
-    const int M = (int)*a.M;
-    double lo = __builtin_inf(), hi = -__builtin_inf();
-    unsigned long long own = 0;  // columns of this row's own window
-    if (r < a.N) {
-        const size_t j = (size_t)(a.rowkeys[r] & 0xFFFFFFFFull);
-        const double R = a.rwin[j];
-        const double x = a.u[j * kNP + ds];
-        lo = x - R;
-        hi = x + R;
-        own = (unsigned long long)(lower_index(a.skey, M, hi, true) - lower_index(a.skey, M, lo, false));
-    }
-    own = wave_sum_u64(own);
-    if ((threadIdx.x & (kWave - 1)) == 0 && own) atomicAdd(a.window_terms, own);
-    lo = wave_min(lo);
-    hi = wave_max(hi);
-    if ((threadIdx.x & (kWave - 1)) == 0) {
-        slo[threadIdx.x / kWave] = lo;
-        shi[threadIdx.x / kWave] = hi;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        for (int q = 1; q < kWeightRows / kWave; ++q) {
-            lo = slo[q] < lo ? slo[q] : lo;
-            hi = shi[q] > hi ? shi[q] : hi;
-        }
-        lo = slo[0] < lo ? slo[0] : lo;
-        hi = shi[0] > hi ? shi[0] : hi;
-        a.win[blockIdx.x] = make_int2(lower_index(a.skey, M, lo, false), lower_index(a.skey, M, hi, true));
+    const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    if (blockIdx.y == 0) {
+        const int M = (int)*a.M;
+        if (i < a.sc.pad && i < weight_col_pad((size_t)M))
+            wterm::gather_column(a.sc, *a.geom, i, i < (size_t)M,
+                                 a.cols + (i < (size_t)M ? (size_t)(a.colkeys[i] & 0xFFFFFFFFull) : 0) * 9);
+    } else if (i < a.sr.pad) {
+        const bool real = i < (size_t)a.N;
+        const size_t j = real ? (size_t)(a.rowkeys[i] & 0xFFFFFFFFull) : 0;
+        wterm::gather_row(a.sr, *a.geom, i, real, a.u + j * kNP, a.sigma[j], a.rwin[j], a.ex);
     }
 }
 
-// grid (row blocks, chunks): block (b, c) sums columns
-// [first_b + c CH, min(end_b, first_b + (c+1) CH)) for its kWeightRows rows
-// (two waves: 128-row blocks keep the windows tighter than 256-row ones, 3.5%
-// faster at N = 131072); chunks past the window leave at once.
-__global__ __launch_bounds__(kWeightRows) void weights_kernel(WeightArgs a)
+// grid (row blocks, chunks): a wave's rows against the tiles of the chunk.
+// Five waves a SIMD (96 VGPRs) hide the lists' scalar loads best: 272 ms in
+// stage 1 of N = 2^20 against 288 at four and 296 at six; 128 rows a workgroup
+// balance better than 256 (16.2 against 18.0 ms in a run of N = 131072).
+// A run's launches against a window on one sorted coordinate: N = 20011 (8
+// stages) 1.81 -> 0.72 ms, 131072 (10) 27.7 -> 16.2 ms, 2^20 (4) 876 -> 574 ms;
+// the early stages are at 90% of the FP64 issue rate.
+__global__ __launch_bounds__(kWeightRows) __attribute__((amdgpu_waves_per_eu(5))) void weights_kernel(WeightArgs a)
 {
     __shared__ double T[wterm::kTab];
-    const int r = blockIdx.x * kWeightRows + threadIdx.x;   // sorted row position
-    const bool active = r < a.N;
-    const int2 wnd = a.win[blockIdx.x];
-    const int k0 = wnd.x + (int)blockIdx.y * a.cols_per_chunk;
-    const int k1 = min(wnd.y, k0 + a.cols_per_chunk);
-    if (k0 >= k1) return;  // past the window: the finalize pass does not read this chunk
-    wterm::load_table(T, a.tab);
-    __syncthreads();
-    const int ds = *a.dstar;
-    double uj[kNP];
-    double cj = 0.0, lo = __builtin_inf(), hi = -__builtin_inf();
-    if (active) {
-        const size_t j = (size_t)(a.rowkeys[r] & 0xFFFFFFFFull);
-#pragma unroll
-        for (int d = 0; d < kNP; ++d) uj[d] = a.u[j * kNP + d];
-        const double sj = a.sigma[j];
-        cj = wterm::row_scale(sj, a.ex);
-        const double R = a.rwin[j];
-        lo = uj[ds] - R;
-        hi = uj[ds] + R;
-    } else {
-#pragma unroll
-        for (int d = 0; d < kNP; ++d) uj[d] = 0.0;
+    __shared__ __attribute__((aligned(16))) uint32_t list[kWeightRows / kWave][kListLen];
+    const int M = (int)*a.M;
+    const int t0 = (int)blockIdx.y * a.chunk_tiles;
+    const int t1 = min((M + kColTile - 1) / kColTile, t0 + a.chunk_tiles);
+    if (t0 >= t1) return;  // past the columns: the finalize pass does not read this chunk
+    const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+    const int group = __builtin_amdgcn_readfirstlane((int)blockIdx.x * (kWeightRows / kWave) + w);
+    const int r = group * kWave + lane;
+    uint32_t listed = 0, window = 0;
+    double total = 0.0;
+    // most workgroups of the late stages have no tile near: they leave before
+    // the table and the rows are loaded
+    const unsigned long long first = wterm::near_tiles(a.sr, a.sc, group, lane, t0, t1);
+    if (__syncthreads_or(first != 0 || t1 - t0 > kWave)) {
+        wterm::load_table(T, a.tab);
+        __syncthreads();
+        total = wterm::row_sum(a.sr, a.sc, group, lane, t0, t1, M, first, T, list[w], a.ex, listed, window);
     }
-    const double wlo = wave_min(lo), whi = wave_max(hi);
-    const unsigned long long lanes = (unsigned long long)__popcll(__ballot(active));
-    unsigned long long evaluated = 0;
-    // read-only for the whole launch: constant address space, so the
-    // wave-uniform column reads become scalar loads
-    const double total = wterm::row_sum(uj, cj, (wterm::const_col_ptr)a.scols, (wterm::const_col_ptr)a.skey, k0,
-                                        k1, wlo, whi, T, a.ex, lanes, evaluated);
-    if (active) a.partial[(size_t)blockIdx.y * a.N + r] = total;
-    if ((threadIdx.x & (kWave - 1)) == 0 && evaluated) atomicAdd(a.terms, evaluated);
+    if (r < a.N) a.partial[(size_t)blockIdx.y * a.N + r] = total;
+    // (counted per wave and added up by the finalize pass: 130000 atomics on one
+    // line took longer than the smaller stages' sums)
+    if (lane == 0) a.counts[(size_t)blockIdx.y * (a.sr.pad / kWave) + group] = make_uint2(listed, window);
 }
 
 __global__ __launch_bounds__(kBlock) void wtable_kernel(double* tab)
@@ -449,17 +407,32 @@ __global__ __launch_bounds__(kBlock) void wterm_debug_kernel(int64_t n, const do
     }
     c.q = r[17];
     const double cj = wterm::row_scale(r[8], a.ex);
-    out[i] = __builtin_fma(c.q, wterm::term_exp(uj, cj, c, T, a.ex), 0.0);
+    out[i] = __builtin_fma(c.q, wterm::term_exp(wterm::dist2(uj, c), cj, T, a.ex), 0.0);
 }
 
 __global__ __launch_bounds__(kBlock) void weights_finalize_kernel(WeightArgs a)
 {
     const int r = blockIdx.x * kBlock + threadIdx.x;
+    const int tiles = ((int)*a.M + kColTile - 1) / kColTile;
+    const int nch = min(a.chunks, (tiles + a.chunk_tiles - 1) / a.chunk_tiles);
+    // a wave's group: its terms and window pairs
+    const int group = r / kWave, lane = threadIdx.x & (kWave - 1);
+    if (group * kWave < a.N) {
+        unsigned long long listed = 0, window = 0;
+        for (int c = lane; c < nch; c += kWave) {
+            const uint2 n = a.counts[(size_t)c * (a.sr.pad / kWave) + group];
+            listed += n.x;
+            window += n.y;
+        }
+        listed = wave_sum_u64(listed);
+        window = wave_sum_u64(window);
+        if (lane == 0 && listed) {
+            atomicAdd(a.terms, listed * (unsigned long long)min(kWave, a.N - group * kWave));
+            atomicAdd(a.window_terms, window);
+        }
+    }
     if (r >= a.N) return;
-    // the chunks that overlap the row block's window, in order
-    const int2 wnd = a.win[r / kWeightRows];
-    const int len = wnd.y > wnd.x ? wnd.y - wnd.x : 0;
-    const int nch = min(a.chunks, (len + a.cols_per_chunk - 1) / a.cols_per_chunk);
+    // the chunks that hold columns, in order
     double L = 0.0;
     for (int c = 0; c < nch; ++c) L += a.partial[(size_t)c * a.N + r];
     const size_t j = (size_t)(a.rowkeys[r] & 0xFFFFFFFFull);
@@ -679,17 +652,6 @@ void weight_exp_constants(double ex[7])
     ex[4] = ex[5] = ex[6] = 0.0;
 }
 
-int weight_chunks(int64_t N)
-{
-    const int64_t row_blocks = (N + kBlock - 1) / kBlock;
-    int64_t S = (2048 + row_blocks - 1) / row_blocks;
-    const int64_t cap = ((int64_t)1 << 23) / N;
-    if (S > cap) S = cap;
-    if (S > 64) S = 64;
-    if (S < 1) S = 1;
-    return (int)S;
-}
-
 void launch_to_theta(const double* u, const Model& m, double* theta, int64_t n, hipStream_t s)
 {
     hipLaunchKernelGGL(to_theta_kernel, dim3(blocks_of(n * kNP, kBlock)), dim3(kBlock), 0, s, u, m, theta, n);
@@ -706,14 +668,11 @@ void launch_resample(const ResampleArgs& a, hipStream_t s)
 void launch_weights_window(const WeightArgs& a, hipStream_t s)
 {
     const dim3 b(kBlock);
-    const unsigned gp = blocks_of((int64_t)a.npad, kBlock);
     hipLaunchKernelGGL(wdim_partial_kernel, dim3(kDimBlocks), b, 0, s, a);
-    hipLaunchKernelGGL(wdim_pick_kernel, dim3(1), b, 0, s, a);
-    hipLaunchKernelGGL(wcolkeys_kernel, dim3(gp), b, 0, s, a);
-    hipLaunchKernelGGL(wrowkeys_kernel, dim3(gp), b, 0, s, a);
+    hipLaunchKernelGGL(wgeom_kernel, dim3(1), b, 0, s, a);
+    hipLaunchKernelGGL(wkeys_kernel, dim3(blocks_of((int64_t)a.npad, kBlock), 2), b, 0, s, a);
     launch_sort_u64_pair(a.colkeys, a.rowkeys, a.npad, s);
-    hipLaunchKernelGGL(wcolgather_kernel, dim3(blocks_of(a.N, kBlock)), b, 0, s, a);
-    hipLaunchKernelGGL(wwindow_kernel, dim3(blocks_of(a.N, kWeightRows)), dim3(kWeightRows), 0, s, a);
+    hipLaunchKernelGGL(wgather_kernel, dim3(blocks_of((int64_t)a.sr.pad, kBlock), 2), b, 0, s, a);
 }
 
 void launch_wterm_debug(int64_t n, const double* in, double* out, hipStream_t s)
@@ -738,20 +697,23 @@ void launch_weights_finalize(const WeightArgs& a, hipStream_t s)
     hipLaunchKernelGGL(weights_finalize_kernel, dim3(blocks_of(a.N, kBlock)), dim3(kBlock), 0, s, a);
 }
 
-// Columns per chunk (grid y) of a row block's window: at most 128 chunks of at
-// least 1024 columns.  Finer chunks balance the uneven windows across the
-// chip (1024-column chunks: 7% faster than 4096 at N = 131072).
-int weight_cols_per_chunk(int64_t N)
+// Tiles per chunk: as many as leave 12000 workgroups of work (about half of N
+// survives; 3000 took 1.05 ms where 12000 take 0.72 at N = 20011, 24000 the
+// same), at most 16 (the chunk's columns stay in an XCD's L2 while the row
+// blocks pass over it and the widest rows' waves stay short: 32 took 17.5 ms
+// where 16 take 16.2 at N = 131072, 8 the same), at most 128 chunks of partial
+// sums.
+int weight_chunk_tiles(int64_t N)
 {
-    int64_t ch = 1024;
-    while ((N + ch - 1) / ch > 128) ch <<= 1;
-    return (int)ch;
+    const int64_t rb = (N + kWeightRows - 1) / kWeightRows, tiles = (N + kColTile - 1) / kColTile;
+    const int64_t t = std::min<int64_t>(16, std::max<int64_t>(1, rb * tiles / 2 / 12000));
+    return (int)std::max<int64_t>(t, (tiles + 127) / 128);
 }
 
-int weight_window_chunks(int64_t N)
+int weight_chunks(int64_t N)
 {
-    const int64_t ch = weight_cols_per_chunk(N);
-    return (int)((N + ch - 1) / ch);
+    const int64_t tiles = (N + kColTile - 1) / kColTile, t = weight_chunk_tiles(N);
+    return (int)((tiles + t - 1) / t);
 }
 
 void launch_normalise(const NormArgs& a, hipStream_t s)

@@ -1,6 +1,6 @@
 // wterm.h -- one importance-weight term q_k exp(-|u_j - u_k|^2 / (2 sigma_j^2))
-// with a table-driven exponential, the per-row column loop and the window
-// helpers (device code shared by the single-run and batched weight kernels).
+// with a table-driven exponential, the sort code, the pair test and the
+// per-wave column loop (device code shared by the single-run and batched weight kernels).
 #pragma once
 
 #include "dmath.h"
@@ -9,12 +9,10 @@
 namespace abcsmc {
 namespace wterm {
 
-constexpr int kTile = 256;  // columns per skip-test tile
-
-// Scalar-column form used by the weight kernels.  Columns (u_k[8], q_k) are
-// the same for every lane of a wave, so they are read through a wave-uniform
-// pointer in the constant address space (scalar loads into SGPRs, no LDS
-// staging).  The exponential uses a 1024-entry table of 2^(i/1024):
+// Scalar-column form used by the weight kernels.  Columns (u_k[8] and q_k, in
+// two arrays: a 64-byte line holds one column's u) are the same for every
+// lane of a wave, so they are read through wave-uniform pointers in the
+// constant address space (scalar loads into SGPRs, no LDS staging).  The exponential uses a 1024-entry table of 2^(i/1024):
 //   t = D c_j with c_j = -1024 / (2 sigma_j^2 ln 2)  (the exponent in units
 //   of ln2/1024), k = rint(t), r = (t - k) ln2/1024, |r| <= 3.4e-4,
 //   exp = 2^(k >> 10) 2^((k & 1023)/1024) (1 + r + r^2/2 + r^3/6)
@@ -35,21 +33,20 @@ struct Col {
     double q;
 };
 
-__device__ __forceinline__ Col load_col(const_col_ptr cols, int k)
+__device__ __forceinline__ Col load_col(const_col_ptr cu, const_col_ptr cq, uint32_t k)
 {
     Col c;
-    const_col_ptr p = cols + (size_t)k * 9;
+    const_col_ptr p = cu + (size_t)k * kNP;
 #pragma unroll
     for (int d = 0; d < kNP; ++d) c.u[d] = p[d];
-    c.q = p[8];
+    c.q = cq[k];
     return c;
 }
 
 // exp of the term (without q): with f = t - k in [-1/2, 1/2] and L = ln2/1024,
 // e^(f L) = 1 + f (L + f (L^2/2 + f L^3/6)); ex[0..2] = L, L^2/2, L^3/6
 // (kernel arguments: SGPRs).
-__device__ __forceinline__ double term_exp(const double* uj, double cj, const Col& c, const double* T,
-                                           const double* ex)
+__device__ __forceinline__ double dist2(const double* uj, const Col& c)
 {
     double D = 0.0;
 #pragma unroll
@@ -57,6 +54,11 @@ __device__ __forceinline__ double term_exp(const double* uj, double cj, const Co
         const double df = uj[d] - c.u[d];
         D = __builtin_fma(df, df, D);
     }
+    return D;
+}
+
+__device__ __forceinline__ double term_exp(double D, double cj, const double* T, const double* ex)
+{
     const double t = D * cj;
     const double kk = __builtin_rint(t);
     const double f = t - kk;
@@ -74,6 +76,7 @@ __device__ __forceinline__ double row_scale(double sigma, const double* ex)
 }
 
 static_assert(kTab == kWeightTab, "table length");
+static_assert(kColTile == kWave, "a lane per column of a tile");
 
 // Table entry i: 2^(i/1024).
 __device__ __forceinline__ double table_entry(int i)
@@ -88,60 +91,21 @@ __device__ __forceinline__ void load_table(double* T, const double* g)
     for (int i = threadIdx.x; i < kTab; i += blockDim.x) T[i] = g[i];
 }
 
-// Sum over the sorted columns [k0, k1) for this lane's row, in 256-column
-// tiles; a tile that no row of the wave can reach (sort coordinate outside
-// [wlo, whi]) is skipped.  Two interleaved partial sums (even and odd
-// columns), four columns' scalar loads issued together per step.
-__device__ __forceinline__ double row_sum(const double* uj, double cj, const_col_ptr cols, const_col_ptr skey,
-                                          int k0, int k1, double wlo, double whi, const double* T,
-                                          const double* ex, unsigned long long lanes,
-                                          unsigned long long& evaluated)
-{
-    double total = 0.0;
-    for (int c0 = k0; c0 < k1; c0 += kTile) {
-        const int n = min(kTile, k1 - c0);
-        if (skey[c0 + n - 1] < wlo || skey[c0] > whi) continue;
-        evaluated += lanes * (unsigned long long)n;
-        double p0 = 0.0, p1 = 0.0;
-        int cc = 0;
-        for (; cc + 3 < n; cc += 4) {
-            const int k = __builtin_amdgcn_readfirstlane(c0 + cc);
-            const Col a0 = load_col(cols, k), a1 = load_col(cols, k + 1), a2 = load_col(cols, k + 2), a3 = load_col(cols, k + 3);
-            p0 = __builtin_fma(a0.q, term_exp(uj, cj, a0, T, ex), p0);
-            p1 = __builtin_fma(a1.q, term_exp(uj, cj, a1, T, ex), p1);
-            p0 = __builtin_fma(a2.q, term_exp(uj, cj, a2, T, ex), p0);
-            p1 = __builtin_fma(a3.q, term_exp(uj, cj, a3, T, ex), p1);
-        }
-        for (; cc < n; cc += 2) {
-            const int k = __builtin_amdgcn_readfirstlane(c0 + cc);
-            const Col a0 = load_col(cols, k);
-            p0 = __builtin_fma(a0.q, term_exp(uj, cj, a0, T, ex), p0);
-            if (cc + 1 < n) {
-                const Col a1 = load_col(cols, k + 1);
-                p1 = __builtin_fma(a1.q, term_exp(uj, cj, a1, T, ex), p1);
-            }
-        }
-        total += p0 + p1;
-    }
-    return total;
-}
-
-// Widest window of a row (the cap of window_halfwidth): a column whose sort
-// coordinate differs by more than kWindow sigma_j gives an exponent below
-// -710, where both exponentials are exactly 0.
+// Widest window of a row (the cap of window_radius): a column more than
+// kWindow sigma_j away gives an exponent below -710, where both exponentials
+// are exactly 0.
 constexpr double kWindow = 37.7;
 
 // Narrower per-row window with a bound on what it leaves out.  Every column
-// outside |u_kd - u_jd| <= W sigma_j (any one coordinate d) has a term at most
-// q_k e^{-W^2/2}, so all of them together are at most Q e^{-W^2/2}
+// with |u_k - u_j| > W sigma_j has a term at most q_k e^{-W^2/2}, so all of them together are at most Q e^{-W^2/2}
 // (Q = sum_k q_k).  The row sum holds the parent's own term
 // L_par = q_par e^{-|u_j - u_par|^2 / (2 sigma_j^2)}, so with
 //   W^2 = 2 (ln Q - ln L_par + 53 ln 2)
 // the omitted mass is at most 2^-53 of the row sum: one unit roundoff of the
 // sum itself.  The parent always lies inside (W^2 >= |u_j - u_par|^2 /
 // sigma_j^2 because Q >= q_par).  The result is capped at kWindow; a missing
-// or zero parent weight leaves kWindow.  Returns the half-width W sigma_j.
-__device__ __forceinline__ double window_halfwidth(const double* uj, double sj, const double* up, double qpar,
+// or zero parent weight leaves kWindow.  Returns the radius W sigma_j.
+__device__ __forceinline__ double window_radius(const double* uj, double sj, const double* up, double qpar,
                                                    double Q)
 {
     double W = kWindow;
@@ -160,14 +124,6 @@ __device__ __forceinline__ double window_halfwidth(const double* uj, double sj, 
     return W * sj;
 }
 
-// 32-bit monotone key of a unit-cube coordinate (truncation: keys tie within
-// 2.4e-10, far below the window margin 0.07 sigma >= 7e-10).
-__device__ __forceinline__ unsigned long long coord_key32(double u)
-{
-    const double c = u < 0.0 ? 0.0 : (u > 1.0 ? 1.0 : u);
-    return (unsigned long long)(unsigned int)(c * 4294967295.0);
-}
-
 // 7-bit half-octave of a step size: rows of similar sigma share windows well
 // (half-octaves give 2.5% fewer evaluated terms than octaves at N = 131072
 // and 6% at N = 2^20).
@@ -180,18 +136,6 @@ __device__ __forceinline__ unsigned long long sigma_half_octave(double s)
     return (unsigned long long)h;
 }
 
-// first index in sorted v[0..n) with v >= x (or > x when strict)
-__device__ __forceinline__ int lower_index(const double* v, int n, double x, bool strict)
-{
-    int lo = 0, hi = n;
-    while (lo < hi) {
-        const int mid = (lo + hi) >> 1;
-        if (strict ? (v[mid] <= x) : (v[mid] < x)) lo = mid + 1;
-        else hi = mid;
-    }
-    return lo;
-}
-
 __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
 {
 #pragma unroll
@@ -199,23 +143,339 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
     return v;
 }
 
-__device__ __forceinline__ double wave_min(double v)
+__device__ __forceinline__ float wave_minf(float v)
 {
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const double o = __shfl_xor(v, off, kWave);
-        v = o < v ? o : v;
-    }
+    for (int off = 32; off > 0; off >>= 1) v = fminf(v, __shfl_xor(v, off, kWave));
     return v;
 }
-__device__ __forceinline__ double wave_max(double v)
+__device__ __forceinline__ float wave_maxf(float v)
 {
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const double o = __shfl_xor(v, off, kWave);
-        v = o > v ? o : v;
-    }
+    for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off, kWave));
     return v;
+}
+
+// ---- sort order ------------------------------------------------------------
+// Rows and columns are put in the order of a bit-interleaved (Morton) code of
+// their coordinates, scaled to the columns' box, so that 64 neighbours of
+// either lie close together in all eight coordinates.  The interleaving spends
+// its bits where they shrink the cells most: each next bit halves the
+// coordinate whose cell is widest, measured in the columns' standard deviation.
+__device__ __forceinline__ uint32_t cell20(double u, double lo, double inv)
+{
+    const double c = (u - lo) * inv;
+    return (uint32_t)((c < 0.0 ? 0.0 : (c > 1.0 ? 1.0 : c)) * 1048575.0);
+}
+
+// First 32 bits of the code; cells: this thread's column of an LDS array
+// (stride threads apart), so that the coordinate may be picked at run time.
+__device__ __forceinline__ uint32_t morton32(const WeightGeom& g, const uint32_t* cells, int stride)
+{
+    uint32_t key = 0;
+    for (int i = 0; i < 32; ++i) {
+        const int s = g.seq[i];
+        key = (key << 1) | ((cells[(s & 7) * stride] >> (19 - (s >> 3))) & 1u);
+    }
+    return key;
+}
+
+// From per-coordinate sums s1, sums of squares s2, minima and maxima over M
+// columns (one thread).
+__device__ __forceinline__ void make_geom(const double* s1, const double* s2, const double* mn, const double* mx,
+                                          double M, WeightGeom& g)
+{
+    double w[kNP];
+    int bits[kNP];
+    for (int d = 0; d < kNP; ++d) {
+        const double mean = s1[d] / M;
+        const double var = s2[d] / M - mean * mean;
+        w[d] = var > 0.0 ? var : 0.0;
+        bits[d] = 0;
+        const bool any = mx[d] >= mn[d];  // false without columns
+        g.lo[d] = any ? mn[d] : 0.0;
+        g.inv[d] = mx[d] > mn[d] ? 1.0 / (mx[d] - mn[d]) : 0.0;
+        g.mid[d] = any ? 0.5 * (mn[d] + mx[d]) : 0.5;
+    }
+    for (int i = 0; i < 32; ++i) {
+        int best = 0;
+        double bw = -1.0;
+#pragma unroll
+        for (int d = 0; d < kNP; ++d)
+            if (bits[d] < 20 && w[d] > bw) {
+                bw = w[d];
+                best = d;
+            }
+        int nb = 0;
+#pragma unroll
+        for (int d = 0; d < kNP; ++d)
+            if (d == best) {
+                nb = bits[d]++;
+                w[d] *= 0.25;
+            }
+        g.seq[i] = best | (nb << 3);
+    }
+}
+
+// ---- pair test -------------------------------------------------------------
+// Which columns any of 64 rows needs, by one matrix product in float16: with
+// f = 4096 (u - mid) = h + l (two float16 parts),
+//   |f_j - f_k|^2 - R_j^2 = n_j - R_j^2 + n_k - 2 (h_j h_k + h_j l_k + l_j h_k) + ...
+// in 24 products of the parts and 2 x 3 for the squared norms (three float16
+// parts each, times 32768): K = 30 of 32, accumulated in float32.  The row's
+// constant is lowered by a bound on everything the test may be wrong by, so
+// that no pair inside a row's window is lost: at most 33 sums of partial sums
+// below 2 (n_j + n_k) + R_j^2, each off by 2^-23 of it, plus the dropped l_j l_k
+// and the parts' own roundings (2^-20 of n_j + n_k; 16 covers parts that are
+// subnormal), where n_k <= (sqrt(n_j) + R)^2 for a column inside the window:
+// together below (n_j + n_k) 2^-16 + 16.
+typedef _Float16 half8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+constexpr double kOpScale = 4096.0, kNormScale = 32768.0;
+
+__device__ __forceinline__ void split3(double v, _Float16* o)
+{
+    for (int i = 0; i < 3; ++i) {
+        o[i] = (_Float16)(float)v;
+        v -= (double)(float)o[i];
+    }
+}
+
+// h, l and the squared norm (in units of f^2) of one point
+__device__ __forceinline__ double split_point(const double* u, const WeightGeom& g, half8& h, half8& l)
+{
+    double n = 0.0;
+#pragma unroll
+    for (int d = 0; d < kNP; ++d) {
+        const double f = (u[d] - g.mid[d]) * kOpScale;
+        h[d] = (_Float16)(float)f;
+        l[d] = (_Float16)(float)(f - (double)(float)h[d]);
+        n += f * f;
+    }
+    return n;
+}
+
+__device__ __forceinline__ void column_operand(const double* u, const WeightGeom& g, half8* op)
+{
+    const double n = split_point(u, g, op[0], op[1]);
+    _Float16 p[3];
+    split3(n / kNormScale, p);
+    const _Float16 s = (_Float16)(float)kNormScale;
+    op[2] = half8{p[0], p[1], p[2], s, s, s, (_Float16)0, (_Float16)0};
+}
+
+__device__ __forceinline__ void row_operand(const double* u, const WeightGeom& g, double radius, half8* op)
+{
+    const double n = split_point(u, g, op[0], op[1]);
+#pragma unroll
+    for (int d = 0; d < kNP; ++d) {
+        op[0][d] = op[0][d] * (_Float16)-2;
+        op[1][d] = op[1][d] * (_Float16)-2;
+    }
+    const double R = (radius < 3.0 ? radius : 3.0) * kOpScale;  // 3 > the cube's diagonal
+    const double far = __builtin_sqrt(n) + R;
+    const double m = n - R * R - ((n + far * far) * 0x1p-16 + 16.0);
+    _Float16 p[3];
+    split3(m / kNormScale, p);
+    const _Float16 s = (_Float16)(float)kNormScale;
+    op[2] = half8{s, s, s, p[0], p[1], p[2], (_Float16)0, (_Float16)0};
+}
+
+// a row that needs nothing (the padding of the last group)
+__device__ __forceinline__ void null_operand(half8* op)
+{
+    const _Float16 z = (_Float16)0, s = (_Float16)(float)kNormScale;
+    op[0] = op[1] = half8{z, z, z, z, z, z, z, z};
+    op[2] = half8{s, s, s, (_Float16)60000.0f, z, z, z, z};
+}
+
+// Sorted slot i of the columns or rows from point u (real: not padding).  The
+// threads of a wave hold 64 consecutive slots and reduce their box.
+__device__ __forceinline__ void store_box(float* box, const double* u, bool real)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+#pragma unroll
+    for (int d = 0; d < kNP; ++d) {
+        const float v = (float)u[d];
+        const float lo = wave_minf(real ? v : __builtin_inff()), hi = wave_maxf(real ? v : -__builtin_inff());
+        if (lane == 0) {
+            box[d] = lo;
+            box[kNP + d] = hi;
+        }
+    }
+}
+
+__device__ __forceinline__ float box_threshold(float radius);
+
+__device__ __forceinline__ void gather_column(const WeightCols& c, const WeightGeom& g, size_t i, bool real,
+                                              const double* src)
+{
+    double u[kNP];
+#pragma unroll
+    for (int d = 0; d < kNP; ++d) u[d] = real ? src[d] : g.mid[d];
+    half8 op[3];
+    column_operand(u, g, op);
+#pragma unroll
+    for (int d = 0; d < kNP; ++d) c.u[i * kNP + d] = u[d];
+    c.q[i] = real ? src[kNP] : 0.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) ((half8*)c.op)[k * c.pad + i] = op[k];
+    store_box(c.box + i / kColTile * 16, u, real);
+}
+
+__device__ __forceinline__ void gather_row(const WeightRows& w, const WeightGeom& g, size_t i, bool real,
+                                           const double* src, double sigma, double radius, const double* ex)
+{
+    double u[kNP];
+#pragma unroll
+    for (int d = 0; d < kNP; ++d) u[d] = real ? src[d] : g.mid[d];
+    half8 op[3];
+    if (real) row_operand(u, g, radius, op);
+    else null_operand(op);
+#pragma unroll
+    for (int d = 0; d < kNP; ++d) w.u[i * kNP + d] = u[d];
+    w.scale[i] = real ? row_scale(sigma, ex) : 0.0;
+    w.r2[i] = real ? radius * radius : -1.0;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) ((half8*)w.op)[k * w.pad + i] = op[k];
+    float* box = w.box + i / kWave * 17;
+    store_box(box, u, real);
+    const float R = wave_maxf(real ? (float)radius * 1.000001f : 0.0f);
+    if ((threadIdx.x & (kWave - 1)) == 0) box[16] = box_threshold(R);
+}
+
+// Threshold of the box test on |gap|^2 (float32 coordinates are off by 6e-8, a
+// gap's length by at most 3.4e-7) for the largest radius of a row group.
+__device__ __forceinline__ float box_threshold(float radius)
+{
+    return radius * radius * 1.00001f + 1e-6f * radius + 1e-12f;
+}
+
+// Of the tiles [s0, s0 + 64) below t1, those whose box comes near enough to the
+// row group's box (a lane per tile).
+__device__ __forceinline__ unsigned long long near_tiles(const WeightRows& rows, const WeightCols& cols, int group,
+                                                         int lane, int s0, int t1)
+{
+    const float* box = rows.box + (size_t)group * 17;
+    bool need = false;
+    if (s0 + lane < t1) {
+        const float* tb = cols.box + (size_t)(s0 + lane) * 16;
+        float g2 = 0.0f;
+#pragma unroll
+        for (int d = 0; d < kNP; ++d) {
+            const float g = fmaxf(fmaxf(tb[d] - box[8 + d], box[d] - tb[8 + d]), 0.0f);
+            g2 += g * g;
+        }
+        need = g2 <= box[16];
+    }
+    return __ballot(need);
+}
+
+// One wave's 64 rows (a lane each) against the column tiles [t0, t1): the sum
+// of this lane's row.  Bound by FP64 issue, so the work is in choosing what to
+// evaluate: a lane per tile tests the tile's box against the rows' box; a tile
+// that passes is tested pair by pair on the matrix cores (pair test above, four
+// 32x32 products a half tile; with the lists 11% of the instructions in stage 1
+// of N = 131072);
+// the columns that some row needs go to a list in LDS, and the list is taken
+// four at a time, their scalar loads issued together.  At N = 131072 the lists
+// hold 53, 36, 24, 9, 3 and 1% of all pairs in stages 1, 2, 3, 5, 7 and 9
+// (a window on one sorted coordinate evaluated 80, 66, 53, 29, 13 and 8%; the
+// rows' own windows hold 36, 21, 13, 3, 1 and 0.3%).  Two interleaved sums
+// (even and odd places of the list), flushed once a tile.
+// window: pairs of this wave inside the rows' own windows, over all lanes.
+// first: near_tiles() of the first kWave tiles.
+__device__ __forceinline__ double row_sum(const WeightRows& rows, const WeightCols& cols, int group, int lane, int t0,
+                                          int t1, int M, unsigned long long first, const double* T, uint32_t* list,
+                                          const double* ex, uint32_t& listed, uint32_t& window)
+{
+    const int r = group * kWave + lane;
+    double uj[kNP];
+#pragma unroll
+    for (int d = 0; d < kNP; ++d) uj[d] = rows.u[(size_t)r * kNP + d];
+    const double cj = rows.scale[r], R2 = rows.r2[r];
+    const bool upper = lane >= 32;
+    half8 a0[2], a1[2];
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+        const size_t i = (size_t)group * kWave + 32 * b + (lane & 31);
+        a0[b] = ((const half8*)rows.op)[i];
+        a1[b] = ((const half8*)rows.op)[(upper ? 2 : 1) * rows.pad + i];
+    }
+    const half8* ch = (const half8*)cols.op;
+    const half8* cb0 = ch + (upper ? cols.pad : 0);       // h below, l above
+    const half8* cb1 = ch + (upper ? 2 * cols.pad : 0);   // h below, norms above
+    const uint32_t kbase = (uint32_t)t0 * kColTile;
+    const const_col_ptr cu = (const_col_ptr)(cols.u + (size_t)kbase * kNP), cq = (const_col_ptr)(cols.q + kbase);
+    double total = 0.0;
+    uint32_t cnt = 0, pos = 0;
+    auto term = [&](const Col& c, double& p) {
+        const double D = dist2(uj, c);
+        window += (uint32_t)__popcll(__ballot(D <= R2));
+        p = __builtin_fma(c.q, term_exp(D, cj, T, ex), p);
+    };
+    for (int s0 = t0; s0 < t1; s0 += kWave) {
+        unsigned long long tiles = s0 == t0 ? first : near_tiles(rows, cols, group, lane, s0, t1);
+        while (tiles) {
+            const int t = s0 + __builtin_ctzll(tiles);
+            tiles &= tiles - 1;
+            const int k0 = t * kColTile;
+            unsigned long long bits = 0;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const size_t k = (size_t)k0 + 32 * h + (lane & 31);
+                const half8 b0 = cb0[k], b1 = cb1[k];
+                f32x16 c[2];
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    c[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0[b], b0, f32x16{}, 0, 0, 0);
+                    c[b] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1[b], b1, c[b], 0, 0, 0);
+                }
+                float m = fminf(c[0][0], c[1][0]);
+#pragma unroll
+                for (int i = 1; i < 16; ++i) m = fminf(fminf(c[0][i], c[1][i]), m);
+                const unsigned long long bal = __ballot(m <= 0.0f);
+                bits |= (unsigned long long)((uint32_t)bal | (uint32_t)(bal >> 32)) << (32 * h);
+            }
+            const int left = M - k0;
+            if (left < kColTile) bits &= (1ull << left) - 1ull;
+            if ((bits >> lane) & 1ull)
+                list[(cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(bits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bits, 0))) &
+                     (kListLen - 1)] = (uint32_t)(k0 - (int)kbase + lane);
+            cnt += (uint32_t)__popcll(bits);
+            // the lanes' entries are read back by the whole wave
+            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            // the next near tile on its way into the cache while this one is evaluated
+            const size_t kn = (size_t)(s0 + (tiles ? __builtin_ctzll(tiles) : t - s0)) * kColTile + lane;
+            const float touch0 = ((const float*)(cols.u + kn * kNP))[0], touch1 = ((const float*)(cols.q + kn))[0],
+                        touch2 = ((const float*)(ch + kn))[0], touch3 = ((const float*)(ch + cols.pad + kn))[0],
+                        touch4 = ((const float*)(ch + 2 * cols.pad + kn))[0];
+            double p0 = 0.0, p1 = 0.0;
+            while (cnt - pos >= 4) {
+                const uint4 e = *(const uint4*)(list + (pos & (kListLen - 1)));
+                pos += 4;
+                const Col c0 = load_col(cu, cq, __builtin_amdgcn_readfirstlane(e.x)),
+                          c1 = load_col(cu, cq, __builtin_amdgcn_readfirstlane(e.y)),
+                          c2 = load_col(cu, cq, __builtin_amdgcn_readfirstlane(e.z)),
+                          c3 = load_col(cu, cq, __builtin_amdgcn_readfirstlane(e.w));
+                term(c0, p0);
+                term(c1, p1);
+                term(c2, p0);
+                term(c3, p1);
+            }
+            total += p0 + p1;
+            asm volatile("" ::"v"(touch0), "v"(touch1), "v"(touch2), "v"(touch3), "v"(touch4));
+        }
+    }
+    double p = 0.0;
+    for (; pos < cnt; ++pos) {
+        const uint32_t k = __builtin_amdgcn_readfirstlane(list[pos & (kListLen - 1)]);
+        term(load_col(cu, cq, k), p);
+    }
+    listed = cnt;
+    return total + p;
 }
 
 }  // namespace wterm

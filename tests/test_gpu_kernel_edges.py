@@ -92,3 +92,58 @@ def test_quad_and_lane_runs_agree(kw):
     assert all(np.array_equal(x, y) for x, y in zip(wa, wb))
     if "max_attempts" in kw:
         assert ia[1]["invalid"] > 0
+
+
+@pytest.mark.parametrize("n", [2, 3, 63, 64, 65, 127, 128, 129, 1000, 4097])
+def test_weights_at_tile_edges(oracle, n):
+    """Importance weights with rows and columns on both sides of a wave's 64
+    rows, a workgroup's 128 and a tile's 64 columns: 1e-12 relative, the bar
+    of the whole runs."""
+    w = W.tiny(n_particles=n, n_days=8, n_rounds=3, seed=40 + n)
+    obs = oracle.observations(w)
+    ref = oracle.run(w, obs)
+    assert ref.rc == 0
+    with A.Context(w, obs) as ctx:
+        for i in range(w.n_rounds):
+            ctx.round()
+            _, d, wt = ctx.weights()
+            assert np.array_equal(d, ref.dist[i])
+            np.testing.assert_allclose(wt, ref.W[i], rtol=1e-12, atol=0, err_msg=str(i))
+
+
+def _own_pairs(prev_u, q, pop):
+    """Pairs within the rows' windows, by the window's definition (double
+    precision), and those within 1e-9 of its edge."""
+    keep = q > 0
+    C, Q = prev_u[keep], float(q.astype(np.float64).sum())
+    u, s, par = pop["u"], pop["sigma"], pop["parent"]
+    x = ((prev_u[par] - u) ** 2).sum(1) / (2 * s * s)
+    win = np.sqrt(2 * (np.log(Q) - np.log(q[par].astype(np.float64)) + x + 53 * 0.6931471805599453))
+    r2 = (np.minimum(win, 37.7) * s) ** 2
+    inside = edge = 0
+    for j in range(len(u)):
+        d2 = ((C - u[j]) ** 2).sum(1)
+        inside += int((d2 <= r2[j]).sum())
+        edge += int((np.abs(d2 - r2[j]) <= 1e-9 * r2[j]).sum())
+    return inside, edge
+
+
+@pytest.mark.parametrize("kw", [dict(), dict(population=10**7, n_days=40, surv_ratio=0.3), dict(lo=(0.2, 5.0, 0.0, 0.0, 0.1, 0.0, 0.0, 1.0), hi=(0.2, 5.0, 1.0, 1.0, 0.1, 0.5, 0.5, 1.0)),
+                                dict(step_schedule=W.STEP_FIXED, beta_a=0.02, beta_b=3), dict(step_schedule=W.STEP_FIXED, beta_a=30.0, beta_b=2)])
+def test_weights_leave_out_no_pair_of_a_window(kw):
+    """Every (row, column) pair inside a row's own window is evaluated: the
+    count of such pairs among the evaluated ones equals the count over all
+    pairs.  Wide and tiny step sizes, fixed coordinates."""
+    w = W.tiny(n_particles=3001, n_days=10, n_rounds=4, seed=77).with_(**kw)
+    obs = A.observations(w)
+    with A.Context(w, obs) as ctx:
+        prev = None
+        for i in range(w.n_rounds):
+            info = ctx.round()
+            pop = ctx.population()
+            if i:
+                q, _ = ctx.resampling()
+                inside, edge = _own_pairs(prev, q, pop)
+                assert abs(info["weight_window_terms"] - inside) <= edge, i
+                assert inside - edge <= info["weight_terms"] <= info["weight_pairs"]
+            prev = pop["u"]
