@@ -56,7 +56,22 @@ __device__ __forceinline__ double bmax(double v, double* sh)
     return r;
 }
 
-using bsel::bscan_excl;
+// Exclusive scan of one value per thread (Hillis-Steele in LDS).
+__device__ __forceinline__ unsigned long long bscan_excl(unsigned long long v, unsigned long long* sh)
+{
+    const int t = threadIdx.x;
+    sh[t] = v;
+    __syncthreads();
+    for (int off = 1; off < kBlock; off <<= 1) {
+        const unsigned long long x = t >= off ? sh[t - off] : 0ull;
+        __syncthreads();
+        sh[t] += x;
+        __syncthreads();
+    }
+    const unsigned long long r = sh[t] - v;
+    __syncthreads();
+    return r;
+}
 
 // ------------------------------------------------------------------ begin/end
 
@@ -655,15 +670,14 @@ __global__ __launch_bounds__(kBlock) void bnormalise_kernel(BatchArgs a, int uni
 
 // ------------------------------------------------------------------ select
 
-// One block per run: eq. 8 type-7 percentile by radix select in LDS (same
-// digits and interpolation as the single-run kernels).
-__global__ __launch_bounds__(kBlock) void bselect_kernel(BatchArgs a)
+// One block per run: eq. 8 type-7 percentile.
+__global__ __launch_bounds__(bsel::kThreads) void bselect_kernel(BatchArgs a)
 {
     __shared__ bsel::Shared sh;
     const BRun& R = a.runs[blockIdx.x];
     BState& S = a.st[blockIdx.x];
     if (S.failed) return;  // uniform across the block
-    const double res = bsel::quantile7(R.d[S.nxt], R.N, 1, R.surv_ratio, sh);
+    const double res = bsel::quantile7(R.d[S.nxt], R.N, R.surv_ratio, sh);
     if (threadIdx.x == 0) S.eps_next = res;
 }
 
@@ -699,7 +713,7 @@ void batch_launch_stage(const BatchArgs& a, bool stage0, hipStream_t s)
         hipLaunchKernelGGL(bfinalize_kernel, dim3(a.n_fin_blocks), bw, 0, s, a);
     }
     hipLaunchKernelGGL(bnormalise_kernel, dim3(a.n_runs), b, 0, s, a, stage0 ? 1 : 0);
-    hipLaunchKernelGGL(bselect_kernel, dim3(a.n_runs), b, 0, s, a);
+    hipLaunchKernelGGL(bselect_kernel, dim3(a.n_runs), dim3(bsel::kThreads), 0, s, a);
     hipLaunchKernelGGL(end_kernel, dim3(1), b, 0, s, a);
 }
 

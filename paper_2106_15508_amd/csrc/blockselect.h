@@ -1,8 +1,18 @@
 // blockselect.h -- one workgroup's exact type-7 quantile of n non-negative
-// doubles (eq. 8's percentile; numpy "linear" interpolation), by radix
-// select on the IEEE bit patterns in LDS: 11/11/11/11/11/9-bit digits,
-// both order statistics of the interpolation tracked at once.  Shared by the
-// batched mode's per-run percentile and the predictive bands.
+// doubles (eq. 8's percentile; numpy "linear" interpolation): the order
+// statistic by radix select on the IEEE bit patterns, the next one beside it.
+// Used by the single run's and the batched runs' percentile and by the
+// predictive bands.
+//
+// Bound by the passes over the data (L2 to one compute unit) and by barriers.
+// A pass finds the highest bit in which the values differ, a second one
+// histograms the 11 bits from there (values of one stage share sign, exponent
+// and often more, so digits at fixed places would send every value to the same
+// few bins and the same LDS words), a third collects the bin that holds the
+// rank, which is finished in LDS; only bins of more than kKeep values are
+// histogrammed again, at most until their values are equal.  Three passes where
+// six fixed digits for two ranks took twelve: 32768 values x 453 rows x 3
+// quantiles 1226 -> 427 us.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -12,100 +22,181 @@
 namespace abcsmc {
 namespace bsel {
 
+constexpr int kThreads = 1024;
+constexpr int kWaves = kThreads / kWave;
 constexpr int kBins = 2048;
+constexpr int kKeep = 256;  // values finished in LDS, a thread each
 
 struct Shared {
-    unsigned int h[2][kBins];
-    unsigned long long part[kBlock];
-    unsigned long long st[8];
-    double res;
+    unsigned int h[kBins];
+    unsigned long long keep[kKeep];
+    unsigned long long lo[kWaves], hi[kWaves];
+    unsigned int sum[kWaves];
+    unsigned int n_keep, bin, below, count;
+    unsigned long long xa, xb;
 };
 
-__device__ __forceinline__ unsigned long long bscan_excl(unsigned long long v, unsigned long long* sh)
+__device__ __forceinline__ unsigned long long wave_min64(unsigned long long v)
 {
-    const int t = threadIdx.x;
-    sh[t] = v;
-    __syncthreads();
-    for (int off = 1; off < kBlock; off <<= 1) {
-        const unsigned long long x = t >= off ? sh[t - off] : 0ull;
-        __syncthreads();
-        sh[t] += x;
-        __syncthreads();
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+        const unsigned long long o = __shfl_xor(v, off, kWave);
+        v = o < v ? o : v;
     }
-    const unsigned long long r = sh[t] - v;
-    __syncthreads();
-    return r;
+    return v;
+}
+__device__ __forceinline__ unsigned long long wave_max64(unsigned long long v)
+{
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) {
+        const unsigned long long o = __shfl_xor(v, off, kWave);
+        v = o > v ? o : v;
+    }
+    return v;
 }
 
-// x[k * stride], k < n (n >= 1); every thread of the block calls it and gets
-// the result.
-__device__ __forceinline__ double quantile7(const double* x, int64_t n, int64_t stride, double alpha, Shared& S)
+__device__ __forceinline__ unsigned long long bits_of(double v)
+{
+    // distances and counts are never negative; a NaN sorts above +inf
+    return (unsigned long long)__double_as_longlong(v);
+}
+
+// Ranks r0, r1 of the two order statistics that the type-7 quantile alpha of n
+// values lies between, and the quantile from them (numpy's arithmetic).
+__device__ __forceinline__ void ranks7(int n, double alpha, int& r0, int& r1)
 {
     const double v = ((double)n - 1.0) * alpha;
-    long long r0, r1;
     if (v >= (double)n - 1.0) {
         r0 = r1 = n - 1;
     } else if (v < 0.0) {
         r0 = r1 = 0;
     } else {
-        r0 = (long long)__builtin_floor(v);
+        r0 = (int)__builtin_floor(v);
         r1 = r0 + 1;
     }
-    if (threadIdx.x == 0) {
-        S.st[0] = S.st[1] = S.st[2] = S.st[3] = 0ull;  // prefixes, masks
-        S.st[4] = (unsigned long long)r0;
-        S.st[5] = (unsigned long long)r1;
+}
+
+__device__ __forceinline__ double interpolate7(int n, double alpha, unsigned long long xa_bits, unsigned long long xb_bits)
+{
+    int r0, r1;
+    ranks7(n, alpha, r0, r1);
+    const double xa = __longlong_as_double((long long)xa_bits), xb = __longlong_as_double((long long)xb_bits);
+    if (r0 == r1) return xa;
+    const double v = ((double)n - 1.0) * alpha;
+    const double g = v - __builtin_floor(v);
+    const double diff = xb - xa;
+    return g >= 0.5 ? xb - diff * (1.0 - g) : xa + diff * g;
+}
+
+// Bits of the order statistics rank and rank + 1 (all ones if there is none)
+// of x[k], k < n (1 <= n < 2^31), in S.xa and S.xb; every thread of the
+// kThreads calls it.
+__device__ __forceinline__ void order_pair(const double* __restrict__ x, int n, unsigned int rank, Shared& S)
+{
+    const int t = threadIdx.x, w = t / kWave, lane = t & (kWave - 1);
+    // the range of the values
+    unsigned long long lo = ~0ull, hi = 0ull;
+#pragma unroll 8
+    for (int k = t; k < n; k += kThreads) {
+        const unsigned long long b = bits_of(x[k]);
+        lo = b < lo ? b : lo;
+        hi = b > hi ? b : hi;
+    }
+    lo = wave_min64(lo);
+    hi = wave_max64(hi);
+    if (lane == 0) {
+        S.lo[w] = lo;
+        S.hi[w] = hi;
     }
     __syncthreads();
-    for (int pass = 0; pass < 6; ++pass) {
-        for (int b = threadIdx.x; b < 2 * kBins; b += kBlock) (&S.h[0][0])[b] = 0u;
+    lo = wave_min64(S.lo[lane & (kWaves - 1)]);
+    hi = wave_max64(S.hi[lane & (kWaves - 1)]);
+    unsigned int count = (unsigned int)n;  // values in [lo, hi], the rank counted from there
+    // values in [lo, hi] (a range of one prefix) until they are few or equal
+    while (count > (unsigned)kKeep && lo != hi) {
+        const int top = 63 - __builtin_clzll(lo ^ hi);
+        const int sh = top > 10 ? top - 10 : 0;
+        const unsigned long long base = lo >> sh;
+        for (int b = t; b < kBins; b += kThreads) S.h[b] = 0u;
         __syncthreads();
-        const int sh = pass < 5 ? 53 - 11 * pass : 0;
-        const unsigned long long dmk = (1ull << (pass < 5 ? 11 : 9)) - 1ull;
-        const unsigned long long p0 = S.st[0], p1 = S.st[1], m0 = S.st[2], m1 = S.st[3];
-        for (int64_t k = threadIdx.x; k < n; k += kBlock) {
-            const unsigned long long bits = (unsigned long long)__double_as_longlong(x[k * stride]);
-            const unsigned int dig = (unsigned int)((bits >> sh) & dmk);
-            if ((bits & m0) == p0) atomicAdd(&S.h[0][dig], 1u);
-            if ((bits & m1) == p1) atomicAdd(&S.h[1][dig], 1u);
+#pragma unroll 8
+        for (int k = t; k < n; k += kThreads) {
+            const unsigned long long b = bits_of(x[k]);
+            if (b >= lo && b <= hi) atomicAdd(&S.h[(unsigned)((b >> sh) - base)], 1u);
         }
         __syncthreads();
-        const int nb = (int)dmk + 1;
-        const int per = (nb + kBlock - 1) / kBlock;
-        for (int which = 0; which < 2; ++which) {
-            const unsigned long long rank = S.st[4 + which];
-            const int b0 = threadIdx.x * per, b1 = min(nb, b0 + per);
-            unsigned long long s = 0;
-            for (int b = b0; b < b1; ++b) s += S.h[which][b];
-            unsigned long long run = bscan_excl(s, S.part);
-            for (int b = b0; b < b1; ++b) {
-                if (run <= rank && rank < run + S.h[which][b]) {
-                    S.st[4 + which] = rank - run;
-                    S.st[which] |= (unsigned long long)b << sh;
-                    S.st[2 + which] |= dmk << sh;
-                }
-                run += S.h[which][b];
+        // exclusive prefix of the bins, two a thread
+        const unsigned int h0 = S.h[2 * t], h1 = S.h[2 * t + 1];
+        unsigned int incl = h0 + h1;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const unsigned int o = __shfl_up(incl, off, kWave);
+            if (lane >= off) incl += o;
+        }
+        if (lane == kWave - 1) S.sum[w] = incl;
+        __syncthreads();
+        unsigned int below = incl - h0 - h1;
+        for (int i = 0; i < w; ++i) below += S.sum[i];
+        if (rank >= below && rank - below < h0 + h1) {
+            const bool second = rank - below >= h0;
+            S.bin = 2 * t + (second ? 1 : 0);
+            S.below = below + (second ? h0 : 0);
+            S.count = second ? h1 : h0;
+        }
+        __syncthreads();
+        rank -= S.below;
+        count = S.count;
+        const unsigned long long first = (base + S.bin) << sh, last = first + ((1ull << sh) - 1ull);
+        lo = first > lo ? first : lo;
+        hi = last < hi ? last : hi;
+        __syncthreads();
+    }
+    // the values in [lo, hi] (their number is known to be small, or they are
+    // equal) and the smallest value above them
+    const bool equal = lo == hi;
+    if (t == 0) S.n_keep = 0;
+    __syncthreads();
+    unsigned long long above = ~0ull;
+#pragma unroll 8
+    for (int k = t; k < n; k += kThreads) {
+        const unsigned long long b = bits_of(x[k]);
+        if (b > hi) above = b < above ? b : above;
+        else if (!equal && b >= lo) S.keep[atomicAdd(&S.n_keep, 1u)] = b;
+    }
+    above = wave_min64(above);
+    if (lane == 0) S.lo[w] = above;
+    __syncthreads();
+    above = wave_min64(S.lo[lane & (kWaves - 1)]);
+    if (equal) {
+        if (t == 0) {
+            S.xa = lo;
+            S.xb = rank + 1 < count ? lo : above;
+        }
+    } else {
+        if (t == 0 && rank + 1 >= count) S.xb = above;
+        if (t < (int)count) {
+            const unsigned long long mine = S.keep[t];
+            unsigned int less = 0;
+            for (int i = 0; i < (int)count; ++i) {
+                const unsigned long long o = S.keep[i];
+                less += (o < mine || (o == mine && i < t)) ? 1u : 0u;
             }
-            __syncthreads();
+            if (less == rank) S.xa = mine;
+            if (less == rank + 1) S.xb = mine;
         }
     }
-    if (threadIdx.x == 0) {
-        const double xa = __longlong_as_double((long long)S.st[0]);
-        const double xb = __longlong_as_double((long long)S.st[1]);
-        double res;
-        if (r0 == r1) {
-            res = xa;
-        } else {
-            const double g = v - __builtin_floor(v);
-            const double diff = xb - xa;
-            res = g >= 0.5 ? xb - diff * (1.0 - g) : xa + diff * g;
-        }
-        S.res = res;
-    }
     __syncthreads();
-    const double out = S.res;
+}
+
+// The quantile; every thread gets it.
+__device__ __forceinline__ double quantile7(const double* __restrict__ x, int n, double alpha, Shared& S)
+{
+    int r0, r1;
+    ranks7(n, alpha, r0, r1);
+    order_pair(x, n, (unsigned int)r0, S);
+    const double r = interpolate7(n, alpha, S.xa, S.xb);
     __syncthreads();
-    return out;
+    return r;
 }
 
 }  // namespace bsel

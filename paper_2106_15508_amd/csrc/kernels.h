@@ -94,14 +94,16 @@ struct CompactArgs {
 
 // Per-block partial results of the multi-block reductions and scans.
 constexpr int kRedMax = 4096;  // max blocks of a reduction (N <= 2^22 at 1024 per block)
+constexpr int kSelectList = 1 << 16;
 struct Scratch {
     unsigned long long* u0;  // kRedMax
     unsigned long long* u1;  // kRedMax
     unsigned long long* u2;  // kRedMax
     double* d0;              // kRedMax
     double* d1;              // kRedMax
-    unsigned int* hist;      // 2 x 2048 radix-select bins
-    unsigned long long* sel; // radix-select state: prefix[2], mask[2], rank[2], r0, r1
+    unsigned int* hist;      // 2048 bins of the multi-block select
+    unsigned long long* sel; // its state: values collected, values below the bin, values in the bin
+    double* list;            // kSelectList collected values
 };
 
 struct ResampleArgs {

@@ -32,13 +32,13 @@ __global__ __launch_bounds__(kBlock) void predict_series_kernel(PredictArgs a)
 }
 
 // One block per (day, series) row: its n_quant quantiles.
-__global__ __launch_bounds__(kBlock) void predict_band_kernel(PredictArgs a)
+__global__ __launch_bounds__(bsel::kThreads) void predict_band_kernel(PredictArgs a)
 {
     __shared__ bsel::Shared sh;
     const int64_t row = blockIdx.x;  // 3 t + c
     const double* x = a.series + (size_t)row * a.n;
     for (int k = 0; k < a.n_quant; ++k) {
-        const double v = bsel::quantile7(x, a.n, 1, a.quant[k], sh);
+        const double v = bsel::quantile7(x, (int)a.n, a.quant[k], sh);
         if (threadIdx.x == 0) a.bands[row * a.n_quant + k] = v;
     }
 }
@@ -56,7 +56,7 @@ void launch_predict(const PredictArgs& a, hipStream_t s)
         if (quad) hipLaunchKernelGGL((predict_series_kernel<1, true>), grid, dim3(kBlock), 0, s, a);
         else hipLaunchKernelGGL((predict_series_kernel<1, false>), grid, dim3(kBlock), 0, s, a);
     }
-    hipLaunchKernelGGL(predict_band_kernel, dim3((unsigned)(3 * (a.m.T + 1))), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(predict_band_kernel, dim3((unsigned)(3 * (a.m.T + 1))), dim3(bsel::kThreads), 0, s, a);
 }
 
 }  // namespace abcsmc

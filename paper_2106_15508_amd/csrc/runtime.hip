@@ -74,7 +74,8 @@ Layout make_layout(const abcsmc_config& c)
     L.scal = take(8 * sizeof(double));
     L.theta = take(N * kNP * sizeof(double));
     for (int r = 0; r < 5; ++r) L.red[r] = take(kRedMax * 8);
-    L.hist = take(2 * 2048 * sizeof(unsigned int));
+    L.hist = take(2048 * sizeof(unsigned int));
+    L.sellist = take(kSelectList * sizeof(double));
     L.sel = take(8 * sizeof(unsigned long long));
     L.wpart = take((size_t)weight_chunks((int64_t)N) * N * sizeof(double));
     const size_t npad = sort_padded_size(N);

@@ -2,9 +2,10 @@
 //   resample   prior set, eq. 10 weights and the integer CDF of eq. 11
 //   weights    N x M importance-weight row sums, windowed, FP64
 //   normalise  W = softmax(log-weights), effective sample size
-//   select     exact type-7 percentile of eq. 8 by radix select
+//   select     exact type-7 percentile of eq. 8
 // All reductions combine per-block partials in a fixed order, so every result
 // is bitwise reproducible run to run.
+#include "blockselect.h"
 #include "dmath.h"
 #include "kernels.h"
 #include "wterm.h"
@@ -434,6 +435,7 @@ __global__ __launch_bounds__(kBlock) void weights_finalize_kernel(WeightArgs a)
     if (r >= a.N) return;
     // the chunks that hold columns, in order
     double L = 0.0;
+#pragma unroll 8
     for (int c = 0; c < nch; ++c) L += a.partial[(size_t)c * a.N + r];
     const size_t j = (size_t)(a.rowkeys[r] & 0xFFFFFFFFull);
     a.logw[j] = 8.0 * dm::log(a.sigma[j]) - dm::log(L);
@@ -518,115 +520,180 @@ __global__ __launch_bounds__(kBlock) void uniform_weights_kernel(double* W, doub
 }
 
 // ---------------------------------------------------------------------------
-// eq. 8 tolerance: type-7 percentile with numpy's "linear" arithmetic:
-// v = (N-1) alpha, order statistics x_(floor v) and x_(floor v + 1) found by a
-// radix select on the IEEE bit patterns (non-negative doubles order as
-// unsigned integers; digits of 11, 11, 11, 11, 11, 9 bits from the top), then
-// a + (b-a) g, or b - (b-a)(1-g) when g >= 1/2.  Per pass: every block
-// histograms its slice in LDS and adds it to the global bins; one block then
-// picks the digit of both ranks.
+// eq. 8 tolerance: type-7 percentile with numpy's "linear" arithmetic.  Up to
+// kSelectOne values one workgroup selects (blockselect.h: three passes at one
+// compute unit's L2 rate, 25 us at 20011 values).  More take four launches of the same
+// method: the range of the values, a histogram of the 11 bits from the highest
+// one they differ in, the values of the rank's bin collected beside the
+// smallest value above it, and one workgroup that finishes among those.
+// 38-50 us at 2^17 and 54-78 at 2^18 (one workgroup: 88 and 165), where six
+// fixed digits in thirteen launches took 76 at 2^17.
 // ---------------------------------------------------------------------------
-constexpr int kBins = 2048;
-enum { kPref0 = 0, kPref1, kMask0, kMask1, kRank0, kRank1, kR0, kR1 };
+constexpr int kSelectOne = 1 << 15;
+constexpr int kBins = bsel::kBins;
 
-__device__ __forceinline__ int pass_shift(int pass) { return pass < 5 ? 53 - 11 * pass : 0; }
-__device__ __forceinline__ unsigned long long pass_mask(int pass) { return (1ull << (pass < 5 ? 11 : 9)) - 1ull; }
-
-__global__ __launch_bounds__(kBlock) void select_init_kernel(SelectArgs a)
+__global__ __launch_bounds__(bsel::kThreads) void select_one_kernel(SelectArgs a)
 {
-    const int N = a.N;
-    const double v = ((double)N - 1.0) * a.alpha;
-    long long r0, r1;
-    if (v >= (double)N - 1.0) {
-        r0 = r1 = N - 1;
-    } else if (v < 0.0) {
-        r0 = r1 = 0;
-    } else {
-        r0 = (long long)__builtin_floor(v);
-        r1 = r0 + 1;
-    }
-    for (int b = threadIdx.x; b < 2 * kBins; b += kBlock) a.sc.hist[b] = 0u;
-    if (threadIdx.x == 0) {
-        unsigned long long* st = a.sc.sel;
-        st[kPref0] = st[kPref1] = st[kMask0] = st[kMask1] = 0ull;
-        st[kRank0] = (unsigned long long)r0;
-        st[kRank1] = (unsigned long long)r1;
-        st[kR0] = (unsigned long long)r0;
-        st[kR1] = (unsigned long long)r1;
-    }
+    __shared__ bsel::Shared sh;
+    const double r = bsel::quantile7(a.x, a.N, a.alpha, sh);
+    if (threadIdx.x == 0) *a.out = r;
 }
 
-__global__ __launch_bounds__(kBlock) void select_hist_kernel(SelectArgs a, int pass)
+// Per-block minimum and maximum (u0, u1); block 0 clears the histogram and the
+// collected count.
+__global__ __launch_bounds__(kBlock) void select_range_kernel(SelectArgs a)
 {
-    __shared__ unsigned int h[2][kBins];
-    for (int b = threadIdx.x; b < 2 * kBins; b += kBlock) (&h[0][0])[b] = 0u;
-    __syncthreads();
-    const unsigned long long* st = a.sc.sel;
-    const unsigned long long p0 = st[kPref0], p1 = st[kPref1], m0 = st[kMask0], m1 = st[kMask1];
-    const int sh = pass_shift(pass);
-    const unsigned long long dmk = pass_mask(pass);
+    __shared__ unsigned long long slo[kBlock / kWave], shi[kBlock / kWave];
+    unsigned long long lo = ~0ull, hi = 0ull;
+#pragma unroll 4
     for (int k = blockIdx.x * kBlock + threadIdx.x; k < a.N; k += gridDim.x * kBlock) {
-        const unsigned long long bits = (unsigned long long)__double_as_longlong(a.x[k]);
-        const unsigned int dig = (unsigned int)((bits >> sh) & dmk);
-        if ((bits & m0) == p0) atomicAdd(&h[0][dig], 1u);
-        if ((bits & m1) == p1) atomicAdd(&h[1][dig], 1u);
+        const unsigned long long b = bsel::bits_of(a.x[k]);
+        lo = b < lo ? b : lo;
+        hi = b > hi ? b : hi;
+    }
+    lo = bsel::wave_min64(lo);
+    hi = bsel::wave_max64(hi);
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        slo[threadIdx.x / kWave] = lo;
+        shi[threadIdx.x / kWave] = hi;
     }
     __syncthreads();
-    for (int b = threadIdx.x; b < 2 * kBins; b += kBlock) {
-        const unsigned int v = (&h[0][0])[b];
-        if (v) atomicAdd(&a.sc.hist[b], v);
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kBlock / kWave; ++w) {
+            lo = slo[w] < lo ? slo[w] : lo;
+            hi = shi[w] > hi ? shi[w] : hi;
+        }
+        a.sc.u0[blockIdx.x] = lo;
+        a.sc.u1[blockIdx.x] = hi;
+    }
+    if (blockIdx.x == 0) {
+        for (int b = threadIdx.x; b < kBins; b += kBlock) a.sc.hist[b] = 0u;
+        if (threadIdx.x == 0) a.sc.sel[0] = 0ull;
     }
 }
 
-// One block: for each rank find the bin whose cumulative count passes it.
-__global__ __launch_bounds__(kBlock) void select_pick_kernel(SelectArgs a, int pass)
+// The range of all values from the blocks' (every thread gets it), the digit's
+// shift and the first bin's prefix.
+struct Digit {
+    unsigned long long lo, hi, base;
+    int sh;
+};
+
+__device__ __forceinline__ Digit select_digit(const SelectArgs& a, int G, unsigned long long* shu)
 {
-    __shared__ unsigned long long part[kBlock];
-    __shared__ unsigned long long s_bin[2], s_below[2];
-    unsigned long long* st = a.sc.sel;
-    const int sh = pass_shift(pass);
-    const int nb = (int)pass_mask(pass) + 1;
-    const int per = (nb + kBlock - 1) / kBlock;  // contiguous bins per thread
-    for (int which = 0; which < 2; ++which) {
-        const unsigned int* h = a.sc.hist + which * kBins;
-        const unsigned long long rank = st[kRank0 + which];
-        const int b0 = threadIdx.x * per, b1 = min(nb, b0 + per);
-        unsigned long long s = 0;
-        for (int b = b0; b < b1; ++b) s += h[b];
-        unsigned long long tot;
-        unsigned long long run = block_excl_scan_u64(s, part, &tot);
-        // the thread whose run contains the rank locates the bin
-        for (int b = b0; b < b1; ++b) {
-            if (run <= rank && rank < run + h[b]) {
-                s_bin[which] = (unsigned long long)b;
-                s_below[which] = run;
-            }
-            run += h[b];
-        }
-        __syncthreads();
+    Digit g{~0ull, 0ull, 0ull, 0};
+    for (int b = threadIdx.x; b < G; b += kBlock) {
+        g.lo = a.sc.u0[b] < g.lo ? a.sc.u0[b] : g.lo;
+        g.hi = a.sc.u1[b] > g.hi ? a.sc.u1[b] : g.hi;
     }
-    for (int b = threadIdx.x; b < 2 * kBins; b += kBlock) a.sc.hist[b] = 0u;
+    g.lo = bsel::wave_min64(g.lo);
+    g.hi = bsel::wave_max64(g.hi);
+    constexpr int nw = kBlock / kWave;
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        shu[threadIdx.x / kWave] = g.lo;
+        shu[nw + threadIdx.x / kWave] = g.hi;
+    }
+    __syncthreads();
+    for (int w = 0; w < nw; ++w) {
+        g.lo = shu[w] < g.lo ? shu[w] : g.lo;
+        g.hi = shu[nw + w] > g.hi ? shu[nw + w] : g.hi;
+    }
+    const int top = g.lo == g.hi ? 0 : 63 - __builtin_clzll(g.lo ^ g.hi);
+    g.sh = top > 10 ? top - 10 : 0;
+    g.base = g.lo >> g.sh;
+    __syncthreads();
+    return g;
+}
+
+__global__ __launch_bounds__(kBlock) void select_hist_kernel(SelectArgs a)
+{
+    __shared__ unsigned int h[kBins];
+    __shared__ unsigned long long shu[2 * kBlock / kWave];
+    for (int b = threadIdx.x; b < kBins; b += kBlock) h[b] = 0u;
+    const Digit g = select_digit(a, gridDim.x, shu);
+#pragma unroll 4
+    for (int k = blockIdx.x * kBlock + threadIdx.x; k < a.N; k += gridDim.x * kBlock)
+        atomicAdd(&h[(unsigned)((bsel::bits_of(a.x[k]) >> g.sh) - g.base)], 1u);
+    __syncthreads();
+    for (int b = threadIdx.x; b < kBins; b += kBlock)
+        if (h[b]) atomicAdd(&a.sc.hist[b], h[b]);
+}
+
+// Bin of the rank (every block finds it), its values collected into the list
+// (at most kSelectList of them are kept), the block's smallest value above.
+__global__ __launch_bounds__(kBlock) void select_collect_kernel(SelectArgs a)
+{
+    __shared__ unsigned long long shu[kBlock];
+    __shared__ unsigned int s_bin, s_below, s_count;
+    const Digit g = select_digit(a, gridDim.x, shu);
+    int r0, r1;
+    bsel::ranks7(a.N, a.alpha, r0, r1);
+    constexpr int per = kBins / kBlock;
+    unsigned int h[per];
+    unsigned long long s = 0, tot;
+#pragma unroll
+    for (int i = 0; i < per; ++i) {
+        h[i] = a.sc.hist[threadIdx.x * per + i];
+        s += h[i];
+    }
+    unsigned long long run = block_excl_scan_u64(s, shu, &tot);
+#pragma unroll
+    for (int i = 0; i < per; ++i) {
+        if (run <= (unsigned)r0 && (unsigned)r0 < run + h[i]) {
+            s_bin = threadIdx.x * per + i;
+            s_below = (unsigned int)run;
+            s_count = h[i];
+        }
+        run += h[i];
+    }
+    __syncthreads();
+    const unsigned long long want = g.base + s_bin;
+    unsigned long long above = ~0ull;
+#pragma unroll 4
+    for (int k = blockIdx.x * kBlock + threadIdx.x; k < a.N; k += gridDim.x * kBlock) {
+        const double x = a.x[k];
+        const unsigned long long b = bsel::bits_of(x), d = b >> g.sh;
+        if (d == want) {
+            const unsigned long long at = atomicAdd(&a.sc.sel[0], 1ull);
+            if (at < kSelectList) a.sc.list[at] = x;
+        } else if (d > want && b < above) {
+            above = b;
+        }
+    }
+    above = bsel::wave_min64(above);
+    if ((threadIdx.x & (kWave - 1)) == 0) shu[threadIdx.x / kWave] = above;
+    __syncthreads();
     if (threadIdx.x == 0) {
-        for (int which = 0; which < 2; ++which) {
-            st[kRank0 + which] -= s_below[which];
-            st[kPref0 + which] |= s_bin[which] << sh;
-            st[kMask0 + which] |= pass_mask(pass) << sh;
-        }
-        if (pass == 5) {
-            const double xa = __longlong_as_double((long long)st[kPref0]);
-            const double xb = __longlong_as_double((long long)st[kPref1]);
-            double res;
-            if (st[kR0] == st[kR1]) {
-                res = xa;
-            } else {
-                const double v = ((double)a.N - 1.0) * a.alpha;
-                const double g = v - __builtin_floor(v);
-                const double diff = xb - xa;
-                res = g >= 0.5 ? xb - diff * (1.0 - g) : xa + diff * g;
-            }
-            *a.out = res;
+        for (int w = 1; w < kBlock / kWave; ++w) above = shu[w] < above ? shu[w] : above;
+        a.sc.u2[blockIdx.x] = above;
+        if (blockIdx.x == 0) {
+            a.sc.sel[1] = s_below;
+            a.sc.sel[2] = s_count;
         }
     }
+}
+
+__global__ __launch_bounds__(bsel::kThreads) void select_finish_kernel(SelectArgs a, int G)
+{
+    __shared__ bsel::Shared sh;
+    int r0, r1;
+    bsel::ranks7(a.N, a.alpha, r0, r1);
+    const unsigned int count = (unsigned int)a.sc.sel[2], rank = (unsigned int)r0 - (unsigned int)a.sc.sel[1];
+    unsigned long long xa, xb;
+    if (count > (unsigned)kSelectList) {  // values crowded into one of 2048 bins: all of them again
+        bsel::order_pair(a.x, a.N, (unsigned int)r0, sh);
+        xa = sh.xa;
+        xb = sh.xb;
+    } else {
+        bsel::order_pair(a.sc.list, (int)count, rank, sh);
+        xa = sh.xa;
+        xb = sh.xb;
+        if (rank + 1 >= count) {
+            xb = ~0ull;
+            for (int b = 0; b < G; ++b) xb = a.sc.u2[b] < xb ? a.sc.u2[b] : xb;
+        }
+    }
+    if (threadIdx.x == 0) *a.out = bsel::interpolate7(a.N, a.alpha, xa, xb);
 }
 
 // theta_d = lo_d + u_d (hi_d - lo_d) for the copy-out of a population.
@@ -732,13 +799,15 @@ void launch_uniform_weights(double* W, double* logw, int32_t N, hipStream_t s)
 
 void launch_select(const SelectArgs& a, hipStream_t s)
 {
-    unsigned G = blocks_of(a.N, 4 * kBlock);
-    if (G > 1024) G = 1024;
-    hipLaunchKernelGGL(select_init_kernel, dim3(1), dim3(kBlock), 0, s, a);
-    for (int pass = 0; pass < 6; ++pass) {
-        hipLaunchKernelGGL(select_hist_kernel, dim3(G), dim3(kBlock), 0, s, a, pass);
-        hipLaunchKernelGGL(select_pick_kernel, dim3(1), dim3(kBlock), 0, s, a, pass);
+    if (a.N <= kSelectOne) {
+        hipLaunchKernelGGL(select_one_kernel, dim3(1), dim3(bsel::kThreads), 0, s, a);
+        return;
     }
+    const unsigned G = std::min(blocks_of(a.N, 4 * kBlock), 512u);
+    hipLaunchKernelGGL(select_range_kernel, dim3(G), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(select_hist_kernel, dim3(G), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(select_collect_kernel, dim3(G), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(select_finish_kernel, dim3(1), dim3(bsel::kThreads), 0, s, a, (int)G);
 }
 
 }  // namespace abcsmc

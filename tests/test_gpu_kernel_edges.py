@@ -147,3 +147,17 @@ def test_weights_leave_out_no_pair_of_a_window(kw):
                 assert abs(info["weight_window_terms"] - inside) <= edge, i
                 assert inside - edge <= info["weight_terms"] <= info["weight_pairs"]
             prev = pop["u"]
+
+
+@pytest.mark.parametrize("n", [2, 3, 255, 256, 257, 1000, 32767, 32768, 32769, 100_003])
+@pytest.mark.parametrize("kw", [dict(population=10**7, n_days=30), dict(population=60, n_days=3), dict(population=20_000, n_days=5)])
+def test_tolerance_is_numpys_quantile(n, kw):
+    """eq. 8 at the ends of its workgroup and multi-block forms, on spread and
+    on crowded distances (a population of 60 leaves a few dozen distinct
+    values), at ranks near both ends: equal to numpy's linear quantile."""
+    for ratio in (0.001, 0.5, 0.999):
+        w = W.C2.with_(n_particles=n, surv_ratio=ratio, **kw)
+        with A.Context(w, A.observations(w), flags=A.F_SKIP_WEIGHTS) as ctx:
+            info = ctx.round()
+            _, d, _ = ctx.weights()
+            assert info["eps_next"] == np.quantile(d, ratio), (ratio, np.unique(d).size)
