@@ -677,7 +677,7 @@ __global__ __launch_bounds__(bsel::kThreads) void bselect_kernel(BatchArgs a)
     const BRun& R = a.runs[blockIdx.x];
     BState& S = a.st[blockIdx.x];
     if (S.failed) return;  // uniform across the block
-    const double res = bsel::quantile7(R.d[S.nxt], R.N, R.surv_ratio, sh);
+    const double res = bsel::quantile7(bsel::FromMemory{R.d[S.nxt], R.N}, R.N, R.surv_ratio, sh);
     if (threadIdx.x == 0) S.eps_next = res;
 }
 

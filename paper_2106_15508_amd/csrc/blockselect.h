@@ -88,20 +88,50 @@ __device__ __forceinline__ double interpolate7(int n, double alpha, unsigned lon
     return g >= 0.5 ? xb - diff * (1.0 - g) : xa + diff * g;
 }
 
+// A thread's share of x[k], k < n: every kThreads-th value, read from memory in
+// each pass, or read once into registers (n <= K kThreads).
+struct FromMemory {
+    const double* __restrict__ x;
+    int n;
+    template <class F>
+    __device__ __forceinline__ void each(F f) const
+    {
+#pragma unroll 8
+        for (int k = threadIdx.x; k < n; k += kThreads) f(bits_of(x[k]));
+    }
+};
+
+template <int K>
+struct FromRegisters {
+    double v[K];
+    int n;
+    __device__ __forceinline__ FromRegisters(const double* x, int n) : n(n)
+    {
+#pragma unroll
+        for (int i = 0; i < K; ++i) v[i] = i * kThreads + (int)threadIdx.x < n ? x[i * kThreads + threadIdx.x] : 0.0;
+    }
+    template <class F>
+    __device__ __forceinline__ void each(F f) const
+    {
+#pragma unroll
+        for (int i = 0; i < K; ++i)
+            if (i * kThreads + (int)threadIdx.x < n) f(bits_of(v[i]));
+    }
+};
+
 // Bits of the order statistics rank and rank + 1 (all ones if there is none)
-// of x[k], k < n (1 <= n < 2^31), in S.xa and S.xb; every thread of the
-// kThreads calls it.
-__device__ __forceinline__ void order_pair(const double* __restrict__ x, int n, unsigned int rank, Shared& S)
+// of n values (1 <= n < 2^31), in S.xa and S.xb; every thread of the kThreads
+// calls it.
+template <class Values>
+__device__ __forceinline__ void order_pair(const Values& values, int n, unsigned int rank, Shared& S)
 {
     const int t = threadIdx.x, w = t / kWave, lane = t & (kWave - 1);
     // the range of the values
     unsigned long long lo = ~0ull, hi = 0ull;
-#pragma unroll 8
-    for (int k = t; k < n; k += kThreads) {
-        const unsigned long long b = bits_of(x[k]);
+    values.each([&](unsigned long long b) {
         lo = b < lo ? b : lo;
         hi = b > hi ? b : hi;
-    }
+    });
     lo = wave_min64(lo);
     hi = wave_max64(hi);
     if (lane == 0) {
@@ -119,11 +149,9 @@ __device__ __forceinline__ void order_pair(const double* __restrict__ x, int n, 
         const unsigned long long base = lo >> sh;
         for (int b = t; b < kBins; b += kThreads) S.h[b] = 0u;
         __syncthreads();
-#pragma unroll 8
-        for (int k = t; k < n; k += kThreads) {
-            const unsigned long long b = bits_of(x[k]);
+        values.each([&](unsigned long long b) {
             if (b >= lo && b <= hi) atomicAdd(&S.h[(unsigned)((b >> sh) - base)], 1u);
-        }
+        });
         __syncthreads();
         // exclusive prefix of the bins, two a thread
         const unsigned int h0 = S.h[2 * t], h1 = S.h[2 * t + 1];
@@ -157,12 +185,10 @@ __device__ __forceinline__ void order_pair(const double* __restrict__ x, int n, 
     if (t == 0) S.n_keep = 0;
     __syncthreads();
     unsigned long long above = ~0ull;
-#pragma unroll 8
-    for (int k = t; k < n; k += kThreads) {
-        const unsigned long long b = bits_of(x[k]);
+    values.each([&](unsigned long long b) {
         if (b > hi) above = b < above ? b : above;
         else if (!equal && b >= lo) S.keep[atomicAdd(&S.n_keep, 1u)] = b;
-    }
+    });
     above = wave_min64(above);
     if (lane == 0) S.lo[w] = above;
     __syncthreads();
@@ -189,11 +215,12 @@ __device__ __forceinline__ void order_pair(const double* __restrict__ x, int n, 
 }
 
 // The quantile; every thread gets it.
-__device__ __forceinline__ double quantile7(const double* __restrict__ x, int n, double alpha, Shared& S)
+template <class Values>
+__device__ __forceinline__ double quantile7(const Values& values, int n, double alpha, Shared& S)
 {
     int r0, r1;
     ranks7(n, alpha, r0, r1);
-    order_pair(x, n, (unsigned int)r0, S);
+    order_pair(values, n, (unsigned int)r0, S);
     const double r = interpolate7(n, alpha, S.xa, S.xb);
     __syncthreads();
     return r;

@@ -535,7 +535,7 @@ constexpr int kBins = bsel::kBins;
 __global__ __launch_bounds__(bsel::kThreads) void select_one_kernel(SelectArgs a)
 {
     __shared__ bsel::Shared sh;
-    const double r = bsel::quantile7(a.x, a.N, a.alpha, sh);
+    const double r = bsel::quantile7(bsel::FromMemory{a.x, a.N}, a.N, a.alpha, sh);
     if (threadIdx.x == 0) *a.out = r;
 }
 
@@ -681,11 +681,11 @@ __global__ __launch_bounds__(bsel::kThreads) void select_finish_kernel(SelectArg
     const unsigned int count = (unsigned int)a.sc.sel[2], rank = (unsigned int)r0 - (unsigned int)a.sc.sel[1];
     unsigned long long xa, xb;
     if (count > (unsigned)kSelectList) {  // values crowded into one of 2048 bins: all of them again
-        bsel::order_pair(a.x, a.N, (unsigned int)r0, sh);
+        bsel::order_pair(bsel::FromMemory{a.x, a.N}, a.N, (unsigned int)r0, sh);
         xa = sh.xa;
         xb = sh.xb;
     } else {
-        bsel::order_pair(a.sc.list, (int)count, rank, sh);
+        bsel::order_pair(bsel::FromMemory{a.sc.list, (int)count}, (int)count, rank, sh);
         xa = sh.xa;
         xb = sh.xb;
         if (rank + 1 >= count) {
