@@ -491,7 +491,7 @@ __global__ __launch_bounds__(kDimThreads) void bwgeom_kernel(BatchArgs a)
         }
         __syncthreads();
     }
-    if (t == 0) wterm::make_geom(sh[0], sh[1], sh[2], sh[3], (double)M, S.geom);
+    wterm::make_geom(sh[0], sh[1], sh[2], sh[3], (double)M, &S.geom);
 }
 
 // run owning batch-wide slot i (i < n_total)

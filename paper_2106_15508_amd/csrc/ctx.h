@@ -31,8 +31,8 @@ struct DevPop {
 // Byte layout of the device workspace (every region 256-byte aligned).
 struct Layout {
     size_t obs, pop[2][8], q, cdf, cols, st_u, st_d, st_sigma, st_parent, st_att, wave_mask, wave_off,
-        ctr, scal, theta, red[5], hist, sel, sellist, wpart, rowkeys, colkeys, scu, scq, scop, scbox, sru, srscale,
-        srr2, srop, srbox, dimpart, geom, wcounts, rwin, wtab, total;
+        ctr, theta, red[5], hist, sel, sellist, wpart, rowkeys, colkeys, scu, scq, scop, scbox, sru, srscale,
+        srr2, srop, srbox, dimpart, geom, wcounts, rank[2], rwin, wtab, total;
 };
 
 inline int fail(std::string* where, int code, const std::string& msg)
@@ -94,7 +94,8 @@ struct abcsmc_ctx {
     bool own_ws = false;
     bool broken = false;
     std::string err;
-    hipEvent_t ev[9] = {};
+    abcsmc::StageCounters* host = nullptr;  // pinned: a stage's counters and results
+    double tick_ms = 1e-5;       // of the constant-rate clock
     abcsmc::rt::DevPop pop[2]{};
     int cur = 0;                 // pop[cur] holds the last completed stage
     int32_t rounds = 0;          // stages completed

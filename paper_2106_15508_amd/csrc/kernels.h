@@ -23,18 +23,26 @@ struct Model {
     uint64_t seed;
 };
 
-// Device counters of one stage (8-byte words).
+// Points of a stage whose device time is noted (StageCounters::ts).
+enum StageMark { kTsBegin, kTsPropose, kTsProposed, kTsWeights, kTsSum, kTsSummed, kTsSelect, kTsEnd, kTsCount };
+
+// Device counters and results of one stage (8-byte words), read back together.
 struct StageCounters {
     unsigned long long accepted;   // acceptances over the batches run so far
     unsigned long long proposals;  // index of the N-th acceptance + 1 (0 until reached)
     unsigned long long invalid;    // void proposals over the batches run so far
     unsigned long long attempts;   // perturbation attempts over the batches run so far
-    unsigned long long base_rank;  // acceptances before the current batch
     unsigned long long survivors;  // previous particles with q > 0
     unsigned long long fallback;   // 1 if the prior set used d <= eps (no d < eps)
     unsigned long long days;       // proposal-days simulated over the batches run so far
     unsigned long long terms;      // importance-weight terms evaluated (inside the windows)
     unsigned long long window_terms;  // sum over rows of the row's own window (terms the rows need)
+    double eps_next;               // eq. 8 of the accepted distances
+    double ess;                    // effective sample size
+    // the constant-rate clock when the first workgroup of a phase's first kernel
+    // starts: the phases' times without an event record (a few us of idle GPU
+    // each) between the kernels
+    unsigned long long ts[kTsCount];
 };
 
 // Population of one stage, array-of-structures for the per-particle gathers.
@@ -80,6 +88,7 @@ struct ProposeArgs {
 struct CompactArgs {
     uint32_t base;
     uint32_t count;
+    unsigned long long before;  // acceptances of the stage's earlier batches
     int32_t N;
     const unsigned long long* wave_mask;
     uint32_t* wave_off;   // exclusive prefix of popcounts
@@ -117,6 +126,20 @@ struct ResampleArgs {
     Scratch sc;
     StageCounters* ctr;
 };
+
+// N up to which one workgroup of kOneThreads threads takes a pass over the
+// particles instead of a chain of launches (each about 4.5 us and 1.5 us of gap):
+//   resampling     22 us at 4096 (44 at 8192) against three launches of 24 and two gaps
+//   sort keys      18 us at 1024 (26 at 2048) against three launches of 19 and two gaps
+//   stage end      15-20 us at 16384 (normalisation and percentile side by side)
+//                  against four launches of 20 and the percentile's 20
+// and up to which the sort counts smaller keys (34 us at 16384, growing with
+// N^2, against 71 us and ten gaps for the bitonic launches at 20011).
+constexpr int kOneThreads = 1024;
+constexpr int kOneResample = 1 << 12;
+constexpr int kOnePrep = 1 << 10;
+constexpr int kOneEnd = 1 << 14;
+constexpr int kRankSort = 24576;
 
 // Entries of the weight kernels' exponential table (2^(i/1024)).
 constexpr int kWeightTab = 1024;
@@ -164,6 +187,8 @@ struct WeightArgs {
     double* logw;           // N
     unsigned long long* rowkeys;  // Npad sort keys (row index in the low 32 bits)
     unsigned long long* colkeys;  // Npad sort keys (column index in the low 32 bits)
+    unsigned long long* unsorted[2];  // up to kRankSort: the columns' and rows' keys before the sort
+    StageCounters* ctr;
     WeightCols sc;
     WeightRows sr;
     double* dimpart;        // kDimBlocks x 32 per-block statistics of the columns
@@ -200,9 +225,10 @@ void launch_sort_u64(unsigned long long* keys, size_t n_pow2, hipStream_t s);
 void launch_sort_u64_pair(unsigned long long* keys0, unsigned long long* keys1, size_t n_pow2, hipStream_t s);
 
 struct NormArgs {
-    const double* logw;
+    double* logw;
     double* W;
     int32_t N;
+    int32_t uniform;        // 1: W = 1/N, log-weights 0 (stage 0, weight-free runs)
     Scratch sc;
     double* ess;            // device scalar
 };
@@ -213,6 +239,7 @@ struct SelectArgs {
     double alpha;
     Scratch sc;
     double* out;            // device scalar: type-7 quantile
+    StageCounters* ctr;     // where its start is noted, or null
 };
 
 // Column tiles per chunk (grid y) and chunks of the weight kernel for N rows.
@@ -245,9 +272,11 @@ void launch_resample(const ResampleArgs& a, hipStream_t s);
 void launch_weights_window(const WeightArgs& a, hipStream_t s);
 void launch_weights_sum(const WeightArgs& a, hipStream_t s);
 void launch_weights_finalize(const WeightArgs& a, hipStream_t s);
-void launch_normalise(const NormArgs& a, hipStream_t s);
 void launch_select(const SelectArgs& a, hipStream_t s);
-void launch_uniform_weights(double* W, double* logw, int32_t N, hipStream_t s);
+// Normalised (or uniform) weights and the next tolerance.
+void launch_stage_end(const NormArgs& n, const SelectArgs& q, hipStream_t s);
+// The stage's counters to pinned host memory.
+void launch_publish(StageCounters* ctr, StageCounters* host, hipStream_t s);
 void launch_simulate_traj(const TrajArgs& a, hipStream_t s);
 void launch_to_theta(const double* u, const Model& m, double* theta, int64_t n, hipStream_t s);
 void launch_debug_eval(int32_t fn, int64_t n, const void* in, void* out, double pa, int32_t pb,

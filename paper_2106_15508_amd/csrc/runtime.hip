@@ -71,7 +71,6 @@ Layout make_layout(const abcsmc_config& c)
     L.wave_mask = take((B / kWave + 4) * sizeof(unsigned long long));
     L.wave_off = take((B / kWave + 4) * sizeof(uint32_t));
     L.ctr = take(sizeof(StageCounters));
-    L.scal = take(8 * sizeof(double));
     L.theta = take(N * kNP * sizeof(double));
     for (int r = 0; r < 5; ++r) L.red[r] = take(kRedMax * 8);
     L.hist = take(2048 * sizeof(unsigned int));
@@ -94,6 +93,7 @@ Layout make_layout(const abcsmc_config& c)
     L.dimpart = take(kDimBlocks * 32 * sizeof(double));
     L.geom = take(sizeof(WeightGeom));
     L.wcounts = take((size_t)weight_chunks((int64_t)N) * (rpad / kWave) * sizeof(uint2));
+    for (auto& r : L.rank) r = take(std::min<size_t>(N, kRankSort) * 8);
     L.rwin = take(N * sizeof(double));
     L.wtab = take(kWeightTab * sizeof(double));
     L.total = o;
@@ -180,6 +180,16 @@ void bind_pops(abcsmc_ctx* x)
     }
 }
 
+// The stage's counters as they are now on the context's stream.
+int read_counters(abcsmc_ctx* x, StageCounters& h)
+{
+    launch_publish(x->at<StageCounters>(x->L.ctr), x->host, x->stream);
+    HIPCHK(x, hipGetLastError());
+    HIPCHK(x, hipStreamSynchronize(x->stream));
+    h = *x->host;
+    return ABCSMC_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -220,8 +230,7 @@ void abcsmc_free(abcsmc_ctx* ctx)
     if (!ctx) return;
     if (ctx->stream) (void)hipStreamSynchronize(ctx->stream);
     surrogate_free(ctx->sur);
-    for (auto& e : ctx->ev)
-        if (e) (void)hipEventDestroy(e);
+    if (ctx->host) (void)hipHostFree(ctx->host);
     if (ctx->stage_host) (void)hipHostFree(ctx->stage_host);
     if (ctx->own_ws && ctx->ws) (void)hipFree(ctx->ws);
     if (ctx->own_stream && ctx->stream) (void)hipStreamDestroy(ctx->stream);
@@ -285,11 +294,16 @@ int abcsmc_init(const abcsmc_config* cfg, const int64_t* obs, abcsmc_ctx** out)
     }
     bind_pops(x);
     x->first_batch = propose_first_batch_lanes();
-    for (auto& ev : x->ev)
-        if (hipEventCreate(&ev) != hipSuccess) {
-            x->err = "hipEventCreate failed";
-            return bail(ABCSMC_EDEVICE);
-        }
+    if (hipHostMalloc((void**)&x->host, sizeof(StageCounters), hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        x->host = nullptr;
+        x->err = "hipHostMalloc of the stage counters failed";
+        return bail(ABCSMC_ENOMEM);
+    }
+    int dev = 0, khz = 0;
+    if (hipGetDevice(&dev) == hipSuccess &&
+        hipDeviceGetAttribute(&khz, hipDeviceAttributeWallClockRate, dev) == hipSuccess && khz > 0)
+        x->tick_ms = 1.0 / khz;
     std::vector<double> od(x->obs.begin(), x->obs.end());
     launch_weight_table(x->at<double>(x->L.wtab), x->stream);
     if (hipGetLastError() != hipSuccess ||
@@ -332,7 +346,6 @@ int abcsmc_round(abcsmc_ctx* x, abcsmc_round_info* info)
     const DevPop& prev = x->pop[x->cur];
     const DevPop& dst = x->pop[nxt];
     StageCounters* ctr = x->at<StageCounters>(x->L.ctr);
-    double* scal = x->at<double>(x->L.scal);
     hipStream_t s = x->stream;
 
     // eq. 8's percentile of the last stage, or the replayed schedule
@@ -374,19 +387,18 @@ int abcsmc_round(abcsmc_ctx* x, abcsmc_round_info* info)
                                 : INFINITY;
 
     const bool screened = surrogate_screens(x, r);
-    HIPCHK(x, hipMemsetAsync(ctr, 0, sizeof(StageCounters), s));
+    // one workgroup's resampling clears the counters itself
+    if (r == 0 || N > kOneResample) HIPCHK(x, hipMemsetAsync(ctr, 0, sizeof(StageCounters), s));
     if (x->sur) {
         const int rc = surrogate_stage_begin(x, nxt);
         if (rc) return rc;
     }
-    HIPCHK(x, hipEventRecord(x->ev[0], s));
     if (r > 0) {
         ResampleArgs ra{prev.d, prev.u, N, eps, x->at<uint64_t>(x->L.q), x->at<uint64_t>(x->L.cdf),
                         x->at<double>(x->L.cols), x->scratch(), ctr};
         launch_resample(ra, s);
         HIPCHK(x, hipGetLastError());
     }
-    HIPCHK(x, hipEventRecord(x->ev[1], s));
 
     ProposeArgs pa{};
     pa.m = x->model;
@@ -442,8 +454,10 @@ int abcsmc_round(abcsmc_ctx* x, abcsmc_round_info* info)
     bool spec_ok = !screened && !mcmc && !x->sur && r != 1;
     int64_t pending = 0;  // size of a batch whose counters are not yet read
     const bool weighted = r > 0 && !(c.flags & ABCSMC_F_SKIP_WEIGHTS);
-    double hs[2] = {0, 0};
-    unsigned long long hterms[2] = {0, 0};  // terms, window_terms (adjacent counters)
+    auto span = [&](const StageCounters& h, int a, int b) {
+        return h.ts[a] && h.ts[b] >= h.ts[a] ? (double)(h.ts[b] - h.ts[a]) * x->tick_ms : 0.0;
+    };
+    unsigned long long ts_propose = hc.ts[kTsPropose];  // start of the first batch
     for (;;) {
         while (!screened) {
             int64_t B;
@@ -472,10 +486,9 @@ int abcsmc_round(abcsmc_ctx* x, abcsmc_round_info* info)
             if (B <= 0) return fail(&x->err, ABCSMC_EBUDGET, "stage exhausted its proposal budget");
             pa.base = (uint32_t)base;
             pa.count = (uint32_t)B;
-            HIPCHK(x, hipEventRecord(x->ev[5], s));
             launch_propose(pa, r == 0, s);
             HIPCHK(x, hipGetLastError());
-            HIPCHK(x, hipEventRecord(x->ev[6], s));
+            ca.before = hc.accepted;
             ca.base = pa.base;
             ca.count = pa.count;
             launch_compact(ca, s);
@@ -484,9 +497,9 @@ int abcsmc_round(abcsmc_ctx* x, abcsmc_round_info* info)
                 pending = B;  // read back with the tolerance at the end of the stage
                 break;
             }
-            HIPCHK(x, hipMemcpyAsync(&hc, ctr, sizeof hc, hipMemcpyDeviceToHost, s));
-            HIPCHK(x, hipStreamSynchronize(s));
-            ms_k_propose += elapsed(x->ev[5], x->ev[6]);
+            if (const int rc = read_counters(x, hc)) return rc;
+            ms_k_propose += span(hc, kTsPropose, kTsProposed);
+            if (batches == 0) ts_propose = hc.ts[kTsPropose];
             base += B;
             ++batches;
             if (mcmc && r > 0 && x->mcmc_tunes < c.mcmc_tune) {
@@ -504,10 +517,7 @@ int abcsmc_round(abcsmc_ctx* x, abcsmc_round_info* info)
             if (hc.accepted >= (unsigned long long)N) break;
             if (r > 0 && base > 0) x->last_rate = (double)hc.accepted / (double)base;
         }
-        HIPCHK(x, hipEventRecord(x->ev[2], s));
-        if (!weighted) {
-            launch_uniform_weights(dst.W, dst.logw, N, s);
-        } else {
+        if (weighted) {
             WeightArgs wa{};
             wa.u = dst.u;
             wa.sigma = dst.sigma;
@@ -528,6 +538,8 @@ int abcsmc_round(abcsmc_ctx* x, abcsmc_round_info* info)
                                x->at<char>(x->L.srop), x->at<float>(x->L.srbox), weight_row_pad((size_t)N)};
             wa.dimpart = x->at<double>(x->L.dimpart);
             wa.geom = x->at<WeightGeom>(x->L.geom);
+            for (int k = 0; k < 2; ++k) wa.unsorted[k] = x->at<unsigned long long>(x->L.rank[k]);
+            wa.ctr = ctr;
             wa.counts = x->at<uint2>(x->L.wcounts);
             wa.npad = sort_padded_size((size_t)N);
             wa.parent = dst.parent;
@@ -540,31 +552,26 @@ int abcsmc_round(abcsmc_ctx* x, abcsmc_round_info* info)
             weight_exp_constants(wa.ex);
             launch_weights_window(wa, s);
             HIPCHK(x, hipGetLastError());
-            HIPCHK(x, hipEventRecord(x->ev[7], s));
             launch_weights_sum(wa, s);
             HIPCHK(x, hipGetLastError());
-            HIPCHK(x, hipEventRecord(x->ev[8], s));
             launch_weights_finalize(wa, s);
             HIPCHK(x, hipGetLastError());
             if (screened) {
                 const int rc = surrogate_weights(x, dst, nxt);
                 if (rc) return rc;
             }
-            NormArgs na{dst.logw, dst.W, N, x->scratch(), scal + 1};
-            launch_normalise(na, s);
         }
+        const NormArgs na{dst.logw, dst.W, N, weighted ? 0 : 1, x->scratch(), &ctr->ess};
+        const SelectArgs sa{dst.d, N, c.surv_ratio, x->scratch(), &ctr->eps_next, ctr};
+        launch_stage_end(na, sa, s);
         HIPCHK(x, hipGetLastError());
-        HIPCHK(x, hipEventRecord(x->ev[3], s));
-        SelectArgs sa{dst.d, N, c.surv_ratio, x->scratch(), scal + 0};
-        launch_select(sa, s);
-        HIPCHK(x, hipGetLastError());
-        HIPCHK(x, hipEventRecord(x->ev[4], s));
-        HIPCHK(x, hipMemcpyAsync(hs, scal, sizeof hs, hipMemcpyDeviceToHost, s));
-        HIPCHK(x, hipMemcpyAsync(hterms, &ctr->terms, sizeof hterms, hipMemcpyDeviceToHost, s));
-        if (pending) HIPCHK(x, hipMemcpyAsync(&hc, ctr, sizeof hc, hipMemcpyDeviceToHost, s));
-        HIPCHK(x, hipStreamSynchronize(s));
+        StageCounters h{};
+        if (const int rc = read_counters(x, h)) return rc;
+        if (screened) h.accepted = hc.accepted;  // counted by the screen's own batches
+        hc = h;
         if (pending) {
-            ms_k_propose += elapsed(x->ev[5], x->ev[6]);
+            ms_k_propose += span(hc, kTsPropose, kTsProposed);
+            ts_propose = hc.ts[kTsPropose];
             base += pending;
             ++batches;
             pending = 0;
@@ -586,7 +593,7 @@ int abcsmc_round(abcsmc_ctx* x, abcsmc_round_info* info)
     x->cur = nxt;
     x->rounds = r + 1;
     if (r == 1) x->eps1 = eps;
-    x->eps_next = hs[0];
+    x->eps_next = hc.eps_next;
     if (screened) {
         const int rc = surrogate_stage_end(x, r);
         if (rc) return rc;
@@ -596,28 +603,31 @@ int abcsmc_round(abcsmc_ctx* x, abcsmc_round_info* info)
         std::memset(&I, 0, sizeof I);
         I.round = r;
         I.eps = eps;
-        I.eps_next = hs[0];
+        I.eps_next = hc.eps_next;
         I.beta_a = ba;
         I.beta_b = bb;
-        I.ess = weighted ? hs[1] : (double)N;
+        I.ess = weighted ? hc.ess : (double)N;
         I.proposals = (int64_t)hc.proposals;
         I.simulated = base;
         I.invalid = (int64_t)hc.invalid;
         I.attempts = (int64_t)hc.attempts;
         I.survivors = r == 0 ? 0 : (int64_t)hc.survivors;
         I.batches = batches;
-        I.ms_resample = elapsed(x->ev[0], x->ev[1]);
-        I.ms_simulate = elapsed(x->ev[1], x->ev[2]);
-        I.ms_weights = elapsed(x->ev[2], x->ev[3]);
-        I.ms_select = elapsed(x->ev[3], x->ev[4]);
-        I.ms_total = elapsed(x->ev[0], x->ev[4]);
+        if (ts_propose) hc.ts[kTsPropose] = ts_propose;
+        if (r == 0 || !hc.ts[kTsBegin]) hc.ts[kTsBegin] = hc.ts[kTsPropose];
+        const int after = weighted ? kTsWeights : kTsSelect;  // the phase after the proposals
+        I.ms_resample = span(hc, kTsBegin, kTsPropose);
+        I.ms_simulate = span(hc, kTsPropose, after);
+        I.ms_weights = weighted ? span(hc, kTsWeights, kTsSelect) : 0.0;
+        I.ms_select = span(hc, kTsSelect, kTsEnd);
+        I.ms_total = span(hc, kTsBegin, kTsEnd);
         I.ms_k_propose = ms_k_propose;
-        I.ms_k_weights = weighted ? elapsed(x->ev[7], x->ev[8]) : 0.0;
+        I.ms_k_weights = weighted ? span(hc, kTsSum, kTsSummed) : 0.0;
         I.n_k_propose = batches;
         I.sim_days = (int64_t)hc.days;
         I.weight_pairs = weighted ? (int64_t)N * (int64_t)hc.survivors : 0;
-        I.weight_terms = (int64_t)hterms[0];
-        I.weight_window_terms = (int64_t)hterms[1];
+        I.weight_terms = (int64_t)hc.terms;
+        I.weight_window_terms = (int64_t)hc.window_terms;
         I.mcmc_s = mcmc ? x->mcmc_s : 0.0;
         I.beta_b_real = general ? bb_real : (double)bb;
     }

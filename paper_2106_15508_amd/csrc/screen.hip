@@ -24,6 +24,7 @@ constexpr uint32_t kMlpInit = 5;
 
 __global__ __launch_bounds__(kBlock) void perturb_only_kernel(PerturbArgs a)
 {
+    if (a.base == 0 && blockIdx.x == 0 && threadIdx.x == 0) a.ctr->ts[kTsPropose] = wall_clock64();
     const uint32_t p = blockIdx.x * kBlock + threadIdx.x;
     const bool active = p < a.count;
     int32_t att = 0;

@@ -25,6 +25,7 @@ template <bool kRound0, int kSampler>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(ABCSMC_PROPOSE_WAVES)))
 void propose_kernel(ProposeArgs a)
 {
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->ts[kTsPropose] = wall_clock64();
     const uint32_t p = blockIdx.x * kBlock + threadIdx.x;
     const bool active = p < a.count;
     const uint32_t j = a.base + p;
@@ -61,6 +62,7 @@ void propose_kernel(ProposeArgs a)
 template <bool kRound0, int kSampler>
 __global__ __launch_bounds__(kBlock) void propose_quad_kernel(ProposeArgs a)
 {
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->ts[kTsPropose] = wall_clock64();
     const uint32_t p = blockIdx.x * (kBlock / 4) + threadIdx.x / 4;
     const bool active = p < a.count, lead = (threadIdx.x & 3u) == 0;
     const uint32_t j = a.base + p;
@@ -96,12 +98,12 @@ __global__ __launch_bounds__(kBlock) void propose_quad_kernel(ProposeArgs a)
     }
 }
 
-// Exclusive prefix of the per-wave acceptance counts (one workgroup) and the
-// batch's starting rank.
+// Exclusive prefix of the per-wave acceptance counts (one workgroup).
 constexpr int kScanThreads = 1024;
 
 __global__ __launch_bounds__(kScanThreads) void compact_scan_kernel(CompactArgs a)
 {
+    if (threadIdx.x == 0) a.ctr->ts[kTsProposed] = wall_clock64();
     __shared__ unsigned long long part[kScanThreads];
     const uint32_t nW = (a.count + kWave - 1) / kWave;
     const uint32_t per = (nW + kScanThreads - 1) / kScanThreads;
@@ -123,24 +125,45 @@ __global__ __launch_bounds__(kScanThreads) void compact_scan_kernel(CompactArgs 
         a.wave_off[w] = (uint32_t)run;
         run += __popcll(a.wave_mask[w]);
     }
-    if (t == kScanThreads - 1) {
-        const unsigned long long before = a.ctr->accepted;
-        a.ctr->base_rank = before;
-        a.ctr->accepted = before + part[t];
-    }
+    if (t == kScanThreads - 1) a.ctr->accepted = a.before + part[t];
 }
 
 // Scatter the acceptances of the batch into population slots in proposal
 // order; slots >= N are dropped (the stage keeps its first N acceptances).
+// kScan: every workgroup adds up the ballots before its own (up to kCompactOne
+// proposals 16 words a thread) instead of a scan in a launch of its own.
+constexpr uint32_t kCompactOne = 1u << 18;
+
+template <bool kScan>
 __global__ __launch_bounds__(kBlock) void compact_scatter_kernel(CompactArgs a)
 {
+    __shared__ unsigned int part[kBlock / kWave];
     const uint32_t p = blockIdx.x * kBlock + threadIdx.x;
+    const uint32_t w = p / kWave, lane = p % kWave, nW = (a.count + kWave - 1) / kWave;
+    unsigned long long offset = 0;  // acceptances of the batch before wave w
+    if (kScan) {
+        const uint32_t first = blockIdx.x * (kBlock / kWave);
+        unsigned int s = 0;
+        for (uint32_t i = threadIdx.x; i < first; i += kBlock) s += (unsigned int)__popcll(a.wave_mask[i]);
+#pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1) s += __shfl_xor(s, off, kWave);
+        if (lane == 0) part[threadIdx.x / kWave] = s;
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < kBlock / kWave; ++i) offset += part[i];
+        for (uint32_t i = first; i < w && i < nW; ++i) offset += __popcll(a.wave_mask[i]);
+        if (w == nW - 1 && lane == 0) {
+            a.ctr->accepted = a.before + offset + __popcll(a.wave_mask[w]);
+        }
+        if (p == 0) a.ctr->ts[kTsProposed] = wall_clock64();
+    } else if (p < a.count) {
+        offset = a.wave_off[w];
+    }
     if (p >= a.count) return;
-    const uint32_t w = p / kWave, lane = p % kWave;
     const unsigned long long mask = a.wave_mask[w];
     if (!((mask >> lane) & 1ull)) return;
     const unsigned long long below = lane ? (mask & ((1ull << lane) - 1ull)) : 0ull;
-    const unsigned long long gr = a.ctr->base_rank + a.wave_off[w] + (unsigned long long)__popcll(below);
+    const unsigned long long gr = a.before + offset + (unsigned long long)__popcll(below);
     if (gr >= (unsigned long long)a.N) return;
     const double* su = a.st_u + (size_t)p * kNP;
     double* du = a.pop.u + (size_t)gr * kNP;
@@ -280,8 +303,12 @@ void launch_propose(const ProposeArgs& a, bool round0, hipStream_t s)
 
 void launch_compact(const CompactArgs& a, hipStream_t s)
 {
+    if (a.count <= kCompactOne) {
+        hipLaunchKernelGGL(compact_scatter_kernel<true>, dim3(grid_for(a.count)), dim3(kBlock), 0, s, a);
+        return;
+    }
     hipLaunchKernelGGL(compact_scan_kernel, dim3(1), dim3(kScanThreads), 0, s, a);
-    hipLaunchKernelGGL(compact_scatter_kernel, dim3(grid_for(a.count)), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(compact_scatter_kernel<false>, dim3(grid_for(a.count)), dim3(kBlock), 0, s, a);
 }
 
 void launch_simulate_traj(const TrajArgs& a, hipStream_t s)

@@ -94,6 +94,7 @@ __global__ __launch_bounds__(kBlock) void resample_stats_kernel(ResampleArgs a)
 {
     __shared__ unsigned long long shu[kBlock];
     __shared__ double shd[kBlock];
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->ts[kTsBegin] = wall_clock64();
     const int k0 = blockIdx.x * kChunk;
     unsigned long long ns = 0;
     double wmx = 0.0;
@@ -219,6 +220,114 @@ __global__ __launch_bounds__(kBlock) void resample_write_kernel(ResampleArgs a)
     }
 }
 
+// Block sums, maxima and scans of kOneThreads threads: wave by wave in
+// registers, then the waves' values in LDS.
+constexpr int kOneWaves = kOneThreads / kWave;
+
+template <class T, class Op>
+__device__ __forceinline__ T one_reduce(T v, T* sh, Op op)
+{
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) v = op(v, __shfl_xor(v, off, kWave));
+    __syncthreads();
+    if ((threadIdx.x & (kWave - 1)) == 0) sh[threadIdx.x / kWave] = v;
+    __syncthreads();
+    v = sh[0];
+#pragma unroll
+    for (int w = 1; w < kOneWaves; ++w) v = op(v, sh[w]);
+    return v;
+}
+
+__device__ __forceinline__ unsigned long long one_excl_scan(unsigned long long v, unsigned long long* sh,
+                                                            unsigned long long* total)
+{
+    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+    unsigned long long incl = v;
+#pragma unroll
+    for (int off = 1; off < kWave; off <<= 1) {
+        const unsigned long long o = __shfl_up(incl, off, kWave);
+        if (lane >= off) incl += o;
+    }
+    __syncthreads();
+    if (lane == kWave - 1) sh[w] = incl;
+    __syncthreads();
+    unsigned long long before = 0, all = 0;
+#pragma unroll
+    for (int i = 0; i < kOneWaves; ++i) {
+        if (i < w) before += sh[i];
+        all += sh[i];
+    }
+    *total = all;
+    return before + incl - v;
+}
+
+// The three passes in one workgroup (N <= kOneResample), which also clears the
+// stage's counters.
+__global__ __launch_bounds__(kOneThreads) void resample_one_kernel(ResampleArgs a)
+{
+    __shared__ unsigned long long shu[kOneWaves];
+    __shared__ double shd[kOneWaves];
+    __shared__ uint16_t place[kOneResample];  // column of a survivor
+    constexpr int kMost = kOneResample / kOneThreads;
+    constexpr uint16_t kNone = 0xFFFF;
+    const int t = threadIdx.x;
+    if (t < (int)(sizeof(StageCounters) / 8)) {
+        unsigned long long* c = (unsigned long long*)a.ctr;
+        c[t] = c + t == &a.ctr->ts[kTsBegin] ? wall_clock64() : 0ull;
+    }
+    const int per = (a.N + kOneThreads - 1) / kOneThreads, k0 = t * per;
+    double d[kMost];
+    unsigned long long ns = 0;
+    double wmx = 0.0;
+#pragma unroll
+    for (int i = 0; i < kMost; ++i) {
+        const int k = k0 + i;
+        d[i] = i < per && k < a.N ? a.d_prev[k] : __builtin_inf();
+        if (d[i] < a.eps) {
+            ++ns;
+            const double w = a.eps - d[i];
+            wmx = w > wmx ? w : wmx;
+        }
+    }
+    ns = one_reduce(ns, shu, [](unsigned long long x, unsigned long long y) { return x + y; });
+    wmx = one_reduce(wmx, shd, [](double x, double y) { return x > y ? x : y; });
+    const bool strict = ns > 0;
+    const double wmax = strict ? wmx : 0.0;
+    unsigned long long sq = 0, sc = 0, tot, survivors;
+#pragma unroll
+    for (int i = 0; i < kMost; ++i) {
+        if (i < per && k0 + i < a.N) {
+            const unsigned long long q = quantise(d[i], a.eps, strict, wmax);
+            sq += q;
+            sc += q > 0;
+        }
+    }
+    unsigned long long run = one_excl_scan(sq, shu, &tot);
+    unsigned long long col = one_excl_scan(sc, shu, &survivors);
+#pragma unroll
+    for (int i = 0; i < kMost; ++i) {
+        const int k = k0 + i;
+        if (i < per && k < a.N) {
+            const unsigned long long q = quantise(d[i], a.eps, strict, wmax);
+            run += q;
+            a.q[k] = q;
+            a.cdf[k] = run;
+            place[k] = q > 0 ? (uint16_t)col : kNone;
+            if (q > 0) a.cols[(size_t)col++ * 9 + 8] = (double)q;
+        }
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int e = t; e < a.N * kNP; e += kOneThreads) {
+        const uint16_t c = place[e / kNP];
+        if (c != kNone) a.cols[(size_t)c * 9 + e % kNP] = a.u_prev[e];
+    }
+    if (t == 0) {
+        a.ctr->survivors = survivors;
+        a.ctr->fallback = strict ? 0ull : 1ull;
+    }
+}
+
 // ---------------------------------------------------------------------------
 // Importance weights.  Row j (an accepted particle with step sigma_j) gets
 //   L_j = sum_k q_k exp(-|u_j - u_k|^2 / (2 sigma_j^2))
@@ -251,6 +360,7 @@ using wterm::wave_sum_u64;
 // Thread t takes coordinate t % 8 of every 32nd column.
 __global__ __launch_bounds__(kBlock) void wdim_partial_kernel(WeightArgs a)
 {
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.ctr->ts[kTsWeights] = wall_clock64();
     __shared__ double sh[4][kBlock];
     const int M = (int)*a.M, t = threadIdx.x, d = t & 7;
     double s1 = 0.0, s2 = 0.0, mn = __builtin_inf(), mx = -__builtin_inf();
@@ -296,30 +406,21 @@ __global__ __launch_bounds__(kBlock) void wgeom_kernel(WeightArgs a)
         }
         __syncthreads();
     }
-    if (t == 0) wterm::make_geom(sh, sh + 8, sh + 16, sh + 24, (double)*a.M, *a.geom);
+    wterm::make_geom(sh, sh + 8, sh + 16, sh + 24, (double)*a.M, a.geom);
 }
 
-// Sort keys of the columns (grid.y 0) and of the rows (grid.y 1), and the
-// rows' window radii.
-__global__ __launch_bounds__(kBlock) void wkeys_kernel(WeightArgs a)
+// Sort key of column i, or of row i, whose window radius it stores; cells: this
+// thread's column of an LDS array, `stride` threads apart.
+__device__ __forceinline__ unsigned long long sort_key(const WeightArgs& a, const WeightGeom& g, size_t i, bool row,
+                                                       uint32_t* cells, int stride)
 {
-    __shared__ uint32_t cells[kNP * kBlock];
-    const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= a.npad) return;  // each thread uses its own LDS column only
-    const bool row = blockIdx.y != 0;
-    unsigned long long* keys = row ? a.rowkeys : a.colkeys;
-    if (i >= (size_t)(row ? a.N : (int)*a.M)) {
-        keys[i] = ~0ull;
-        return;
-    }
-    const WeightGeom& g = *a.geom;
     double u[kNP];
 #pragma unroll
     for (int d = 0; d < kNP; ++d) {
         u[d] = row ? a.u[i * kNP + d] : a.cols[i * 9 + d];
-        cells[d * kBlock + threadIdx.x] = wterm::cell20(u[d], g.lo[d], g.inv[d]);
+        cells[d * stride] = wterm::cell20(u[d], g.lo[d], g.inv[d]);
     }
-    uint32_t key = wterm::morton32(g, cells + threadIdx.x, kBlock);
+    uint32_t key = wterm::morton32(g, cells, stride);
     if (row) {
         const double sj = a.sigma[i];
         // half-octaves in descending order: the widest windows are dispatched first
@@ -329,7 +430,107 @@ __global__ __launch_bounds__(kBlock) void wkeys_kernel(WeightArgs a)
         a.rwin[i] = wterm::window_radius(u, sj, ok ? a.u_prev + (size_t)par * kNP : u, ok ? (double)a.q_prev[par] : 0.0,
                                          (double)a.cdf[a.n_prev - 1]);
     }
-    keys[i] = ((unsigned long long)key << 32) | (unsigned long long)i;
+    return ((unsigned long long)key << 32) | (unsigned long long)i;
+}
+
+// Keys of the columns (grid.y 0) and of the rows (grid.y 1), padded for the
+// bitonic sort unless they go to the counting sort.
+__global__ __launch_bounds__(kBlock) void wkeys_kernel(WeightArgs a)
+{
+    __shared__ uint32_t cells[kNP * kBlock];
+    const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
+    const bool row = blockIdx.y != 0, rank = a.N <= kRankSort;
+    const size_t n = (size_t)(row ? a.N : (int)*a.M);
+    unsigned long long* keys = rank ? a.unsorted[row] : (row ? a.rowkeys : a.colkeys);
+    if (i < n) keys[i] = sort_key(a, *a.geom, i, row, cells + threadIdx.x, kBlock);
+    else if (!rank && i < a.npad) keys[i] = ~0ull;
+}
+
+// Statistics, sort code and keys in one workgroup (N <= kOnePrep).
+__global__ __launch_bounds__(kOneThreads) void wprep_one_kernel(WeightArgs a)
+{
+    __shared__ union {
+        double stat[4][kOneThreads];
+        uint32_t cells[kNP * kOneThreads];
+    } sh;
+    __shared__ double fin[32];
+    __shared__ WeightGeom g;
+    const int M = (int)*a.M, t = threadIdx.x, d = t & 7;
+    if (t == 0) a.ctr->ts[kTsWeights] = wall_clock64();
+    double v[4] = {0.0, 0.0, __builtin_inf(), -__builtin_inf()};
+    for (int k = t / 8; k < M; k += kOneThreads / 8) {
+        const double x = a.cols[(size_t)k * 9 + d];
+        v[0] += x;
+        v[1] += x * x;
+        v[2] = x < v[2] ? x : v[2];
+        v[3] = x > v[3] ? x : v[3];
+    }
+    // the eight threads of a wave that share a coordinate, then the waves
+#pragma unroll
+    for (int off = 8; off < kWave; off <<= 1) {
+        v[0] += __shfl_xor(v[0], off, kWave);
+        v[1] += __shfl_xor(v[1], off, kWave);
+        const double lo = __shfl_xor(v[2], off, kWave), hi = __shfl_xor(v[3], off, kWave);
+        v[2] = lo < v[2] ? lo : v[2];
+        v[3] = hi > v[3] ? hi : v[3];
+    }
+    if ((t & (kWave - 1)) < 8)
+        for (int q = 0; q < 4; ++q) sh.stat[q][(t / kWave) * 8 + d] = v[q];
+    __syncthreads();
+    if (t < 32) {
+        const int q = t >> 3;
+        double r = sh.stat[q][t & 7];
+        for (int w = 1; w < kOneWaves; ++w) {
+            const double o = sh.stat[q][w * 8 + (t & 7)];
+            r = q < 2 ? r + o : (q == 2 ? (o < r ? o : r) : (o > r ? o : r));
+        }
+        fin[t] = r;
+    }
+    __syncthreads();
+    wterm::make_geom(fin, fin + 8, fin + 16, fin + 24, (double)M, &g);
+    __syncthreads();
+    if (t == 0) *a.geom = g;
+    for (int i = t; i < M; i += kOneThreads) a.unsorted[0][i] = sort_key(a, g, i, false, sh.cells + t, kOneThreads);
+    for (int i = t; i < a.N; i += kOneThreads) a.unsorted[1][i] = sort_key(a, g, i, true, sh.cells + t, kOneThreads);
+}
+
+// Counting sort of unique keys: a key's place is the number of smaller ones.
+// 64 keys a workgroup; its sixteen waves count among a share each of every
+// LDS tile of all keys (scalar loads instead left each wave waiting for the
+// next eight keys, 48 us at 5003).  n^2 comparisons on the whole chip: 4.6 us
+// up to 1024, 11 us at 5003 and 34 us at 16384, rows and columns together,
+// where the bitonic sort's first launch alone takes 24.
+constexpr int kRankTile = 2048;
+
+__global__ __launch_bounds__(kOneThreads) void wrank_kernel(WeightArgs a)
+{
+    __shared__ unsigned long long tile[kRankTile];
+    __shared__ unsigned int part[kOneWaves][kWave];
+    const bool row = blockIdx.y != 0;
+    const int n = row ? a.N : (int)*a.M;
+    if ((int)blockIdx.x * kWave >= n) return;
+    const unsigned long long* keys = a.unsorted[row];
+    const int t = threadIdx.x, w = t / kWave, lane = t & (kWave - 1);
+    const int i = blockIdx.x * kWave + lane;
+    const unsigned long long mine = i < n ? keys[i] : 0ull;
+    constexpr int share = kRankTile / kOneWaves;
+    unsigned int less = 0;
+    for (int base = 0; base < n; base += kRankTile) {
+        __syncthreads();
+#pragma unroll
+        for (int k = t; k < kRankTile; k += kOneThreads) tile[k] = base + k < n ? keys[base + k] : ~0ull;
+        __syncthreads();
+        if (base + w * share < n) {
+#pragma unroll 16
+            for (int j = 0; j < share; ++j) less += tile[w * share + j] < mine ? 1u : 0u;
+        }
+    }
+    part[w][lane] = less;
+    __syncthreads();
+    if (w == 0 && i < n) {
+        for (int k = 1; k < kOneWaves; ++k) less += part[k][lane];
+        (row ? a.rowkeys : a.colkeys)[less] = mine;
+    }
 }
 
 // Sorted columns (a wave per tile) and sorted rows (a wave per group).
@@ -359,6 +560,7 @@ __global__ __launch_bounds__(kWeightRows) __attribute__((amdgpu_waves_per_eu(5))
 {
     __shared__ double T[wterm::kTab];
     __shared__ __attribute__((aligned(16))) uint32_t list[kWeightRows / kWave][kListLen];
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.ctr->ts[kTsSum] = wall_clock64();
     const int M = (int)*a.M;
     const int t0 = (int)blockIdx.y * a.chunk_tiles;
     const int t1 = min((M + kColTile - 1) / kColTile, t0 + a.chunk_tiles);
@@ -414,6 +616,7 @@ __global__ __launch_bounds__(kBlock) void wterm_debug_kernel(int64_t n, const do
 __global__ __launch_bounds__(kBlock) void weights_finalize_kernel(WeightArgs a)
 {
     const int r = blockIdx.x * kBlock + threadIdx.x;
+    if (r == 0) a.ctr->ts[kTsSummed] = wall_clock64();
     const int tiles = ((int)*a.M + kColTile - 1) / kColTile;
     const int nch = min(a.chunks, (tiles + a.chunk_tiles - 1) / a.chunk_tiles);
     // a wave's group: its terms and window pairs
@@ -510,13 +713,58 @@ __global__ __launch_bounds__(kBlock) void norm_ess_kernel(NormArgs a, int G)
     if (threadIdx.x == 0) *a.ess = 1.0 / s2;
 }
 
-__global__ __launch_bounds__(kBlock) void uniform_weights_kernel(double* W, double* logw, int32_t N)
+__global__ __launch_bounds__(kBlock) void uniform_weights_kernel(NormArgs a)
 {
     const int j = blockIdx.x * kBlock + threadIdx.x;
-    if (j < N) {
-        W[j] = 1.0 / (double)N;
-        logw[j] = 0.0;
+    if (j < a.N) {
+        a.W[j] = 1.0 / (double)a.N;
+        a.logw[j] = 0.0;
     }
+}
+
+// The same in one workgroup (N <= kOneEnd).
+__device__ __forceinline__ void normalise_one(const NormArgs& a, double* sh)
+{
+    const int t = threadIdx.x;
+    if (a.uniform) {
+        for (int j = t; j < a.N; j += kOneThreads) {
+            a.W[j] = 1.0 / (double)a.N;
+            a.logw[j] = 0.0;
+        }
+        return;
+    }
+    constexpr int kMost = kOneEnd / kOneThreads;
+    double e[kMost];
+    double mx = -__builtin_inf();
+#pragma unroll
+    for (int i = 0; i < kMost; ++i) {
+        const int j = t + i * kOneThreads;
+        e[i] = j < a.N ? a.logw[j] : -__builtin_inf();
+        mx = e[i] > mx ? e[i] : mx;
+    }
+    mx = one_reduce(mx, sh, [](double x, double y) { return x > y ? x : y; });
+    const auto add = [](double x, double y) { return x + y; };
+    double s = 0.0;
+#pragma unroll
+    for (int i = 0; i < kMost; ++i) {
+        if (t + i * kOneThreads < a.N) {
+            e[i] = dm::exp(e[i] - mx);
+            s += e[i];
+        }
+    }
+    s = one_reduce(s, sh, add);
+    double s2 = 0.0;
+#pragma unroll
+    for (int i = 0; i < kMost; ++i) {
+        const int j = t + i * kOneThreads;
+        if (j < a.N) {
+            const double w = e[i] / s;
+            a.W[j] = w;
+            s2 += w * w;
+        }
+    }
+    s2 = one_reduce(s2, sh, add);
+    if (t == 0) *a.ess = 1.0 / s2;
 }
 
 // ---------------------------------------------------------------------------
@@ -532,11 +780,44 @@ __global__ __launch_bounds__(kBlock) void uniform_weights_kernel(double* W, doub
 constexpr int kSelectOne = 1 << 15;
 constexpr int kBins = bsel::kBins;
 
+__device__ __forceinline__ void note_select(const SelectArgs& a)
+{
+    if (a.ctr && blockIdx.x == 0 && threadIdx.x == 0) a.ctr->ts[kTsSelect] = wall_clock64();
+}
+
 __global__ __launch_bounds__(bsel::kThreads) void select_one_kernel(SelectArgs a)
 {
     __shared__ bsel::Shared sh;
+    note_select(a);
     const double r = bsel::quantile7(bsel::FromMemory{a.x, a.N}, a.N, a.alpha, sh);
     if (threadIdx.x == 0) *a.out = r;
+}
+
+// The end of a small stage: workgroup 0 selects, workgroup 1 normalises.
+__global__ __launch_bounds__(kOneThreads) void stage_end_one_kernel(NormArgs n, SelectArgs q)
+{
+    __shared__ union {
+        bsel::Shared sel;
+        double red[kOneWaves];
+    } sh;
+    if (blockIdx.x == 0) {
+        note_select(q);
+        const double r = bsel::quantile7(bsel::FromMemory{q.x, q.N}, q.N, q.alpha, sh.sel);
+        if (threadIdx.x == 0) *q.out = r;
+    } else {
+        normalise_one(n, sh.red);
+    }
+}
+
+// Counters and results of the stage to host memory, a thread a word.
+__global__ __launch_bounds__(kWave) void publish_kernel(StageCounters* ctr, StageCounters* host)
+{
+    constexpr int words = sizeof(StageCounters) / 8;
+    static_assert(words <= kWave, "a thread a word");
+    if (threadIdx.x == 0) ctr->ts[kTsEnd] = wall_clock64();
+    __syncthreads();
+    if (threadIdx.x < words) ((unsigned long long*)host)[threadIdx.x] = ((unsigned long long*)ctr)[threadIdx.x];
+    __threadfence_system();
 }
 
 // Per-block minimum and maximum (u0, u1); block 0 clears the histogram and the
@@ -544,6 +825,7 @@ __global__ __launch_bounds__(bsel::kThreads) void select_one_kernel(SelectArgs a
 __global__ __launch_bounds__(kBlock) void select_range_kernel(SelectArgs a)
 {
     __shared__ unsigned long long slo[kBlock / kWave], shi[kBlock / kWave];
+    note_select(a);
     unsigned long long lo = ~0ull, hi = 0ull;
 #pragma unroll 4
     for (int k = blockIdx.x * kBlock + threadIdx.x; k < a.N; k += gridDim.x * kBlock) {
@@ -726,6 +1008,10 @@ void launch_to_theta(const double* u, const Model& m, double* theta, int64_t n, 
 
 void launch_resample(const ResampleArgs& a, hipStream_t s)
 {
+    if (a.N <= kOneResample) {
+        hipLaunchKernelGGL(resample_one_kernel, dim3(1), dim3(kOneThreads), 0, s, a);
+        return;
+    }
     const dim3 g(blocks_of(a.N, kChunk)), b(kBlock);
     hipLaunchKernelGGL(resample_stats_kernel, g, b, 0, s, a);
     hipLaunchKernelGGL(resample_count_kernel, g, b, 0, s, a);
@@ -735,10 +1021,16 @@ void launch_resample(const ResampleArgs& a, hipStream_t s)
 void launch_weights_window(const WeightArgs& a, hipStream_t s)
 {
     const dim3 b(kBlock);
-    hipLaunchKernelGGL(wdim_partial_kernel, dim3(kDimBlocks), b, 0, s, a);
-    hipLaunchKernelGGL(wgeom_kernel, dim3(1), b, 0, s, a);
-    hipLaunchKernelGGL(wkeys_kernel, dim3(blocks_of((int64_t)a.npad, kBlock), 2), b, 0, s, a);
-    launch_sort_u64_pair(a.colkeys, a.rowkeys, a.npad, s);
+    if (a.N <= kOnePrep) {
+        hipLaunchKernelGGL(wprep_one_kernel, dim3(1), dim3(kOneThreads), 0, s, a);
+    } else {
+        const size_t n = a.N <= kRankSort ? (size_t)a.N : a.npad;
+        hipLaunchKernelGGL(wdim_partial_kernel, dim3(kDimBlocks), b, 0, s, a);
+        hipLaunchKernelGGL(wgeom_kernel, dim3(1), b, 0, s, a);
+        hipLaunchKernelGGL(wkeys_kernel, dim3(blocks_of((int64_t)n, kBlock), 2), b, 0, s, a);
+    }
+    if (a.N <= kRankSort) hipLaunchKernelGGL(wrank_kernel, dim3(blocks_of(a.N, kWave), 2), dim3(kOneThreads), 0, s, a);
+    else launch_sort_u64_pair(a.colkeys, a.rowkeys, a.npad, s);
     hipLaunchKernelGGL(wgather_kernel, dim3(blocks_of((int64_t)a.sr.pad, kBlock), 2), b, 0, s, a);
 }
 
@@ -783,18 +1075,27 @@ int weight_chunks(int64_t N)
     return (int)((tiles + t - 1) / t);
 }
 
-void launch_normalise(const NormArgs& a, hipStream_t s)
+void launch_stage_end(const NormArgs& a, const SelectArgs& q, hipStream_t s)
 {
-    const unsigned G = blocks_of(a.N, kChunk);
-    hipLaunchKernelGGL(norm_max_kernel, dim3(G), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(norm_exp_kernel, dim3(G), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(norm_scale_kernel, dim3(G), dim3(kBlock), 0, s, a);
-    hipLaunchKernelGGL(norm_ess_kernel, dim3(1), dim3(kBlock), 0, s, a, (int)G);
+    if (a.N <= kOneEnd) {
+        hipLaunchKernelGGL(stage_end_one_kernel, dim3(2), dim3(kOneThreads), 0, s, a, q);
+        return;
+    }
+    if (a.uniform) {
+        hipLaunchKernelGGL(uniform_weights_kernel, dim3(blocks_of(a.N, kBlock)), dim3(kBlock), 0, s, a);
+    } else {
+        const unsigned G = blocks_of(a.N, kChunk);
+        hipLaunchKernelGGL(norm_max_kernel, dim3(G), dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL(norm_exp_kernel, dim3(G), dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL(norm_scale_kernel, dim3(G), dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL(norm_ess_kernel, dim3(1), dim3(kBlock), 0, s, a, (int)G);
+    }
+    launch_select(q, s);
 }
 
-void launch_uniform_weights(double* W, double* logw, int32_t N, hipStream_t s)
+void launch_publish(StageCounters* ctr, StageCounters* host, hipStream_t s)
 {
-    hipLaunchKernelGGL(uniform_weights_kernel, dim3(blocks_of(N, kBlock)), dim3(kBlock), 0, s, W, logw, N);
+    hipLaunchKernelGGL(publish_kernel, dim3(1), dim3(kWave), 0, s, ctr, host);
 }
 
 void launch_select(const SelectArgs& a, hipStream_t s)

@@ -61,7 +61,7 @@ struct Surrogate {
     ScreenCounters* sc = nullptr;
     double* tau = nullptr;
     bool active = true;
-    hipEvent_t ev[4] = {};
+    hipEvent_t ev[6] = {};
 };
 
 namespace {
@@ -318,7 +318,7 @@ int surrogate_batches(abcsmc_ctx* x, const ProposeArgs& pa, const DevPop& dst, i
         mlp_infer(S.tr.params, S.wb, S.px, B, nullptr, S.score, s);
         if (batches == 0) {
             // tau: keep_frac percentile of the stage's first batch of scores
-            SelectArgs ta{S.score, (int32_t)B, S.cfg.keep_frac, x->scratch(), S.tau};
+            SelectArgs ta{S.score, (int32_t)B, S.cfg.keep_frac, x->scratch(), S.tau, nullptr};
             launch_select(ta, s);
         }
         ka.base = (uint32_t)base;
@@ -335,7 +335,7 @@ int surrogate_batches(abcsmc_ctx* x, const ProposeArgs& pa, const DevPop& dst, i
 
         const int64_t ntune = batches == 0 ? std::min<int64_t>((int64_t)nk, S.tune_cap) : 0;
         sa.base = (uint32_t)base;
-        HIPCHK(x, hipEventRecord(x->ev[5], s));
+        HIPCHK(x, hipEventRecord(S.ev[4], s));
         if (ntune > 0) {
             sa.first = 0;
             sa.n = (uint32_t)ntune;
@@ -349,7 +349,7 @@ int surrogate_batches(abcsmc_ctx* x, const ProposeArgs& pa, const DevPop& dst, i
         sa.tune_x = nullptr;
         sa.tune_y = nullptr;
         launch_sim_kept(sa, s);
-        HIPCHK(x, hipEventRecord(x->ev[6], s));
+        HIPCHK(x, hipEventRecord(S.ev[5], s));
         MaskArgs mb{(uint32_t)nk, S.mask_kept, S.off_kept, S.totals + 1, nullptr};
         launch_mask_list(mb, s);
         ca.base = (uint32_t)base;
@@ -360,7 +360,7 @@ int surrogate_batches(abcsmc_ctx* x, const ProposeArgs& pa, const DevPop& dst, i
         unsigned long long na = 0;
         HIPCHK(x, hipMemcpyAsync(&na, S.totals + 1, sizeof na, hipMemcpyDeviceToHost, s));
         HIPCHK(x, hipStreamSynchronize(s));
-        ms_k += elapsed(x->ev[5], x->ev[6]);
+        ms_k += elapsed(S.ev[4], S.ev[5]);
         acc_total += na;
         base += B;
         ++batches;

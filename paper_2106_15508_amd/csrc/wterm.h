@@ -181,39 +181,33 @@ __device__ __forceinline__ uint32_t morton32(const WeightGeom& g, const uint32_t
 }
 
 // From per-coordinate sums s1, sums of squares s2, minima and maxima over M
-// columns (one thread).
+// columns (in LDS); at least 160 threads take part.  Bit b of coordinate d has
+// the cell width var_d / 4^b (squared); the bits are taken widest first, equal
+// ones by coordinate, so a bit's place is the number of bits before it.
 __device__ __forceinline__ void make_geom(const double* s1, const double* s2, const double* mn, const double* mx,
-                                          double M, WeightGeom& g)
+                                          double M, WeightGeom* g)
 {
-    double w[kNP];
-    int bits[kNP];
-    for (int d = 0; d < kNP; ++d) {
-        const double mean = s1[d] / M;
-        const double var = s2[d] / M - mean * mean;
-        w[d] = var > 0.0 ? var : 0.0;
-        bits[d] = 0;
-        const bool any = mx[d] >= mn[d];  // false without columns
-        g.lo[d] = any ? mn[d] : 0.0;
-        g.inv[d] = mx[d] > mn[d] ? 1.0 / (mx[d] - mn[d]) : 0.0;
-        g.mid[d] = any ? 0.5 * (mn[d] + mx[d]) : 0.5;
+    constexpr int bits = 20;
+    __shared__ double width[kNP * bits];
+    const int t = threadIdx.x;
+    if (t < kNP * bits) {
+        const double mean = s1[t / bits] / M;
+        const double var = s2[t / bits] / M - mean * mean;
+        width[t] = var > 0.0 ? __builtin_ldexp(var, -2 * (t % bits)) : 0.0;
     }
-    for (int i = 0; i < 32; ++i) {
-        int best = 0;
-        double bw = -1.0;
-#pragma unroll
-        for (int d = 0; d < kNP; ++d)
-            if (bits[d] < 20 && w[d] > bw) {
-                bw = w[d];
-                best = d;
-            }
-        int nb = 0;
-#pragma unroll
-        for (int d = 0; d < kNP; ++d)
-            if (d == best) {
-                nb = bits[d]++;
-                w[d] *= 0.25;
-            }
-        g.seq[i] = best | (nb << 3);
+    if (t < kNP) {
+        const bool any = mx[t] >= mn[t];  // false without columns
+        g->lo[t] = any ? mn[t] : 0.0;
+        g->inv[t] = mx[t] > mn[t] ? 1.0 / (mx[t] - mn[t]) : 0.0;
+        g->mid[t] = any ? 0.5 * (mn[t] + mx[t]) : 0.5;
+    }
+    __syncthreads();
+    if (t < kNP * bits) {
+        const double w = width[t];
+        int place = 0;
+#pragma unroll 8
+        for (int o = 0; o < kNP * bits; ++o) place += (width[o] > w || (width[o] == w && o < t)) ? 1 : 0;
+        if (place < 32) g->seq[place] = t / bits | ((t % bits) << 3);
     }
 }
 

@@ -161,3 +161,41 @@ def test_tolerance_is_numpys_quantile(n, kw):
             info = ctx.round()
             _, d, _ = ctx.weights()
             assert info["eps_next"] == np.quantile(d, ratio), (ratio, np.unique(d).size)
+
+
+@pytest.mark.parametrize("n", [1023, 1024, 1025, 4095, 4096, 4097, 16384, 16385, 24576, 24577])
+def test_runs_at_dispatch_edges(oracle, n):
+    """Whole stages on both sides of the sizes where resampling, the sort, the
+    sort keys and the stage's end change from one workgroup to several launches:
+    populations, tolerances and the integer CDF bit for bit, the stage's counts,
+    and the weights of 64 rows within 1e-12 absolute in the log-weight."""
+    w = W.tiny(n_particles=n, n_days=6, n_rounds=3, seed=n, population=5000)
+    obs = oracle.observations(w)
+    with A.Context(w, obs) as ctx:
+        prev = None
+        for i in range(w.n_rounds):
+            info = ctx.round()
+            pop = ctx.population()
+            theta, d, wt = ctx.weights()
+            assert info["eps_next"] == np.quantile(d, w.surv_ratio)
+            assert np.all(np.diff(pop["index"]) > 0) and info["proposals"] == pop["index"][-1] + 1
+            if i == 0:
+                assert np.array_equal(wt, np.full(n, 1.0 / n)) and info["ess"] == n
+            else:
+                eps, pd = info["eps"], prev["d"]
+                strict = (pd < eps).any()
+                keep = pd < eps if strict else pd <= eps
+                top = (eps - pd[keep]).max()
+                want = np.where(keep, np.floor((eps - pd) / top * 2.0**40) if top > 0 else 1.0, 0.0).astype(np.uint64)
+                q, cdf = ctx.resampling()
+                assert np.array_equal(q, want) and np.array_equal(cdf, np.cumsum(want))
+                assert info["survivors"] == int((q > 0).sum())
+                C, lq = prev["u"][q > 0], np.log(q[q > 0].astype(np.float64))
+                for j in np.linspace(0, n - 1, 64).astype(int):
+                    x = lq - ((C - pop["u"][j]) ** 2).sum(1) / (2 * pop["sigma"][j] ** 2)
+                    lw = 8 * np.log(pop["sigma"][j]) - (x.max() + np.log(np.exp(x - x.max()).sum()))
+                    assert abs(lw - pop["logw"][j]) <= 1e-12, (i, j)
+                e = np.exp(pop["logw"] - pop["logw"].max())
+                np.testing.assert_allclose(wt, e / e.sum(), rtol=1e-11)
+                np.testing.assert_allclose(info["ess"], 1.0 / (wt * wt).sum(), rtol=1e-11)
+            prev = dict(pop, d=d)
