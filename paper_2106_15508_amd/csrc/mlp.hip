@@ -22,16 +22,22 @@ constexpr int kLdsK = kTK + 8;  // LDS row pitch (bf16) of the input tile (16-by
 
 __device__ __forceinline__ __bf16 to_bf16(float f) { return (__bf16)f; }  // round to nearest even
 
-// tanh(y) = 1 - 2 / (1 + e^{2y}) with the hardware exp and divide (absolute
-// error ~1e-7, saturates correctly at +-inf).
-__device__ __forceinline__ float tanh_fast(float y) { return 1.0f - __fdividef(2.0f, 1.0f + __expf(2.0f * y)); }
-
-// GELU, tanh form: 0.5 x (1 + tanh(c (x + 0.044715 x^3))), c = sqrt(2/pi)
+// GELU, tanh form: 0.5 x (1 + tanh(c (x + 0.044715 x^3))), c = sqrt(2/pi), with
+// tanh(y) = 1 - 2 / (1 + e^{2y}) (absolute error ~1e-7, saturates at +-inf).
+// One Newton correction of the hardware reciprocal rounds as IEEE division does
+// (d is kept finite: 2 / 2^100 vanishes against 1 as 2 / inf does); factors of 2
+// and 1/2 are moved into constants and exact fmas.  Equal to the written
+// formula, division and all, for every finite float32 x (compared
+// exhaustively), in 15 instructions for 26.
 __device__ __forceinline__ float gelu_f(float x)
 {
     const float c = 0.7978845608028654f;
-    const float t = tanh_fast(c * (x + 0.044715f * x * x * x));
-    return 0.5f * x * (1.0f + t);
+    const float y = c * (x + 0.044715f * x * x * x);
+    const float e = __builtin_amdgcn_exp2f(y * (2.0f * 1.44269504088896340736f));
+    const float d = fminf(1.0f + e, 0x1p100f);
+    const float r = __builtin_amdgcn_rcpf(d);
+    const float t = __builtin_fmaf(__builtin_fmaf(__builtin_fmaf(-d, r, 1.0f), r, r), -2.0f, 1.0f);
+    return x * __builtin_fmaf(t, 0.5f, 0.5f);
 }
 
 // ---------------------------------------------------------------------------
@@ -56,18 +62,27 @@ __global__ __launch_bounds__(256) void to_bf16_kernel(const float* __restrict__ 
     if (i < n) q[i] = to_bf16(p[i]);
 }
 
-// acc + bias, GELU, bf16 into H (rows 16a + 4(lane/16) + e, column n0 + 16b + lane%16)
+typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+
+// acc + bias, GELU, bf16 into H (row 16a + lane%16, columns n0 + 16b + 4(lane/16) + e).
+// The activations' vector instructions bound the kernel, not its products: 65536
+// rows 51.1 us with a general division and 2-byte stores, 41.1 us as it is.
 __device__ __forceinline__ void fused_epilogue(f32x4 (&acc)[8][4], const float* __restrict__ bias, int n0, int lane,
                                                __bf16 (*H)[kHP])
 {
 #pragma unroll
     for (int b = 0; b < 4; ++b) {
-        const int c = n0 + 16 * b + lane % 16;
-        const float bc = bias[c];
+        const int c = n0 + 16 * b + 4 * (lane / 16);
+        float bc[4];
 #pragma unroll
-        for (int a = 0; a < 8; ++a)
+        for (int e = 0; e < 4; ++e) bc[e] = bias[c + e];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) H[16 * a + 4 * (lane / 16) + e][c] = to_bf16(gelu_f(acc[a][b][e] + bc));
+        for (int a = 0; a < 8; ++a) {
+            bf16x4 h;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) h[e] = to_bf16(gelu_f(acc[a][b][e] + bc[e]));
+            *reinterpret_cast<bf16x4*>(&H[16 * a + lane % 16][c]) = h;
+        }
     }
 }
 
@@ -107,7 +122,7 @@ __global__ __launch_bounds__(256) void mlp_fused_kernel(const float* __restrict_
         for (int a = 0; a < 8; ++a) {
             const bf16x8 af = *reinterpret_cast<const bf16x8*>(&X0[16 * a + lane % 16][8 * (lane / 16)]);
 #pragma unroll
-            for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfr[b], acc[a][b], 0, 0, 0);
+            for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[b], af, acc[a][b], 0, 0, 0);
         }
         fused_epilogue(acc, params + kOffB1, n0, lane, H);
     }
@@ -132,7 +147,7 @@ __global__ __launch_bounds__(256) void mlp_fused_kernel(const float* __restrict_
                 const bf16x8 af = *reinterpret_cast<const bf16x8*>(&H[16 * a + lane % 16][k0 + 8 * (lane / 16)]);
 #pragma unroll
                 for (int b = 0; b < 4; ++b)
-                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af, bfr[b], acc[a][b], 0, 0, 0);
+                    acc[a][b] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfr[b], af, acc[a][b], 0, 0, 0);
             }
         }
         __syncthreads();  // every wave has read H
