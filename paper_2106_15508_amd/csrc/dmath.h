@@ -35,6 +35,12 @@ struct u4 {
     uint32_t x, y, z, w;
 };
 
+// x ^ y ^ z in one instruction
+__device__ __forceinline__ uint32_t xor3(uint32_t x, uint32_t y, uint32_t z)
+{
+    return (uint32_t)__builtin_amdgcn_bitop3_b32((int)x, (int)y, (int)z, 0x96);
+}
+
 __device__ __forceinline__ u4 philox10(u4 c, uint32_t k0, uint32_t k1)
 {
 #pragma unroll
@@ -42,9 +48,9 @@ __device__ __forceinline__ u4 philox10(u4 c, uint32_t k0, uint32_t k1)
         const uint64_t m0 = (uint64_t)0xD2511F53u * c.x;
         const uint64_t m1 = (uint64_t)0xCD9E8D57u * c.z;
         u4 n;
-        n.x = (uint32_t)(m1 >> 32) ^ c.y ^ k0;
+        n.x = xor3((uint32_t)(m1 >> 32), c.y, k0);
         n.y = (uint32_t)m1;
-        n.z = (uint32_t)(m0 >> 32) ^ c.w ^ k1;
+        n.z = xor3((uint32_t)(m0 >> 32), c.w, k1);
         n.w = (uint32_t)m0;
         c = n;
         k0 += 0x9E3779B9u;
@@ -68,9 +74,11 @@ __device__ __forceinline__ w2 block_words(uint64_t seed, uint32_t index, uint32_
     return w2{((uint64_t)o.y << 32) | o.x, ((uint64_t)o.w << 32) | o.z};
 }
 
+// ((w >> 12) + 1/2) 2^-52: the 52 bits as the mantissa of a number in [1, 2),
+// less 1 - 2^-53 (exact: the result has 53 bits)
 __device__ __forceinline__ double u01(uint64_t w)
 {
-    return ((double)(w >> 12) + 0.5) * 0x1p-52;
+    return __longlong_as_double((long long)((w >> 12) | 0x3FF0000000000000ull)) - 0x1.fffffffffffffp-1;
 }
 
 // ---------------------------------------------------------------- constants
@@ -293,15 +301,9 @@ __device__ __forceinline__ double log1p(double x)
 
 // ---------------------------------------------------------------- trig / normals
 
-// (cos 2 pi t, sin 2 pi t) for t in [0, 1).
-__device__ __forceinline__ void sincos2pi(double t, double& c, double& s)
+// sin y and cos y for 0 <= y <= pi/4 (Taylor).
+__device__ __forceinline__ void sincos_octant(double y, double& sy, double& pc)
 {
-    const double t4 = t * 4.0;
-    const double q = __builtin_floor(t4);
-    const double f = t4 - q;
-    const bool fold = f > 0.5;
-    const double g = fold ? 1.0 - f : f;
-    const double y = g * kHalfPi;
     const double ny2 = -(y * y);
     double ps = kF17;
     ps = __builtin_fma(ps, ny2, kF15);
@@ -312,8 +314,8 @@ __device__ __forceinline__ void sincos2pi(double t, double& c, double& s)
     ps = __builtin_fma(ps, ny2, kF5);
     ps = __builtin_fma(ps, ny2, kF3);
     ps = __builtin_fma(ps, ny2, kF1);
-    const double sy = y * ps;
-    double pc = kF18;
+    sy = y * ps;
+    pc = kF18;
     pc = __builtin_fma(pc, ny2, kF16);
     pc = __builtin_fma(pc, ny2, kF14);
     pc = __builtin_fma(pc, ny2, kF12);
@@ -323,6 +325,24 @@ __device__ __forceinline__ void sincos2pi(double t, double& c, double& s)
     pc = __builtin_fma(pc, ny2, kF4);
     pc = __builtin_fma(pc, ny2, kF2);
     pc = __builtin_fma(pc, ny2, kF0);
+}
+
+__device__ __forceinline__ double flip_sign(double v, uint32_t bit31)
+{
+    return __longlong_as_double(__double_as_longlong(v) ^ (long long)((uint64_t)bit31 << 32));
+}
+
+// (cos 2 pi t, sin 2 pi t) for t in [0, 1).
+__device__ __forceinline__ void sincos2pi(double t, double& c, double& s)
+{
+    const double t4 = t * 4.0;
+    const double q = __builtin_floor(t4);
+    const double f = t4 - q;
+    const bool fold = f > 0.5;
+    const double g = fold ? 1.0 - f : f;
+    const double y = g * kHalfPi;
+    double sy, pc;
+    sincos_octant(y, sy, pc);
     // quadrant 0: (cf, sf), 1: (-sf, cf), 2: (-cf, -sf), 3: (sf, -cf) with
     // (cf, sf) = (pc, sy), exchanged by the fold; by selection, so that the
     // lanes' quadrants do not split the wave
@@ -334,15 +354,31 @@ __device__ __forceinline__ void sincos2pi(double t, double& c, double& s)
     s = iq & 2u ? -ss : ss;
 }
 
+// sincos2pi((h + 1/2) 2^-32) with the quadrant and the octant fold taken from
+// h's bits: t 4 - q is (r + 1/2) 2^-30 for the low 30 bits r, above 1/2 where
+// bit 29 is set, and 1 - f there has the complement of r; the same values, all
+// of them exact.
+__device__ __forceinline__ void sincos_half(uint32_t h, double& c, double& s)
+{
+    const uint32_t fold = (uint32_t)((int32_t)(h << 2) >> 31);  // all ones where bit 29 is set
+    const double g = ((double)((h ^ fold) & 0x1FFFFFFFu) + 0.5) * 0x1p-30;
+    double sy, pc;
+    sincos_octant(g * kHalfPi, sy, pc);
+    const bool swap = ((h ^ (h >> 1)) & 0x20000000u) != 0;  // fold, or an odd quadrant
+    const double cc = swap ? sy : pc;
+    const double ss = swap ? pc : sy;
+    c = flip_sign(cc, (h ^ (h << 1)) & 0x80000000u);  // quadrants 1 and 2
+    s = flip_sign(ss, h & 0x80000000u);               // quadrants 2 and 3
+}
+
 // Box-Muller pair from one word: u1 = low half, u2 = high half; lu = log u1.
 __device__ __forceinline__ double u1_of(uint64_t w) { return ((double)(uint32_t)w + 0.5) * 0x1p-32; }
 
 __device__ __forceinline__ void normal_from_log(double lu, uint64_t w, double& z0, double& z1)
 {
-    const double u2 = ((double)(uint32_t)(w >> 32) + 0.5) * 0x1p-32;
     const double rho = sqrt_n(-2.0 * lu);  // of [2^-32, 45]
     double c, s;
-    sincos2pi(u2, c, s);
+    sincos_half((uint32_t)(w >> 32), c, s);
     z0 = rho * c;
     z1 = rho * s;
 }
@@ -504,9 +540,9 @@ __device__ __forceinline__ double binomial_draw(double n, const Prob& p, double 
     const double m = n * p.q;
     const bool small = m < kTSwitch;           // false for NaN
     const double sd = sqrt_n(m * (1.0 - p.q));  // used for m >= kTSwitch: in [2, 2^27]
-    double x = __builtin_floor((m + 0.5) + sd * z);
-    x = x < 0.0 ? 0.0 : x;
-    x = x > n ? n : x;
+    const double y = (m + 0.5) + sd * z;        // finite, or NaN where m is
+    // clamped to [0, n]; the product of y and 0 keeps the NaN that max drops
+    double x = __builtin_fma(y, 0.0, __builtin_fmax(__builtin_fmin(__builtin_floor(y), n), 0.0));
     x = small ? 0.0 : x;
     if (small && m > 0.0) {
         double l1, r;

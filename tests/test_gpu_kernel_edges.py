@@ -199,3 +199,15 @@ def test_runs_at_dispatch_edges(oracle, n):
                 np.testing.assert_allclose(wt, e / e.sum(), rtol=1e-11)
                 np.testing.assert_allclose(info["ess"], 1.0 / (wt * wt).sum(), rtol=1e-11)
             prev = dict(pop, d=d)
+
+
+def test_normal_pair_at_octant_edges(oracle):
+    """Angles on both sides of every octant's end and next to each power of
+    two, where the quadrant and the fold are read from the word's bits."""
+    edges = [k << 29 for k in range(8)] + [1 << b for b in range(32)]
+    hi = sorted({(e + d) % 2**32 for e in edges for d in (-2, -1, 0, 1, 2)})
+    w = np.array([(h << 32) | lo for h in hi for lo in (0, 1, 2**31, 2**32 - 1)], dtype=np.uint64)
+    out = np.zeros((w.size, 2))
+    got = A.debug_eval(9, w, w.size, out)
+    want = oracle.box_muller(w)
+    assert np.array_equal(got.view(np.uint64), want.view(np.uint64))
