@@ -152,7 +152,6 @@ struct WeightGeom {
 };
 
 constexpr int kColTile = 64;    // columns per tile of the weight kernels
-constexpr int kListLen = 128;   // entries of a wave's column list (a power of two >= 64 + 8)
 
 // Sorted columns (survivors of the previous stage).
 struct WeightCols {

@@ -550,16 +550,15 @@ __global__ __launch_bounds__(kBlock) void wgather_kernel(WeightArgs a)
 }
 
 // grid (row blocks, chunks): a wave's rows against the tiles of the chunk.
-// Five waves a SIMD (96 VGPRs) hide the lists' scalar loads best: 272 ms in
-// stage 1 of N = 2^20 against 288 at four and 296 at six; 128 rows a workgroup
-// balance better than 256 (16.2 against 18.0 ms in a run of N = 131072).
+// Five waves a SIMD (96 VGPRs) hide the columns' scalar loads best: 262 ms in
+// stage 1 of N = 2^20 against 295 at six; 128 rows a workgroup balance better
+// than 256 (16.2 against 18.0 ms in a run of N = 131072).
 // A run's launches against a window on one sorted coordinate: N = 20011 (8
-// stages) 1.81 -> 0.72 ms, 131072 (10) 27.7 -> 16.2 ms, 2^20 (4) 876 -> 574 ms;
-// the early stages are at 90% of the FP64 issue rate.
+// stages) 1.81 -> 0.66 ms, 131072 (10) 27.7 -> 15.4 ms, 2^20 (4) 876 -> 559 ms;
+// the early stages are at 95% of the vector issue rate.
 __global__ __launch_bounds__(kWeightRows) __attribute__((amdgpu_waves_per_eu(5))) void weights_kernel(WeightArgs a)
 {
     __shared__ double T[wterm::kTab];
-    __shared__ __attribute__((aligned(16))) uint32_t list[kWeightRows / kWave][kListLen];
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.ctr->ts[kTsSum] = wall_clock64();
     const int M = (int)*a.M;
     const int t0 = (int)blockIdx.y * a.chunk_tiles;
@@ -576,7 +575,7 @@ __global__ __launch_bounds__(kWeightRows) __attribute__((amdgpu_waves_per_eu(5))
     if (__syncthreads_or(first != 0 || t1 - t0 > kWave)) {
         wterm::load_table(T, a.tab);
         __syncthreads();
-        total = wterm::row_sum(a.sr, a.sc, group, lane, t0, t1, M, first, T, list[w], a.ex, listed, window);
+        total = wterm::row_sum(a.sr, a.sc, group, lane, t0, t1, M, first, T, a.ex, listed, window);
     }
     if (r < a.N) a.partial[(size_t)blockIdx.y * a.N + r] = total;
     // (counted per wave and added up by the finalize pass: 130000 atomics on one
@@ -610,7 +609,8 @@ __global__ __launch_bounds__(kBlock) void wterm_debug_kernel(int64_t n, const do
     }
     c.q = r[17];
     const double cj = wterm::row_scale(r[8], a.ex);
-    out[i] = __builtin_fma(c.q, wterm::term_exp(wterm::dist2(uj, c), cj, T, a.ex), 0.0);
+    const double D = wterm::dist2(uj, c), R = wterm::kWindow * r[8];
+    out[i] = D <= R * R ? __builtin_fma(c.q, wterm::term_exp(D, cj, T, a.ex, a.ex[1]), 0.0) * wterm::kSumScale : 0.0;
 }
 
 __global__ __launch_bounds__(kBlock) void weights_finalize_kernel(WeightArgs a)

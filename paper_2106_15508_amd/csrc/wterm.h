@@ -17,12 +17,14 @@ namespace wterm {
 //   of ln2/1024), k = rint(t), r = (t - k) ln2/1024, |r| <= 3.4e-4,
 //   exp = 2^(k >> 10) 2^((k & 1023)/1024) (1 + r + r^2/2 + r^3/6)
 // (truncation r^4/24 < 6e-16 relative); the weight q_k enters by one fma
-// into the running sum.  There is no cut-off: a term with
-// exponent below -708 comes out as 0 or a subnormal-size value, which cannot
-// change a row sum (every row holds its own parent's term, >= e^-185) -- the
-// sums are those of the exact-zero convention.  For t below -2^31 (every far
-// column of a row whose sigma is near the 1e-8 floor) the integer conversion
-// saturates (cvt_i32_sat) and 2^(k >> 10) underflows to 0.
+// into the running sum.  A term is added where the column lies in the row's
+// window (D <= R_j^2), which bounds t: k is the low word of t + 1.5 2^52, and
+// the power of two enters by one integer addition to the high word of the
+// table entry (whose own i << 10 is taken off beforehand; entries carry 2^64,
+// the sum's scale, so that exponents down to the widest window's -710 stay
+// normal).  Far columns of a wave's list may give anything and are left out
+// by the execution mask.  27 vector instructions where rint, conversion,
+// ldexp and the column's number from LDS took 31.
 constexpr int kTabBits = 10;
 constexpr int kTab = 1 << kTabBits;
 
@@ -35,11 +37,12 @@ struct Col {
 
 __device__ __forceinline__ Col load_col(const_col_ptr cu, const_col_ptr cq, uint32_t k)
 {
+    typedef const __attribute__((address_space(4))) char* const_byte_ptr;
     Col c;
-    const_col_ptr p = cu + (size_t)k * kNP;
+    const_col_ptr p = (const_col_ptr)((const_byte_ptr)cu + k * (uint32_t)(kNP * sizeof(double)));
 #pragma unroll
     for (int d = 0; d < kNP; ++d) c.u[d] = p[d];
-    c.q = cq[k];
+    c.q = *(const_col_ptr)((const_byte_ptr)cq + k * (uint32_t)sizeof(double));
     return c;
 }
 
@@ -57,17 +60,33 @@ __device__ __forceinline__ double dist2(const double* uj, const Col& c)
     return D;
 }
 
-__device__ __forceinline__ double term_exp(double D, double cj, const double* T, const double* ex)
+// times 2^64, for |D c_j| < 2^20.
+__device__ __forceinline__ double term_exp(double D, double cj, const double* T, const double* ex, double ex1)
 {
-    const double t = D * cj;
-    const double kk = __builtin_rint(t);
-    const double f = t - kk;
-    const int ik = dm::cvt_i32_sat(kk);
-    double p = __builtin_fma(f, ex[2], ex[1]);
+    constexpr double kMagic = 0x1.8p52;
+    const double v = __builtin_fma(D, cj, kMagic);
+    const double f = __builtin_fma(D, cj, -(v - kMagic));
+    const uint32_t k = (uint32_t)__double_as_longlong(v);
+    double p = __builtin_fma(f, ex[2], ex1);
     p = __builtin_fma(p, f, ex[0]);
     p = __builtin_fma(p, f, 1.0);
-    return __builtin_ldexp(T[ik & (kTab - 1)] * p, ik >> kTabBits);
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    u32x2 e = __builtin_bit_cast(u32x2, T[k & (kTab - 1)]);
+    e.y += k << (20 - kTabBits);
+    return __builtin_bit_cast(double, e) * p;
 }
+
+// sum += q x in the lanes of mask.
+__device__ __forceinline__ void add_where(unsigned long long mask, double q, double x, double& sum)
+{
+    unsigned long long all;
+    asm("s_and_saveexec_b64 %1, %2\n\tv_fma_f64 %0, %3, %4, %0\n\ts_mov_b64 exec, %1"
+        : "+v"(sum), "=&s"(all)
+        : "s"(mask), "s"(q), "v"(x)
+        : "scc");
+}
+
+constexpr double kSumScale = 0x1p-64;  // of the sums of term_exp
 
 // Per-lane scale c_j of the row's exponent (ex[3] = 1024 / ln 2).
 __device__ __forceinline__ double row_scale(double sigma, const double* ex)
@@ -78,10 +97,11 @@ __device__ __forceinline__ double row_scale(double sigma, const double* ex)
 static_assert(kTab == kWeightTab, "table length");
 static_assert(kColTile == kWave, "a lane per column of a tile");
 
-// Table entry i: 2^(i/1024).
+// Table entry i: 2^(i/1024 + 64) with i << 10 taken off its high word.
 __device__ __forceinline__ double table_entry(int i)
 {
-    return dm::exp((double)i * (0.6931471805599453 / kTab));
+    const long long e = __double_as_longlong(dm::exp((double)i * (0.6931471805599453 / kTab)));
+    return __longlong_as_double(e + ((64ll << 52) - ((long long)i << (52 - kTabBits))));
 }
 
 // Copy of the table (written once per context by launch_weight_table) into
@@ -371,17 +391,20 @@ __device__ __forceinline__ unsigned long long near_tiles(const WeightRows& rows,
 // that passes is tested pair by pair on the matrix cores (pair test above, four
 // 32x32 products a half tile; with the lists 11% of the instructions in stage 1
 // of N = 131072);
-// the columns that some row needs go to a list in LDS, and the list is taken
-// four at a time, their scalar loads issued together.  At N = 131072 the lists
-// hold 53, 36, 24, 9, 3 and 1% of all pairs in stages 1, 2, 3, 5, 7 and 9
-// (a window on one sorted coordinate evaluated 80, 66, 53, 29, 13 and 8%; the
-// rows' own windows hold 36, 21, 13, 3, 1 and 0.3%).  Two interleaved sums
-// (even and odd places of the list), flushed once a tile.
+// the columns that some row needs are the set bits of a scalar word, taken two
+// at a time by scalar instructions (which issue beside the other waves' vector
+// ones, though not for nothing: 21 a term instead of 14 cost 3%; three or four
+// at a time run out of scalar registers, 262 against 269 ms in stage 1 of
+// N = 2^20, and a list in LDS took 278).  At N = 131072 they are 53, 36, 24,
+// 9, 3 and 1% of all pairs in stages 1, 2, 3, 5, 7 and 9 (a window on one
+// sorted coordinate evaluated 80, 66, 53, 29, 13 and 8%; the rows' own windows
+// hold 36, 21, 13, 3, 1 and 0.3%).  Two interleaved sums
+// (first and second of a pair), flushed once a tile.
 // window: pairs of this wave inside the rows' own windows, over all lanes.
 // first: near_tiles() of the first kWave tiles.
 __device__ __forceinline__ double row_sum(const WeightRows& rows, const WeightCols& cols, int group, int lane, int t0,
-                                          int t1, int M, unsigned long long first, const double* T, uint32_t* list,
-                                          const double* ex, uint32_t& listed, uint32_t& window)
+                                          int t1, int M, unsigned long long first, const double* T, const double* ex,
+                                          uint32_t& listed, uint32_t& window)
 {
     const int r = group * kWave + lane;
     double uj[kNP];
@@ -402,12 +425,17 @@ __device__ __forceinline__ double row_sum(const WeightRows& rows, const WeightCo
     const uint32_t kbase = (uint32_t)t0 * kColTile;
     const const_col_ptr cu = (const_col_ptr)(cols.u + (size_t)kbase * kNP), cq = (const_col_ptr)(cols.q + kbase);
     double total = 0.0;
-    uint32_t cnt = 0, pos = 0;
+    uint32_t cnt = 0;
+    double ex1 = ex[1];  // in vector registers: an fma takes one scalar operand
+    asm volatile("" : "+v"(ex1));
     auto term = [&](const Col& c, double& p) {
         const double D = dist2(uj, c);
-        window += (uint32_t)__popcll(__ballot(D <= R2));
-        p = __builtin_fma(c.q, term_exp(D, cj, T, ex), p);
+        const unsigned long long in = __ballot(D <= R2);
+        window += (uint32_t)__popcll(in);
+        add_where(in, c.q, term_exp(D, cj, T, ex, ex1), p);
     };
+    uint32_t odd = 0;  // a listed column without a partner yet
+    bool have_odd = false;
     for (int s0 = t0; s0 < t1; s0 += kWave) {
         unsigned long long tiles = s0 == t0 ? first : near_tiles(rows, cols, group, lane, s0, t1);
         while (tiles) {
@@ -433,43 +461,39 @@ __device__ __forceinline__ double row_sum(const WeightRows& rows, const WeightCo
             }
             const int left = M - k0;
             if (left < kColTile) bits &= (1ull << left) - 1ull;
-            if ((bits >> lane) & 1ull)
-                list[(cnt + __builtin_amdgcn_mbcnt_hi((uint32_t)(bits >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bits, 0))) &
-                     (kListLen - 1)] = (uint32_t)(k0 - (int)kbase + lane);
-            cnt += (uint32_t)__popcll(bits);
-            // the lanes' entries are read back by the whole wave
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+            int n = __popcll(bits);
+            cnt += (uint32_t)n;
             // the next near tile on its way into the cache while this one is evaluated
             const size_t kn = (size_t)(s0 + (tiles ? __builtin_ctzll(tiles) : t - s0)) * kColTile + lane;
             const float touch0 = ((const float*)(cols.u + kn * kNP))[0], touch1 = ((const float*)(cols.q + kn))[0],
                         touch2 = ((const float*)(ch + kn))[0], touch3 = ((const float*)(ch + cols.pad + kn))[0],
                         touch4 = ((const float*)(ch + 2 * cols.pad + kn))[0];
             double p0 = 0.0, p1 = 0.0;
-            while (cnt - pos >= 4) {
-                const uint4 e = *(const uint4*)(list + (pos & (kListLen - 1)));
-                pos += 4;
-                const Col c0 = load_col(cu, cq, __builtin_amdgcn_readfirstlane(e.x)),
-                          c1 = load_col(cu, cq, __builtin_amdgcn_readfirstlane(e.y)),
-                          c2 = load_col(cu, cq, __builtin_amdgcn_readfirstlane(e.z)),
-                          c3 = load_col(cu, cq, __builtin_amdgcn_readfirstlane(e.w));
+            const uint32_t k1 = (uint32_t)k0 - kbase;
+            auto next = [&]() {
+                const uint32_t k = (uint32_t)__builtin_ctzll(bits);
+                asm("s_bitset0_b64 %0, %1" : "+s"(bits) : "s"(k));
+                return k1 + k;
+            };
+            for (n += have_odd; n >= 2; n -= 2) {
+                const uint32_t e0 = have_odd ? odd : next(), e1 = next();
+                have_odd = false;
+                const Col c0 = load_col(cu, cq, e0), c1 = load_col(cu, cq, e1);
                 term(c0, p0);
                 term(c1, p1);
-                term(c2, p0);
-                term(c3, p1);
+            }
+            if (bits) {
+                odd = next();
+                have_odd = true;
             }
             total += p0 + p1;
             asm volatile("" ::"v"(touch0), "v"(touch1), "v"(touch2), "v"(touch3), "v"(touch4));
         }
     }
     double p = 0.0;
-    for (; pos < cnt; ++pos) {
-        const uint32_t k = __builtin_amdgcn_readfirstlane(list[pos & (kListLen - 1)]);
-        term(load_col(cu, cq, k), p);
-    }
+    if (have_odd) term(load_col(cu, cq, odd), p);
     listed = cnt;
-    return total + p;
+    return (total + p) * kSumScale;
 }
 
 }  // namespace wterm
