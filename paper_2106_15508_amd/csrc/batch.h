@@ -15,6 +15,15 @@ namespace abcsmc {
 constexpr int kChunkP = kBlock;          // proposals per work item of the persistent kernel, one lane each
 constexpr int kChunkQuad = kBlock / 4;   // and with four lanes per proposal
 constexpr int kMaxWChunks = 32;  // column chunks per run in the weight kernel
+constexpr int kKeyUnit = 32;     // shortest region of a run's sort keys
+
+// slots of the sort keys of a run of N particles
+inline size_t sort_region(int64_t N)
+{
+    size_t p = kKeyUnit;
+    while ((int64_t)p < N) p <<= 1;
+    return p;
+}
 
 // Read-only description of one run.
 struct BRun {
@@ -54,7 +63,8 @@ struct BRun {
     double* red_d;             // 1 x res_nblk
     int32_t res_blk0;          // first block of this run in the segmented resample grid
     int32_t res_nblk;
-    int32_t off;               // first slot of this run in the batch-wide sort arrays (sum of earlier N)
+    int32_t off;               // first slot of this run's rows in rwin (sum of earlier N)
+    int32_t koff;              // first slot of this run's region of the sort keys
     WeightCols sc;             // this run's part of the sorted columns and rows
     WeightRows sr;
 };
@@ -96,14 +106,13 @@ struct BatchArgs {
     int32_t n_res_blocks, n_w_blocks, n_fin_blocks;
     int32_t propose_blocks;
     double ex[7];              // table-exp constants (as WeightArgs::ex)
-    // weight window (batch-wide arrays; run r owns slots [off_r, off_r + N_r))
-    unsigned long long* colkeys;  // npad: (run, column key, column) sorted
-    unsigned long long* rowkeys;  // npad: (run, sigma half-octave, row key, row) sorted
+    // sort keys: run r owns the region of sort_region(N_r) slots from koff_r on
+    unsigned long long* colkeys;  // (column key, column) sorted
+    unsigned long long* rowkeys;  // (sigma half-octave, row key, row) sorted
+    const int32_t* key_run;    // run of every kKeyUnit slots
+    SortSpans spans;
     double* rwin;              // n_total per-row window radii (slot off_r + j)
     const double* wtab;        // kWeightTab entries 2^(i/1024) of the table exponential
-    size_t npad;               // power-of-two sort length >= n_total
-    int32_t n_total;           // sum of N_r
-    int32_t n_key_blocks;      // ceil(npad / 256)
 };
 
 void batch_launch_stage(const BatchArgs& a, bool stage0, hipStream_t s);

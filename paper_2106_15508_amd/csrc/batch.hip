@@ -27,13 +27,13 @@ __device__ __forceinline__ int ld_relaxed_i(const int* p)
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <typename T>
+template <int kThreads = kBlock, typename T>
 __device__ __forceinline__ T bsum(T v, T* sh)
 {
     const int t = threadIdx.x;
     sh[t] = v;
     __syncthreads();
-    for (int off = kBlock / 2; off > 0; off >>= 1) {
+    for (int off = kThreads / 2; off > 0; off >>= 1) {
         if (t < off) sh[t] += sh[t + off];
         __syncthreads();
     }
@@ -42,12 +42,13 @@ __device__ __forceinline__ T bsum(T v, T* sh)
     return r;
 }
 
+template <int kThreads = kBlock>
 __device__ __forceinline__ double bmax(double v, double* sh)
 {
     const int t = threadIdx.x;
     sh[t] = v;
     __syncthreads();
-    for (int off = kBlock / 2; off > 0; off >>= 1) {
+    for (int off = kThreads / 2; off > 0; off >>= 1) {
         if (t < off) sh[t] = sh[t] > sh[t + off] ? sh[t] : sh[t + off];
         __syncthreads();
     }
@@ -450,11 +451,13 @@ __global__ __launch_bounds__(kBlock) void bcompact_scatter_kernel(BatchArgs a)
 // ------------------------------------------------------------------ weights
 
 // Weight pass, per run as the single-run one (smc.hip, wterm.h): column
-// statistics choose the run's sort code; columns sorted by (run, code), rows by
-// (run, sigma half-octave descending, code); gathered with what the pair test
-// needs; every wave evaluates the columns one of its rows needs.  One
-// batch-wide bitonic sort per key set: the run index in the top 12 bits keeps
-// every run's keys in its own slot range [off_r, off_r + N_r).
+// statistics choose the run's sort code; columns sorted by code, rows by
+// (sigma half-octave descending, code); gathered with what the pair test
+// needs; every wave evaluates the columns one of its rows needs.  Every
+// run has a region of the key arrays of its own, a power of two long, and all
+// regions are sorted by the same launches (one sort of all runs' keys took 580
+// us of a stage for 1.2 million particles in 48 runs, 200 us so; 72 and
+// 24 at 21500 in 12).
 using wterm::sigma_half_octave;
 
 constexpr int kDimThreads = 1024;
@@ -494,37 +497,24 @@ __global__ __launch_bounds__(kDimThreads) void bwgeom_kernel(BatchArgs a)
     wterm::make_geom(sh[0], sh[1], sh[2], sh[3], (double)M, &S.geom);
 }
 
-// run owning batch-wide slot i (i < n_total)
-__device__ __forceinline__ int slot_run(const BatchArgs& a, int i)
-{
-    int lo = 0, hi = a.n_runs - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (a.runs[mid].off <= i) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
 // grid.y 0: columns, 1: rows.
 __global__ __launch_bounds__(kBlock) void bkeys_kernel(BatchArgs a)
 {
     __shared__ uint32_t cells[kNP * kBlock];
     const size_t i = (size_t)blockIdx.x * kBlock + threadIdx.x;
-    if (i >= a.npad) return;  // each thread uses its own LDS column only
+    if (i >= a.spans.n[0]) return;  // each thread uses its own LDS column only
     const bool row = blockIdx.y != 0;
     unsigned long long* keys = row ? a.rowkeys : a.colkeys;
-    if (i >= (size_t)a.n_total) {
+    const int r = a.key_run[i / kKeyUnit];
+    const BRun& R = a.runs[r];
+    const BState& S = a.st[r];
+    const unsigned long long k = (unsigned long long)((int)i - R.koff);
+    if (k >= (unsigned long long)R.N) {
         keys[i] = ~0ull;
         return;
     }
-    const int r = slot_run(a, (int)i);
-    const BRun& R = a.runs[r];
-    const BState& S = a.st[r];
-    const unsigned long long k = (unsigned long long)((int)i - R.off);
-    const unsigned long long run = (unsigned long long)r << 52;
     if (S.failed || (!row && k >= (unsigned long long)S.survivors)) {
-        keys[i] = run | (0xFFFFFFFFull << 20) | k;
+        keys[i] = (0xFFFFFFFFull << 20) | k;
         return;
     }
     const WeightGeom& g = S.geom;
@@ -542,10 +532,10 @@ __global__ __launch_bounds__(kBlock) void bkeys_kernel(BatchArgs a)
         key = ((127u - (uint32_t)sigma_half_octave(sj)) << 25) | (key >> 7);
         const int32_t par = R.parent[nx][k];
         const bool ok = par >= 0 && par < R.N;
-        a.rwin[i] = wterm::window_radius(u, sj, ok ? R.u[1 - nx] + (size_t)par * kNP : u, ok ? (double)R.q[par] : 0.0,
+        a.rwin[R.off + k] = wterm::window_radius(u, sj, ok ? R.u[1 - nx] + (size_t)par * kNP : u, ok ? (double)R.q[par] : 0.0,
                                          (double)R.cdf[R.N - 1]);
     }
-    keys[i] = run | ((unsigned long long)key << 20) | k;
+    keys[i] = ((unsigned long long)key << 20) | k;
 }
 
 // grid = finalize table (run, row block): the block's slots of the run's
@@ -560,10 +550,10 @@ __global__ __launch_bounds__(kWeightRows) void bgather_kernel(BatchArgs a)
     if (blockIdx.y == 0) {
         const size_t M = (size_t)S.survivors;
         if (i < weight_col_pad(M))
-            wterm::gather_column(R.sc, S.geom, i, i < M, R.cols + (i < M ? (size_t)(a.colkeys[R.off + i] & 0xFFFFFull) : 0) * 9);
+            wterm::gather_column(R.sc, S.geom, i, i < M, R.cols + (i < M ? (size_t)(a.colkeys[R.koff + i] & 0xFFFFFull) : 0) * 9);
     } else {
         const bool real = i < (size_t)R.N;
-        const size_t j = real ? (size_t)(a.rowkeys[R.off + i] & 0xFFFFFull) : 0;
+        const size_t j = real ? (size_t)(a.rowkeys[R.koff + i] & 0xFFFFFull) : 0;
         wterm::gather_row(R.sr, S.geom, i, real, R.u[S.nxt] + j * kNP, R.sigma[S.nxt][j], a.rwin[R.off + j], a.ex);
     }
 }
@@ -627,45 +617,51 @@ __global__ __launch_bounds__(kWeightRows) void bfinalize_kernel(BatchArgs a)
     if (rr >= R.N) return;
     double L = 0.0;
     for (int c = 0; c < R.wchunks; ++c) L += R.wpart[(size_t)c * R.N + rr];
-    const size_t j = (size_t)(a.rowkeys[R.off + rr] & 0xFFFFFull);
+    const size_t j = (size_t)(a.rowkeys[R.koff + rr] & 0xFFFFFull);
     R.logw[S.nxt][j] = 8.0 * dm::log(R.sigma[S.nxt][j]) - dm::log(L);
 }
 
-// One block per run: W = softmax(l), ESS.
-__global__ __launch_bounds__(kBlock) void bnormalise_kernel(BatchArgs a, int uniform)
+constexpr int kNormThreads = 1024;
+
+// One block per run: W = softmax(l), ESS.  Bound by the longest run's passes
+// through one block: 214 us with 256 threads, 54 with 1024 (N = 65536).
+__global__ __launch_bounds__(kNormThreads) void bnormalise_kernel(BatchArgs a, int uniform)
 {
-    __shared__ double sh[kBlock];
+    __shared__ double sh[kNormThreads];
     const BRun& R = a.runs[blockIdx.x];
     BState& S = a.st[blockIdx.x];
     if (S.failed) return;
-    const int nx = S.nxt;
-    const double* l = R.logw[nx];
+    const int nx = S.nxt, N = R.N;
+    double* l = R.logw[nx];
     double* W = R.W[nx];
     if (uniform) {
-        for (int j = threadIdx.x; j < R.N; j += kBlock) {
-            W[j] = 1.0 / (double)R.N;
-            R.logw[nx][j] = 0.0;
+        for (int j = threadIdx.x; j < N; j += kNormThreads) {
+            W[j] = 1.0 / (double)N;
+            l[j] = 0.0;
         }
-        if (threadIdx.x == 0) S.ess = (double)R.N;
+        if (threadIdx.x == 0) S.ess = (double)N;
         return;
     }
     double mx = -__builtin_inf();
-    for (int j = threadIdx.x; j < R.N; j += kBlock) mx = l[j] > mx ? l[j] : mx;
-    mx = bmax(mx, sh);
+#pragma unroll 4
+    for (int j = threadIdx.x; j < N; j += kNormThreads) mx = l[j] > mx ? l[j] : mx;
+    mx = bmax<kNormThreads>(mx, sh);
     double s = 0.0;
-    for (int j = threadIdx.x; j < R.N; j += kBlock) {
+#pragma unroll 4
+    for (int j = threadIdx.x; j < N; j += kNormThreads) {
         const double e = dm::exp(l[j] - mx);
         W[j] = e;
         s += e;
     }
-    s = bsum(s, sh);
+    s = bsum<kNormThreads>(s, sh);
     double s2 = 0.0;
-    for (int j = threadIdx.x; j < R.N; j += kBlock) {
+#pragma unroll 4
+    for (int j = threadIdx.x; j < N; j += kNormThreads) {
         const double w = W[j] / s;
         W[j] = w;
         s2 += w * w;
     }
-    s2 = bsum(s2, sh);
+    s2 = bsum<kNormThreads>(s2, sh);
     if (threadIdx.x == 0) S.ess = 1.0 / s2;
 }
 
@@ -706,14 +702,14 @@ void batch_launch_stage(const BatchArgs& a, bool stage0, hipStream_t s)
     hipLaunchKernelGGL(bcompact_scatter_kernel, dim3(a.max_cap_blocks, a.n_runs), b, 0, s, a);
     if (!stage0) {
         hipLaunchKernelGGL(bwgeom_kernel, dim3(a.n_runs), dim3(kDimThreads), 0, s, a);
-        hipLaunchKernelGGL(bkeys_kernel, dim3(a.n_key_blocks, 2), b, 0, s, a);
-        launch_sort_u64_pair(a.colkeys, a.rowkeys, a.npad, s);
+        hipLaunchKernelGGL(bkeys_kernel, dim3((unsigned)((a.spans.n[0] + kBlock - 1) / kBlock), 2), b, 0, s, a);
+        launch_sort_spans(a.colkeys, a.rowkeys, a.spans, s);
         const dim3 bw(kWeightRows);
         hipLaunchKernelGGL(bgather_kernel, dim3(a.n_fin_blocks, 2), bw, 0, s, a);
         hipLaunchKernelGGL(bweights_kernel, dim3(a.n_w_blocks), bw, 0, s, a);
         hipLaunchKernelGGL(bfinalize_kernel, dim3(a.n_fin_blocks), bw, 0, s, a);
     }
-    hipLaunchKernelGGL(bnormalise_kernel, dim3(a.n_runs), b, 0, s, a, stage0 ? 1 : 0);
+    hipLaunchKernelGGL(bnormalise_kernel, dim3(a.n_runs), dim3(kNormThreads), 0, s, a, stage0 ? 1 : 0);
     hipLaunchKernelGGL(bselect_kernel, dim3(a.n_runs), dim3(bsel::kThreads), 0, s, a);
     hipLaunchKernelGGL(end_kernel, dim3(1), b, 0, s, a);
 }

@@ -9,6 +9,7 @@
 #include <cstdio>
 #include <cstring>
 #include <fstream>
+#include <numeric>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -106,23 +107,25 @@ RunLayout run_layout(const abcsmc_config& c, size_t o)
     return L;
 }
 
-// Batch-wide weight-pass arrays after the tables: column and row sort keys
-// (power-of-two length), the rows' window radii and the exponential table.
+// Batch-wide weight-pass arrays after the tables: column and row sort keys (a
+// region per run), the regions' runs, the rows' window radii and the
+// exponential table.
 struct WinLayout {
-    size_t colkeys, rowkeys, rwin, wtab, end, npad;
+    size_t colkeys, rowkeys, key_run, rwin, wtab, end;
 };
 
-WinLayout win_layout(size_t o, size_t n_total)
+WinLayout win_layout(size_t o, size_t n_total, size_t n_keys)
 {
     WinLayout L{};
-    L.npad = sort_padded_size(n_total);
+    const size_t slots = sort_span_slots(n_keys);
     auto take = [&](size_t bytes) {
         const size_t at = o;
         o = al(o + bytes);
         return at;
     };
-    L.colkeys = take(L.npad * 8);
-    L.rowkeys = take(L.npad * 8);
+    L.colkeys = take(slots * 8);
+    L.rowkeys = take(slots * 8);
+    L.key_run = take(n_keys / kKeyUnit * 4);
     L.rwin = take(n_total * 8);
     L.wtab = take(kWeightTab * 8);
     L.end = o;
@@ -358,10 +361,13 @@ int abcsmc_batch_workspace_size(const abcsmc_config* cfgs, int32_t n_runs, size_
     o = al(o + (size_t)n_res * sizeof(int2));
     o = al(o + (size_t)n_w * sizeof(int4));
     o = al(o + (size_t)n_fin * sizeof(int2));
-    size_t n_total = 0;
-    for (int r = 0; r < n_runs; ++r) n_total += (size_t)cfgs[r].n_particles;
+    size_t n_total = 0, n_keys = 0;
+    for (int r = 0; r < n_runs; ++r) {
+        n_total += (size_t)cfgs[r].n_particles;
+        n_keys += sort_region(cfgs[r].n_particles);
+    }
     if (n_total > ((size_t)1 << 26)) return bfail(nullptr, ABCSMC_EINVAL, "batched runs: sum of N <= 2^26");
-    o = win_layout(o, n_total).end;
+    o = win_layout(o, n_total, n_keys).end;
     *bytes = o;
     return ABCSMC_OK;
 }
@@ -513,11 +519,26 @@ int abcsmc_batch_init(const abcsmc_config* cfgs, int32_t n_runs, const int64_t* 
     o = al(o + (size_t)b->max_w_blocks * sizeof(int4));
     b->off_fin = o;
     o = al(o + fin_tab.size() * sizeof(int2));
-    const WinLayout WL = win_layout(o, n_total);
+    // the runs' regions of the sort keys, longest first
+    SortSpans& sp = b->args.spans;
+    std::vector<int32_t> by_size(n_runs), key_run;
+    std::iota(by_size.begin(), by_size.end(), 0);
+    std::stable_sort(by_size.begin(), by_size.end(), [&](int32_t x, int32_t y) {
+        return sort_region(cfgs[x].n_particles) > sort_region(cfgs[y].n_particles);
+    });
+    std::memset(&sp, 0, sizeof sp);
+    for (const int32_t r : by_size) {
+        const size_t len = sort_region(cfgs[r].n_particles);
+        b->runs[r].koff = (int32_t)sp.n[0];
+        for (int k = 0; k < kSortLevels && ((size_t)1 << k) <= len; ++k) sp.n[k] += len;
+        key_run.insert(key_run.end(), len / kKeyUnit, r);
+    }
+    const WinLayout WL = win_layout(o, n_total, sp.n[0]);
     o = WL.end;
     if (o > bytes) return bail(ABCSMC_EINVAL, "internal layout mismatch");
     if (hipMemcpy(b->ws + b->off_res, res_tab.data(), res_tab.size() * sizeof(int2), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(b->ws + b->off_fin, fin_tab.data(), fin_tab.size() * sizeof(int2), hipMemcpyHostToDevice) != hipSuccess)
+        hipMemcpy(b->ws + b->off_fin, fin_tab.data(), fin_tab.size() * sizeof(int2), hipMemcpyHostToDevice) != hipSuccess ||
+        hipMemcpy(b->ws + WL.key_run, key_run.data(), key_run.size() * 4, hipMemcpyHostToDevice) != hipSuccess)
         return bail(ABCSMC_EDEVICE, "copy of work tables failed");
     b->n_res = (int)res_tab.size();
     b->n_fin = (int)fin_tab.size();
@@ -536,13 +557,11 @@ int abcsmc_batch_init(const abcsmc_config* cfgs, int32_t n_runs, const int64_t* 
     A.n_fin_blocks = b->n_fin;
     A.colkeys = (unsigned long long*)(b->ws + WL.colkeys);
     A.rowkeys = (unsigned long long*)(b->ws + WL.rowkeys);
+    A.key_run = (const int32_t*)(b->ws + WL.key_run);
     A.rwin = (double*)(b->ws + WL.rwin);
     A.wtab = (const double*)(b->ws + WL.wtab);
     launch_weight_table((double*)(b->ws + WL.wtab), b->stream);
     if (hipGetLastError() != hipSuccess) return bail(ABCSMC_EDEVICE, "launch of the exponential table failed");
-    A.npad = WL.npad;
-    A.n_total = (int32_t)n_total;
-    A.n_key_blocks = (int32_t)((WL.npad + kBlock - 1) / kBlock);
     weight_exp_constants(A.ex);
     default_schedule(b->sched);
     if ((rc = apply_schedule(b)) || (rc = initial_states(b))) {

@@ -217,9 +217,20 @@ void launch_weight_table(double* tab, hipStream_t s);
 // Test hook: n importance-weight terms, records {u_j[8], sigma_j, u_k[8], q_k}.
 void launch_wterm_debug(int64_t n, const double* in, double* out, hipStream_t s);
 
+// Regions of 64-bit keys that are sorted each by itself, side by side from
+// slot 0 on: each a power of two long, in descending order of length (so every
+// region lies at a multiple of its length).  n[b]: keys in regions of at least
+// 2^b (n[0] all; 0 past the longest).
+constexpr int kSortLevels = 32;
+struct SortSpans {
+    size_t n[kSortLevels];
+};
+// slots to allocate for n keys of regions (whole LDS tiles)
+size_t sort_span_slots(size_t n);
+void launch_sort_spans(unsigned long long* keys0, unsigned long long* keys1, const SortSpans& sp, hipStream_t s);
+
 // Bitonic sort of 64-bit keys (length a power of two >= 2048).
 size_t sort_padded_size(size_t n);
-void launch_sort_u64(unsigned long long* keys, size_t n_pow2, hipStream_t s);
 // both arrays (each n_pow2 keys; keys1 may be null) by the same launches
 void launch_sort_u64_pair(unsigned long long* keys0, unsigned long long* keys1, size_t n_pow2, hipStream_t s);
 

@@ -211,3 +211,25 @@ def test_normal_pair_at_octant_edges(oracle):
     got = A.debug_eval(9, w, w.size, out)
     want = oracle.box_muller(w)
     assert np.array_equal(got.view(np.uint64), want.view(np.uint64))
+
+
+@pytest.mark.parametrize("sizes", [(2, 31, 32, 33, 63, 300), (2047, 17, 2048, 1025, 2049, 4097), (5003, 9000, 64)])
+def test_batch_of_sizes_at_sort_region_edges(sizes):
+    """Every run of a batch is what it is alone, for sizes at and next to the
+    lengths of its region of the sort keys, in any order."""
+    ws = [W.C1.with_(n_particles=n, n_rounds=3, seed=100 + i) for i, n in enumerate(sizes)]
+    obs = [A.observations(w) for w in ws]
+    with A.Batch(ws, obs) as b:
+        infos = b.run(3)
+        for r, w in enumerate(ws):
+            pop = b.population(r)
+            with A.Context(w, obs[r]) as c:
+                solo = c.run(3)
+                alone = c.population()
+                _, d, wt = c.weights()
+            assert [i["proposals"] for i in solo] == [st[r]["proposals"] for st in infos]
+            for k in ("u", "sigma", "parent", "index", "attempts"):
+                assert np.array_equal(pop[k], alone[k]), (w.n_particles, k)
+            assert np.array_equal(pop["d"], d)
+            np.testing.assert_allclose(pop["logw"], alone["logw"], rtol=0, atol=1e-12)
+            np.testing.assert_allclose(pop["W"], wt, rtol=1e-11)
