@@ -233,3 +233,19 @@ def test_batch_of_sizes_at_sort_region_edges(sizes):
             assert np.array_equal(pop["d"], d)
             np.testing.assert_allclose(pop["logw"], alone["logw"], rtol=0, atol=1e-12)
             np.testing.assert_allclose(pop["W"], wt, rtol=1e-11)
+
+
+def test_batch_population_of_some_arrays():
+    """Any subset of a run's arrays, and runs of different sizes in turn."""
+    ws = [W.C1.with_(n_particles=n, n_rounds=2, seed=n) for n in (300, 2049, 64)]
+    names = ("u", "sigma", "parent", "index", "attempts", "logw", "d", "W")
+    with A.Batch(ws, [A.observations(w) for w in ws]) as b:
+        b.run(2)
+        for r in (2, 1, 0, 1):
+            full = b.population(r)
+            for take in ((0,), (7,), (2, 3), (1, 4, 6), (0, 7), ()):
+                part = {k: np.full_like(full[k], 77) for k in names}
+                ptr = [part[k].ctypes.data if i in take else None for i, k in enumerate(names)]
+                assert b.L.abcsmc_batch_population(b._h, r, *ptr) == 0
+                for i, k in enumerate(names):
+                    assert np.array_equal(part[k], full[k] if i in take else np.full_like(full[k], 77)), (r, take, k)
