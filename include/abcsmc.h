@@ -271,7 +271,7 @@ typedef struct abcsmc_batch abcsmc_batch;
 
 /* Launch schedule of the batched mode (no result depends on it). */
 typedef struct {
-    int32_t propose_blocks;  /* workgroups of the persistent proposal kernel; 0 = 2 per CU */
+    int32_t propose_blocks;  /* workgroups of the persistent proposal kernel; 0 = as many as are resident (2 or 3 per CU) */
     int32_t run_order;       /* order runs are offered to workgroups: 0 index, 1 largest N*T first,
                                 2 largest/smallest interleaved */
     int32_t weight_cols;     /* target columns per weight-kernel workgroup (0 = 4096) */

@@ -310,9 +310,14 @@ __device__ int pick(const BatchArgs& a, int start, bool exact, int* chunk)
     return -1;
 }
 
-// kQuad: four lanes per proposal, kChunkQuad proposals per work item.
+// kQuad: four lanes per proposal, kChunkQuad proposals per work item.  Three
+// waves a SIMD, at the price of some spills outside the day loop, and three
+// workgroups a compute unit for it: 48 runs of 2048 to 65536 particles, 6
+// stages, 87.2 ms at two, 84.0 at three, 92 at four.  The quads have few items
+// to hide latency with and run best without spills (12 small runs: 3.65 ms at
+// two, 4.0 at three).
 template <bool kRound0, bool kQuad>
-__global__ __launch_bounds__(kBlock) void propose_persistent_kernel(BatchArgs a)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kQuad ? 2 : 3))) void propose_persistent_kernel(BatchArgs a)
 {
     __shared__ int s_run, s_chunk;
     __shared__ unsigned long long s_cnt[kBlock / kWave][4];

@@ -262,7 +262,9 @@ int apply_schedule(abcsmc_batch* b)
     (void)hipGetDevice(&dev);
     (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     b->args.n_w_blocks = (int)wt.size();
-    b->args.propose_blocks = s.propose_blocks > 0 ? s.propose_blocks : 2 * cus;
+    // as many as are resident (propose_persistent_kernel)
+    const int resident = b->args.chunk == kChunkQuad ? 2 : 3;
+    b->args.propose_blocks = s.propose_blocks > 0 ? s.propose_blocks : resident * cus;
     b->args.g = reinterpret_cast<BGlobal*>(b->ws + b->off_g);
     return ABCSMC_OK;
 }
