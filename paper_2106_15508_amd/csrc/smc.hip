@@ -549,38 +549,57 @@ __global__ __launch_bounds__(kBlock) void wgather_kernel(WeightArgs a)
     }
 }
 
-// grid (row blocks, chunks): a wave's rows against the tiles of the chunk.
+// grid (row blocks, chunks): kGroups groups of 64 rows against the tiles of the
+// chunk, a group's near tiles dealt in turn to kSplit waves.
 // Five waves a SIMD (96 VGPRs) hide the columns' scalar loads best: 262 ms in
 // stage 1 of N = 2^20 against 295 at six; 128 rows a workgroup balance better
-// than 256 (16.2 against 18.0 ms in a run of N = 131072).
+// than 256 (16.2 against 18.0 ms in a run of N = 131072).  In later stages a
+// few groups of wide rows hold most of the work and the launch lasts as long
+// as their longest wave: dealt to four waves, 8 stages of N = 20011 take 0.60
+// ms for 0.67, the last four of 10 at N = 131072 2.2 for 2.5 (weight_split).
 // A run's launches against a window on one sorted coordinate: N = 20011 (8
-// stages) 1.81 -> 0.66 ms, 131072 (10) 27.7 -> 15.4 ms, 2^20 (4) 876 -> 559 ms;
-// the early stages are at 95% of the vector issue rate.
-__global__ __launch_bounds__(kWeightRows) __attribute__((amdgpu_waves_per_eu(5))) void weights_kernel(WeightArgs a)
+// stages) 1.81 -> 0.60 ms, 131072 (10) 27.7 -> 14.8 ms, 2^20 (4) 876 -> 559 ms;
+// the early stages are at 90-95% of the vector issue rate.
+template <int kGroups, int kSplit>
+__global__ __launch_bounds__(kGroups * kSplit * kWave) __attribute__((amdgpu_waves_per_eu(5))) void weights_kernel(
+    WeightArgs a)
 {
     __shared__ double T[wterm::kTab];
+    __shared__ double part[kGroups][kSplit][kWave];
+    __shared__ uint2 count[kGroups][kSplit];
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.ctr->ts[kTsSum] = wall_clock64();
     const int M = (int)*a.M;
     const int t0 = (int)blockIdx.y * a.chunk_tiles;
     const int t1 = min((M + kColTile - 1) / kColTile, t0 + a.chunk_tiles);
     if (t0 >= t1) return;  // past the columns: the finalize pass does not read this chunk
-    const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
-    const int group = __builtin_amdgcn_readfirstlane((int)blockIdx.x * (kWeightRows / kWave) + w);
-    const int r = group * kWave + lane;
-    uint32_t listed = 0, window = 0;
-    double total = 0.0;
+    const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
+    const int g = w / kSplit, split = w % kSplit;
+    const int group = (int)blockIdx.x * kGroups + g, r = group * kWave + lane;
     // most workgroups of the late stages have no tile near: they leave before
     // the table and the rows are loaded
     const unsigned long long first = wterm::near_tiles(a.sr, a.sc, group, lane, t0, t1);
+    double total = 0.0;
+    uint2 c = make_uint2(0, 0);
     if (__syncthreads_or(first != 0 || t1 - t0 > kWave)) {
         wterm::load_table(T, a.tab);
         __syncthreads();
-        total = wterm::row_sum(a.sr, a.sc, group, lane, t0, t1, M, first, T, a.ex, listed, window);
+        part[g][split][lane] =
+            wterm::row_sum(a.sr, a.sc, group, lane, t0, t1, M, first, T, a.ex, c.x, c.y, split, kSplit);
+        if (lane == 0) count[g][split] = c;
+        __syncthreads();
+        c = make_uint2(0, 0);
+#pragma unroll
+        for (int i = 0; i < kSplit; ++i) {
+            total += part[g][i][lane];
+            c.x += count[g][i].x;
+            c.y += count[g][i].y;
+        }
     }
+    if (split != 0) return;
     if (r < a.N) a.partial[(size_t)blockIdx.y * a.N + r] = total;
-    // (counted per wave and added up by the finalize pass: 130000 atomics on one
+    // (counted per group and added up by the finalize pass: 130000 atomics on one
     // line took longer than the smaller stages' sums)
-    if (lane == 0) a.counts[(size_t)blockIdx.y * (a.sr.pad / kWave) + group] = make_uint2(listed, window);
+    if (lane == 0) a.counts[(size_t)blockIdx.y * (a.sr.pad / kWave) + group] = c;
 }
 
 __global__ __launch_bounds__(kBlock) void wtable_kernel(double* tab)
@@ -1046,9 +1065,22 @@ void launch_weight_table(double* tab, hipStream_t s)
     hipLaunchKernelGGL(wtable_kernel, dim3((wterm::kTab + kBlock - 1) / kBlock), dim3(kBlock), 0, s, tab);
 }
 
+constexpr int kWeightSplit = 4;
+
+// Whether a group's tiles are dealt to four waves.  Below 2048 rows a launch is
+// a few waves' latency (13 us for 14 dealt), from 2^18 on no wave's share
+// stands out, and two groups at the same columns use the scalar cache better
+// (559 ms for 565 in 4 stages of 2^20); 300000: 56.0 and 56.3.
+static bool weight_split(int64_t N) { return N >= 2048 && N < ((int64_t)1 << 18); }
+
 void launch_weights_sum(const WeightArgs& a, hipStream_t s)
 {
-    hipLaunchKernelGGL(weights_kernel, dim3(blocks_of(a.N, kWeightRows), a.chunks), dim3(kWeightRows), 0, s, a);
+    if (weight_split(a.N))
+        hipLaunchKernelGGL((weights_kernel<1, kWeightSplit>), dim3(blocks_of(a.N, kWave), a.chunks), dim3(kWeightSplit * kWave),
+                           0, s, a);
+    else
+        hipLaunchKernelGGL((weights_kernel<kWeightRows / kWave, 1>), dim3(blocks_of(a.N, kWeightRows), a.chunks),
+                           dim3(kWeightRows), 0, s, a);
 }
 
 void launch_weights_finalize(const WeightArgs& a, hipStream_t s)
@@ -1061,10 +1093,18 @@ void launch_weights_finalize(const WeightArgs& a, hipStream_t s)
 // same), at most 16 (the chunk's columns stay in an XCD's L2 while the row
 // blocks pass over it and the widest rows' waves stay short: 32 took 17.5 ms
 // where 16 take 16.2 at N = 131072, 8 the same), at most 128 chunks of partial
-// sums.
+// sums.  Dealt to four waves: 6000 workgroups (0.60 ms at N = 20011; 0.62 at
+// 12000 and 0.65 at 3000), at least a tile a wave, at most 64 tiles (14.7 ms at
+// N = 131072; 15.0 with 32, 15.7 with 16) and 64 chunks.
 int weight_chunk_tiles(int64_t N)
 {
-    const int64_t rb = (N + kWeightRows - 1) / kWeightRows, tiles = (N + kColTile - 1) / kColTile;
+    const int64_t tiles = (N + kColTile - 1) / kColTile;
+    if (weight_split(N)) {
+        const int64_t groups = (N + kWave - 1) / kWave;
+        const int64_t t = std::min<int64_t>(64, std::max<int64_t>(kWeightSplit, groups * tiles / 2 / 6000));
+        return (int)std::max<int64_t>(t, (tiles + 63) / 64);
+    }
+    const int64_t rb = (N + kWeightRows - 1) / kWeightRows;
     const int64_t t = std::min<int64_t>(16, std::max<int64_t>(1, rb * tiles / 2 / 12000));
     return (int)std::max<int64_t>(t, (tiles + 127) / 128);
 }

@@ -400,11 +400,12 @@ __device__ __forceinline__ unsigned long long near_tiles(const WeightRows& rows,
 // sorted coordinate evaluated 80, 66, 53, 29, 13 and 8%; the rows' own windows
 // hold 36, 21, 13, 3, 1 and 0.3%).  Two interleaved sums
 // (first and second of a pair), flushed once a tile.
+// part, parts: of the near tiles in turn, this wave's share.
 // window: pairs of this wave inside the rows' own windows, over all lanes.
 // first: near_tiles() of the first kWave tiles.
 __device__ __forceinline__ double row_sum(const WeightRows& rows, const WeightCols& cols, int group, int lane, int t0,
                                           int t1, int M, unsigned long long first, const double* T, const double* ex,
-                                          uint32_t& listed, uint32_t& window)
+                                          uint32_t& listed, uint32_t& window, int part = 0, int parts = 1)
 {
     const int r = group * kWave + lane;
     double uj[kNP];
@@ -438,9 +439,10 @@ __device__ __forceinline__ double row_sum(const WeightRows& rows, const WeightCo
     bool have_odd = false;
     for (int s0 = t0; s0 < t1; s0 += kWave) {
         unsigned long long tiles = s0 == t0 ? first : near_tiles(rows, cols, group, lane, s0, t1);
+        for (int i = 0; i < part; ++i) tiles &= tiles - 1;
         while (tiles) {
             const int t = s0 + __builtin_ctzll(tiles);
-            tiles &= tiles - 1;
+            for (int i = 0; i < parts; ++i) tiles &= tiles - 1;
             const int k0 = t * kColTile;
             unsigned long long bits = 0;
 #pragma unroll

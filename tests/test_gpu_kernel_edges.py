@@ -249,3 +249,20 @@ def test_batch_population_of_some_arrays():
                 assert b.L.abcsmc_batch_population(b._h, r, *ptr) == 0
                 for i, k in enumerate(names):
                     assert np.array_equal(part[k], full[k] if i in take else np.full_like(full[k], 77)), (r, take, k)
+
+
+@pytest.mark.parametrize("n", [2047, 2048, 2049, 2**18 - 1, 2**18])
+def test_log_weights_where_rows_are_split_over_waves(n):
+    """Both sides of the sizes between which a group's tiles go to four waves:
+    some rows' log-weights against the plain sum over all columns, 1e-12."""
+    w = W.tiny(n_particles=n, n_days=8, n_rounds=3, seed=7)
+    with A.Context(w, A.observations(w)) as ctx:
+        ctx.round()
+        for i in range(1, 3):
+            prev = ctx.population()["u"]
+            ctx.round()
+            pop, q = ctx.population(), ctx.resampling()[0].astype(np.float64)
+            for j in np.linspace(0, n - 1, 40).astype(int):
+                s = pop["sigma"][j]
+                lw = 8 * np.log(s) - np.log((q * np.exp(-((prev - pop["u"][j]) ** 2).sum(1) / (2 * s * s))).sum())
+                assert abs(lw - pop["logw"][j]) <= 1e-12, (i, j)
