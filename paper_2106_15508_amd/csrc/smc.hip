@@ -565,8 +565,6 @@ __global__ __launch_bounds__(kGroups * kSplit * kWave) __attribute__((amdgpu_wav
     WeightArgs a)
 {
     __shared__ double T[wterm::kTab];
-    __shared__ double part[kGroups][kSplit][kWave];
-    __shared__ uint2 count[kGroups][kSplit];
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.ctr->ts[kTsSum] = wall_clock64();
     const int M = (int)*a.M;
     const int t0 = (int)blockIdx.y * a.chunk_tiles;
@@ -583,16 +581,21 @@ __global__ __launch_bounds__(kGroups * kSplit * kWave) __attribute__((amdgpu_wav
     if (__syncthreads_or(first != 0 || t1 - t0 > kWave)) {
         wterm::load_table(T, a.tab);
         __syncthreads();
-        part[g][split][lane] =
-            wterm::row_sum(a.sr, a.sc, group, lane, t0, t1, M, first, T, a.ex, c.x, c.y, split, kSplit);
-        if (lane == 0) count[g][split] = c;
-        __syncthreads();
-        c = make_uint2(0, 0);
+        total = wterm::row_sum(a.sr, a.sc, group, lane, t0, t1, M, first, T, a.ex, c.x, c.y, split, kSplit);
+        if constexpr (kSplit > 1) {  // (a barrier here cost 1% where a wave has its group to itself)
+            __shared__ double part[kGroups][kSplit][kWave];
+            __shared__ uint2 count[kGroups][kSplit];
+            part[g][split][lane] = total;
+            if (lane == 0) count[g][split] = c;
+            __syncthreads();
+            total = 0.0;
+            c = make_uint2(0, 0);
 #pragma unroll
-        for (int i = 0; i < kSplit; ++i) {
-            total += part[g][i][lane];
-            c.x += count[g][i].x;
-            c.y += count[g][i].y;
+            for (int i = 0; i < kSplit; ++i) {
+                total += part[g][i][lane];
+                c.x += count[g][i].x;
+                c.y += count[g][i].y;
+            }
         }
     }
     if (split != 0) return;
