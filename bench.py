@@ -11,8 +11,8 @@ restarts the context at stage 0 (abcsmc_reset), so every step does the same
 work.
 
 Prints one JSON line: accepted particles/s (value), simulations/s, the
-roofline of the dominant kernel (device time from HIP events recorded on the
-library's stream around each launch; algorithmic flops from the op-counting
+roofline of the dominant kernel (device time from clock marks the kernels leave on the
+library's stream; algorithmic flops from the op-counting
 build of the oracle), the CPU oracle timed on a bounded sample of the same
 workload on one core and on all cores, and sub-objects for the large single
 run (c3), the batched mode (c4) and the learned screen (c5).
