@@ -433,11 +433,16 @@ int abcsmc_batch_init(const abcsmc_config* cfgs, int32_t n_runs, const int64_t* 
     // against 7.4, 8.9, 10.8, 10.7; 115000: 12.7 against 12.1).
     int64_t expected = 0;
     int sampler = 0;
+    bool any_rates = false;  // of a binomial run
+    auto box_any_rates = [](const abcsmc_config& c) {
+        return !ordinary_rates(c.prior_lo, kNP) || !ordinary_rates(c.prior_hi, kNP);
+    };
     for (int r = 0; r < n_runs; ++r) {
         expected += cfgs[r].n_particles * 5 / 4;
         sampler = std::max(sampler, cfgs[r].sampler);
+        any_rates |= cfgs[r].sampler == 0 && box_any_rates(cfgs[r]);
     }
-    const int chunk = propose_by_quads(expected / 2, sampler) ? kChunkQuad : kChunkP;
+    const int chunk = !any_rates && propose_by_quads(expected / 2, sampler, false) ? kChunkQuad : kChunkP;
     std::vector<int2> res_tab, fin_tab;
     b->runs.resize(n_runs);
     for (int r = 0; r < n_runs; ++r) {
@@ -458,6 +463,7 @@ int abcsmc_batch_init(const abcsmc_config* cfgs, int32_t n_runs, const int64_t* 
         R.m.D0 = (double)obs[r][2];
         R.m.T = c.n_days;
         R.m.sampler = c.sampler;
+        R.m.any_rates = box_any_rates(c) ? 1 : 0;
         R.m.seed = c.seed;
         char* w = b->ws;
         R.obs = (const double*)(w + L.obs);

@@ -534,7 +534,9 @@ __device__ __forceinline__ double binomial_search(double n, double l1, double r,
 // is an exact integer >= 0 held in a double.  n q < kTSwitch searches, the
 // rest rounds the normal.  The normal branch is taken by nearly every wave
 // and runs unmasked; inv() supplies (l1, r) where a lane searches.
-template <class Inv>
+// kAnyRates: n or p may be NaN.  An empty compartment and a probability of 0
+// then draw 0 whatever the other one is, and the rest stays NaN.
+template <bool kAnyRates, class Inv>
 __device__ __forceinline__ double binomial_draw(double n, const Prob& p, double z, uint64_t wu, Inv inv)
 {
     const double m = n * p.q;
@@ -549,15 +551,15 @@ __device__ __forceinline__ double binomial_draw(double n, const Prob& p, double 
         inv(l1, r);
         x = binomial_search(n, l1, r, wu);
     }
+    if (kAnyRates && m != m && (n <= 0.0 || p.q <= 0.0)) x = 0.0;
     return p.flip ? n - x : x;
 }
 
 // Bin(n, p) from one word: its uniform and its cosine deviate.
 __device__ __forceinline__ double binomial(double n, double p, uint64_t w)
 {
-    if (n <= 0.0) return 0.0;
     const Prob P = make_prob(p);
-    return binomial_draw(n, P, normal_one(w), w, [&](double& l1, double& r) {
+    return binomial_draw<true>(n, P, normal_one(w), w, [&](double& l1, double& r) {
         l1 = log1p_neg(P.q);
         r = odds(P.q);
     });

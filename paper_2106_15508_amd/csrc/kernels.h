@@ -20,8 +20,19 @@ struct Model {
     double A0, R0, D0;  // day-0 observed state
     int32_t T;          // days
     int32_t sampler;    // 0 binomial, 1 floor-normal
+    int32_t any_rates;  // parameters may be undefined or huge (ordinary_rates())
     uint64_t seed;
 };
+
+// Whether n parameters are such that no rate, probability or count of a day
+// can become NaN: every one defined and below 2^1022, so that alpha0 + alpha_c
+// stays finite (products that overflow end as probabilities of 0 or 1).
+inline bool ordinary_rates(const double* v, int64_t n)
+{
+    bool all = true;
+    for (int64_t i = 0; i < n; ++i) all &= __builtin_fabs(v[i]) < 0x1p1022;
+    return all;
+}
 
 // Points of a stage whose device time is noted (StageCounters::ts).
 enum StageMark { kTsBegin, kTsPropose, kTsProposed, kTsWeights, kTsSum, kTsSummed, kTsSelect, kTsEnd, kTsCount };
@@ -273,7 +284,7 @@ void launch_propose(const ProposeArgs& a, bool round0, hipStream_t s);
 // batch never leaves lanes of a second round to run on a mostly idle chip.
 int64_t propose_first_batch_lanes();
 // Whether n trajectories of one launch are made by four lanes each.
-bool propose_by_quads(int64_t n, int sampler);
+bool propose_by_quads(int64_t n, int sampler, bool any_rates);
 void launch_compact(const CompactArgs& a, hipStream_t s);
 void launch_resample(const ResampleArgs& a, hipStream_t s);
 // The weight pass in three parts, so that the caller can time the sum kernel

@@ -55,7 +55,7 @@ __global__ __launch_bounds__(bsel::kThreads) void predict_band_kernel(PredictArg
 
 void launch_predict(const PredictArgs& a, hipStream_t s)
 {
-    const bool quad = propose_by_quads(a.n, a.m.sampler);
+    const bool quad = propose_by_quads(a.n, a.m.sampler, a.m.any_rates);
     const dim3 grid((unsigned)(((quad ? 4 * a.n : a.n) + kBlock - 1) / kBlock));
     if (a.m.sampler == 0) {
         if (quad) hipLaunchKernelGGL((predict_series_kernel<0, true>), grid, dim3(kBlock), 0, s, a);

@@ -36,12 +36,12 @@ namespace lane {
 // is the same as without.
 // With kTraj and series != null the trajectory's (A, R, D) go to
 // series[(3 t + c) * sstride] (day t = 0..T) instead of traj.
-template <int kSampler, bool kTraj, bool kSplit = false>
-__device__ __forceinline__ double simulate_distance(const Model& m, const double* th,
-                                                    const double* __restrict__ obs, uint32_t round,
-                                                    uint32_t index, double exit_thr, int64_t* traj,
-                                                    int32_t& days, double* split = nullptr,
-                                                    double* series = nullptr, int64_t sstride = 0)
+// kAnyRates: rates may be undefined (Model::any_rates, a loop of its own: the
+// draws' tests for it in the one loop cost 1-4% of the launches).
+template <int kSampler, bool kTraj, bool kSplit, bool kAnyRates>
+__device__ __forceinline__ double simulate_days(const Model& m, const double* th, const double* __restrict__ obs,
+                                                uint32_t round, uint32_t index, double exit_thr, int64_t* traj,
+                                                int32_t& days, double* split, double* series, int64_t sstride)
 {
     const double alpha0 = th[0], alpha_c = th[1], n_exp = th[2], beta = th[3];
     const double gamma = th[4], delta = th[5], eta = th[6], kappa = th[7];
@@ -98,14 +98,14 @@ __device__ __forceinline__ double simulate_distance(const Model& m, const double
                     r = od[k];
                 };
             };
-            n1 = dm::binomial_draw(S, pSI, z0, b0.a, [&](double& a, double& r) {
+            n1 = dm::binomial_draw<kAnyRates>(S, pSI, z0, b0.a, [&](double& a, double& r) {
                 a = dm::log1p_neg(pSI.q);
                 r = dm::odds(pSI.q);
             });
-            n2 = dm::binomial_draw(I, pr[0], z1, b0.b, fixed(0));
-            n3 = dm::binomial_draw(A, pr[1], z2, b1.a, fixed(1));
-            n4 = dm::binomial_draw(A - n3, pr[2], z3, b1.b, fixed(2));
-            n5 = dm::binomial_draw(I - n2, pr[3], z4, b2.a, fixed(3));
+            n2 = dm::binomial_draw<kAnyRates>(I, pr[0], z1, b0.b, fixed(0));
+            n3 = dm::binomial_draw<kAnyRates>(A, pr[1], z2, b1.a, fixed(1));
+            n4 = dm::binomial_draw<kAnyRates>(A - n3, pr[2], z3, b1.b, fixed(2));
+            n5 = dm::binomial_draw<kAnyRates>(I - n2, pr[3], z4, b2.a, fixed(3));
         } else {
             n1 = dm::normal_floor(S, rate * S, b0.a);
             n2 = dm::normal_floor(I, gamma * I, b0.b);
@@ -160,6 +160,20 @@ __device__ __forceinline__ double simulate_distance(const Model& m, const double
     return __builtin_sqrt(acc);
 }
 
+template <int kSampler, bool kTraj, bool kSplit = false>
+__device__ __forceinline__ double simulate_distance(const Model& m, const double* th,
+                                                    const double* __restrict__ obs, uint32_t round,
+                                                    uint32_t index, double exit_thr, int64_t* traj,
+                                                    int32_t& days, double* split = nullptr,
+                                                    double* series = nullptr, int64_t sstride = 0)
+{
+    if (kSampler == 0 && m.any_rates)
+        return simulate_days<kSampler, kTraj, kSplit, true>(m, th, obs, round, index, exit_thr, traj, days, split,
+                                                            series, sstride);
+    return simulate_days<kSampler, kTraj, kSplit, false>(m, th, obs, round, index, exit_thr, traj, days, split,
+                                                         series, sstride);
+}
+
 // ---------------------------------------------------------------------------
 // Four lanes per trajectory.  A small batch leaves most of the chip idle and
 // takes as long as one wave's instruction stream, so its parallelism is spent
@@ -167,7 +181,7 @@ __device__ __forceinline__ double simulate_distance(const Model& m, const double
 // lanes 1-3 one Box-Muller pair each while lane 0 takes log C, lanes 0-2 draw
 // S->I, I->A and A->R at once, then lanes 3 and 0 draw A->D and I->Ru.  The
 // state is kept by all four lanes; values change hands by quad permutes.
-// Every value is the one-lane form's, bit for bit.
+// Every value is the one-lane form's, bit for bit.  (Ordinary rates only.)
 // ---------------------------------------------------------------------------
 template <int kCtrl>
 __device__ __forceinline__ uint32_t quad_perm(uint32_t v)
@@ -282,7 +296,7 @@ __device__ __forceinline__ double simulate_distance_quad(const Model& m, const d
             const double na = q == 0 ? S : q == 1 ? I : q == 2 ? A : 0.0;
             const double zs2 = quad_lane<2>(zs), zc23 = quad_perm<0x32>(zc);  // lane 0 <- 2, lane 2 <- 3
             const uint64_t ub = quad_lane<0>(b.b), ua = quad_lane<1>(b.a);
-            const double x = dm::binomial_draw(na, pa, q == 1 ? zs2 : zc23, q == 0 ? b.a : q == 1 ? ub : ua,
+            const double x = dm::binomial_draw<false>(na, pa, q == 1 ? zs2 : zc23, q == 0 ? b.a : q == 1 ? ub : ua,
                                                [&](double& a, double& r) {
                                                    a = l1;
                                                    r = od;
@@ -298,7 +312,7 @@ __device__ __forceinline__ double simulate_distance_quad(const Model& m, const d
             const double nb = q == 3 ? A - n3 : q == 0 ? I - n2 : 0.0;
             const double zc1 = quad_lane<1>(zc);
             const uint64_t u3 = quad_lane<1>(b.b), u4 = quad_lane<2>(b.a);
-            const double y = dm::binomial_draw(nb, own, q == 0 ? zc1 : zs, q == 0 ? u4 : u3,
+            const double y = dm::binomial_draw<false>(nb, own, q == 0 ? zc1 : zs, q == 0 ? u4 : u3,
                                                [&](double& a, double& r) {
                                                    a = l1;
                                                    r = od;

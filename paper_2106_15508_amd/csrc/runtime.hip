@@ -158,6 +158,7 @@ Model make_model(const abcsmc_config& c, const int64_t* obs0)
     m.D0 = (double)obs0[2];
     m.T = c.n_days;
     m.sampler = c.sampler;
+    m.any_rates = ordinary_rates(c.prior_lo, kNP) && ordinary_rates(c.prior_hi, kNP) ? 0 : 1;
     m.seed = c.seed;
     return m;
 }
@@ -813,6 +814,7 @@ int abcsmc_simulate(const abcsmc_config* cfg, int64_t n, const double* theta, co
     TrajArgs ta{};
     ta.m = make_model(*cfg, obs0);
     ta.m.seed = seed;
+    ta.m.any_rates = ordinary_rates(theta, n * kNP) ? 0 : 1;
     ta.n = n;
     ta.round = round;
     ta.index0 = index0;

@@ -267,8 +267,10 @@ int64_t propose_first_batch_lanes()
 // them; at four (550 us) the quads' extra instructions show.  The floor-normal
 // day has no searches to share out: 145, 220-250 and 325-335 us at one, two
 // and three waves against 245-310 us.
-bool propose_by_quads(int64_t n, int sampler)
+// Rates that may be undefined go to the one-lane form.
+bool propose_by_quads(int64_t n, int sampler, bool any_rates)
 {
+    if (any_rates && sampler == 0) return false;
     int dev = 0, cus = 0;
     if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
         (void)hipGetLastError();
@@ -281,7 +283,7 @@ bool propose_by_quads(int64_t n, int sampler)
 void launch_propose(const ProposeArgs& a, bool round0, hipStream_t s)
 {
     const dim3 g(grid_for(a.count)), b(kBlock);
-    if (propose_by_quads(a.count, a.m.sampler)) {
+    if (propose_by_quads(a.count, a.m.sampler, a.m.any_rates)) {
         const dim3 gq(grid_for((int64_t)a.count * 4));
         if (round0) {
             if (a.m.sampler == 0) hipLaunchKernelGGL((propose_quad_kernel<true, 0>), gq, b, 0, s, a);
@@ -313,7 +315,7 @@ void launch_compact(const CompactArgs& a, hipStream_t s)
 
 void launch_simulate_traj(const TrajArgs& a, hipStream_t s)
 {
-    const bool quad = propose_by_quads(a.n, a.m.sampler);
+    const bool quad = propose_by_quads(a.n, a.m.sampler, a.m.any_rates);
     const dim3 g(grid_for(quad ? 4 * a.n : a.n)), b(kBlock);
     if (a.m.sampler == 0) {
         if (quad) hipLaunchKernelGGL((simulate_traj_kernel<0, true>), g, b, 0, s, a);

@@ -266,3 +266,50 @@ def test_log_weights_where_rows_are_split_over_waves(n):
                 s = pop["sigma"][j]
                 lw = 8 * np.log(s) - np.log((q * np.exp(-((prev - pop["u"][j]) ** 2).sum(1) / (2 * s * s))).sum())
                 assert abs(lw - pop["logw"][j]) <= 1e-12, (i, j)
+
+
+@pytest.mark.parametrize("sampler", [W.SAMPLER_BINOMIAL, W.SAMPLER_NORMAL_FLOOR])
+@pytest.mark.parametrize("n", [3, 50_001])
+def test_empty_compartments_draw_nothing_at_undefined_rates(oracle, sampler, n):
+    """A transition out of an empty compartment draws 0 whatever its rate, and
+    a rate of 0 draws 0 whatever the compartment holds, NaN included; four
+    lanes a trajectory and one."""
+    w = W.tiny(sampler=sampler, n_days=4)
+    P = w.population
+    base = np.array([0.3, 2.0, 0.4, 0.1, 0.2, 0.05, 0.3, 0.5])
+    for obs0, params in (((0, 0, 0), (2, 3, 4, 5, 6)), ((P, 0, 0), (0, 1, 2))):
+        for d in params:
+            th = base.copy()
+            th[d] = np.nan
+            got = A.simulate(w, np.tile(th, (n, 1)), seed=5, rnd=1, obs0=obs0)
+            for k in (0, 1, 2, n - 1):
+                want = oracle.simulate(w, th, 5, 1, k, obs0=obs0)
+                assert (want >= 0).all()
+                assert np.array_equal(got[k], want), (obs0, d, k)
+            if obs0 == (0, 0, 0):
+                assert (got == [P, 0, 0, 0, 0, 0]).all()
+    # A is undefined from the first day on; A -> R and I -> Ru have rate 0
+    th = np.array([0.3, 2.0, 0.4, 0.0, 0.2, np.nan, 0.3, 0.5])
+    got = A.simulate(w, np.tile(th, (n, 1)), seed=5, rnd=1, obs0=(50, 0, 0))
+    assert (got[:, :, [3, 5]] == 0).all()
+
+
+def test_runs_at_undefined_rates_of_an_empty_compartment(oracle):
+    """A prior box whose infection rate overflows: infinite times no infected is
+    undefined, and nobody is left to infect.  Single run and batch against the
+    oracle's run, bit for bit."""
+    big = 1.7e308
+    w = W.tiny(n_particles=200, n_rounds=2, n_days=6)
+    obs = np.ascontiguousarray(oracle.simulate(w, w.theta_true, 1, 0, 0, obs0=(w.population, 0, 0))[:, 2:5])
+    w = w.with_(lo=(big, big, 0.0) + tuple(w.lo[3:]), hi=(big, big, 0.0) + tuple(w.hi[3:]))
+    ref = oracle.run(w, obs)
+    assert ref.rc == 0
+    with A.Context(w, obs) as ctx, A.Batch([w, w.with_(seed=5)], [obs, obs]) as b:
+        for i in range(w.n_rounds):
+            ctx.round()
+            b.round()
+            pop, d = ctx.population(), ctx.weights()[1]
+            bp = b.population(0)
+            for p, dist in ((pop, d), (bp, bp["d"])):
+                assert np.array_equal(p["index"], ref.index[i]) and np.array_equal(dist, ref.dist[i])
+                assert np.array_equal(p["u"], ref.u[i])
