@@ -269,12 +269,14 @@ int abcsmc_measure_peaks(int32_t repeats, double* fp64_tflops, double* clock_mhz
  * ------------------------------------------------------------------------- */
 typedef struct abcsmc_batch abcsmc_batch;
 
-/* Launch schedule of the batched mode (no result depends on it). */
+/* Launch schedule of the batched mode.  No particle, distance or tolerance
+ * depends on it; weight_cols sets the order of the weight sums (last bits). */
 typedef struct {
     int32_t propose_blocks;  /* workgroups of the persistent proposal kernel; 0 = as many as are resident (2 or 3 per CU) */
     int32_t run_order;       /* order runs are offered to workgroups: 0 index, 1 largest N*T first,
                                 2 largest/smallest interleaved */
-    int32_t weight_cols;     /* target columns per weight-kernel workgroup (0 = 4096) */
+    int32_t weight_cols;     /* target columns per weight-kernel workgroup, 256 to 2^20 (0 = 256); a run is
+                                split in 32 parts at most */
     double issue_margin;     /* chunk budget N / (rate * 256) x margin before over-issue (0 = 1.1) */
 } abcsmc_schedule;
 

@@ -45,11 +45,18 @@ int run_cap_blocks(const abcsmc_config& c)
 
 int wchunks_max(int64_t N) { return (int)std::min<int64_t>(kMaxWChunks, std::max<int64_t>(1, (N / 2 + 255) / 256)); }
 
-// Column chunks of a run: as the schedule asks, and more where the launch
-// (row_blocks workgroups a chunk) would leave the chip idle.
-int wchunks_for(int64_t N, int weight_cols, int64_t row_blocks)
+// Columns (of the half of N that survives) a workgroup takes by default: as
+// many chunks as wchunks_max() allows.  6 stages, ms, with 256, 1024 and 4096
+// columns: 12 runs, 22166 particles in all, 3.62, 4.07, 4.52; one run of 20011
+// 3.83, 4.26, 5.91; 24 runs, 394059 20.7, 20.3, 22.3; 48 runs, 900602 50.3, 49.3,
+// 51.6; 4 runs, 794090 139.6, 139.6, 146.8.
+constexpr int kWeightCols = 256;
+
+// Column chunks of a run: by its size and the schedule alone, so that its
+// sums are added in the same order whatever runs beside it.
+int wchunks_for(int64_t N, int weight_cols)
 {
-    const int64_t c = std::max<int64_t>((N / 2 + weight_cols - 1) / weight_cols, (8192 + row_blocks - 1) / row_blocks);
+    const int64_t c = (N / 2 + weight_cols - 1) / weight_cols;
     return (int)std::min<int64_t>(std::max<int64_t>(c, 1), wchunks_max(N));
 }
 
@@ -205,7 +212,7 @@ void default_schedule(abcsmc_schedule& s)
 {
     s.propose_blocks = 0;
     s.run_order = 1;
-    s.weight_cols = 4096;
+    s.weight_cols = kWeightCols;
     s.issue_margin = 1.1;
 }
 
@@ -243,9 +250,10 @@ int apply_schedule(abcsmc_batch* b)
     const abcsmc_schedule& s = b->sched;
     std::vector<int32_t> order = run_order(b, s.run_order);
     std::vector<int4> wt;
+    wt.reserve((size_t)b->max_w_blocks);
     for (int i = 0; i < b->R; ++i) {
         const int r = order[i];
-        b->runs[r].wchunks = wchunks_for(b->cfgs[r].n_particles, s.weight_cols, b->n_fin);
+        b->runs[r].wchunks = wchunks_for(b->cfgs[r].n_particles, s.weight_cols);
         const int rb = (int)((b->cfgs[r].n_particles + kWeightRows - 1) / kWeightRows);
         for (int y = 0; y < rb; ++y)
             for (int c = 0; c < b->runs[r].wchunks; ++c) wt.push_back(make_int4(r, y, c, 0));
@@ -594,7 +602,7 @@ int abcsmc_batch_set_schedule(abcsmc_batch* b, const abcsmc_schedule* s)
         (s->issue_margin != 0.0 && !(s->issue_margin >= 1.0 && s->issue_margin <= 8.0)))
         return bfail(&b->err, ABCSMC_EINVAL, "schedule out of range");
     b->sched = *s;
-    if (b->sched.weight_cols == 0) b->sched.weight_cols = 4096;
+    if (b->sched.weight_cols == 0) b->sched.weight_cols = kWeightCols;
     if (b->sched.issue_margin == 0.0) b->sched.issue_margin = 1.1;
     return apply_schedule(b);
 }
@@ -795,7 +803,7 @@ int abcsmc_batch_autotune(abcsmc_batch* b, int32_t stages, const char* cache_pat
     if (rc) return rc;
     const int pb[] = {cus, 2 * cus, 4 * cus, 8 * cus};
     const int ro[] = {0, 1, 2};
-    const int wc[] = {2048, 4096, 8192};
+    const int wc[] = {256, 1024, 4096};
     const double mg[] = {1.05, 1.1, 1.3};
     for (int knob = 0; knob < 4; ++knob) {
         const int n = knob == 0 ? 4 : 3;

@@ -313,3 +313,20 @@ def test_runs_at_undefined_rates_of_an_empty_compartment(oracle):
             for p, dist in ((pop, d), (bp, bp["d"])):
                 assert np.array_equal(p["index"], ref.index[i]) and np.array_equal(dist, ref.dist[i])
                 assert np.array_equal(p["u"], ref.u[i])
+
+
+@pytest.mark.parametrize("n", [1024, 4097, 20_011])
+def test_batched_run_does_not_depend_on_its_companions(n):
+    """A run's particles, log-weights, weights and effective sample size are
+    the same, bit for bit, alone in a batch and beside a few hundred thousand
+    particles of other runs."""
+    w = W.tiny(n_particles=n, n_days=6, seed=3)
+    many = [w.with_(n_particles=300_000, seed=4), w, w.with_(n_particles=2049, seed=5), w.with_(n_particles=200_000, seed=6)]
+    obs = A.observations(w)
+    with A.Batch([w], [obs]) as alone, A.Batch(many, [obs] * 4) as beside:
+        for i in range(3):
+            a, b = alone.round()[0], beside.round()[1]
+            assert a["ess"] == b["ess"] and a["eps_next"] == b["eps_next"], i
+            p, q = alone.population(0), beside.population(1)
+            for k in p:
+                assert np.array_equal(p[k], q[k]), (i, k)
