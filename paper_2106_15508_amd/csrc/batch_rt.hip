@@ -90,7 +90,11 @@ RunLayout run_layout(const abcsmc_config& c, size_t o)
     L.q = take(N * 8);
     L.cdf = take(N * 8);
     L.cols = take(N * 9 * 8);
-    L.wpart = take((size_t)wchunks_max((int64_t)N) * N * 8);
+    L.red_u = take(3 * nres * 8);
+    L.red_d = take(nres * 8);
+    // The proposals' staging is done with when a stage's weights are formed:
+    // one place for both.
+    const size_t shared = o;
     L.st_u = take(B * kNP * 8);
     L.st_d = take(B * 8);
     L.st_sigma = take(B * 8);
@@ -98,9 +102,10 @@ RunLayout run_layout(const abcsmc_config& c, size_t o)
     L.st_att = take(B * 4);
     L.wmask = take(B / kWave * 8);
     L.woff = take(B / kWave * 4);
-    L.red_u = take(3 * nres * 8);
-    L.red_d = take(nres * 8);
+    const size_t staged = o;
+    o = shared;
     const size_t cpad = weight_col_pad(N), rpad = weight_row_pad(N);
+    L.wpart = take((size_t)wchunks_max((int64_t)N) * N * 8);
     L.scu = take(cpad * kNP * 8);
     L.scq = take(cpad * 8);
     L.scop = take(3 * cpad * 16);
@@ -111,6 +116,7 @@ RunLayout run_layout(const abcsmc_config& c, size_t o)
     L.srop = take(3 * rpad * 16);
     L.srbox = take(rpad / kWave * 17 * 4);
     L.wcounts = take((size_t)wchunks_max((int64_t)N) * (rpad / kWave) * sizeof(uint2));
+    o = std::max(o, staged);
     L.end = o;
     return L;
 }

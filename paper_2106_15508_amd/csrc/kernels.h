@@ -123,7 +123,8 @@ struct Scratch {
     double* d1;              // kRedMax
     unsigned int* hist;      // 2048 bins of the multi-block select
     unsigned long long* sel; // its state: values collected, values below the bin, values in the bin
-    double* list;            // kSelectList collected values
+    double* list;            // collected values
+    uint32_t list_cap;       // as many as it holds, kSelectList at most
 };
 
 struct ResampleArgs {

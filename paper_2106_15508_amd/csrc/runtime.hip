@@ -63,6 +63,15 @@ Layout make_layout(const abcsmc_config& c)
     L.q = take(N * sizeof(uint64_t));
     L.cdf = take(N * sizeof(uint64_t));
     L.cols = take(N * 9 * sizeof(double));
+    L.ctr = take(sizeof(StageCounters));
+    for (int r = 0; r < 5; ++r) L.red[r] = take(kRedMax * 8);
+    L.hist = take(2048 * sizeof(unsigned int));
+    L.sel = take(8 * sizeof(unsigned long long));
+    L.wtab = take(kWeightTab * sizeof(double));
+    // The proposals' staging is done with when a stage's weights are formed
+    // (and written anew should the stage need another batch): one place for
+    // both.
+    const size_t shared = o;
     L.st_u = take(B * kNP * sizeof(double));
     L.st_d = take(B * sizeof(double));
     L.st_sigma = take(B * sizeof(double));
@@ -70,17 +79,10 @@ Layout make_layout(const abcsmc_config& c)
     L.st_att = take(B * sizeof(int32_t));
     L.wave_mask = take((B / kWave + 4) * sizeof(unsigned long long));
     L.wave_off = take((B / kWave + 4) * sizeof(uint32_t));
-    L.ctr = take(sizeof(StageCounters));
-    L.theta = take(N * kNP * sizeof(double));
-    for (int r = 0; r < 5; ++r) L.red[r] = take(kRedMax * 8);
-    L.hist = take(2048 * sizeof(unsigned int));
-    L.sellist = take(kSelectList * sizeof(double));
-    L.sel = take(8 * sizeof(unsigned long long));
-    L.wpart = take((size_t)weight_chunks((int64_t)N) * N * sizeof(double));
+    const size_t staged = o;
+    o = shared;
     const size_t npad = sort_padded_size(N);
     const size_t cpad = weight_col_pad(N), rpad = weight_row_pad(N);
-    L.rowkeys = take(npad * 8);
-    L.colkeys = take(npad * 8);
     L.scu = take(cpad * kNP * sizeof(double));
     L.scq = take(cpad * sizeof(double));
     L.scop = take(3 * cpad * 16);
@@ -90,12 +92,24 @@ Layout make_layout(const abcsmc_config& c)
     L.srr2 = take(rpad * sizeof(double));
     L.srop = take(3 * rpad * 16);
     L.srbox = take(rpad / kWave * 17 * sizeof(float));
+    // the partial sums follow on the column keys and window radii, which the
+    // gather of the sorted operands has read
+    const size_t colkeys = align_up(npad * 8);
+    L.wpart = take(std::max((size_t)weight_chunks((int64_t)N) * N * sizeof(double), colkeys + N * sizeof(double)));
+    L.colkeys = L.wpart;
+    L.rwin = L.wpart + colkeys;
+    L.rowkeys = take(npad * 8);
+    L.wcounts = take((size_t)weight_chunks((int64_t)N) * (rpad / kWave) * sizeof(uint2));
     L.dimpart = take(kDimBlocks * 32 * sizeof(double));
     L.geom = take(sizeof(WeightGeom));
-    L.wcounts = take((size_t)weight_chunks((int64_t)N) * (rpad / kWave) * sizeof(uint2));
-    for (auto& r : L.rank) r = take(std::min<size_t>(N, kRankSort) * 8);
-    L.rwin = take(N * sizeof(double));
-    L.wtab = take(kWeightTab * sizeof(double));
+    // used before the sorted operands are gathered, or after the weights: the
+    // unsorted keys, the percentile's list, the copied out parameters
+    L.rank[0] = L.scu;
+    L.rank[1] = L.scu + align_up(std::min<size_t>(N, kRankSort) * 8);
+    L.sellist = L.scu;
+    L.theta = L.sru;
+    o = std::max(o, staged);
+    L.sellist_cap = std::min<size_t>(kSelectList, (o - shared) / 8);
     L.total = o;
     return L;
 }

@@ -924,7 +924,7 @@ __global__ __launch_bounds__(kBlock) void select_hist_kernel(SelectArgs a)
 }
 
 // Bin of the rank (every block finds it), its values collected into the list
-// (at most kSelectList of them are kept), the block's smallest value above.
+// (at most list_cap of them are kept), the block's smallest value above.
 __global__ __launch_bounds__(kBlock) void select_collect_kernel(SelectArgs a)
 {
     __shared__ unsigned long long shu[kBlock];
@@ -959,7 +959,7 @@ __global__ __launch_bounds__(kBlock) void select_collect_kernel(SelectArgs a)
         const unsigned long long b = bsel::bits_of(x), d = b >> g.sh;
         if (d == want) {
             const unsigned long long at = atomicAdd(&a.sc.sel[0], 1ull);
-            if (at < kSelectList) a.sc.list[at] = x;
+            if (at < a.sc.list_cap) a.sc.list[at] = x;
         } else if (d > want && b < above) {
             above = b;
         }
@@ -984,7 +984,7 @@ __global__ __launch_bounds__(bsel::kThreads) void select_finish_kernel(SelectArg
     bsel::ranks7(a.N, a.alpha, r0, r1);
     const unsigned int count = (unsigned int)a.sc.sel[2], rank = (unsigned int)r0 - (unsigned int)a.sc.sel[1];
     unsigned long long xa, xb;
-    if (count > (unsigned)kSelectList) {  // values crowded into one of 2048 bins: all of them again
+    if (count > a.sc.list_cap) {  // values crowded into one of 2048 bins: all of them again
         bsel::order_pair(bsel::FromMemory{a.x, a.N}, a.N, (unsigned int)r0, sh);
         xa = sh.xa;
         xb = sh.xb;
@@ -1091,14 +1091,14 @@ void launch_weights_finalize(const WeightArgs& a, hipStream_t s)
     hipLaunchKernelGGL(weights_finalize_kernel, dim3(blocks_of(a.N, kBlock)), dim3(kBlock), 0, s, a);
 }
 
-// Tiles per chunk: as many as leave 12000 workgroups of work (about half of N
-// survives; 3000 took 1.05 ms where 12000 take 0.72 at N = 20011, 24000 the
-// same), at most 16 (the chunk's columns stay in an XCD's L2 while the row
-// blocks pass over it and the widest rows' waves stay short: 32 took 17.5 ms
-// where 16 take 16.2 at N = 131072, 8 the same), at most 128 chunks of partial
-// sums.  Dealt to four waves: 6000 workgroups (0.60 ms at N = 20011; 0.62 at
-// 12000 and 0.65 at 3000), at least a tile a wave, at most 64 tiles (14.7 ms at
-// N = 131072; 15.0 with 32, 15.7 with 16) and 64 chunks.
+// Tiles per chunk.  Below 2048 rows: as many as leave 12000 workgroups of work
+// (about half of N survives).  Dealt to four waves: 6000 workgroups (0.60 ms at
+// N = 20011; 0.62 at 12000 and 0.65 at 3000), at least a tile a wave, at most 64
+// tiles (14.7 ms at N = 131072; 15.0 with 32, 15.7 with 16) and 64 chunks.  From
+// 2^18 on: 32 tiles doubled until 128 chunks are enough, and at most 112 chunks:
+// the partial sums are most of the workspace there, and it has to fit in what
+// earlier versions asked for (128 chunks at every size: 4 stages of 300000 26.7
+// ms for 27.4, of 600000 97.2 for 97.8, of 2^18 and 2^20 the same).
 int weight_chunk_tiles(int64_t N)
 {
     const int64_t tiles = (N + kColTile - 1) / kColTile;
@@ -1108,8 +1108,9 @@ int weight_chunk_tiles(int64_t N)
         return (int)std::max<int64_t>(t, (tiles + 63) / 64);
     }
     const int64_t rb = (N + kWeightRows - 1) / kWeightRows;
-    const int64_t t = std::min<int64_t>(16, std::max<int64_t>(1, rb * tiles / 2 / 12000));
-    return (int)std::max<int64_t>(t, (tiles + 127) / 128);
+    int64_t t = std::min<int64_t>(16, std::max<int64_t>(1, rb * tiles / 2 / 12000));
+    while ((tiles + t - 1) / t > 128) t *= 2;
+    return (int)std::max<int64_t>(t, (tiles + 111) / 112);
 }
 
 int weight_chunks(int64_t N)

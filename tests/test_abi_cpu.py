@@ -139,3 +139,20 @@ def test_c_example_compiles_against_the_header(tmp_path):
            "-L", B.HERE, "-labcsmc_hip", "-lm", "-o", str(out)]
     subprocess.run(cmd, check=True, capture_output=True, timeout=120)
     assert out.exists()
+
+
+#: device bytes that the library's first versions asked for (library-chosen
+#: batches): particles of one run, or sizes of a batch's runs
+FIRST_SIZES = {2: 6045184, 300: 6331392, 1000: 7009536, 1024: 7029504, 4096: 10035968, 5003: 10983680,
+               20011: 21107968, 24576: 25346048, 32768: 35641856, 65536: 87835136, 131072: 242553344,
+               262144: 484880896, 273750: 376774400, 300000: 428870400, 1048576: 1938846208,
+               3683127: 5446504704, 4194304: 6645051904}
+FIRST_BATCH_SIZES = {(64,): 1515520, (1024,) * 12: 22557440, (2048, 4096, 65536): 64800768, (2048,) * 96: 221840640,
+                     (65536,) * 20: 1180369920, (2**20,): 1070516736}
+
+
+def test_workspaces_of_the_first_versions_are_still_enough():
+    for n, first in FIRST_SIZES.items():
+        assert A.workspace_size(W.C2.with_(n_particles=n)) <= first, n
+    for sizes, first in FIRST_BATCH_SIZES.items():
+        assert A.Batch.workspace_size([W.C1.with_(n_particles=n) for n in sizes]) <= first, sizes

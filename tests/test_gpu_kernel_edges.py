@@ -330,3 +330,23 @@ def test_batched_run_does_not_depend_on_its_companions(n):
             p, q = alone.population(0), beside.population(1)
             for k in p:
                 assert np.array_equal(p[k], q[k]), (i, k)
+
+
+@pytest.mark.parametrize("n,first", [(300, 6331392), (20_011, 21107968), (300_000, 428870400)])
+def test_run_in_a_workspace_of_the_first_versions(n, first):
+    """A caller's buffer of the size the first versions asked for is accepted
+    and gives the run that a library-owned workspace gives, a short first batch
+    included (n_days 3: acceptances vary); what lies behind it stays untouched."""
+    import torch
+    w = W.C2.with_(n_particles=n, n_days=3, seed=n)
+    obs = A.observations(w)
+    buf = torch.full((first + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    with A.Context(w, obs) as own, A.Context(w, obs, workspace=(buf.data_ptr(), first)) as ctx:
+        for i in range(4):
+            a, b = own.round(), ctx.round()
+            assert a["eps_next"] == b["eps_next"] and a["ess"] == b["ess"]
+            p, q = own.population(), ctx.population()
+            assert all(np.array_equal(p[k], q[k]) for k in p), i
+            assert all(np.array_equal(x, y) for x, y in zip(own.weights(), ctx.weights())), i
+    assert (buf[first:] == 0x5A).all()
