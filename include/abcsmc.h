@@ -290,7 +290,8 @@ int abcsmc_batch_set_schedule(abcsmc_batch* b, const abcsmc_schedule* s);
 int abcsmc_batch_get_schedule(const abcsmc_batch* b, abcsmc_schedule* s);
 /* Time schedule variants (coordinate descent over the four knobs, each trial
  * = stage 0 plus `stages` stages from a reset) and keep the fastest; a line
- * per batch shape is appended to / looked up in cache_path (NULL: no cache).
+ * per batch shape, device and kernel form is appended to / looked up in
+ * cache_path (NULL: no cache; lines of other forms are left alone).
  * Leaves the batch reset at stage 0. */
 int abcsmc_batch_autotune(abcsmc_batch* b, int32_t stages, const char* cache_path, abcsmc_schedule* chosen);
 /* Next stage of every run (one graph replay).  infos: n_runs entries or NULL. */

@@ -249,6 +249,17 @@ std::vector<int32_t> run_order(const abcsmc_batch* b, int mode)
     return o;
 }
 
+int compute_units()
+{
+    int dev = 0, cus = 256;
+    (void)hipGetDevice(&dev);
+    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    return cus;
+}
+
+// Resident workgroups per compute unit of propose_persistent_kernel.
+int resident_blocks(const BatchArgs& a) { return a.chunk == kChunkQuad ? 2 : 3; }
+
 // (Re)build the schedule-dependent tables and descriptors and drop old graphs.
 int apply_schedule(abcsmc_batch* b)
 {
@@ -272,13 +283,8 @@ int apply_schedule(abcsmc_batch* b)
     BGlobal g{b->stage, b->R, s.issue_margin > 1.0 ? s.issue_margin : 1.0};
     BCHK(b, hipMemcpyAsync(b->ws + b->off_g, &g, sizeof g, hipMemcpyHostToDevice, b->stream));
     BCHK(b, hipStreamSynchronize(b->stream));
-    int dev = 0, cus = 256;
-    (void)hipGetDevice(&dev);
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
     b->args.n_w_blocks = (int)wt.size();
-    // as many as are resident (propose_persistent_kernel)
-    const int resident = b->args.chunk == kChunkQuad ? 2 : 3;
-    b->args.propose_blocks = s.propose_blocks > 0 ? s.propose_blocks : resident * cus;
+    b->args.propose_blocks = s.propose_blocks > 0 ? s.propose_blocks : resident_blocks(b->args) * compute_units();
     b->args.g = reinterpret_cast<BGlobal*>(b->ws + b->off_g);
     return ABCSMC_OK;
 }
@@ -318,9 +324,14 @@ int capture(abcsmc_batch* b, int which)
     return ABCSMC_OK;
 }
 
+// Cache key of a tuned schedule: the runs' shapes and what else its best values
+// depend on.  kKernelForms is raised when the proposal or weight kernels change
+// their work split or residency, so that schedules tuned for others are not used.
+constexpr uint64_t kKernelForms = 2;
+
 std::string signature(const abcsmc_batch* b)
 {
-    uint64_t h = 1469598103934665603ull;  // FNV-1a over the run shapes
+    uint64_t h = 1469598103934665603ull;  // FNV-1a
     auto mix = [&](uint64_t v) {
         for (int i = 0; i < 8; ++i) {
             h ^= (v >> (8 * i)) & 0xFF;
@@ -332,7 +343,11 @@ std::string signature(const abcsmc_batch* b)
         mix((uint64_t)c.n_days);
         mix((uint64_t)c.population);
         mix((uint64_t)c.step_schedule);
+        mix((uint64_t)c.sampler);
     }
+    mix(kKernelForms);
+    mix((uint64_t)b->args.chunk);
+    mix((uint64_t)compute_units());
     char buf[32];
     snprintf(buf, sizeof buf, "%016llx", (unsigned long long)h);
     return std::string(buf) + "_" + std::to_string(b->R);
@@ -779,9 +794,7 @@ int abcsmc_batch_autotune(abcsmc_batch* b, int32_t stages, const char* cache_pat
             }
         }
     }
-    int dev = 0, cus = 256;
-    (void)hipGetDevice(&dev);
-    (void)hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev);
+    const int cus = compute_units();
     auto measure = [&](const abcsmc_schedule& s, double* ms) -> int {
         int rc = abcsmc_batch_set_schedule(b, &s);
         if (!rc) rc = abcsmc_batch_reset(b);
@@ -807,12 +820,12 @@ int abcsmc_batch_autotune(abcsmc_batch* b, int32_t stages, const char* cache_pat
     double best_ms = 0.0;
     int rc = measure(best, &best_ms);
     if (rc) return rc;
-    const int pb[] = {cus, 2 * cus, 4 * cus, 8 * cus};
+    const int pb[] = {cus, 2 * cus, 3 * cus, 4 * cus, 8 * cus};
     const int ro[] = {0, 1, 2};
     const int wc[] = {256, 1024, 4096};
     const double mg[] = {1.05, 1.1, 1.3};
     for (int knob = 0; knob < 4; ++knob) {
-        const int n = knob == 0 ? 4 : 3;
+        const int n = knob == 0 ? 5 : 3;
         for (int i = 0; i < n; ++i) {
             abcsmc_schedule s = best;
             if (knob == 0) s.propose_blocks = pb[i];

@@ -350,3 +350,25 @@ def test_run_in_a_workspace_of_the_first_versions(n, first):
             assert all(np.array_equal(p[k], q[k]) for k in p), i
             assert all(np.array_equal(x, y) for x, y in zip(own.weights(), ctx.weights())), i
     assert (buf[first:] == 0x5A).all()
+
+
+def test_cached_schedules_are_for_the_kernels_they_were_tuned_on(tmp_path):
+    """A cached schedule is not used for another sampler (whose proposals may
+    be split over the lanes in another way), nor one that was tuned before the
+    kernels' present forms (the key of the four run fields alone)."""
+    ws = [W.tiny(n_particles=n, n_days=5, n_rounds=2, seed=n) for n in (300, 500)]
+    obs = [A.observations(w) for w in ws]
+    h = 1469598103934665603
+    for w in ws:
+        for v in (w.n_particles, w.n_days, w.population, w.step_schedule):
+            for byte in int(v).to_bytes(8, "little"):
+                h = (h ^ byte) * 1099511628211 % 2**64
+    cache = tmp_path / "sched.txt"
+    cache.write_text("%016x_2 7 0 512 1.05 1.0\n" % h)
+    chosen = []
+    for sampler in (W.SAMPLER_BINOMIAL, W.SAMPLER_NORMAL_FLOOR, W.SAMPLER_BINOMIAL):
+        with A.Batch([w.with_(sampler=sampler) for w in ws], obs) as b:
+            chosen.append(b.autotune(stages=1, cache_path=str(cache)))
+    assert all(s["propose_blocks"] != 7 for s in chosen) and chosen[0] == chosen[2]
+    lines = cache.read_text().splitlines()
+    assert len(lines) == 3 and len({l.split()[0] for l in lines}) == 3
