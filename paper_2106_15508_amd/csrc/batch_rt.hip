@@ -9,7 +9,9 @@
 #include <cstdio>
 #include <cstring>
 #include <fstream>
+#include <memory>
 #include <mutex>
+#include <new>
 #include <numeric>
 #include <sstream>
 #include <string>
@@ -757,8 +759,9 @@ int abcsmc_batch_population(const abcsmc_batch* b, int32_t run, double* u, doubl
             x->staging = nullptr;
         }
     }
-    std::vector<char> pageable(x->staging ? 0 : hi - lo);
-    char* st = x->staging ? x->staging : pageable.data();
+    std::unique_ptr<char[]> pageable(x->staging ? nullptr : new (std::nothrow) char[hi - lo]);
+    char* st = x->staging ? x->staging : pageable.get();
+    if (!st) return bfail(&x->err, ABCSMC_ENOMEM, "no host memory for the population's copy-out");
     BCHK(x, hipMemcpyAsync(st, x->ws + lo, hi - lo, hipMemcpyDeviceToHost, x->stream));
     BCHK(x, hipStreamSynchronize(x->stream));
     auto at = [&](size_t off) { return st + (off - lo); };
