@@ -230,7 +230,8 @@ int abcsmc_run(const abcsmc_config* cfg, const int64_t* obs, int32_t n_rounds, d
 int abcsmc_simulate(const abcsmc_config* cfg, int64_t n, const double* theta, const int64_t* obs0,
                     uint64_t seed, uint32_t round, uint32_t index0, int64_t* traj);
 
-/* Test hook: evaluate a device primitive on n inputs (host buffers).
+/* Test hook: evaluate a device primitive on n inputs (host buffers), by the kernels' own functions
+ * on the arguments those meet (log1p: [-1/2, 0); cos, sin: x = (h + 1/2) 2^-32).
  *  fn 0..5: exp, expm1, log, log1p, cos 2 pi x, sin 2 pi x   (in: double[n], out: double[n])
  *  fn 6: sqrt, fn 7: x / y                                  (in: double[2n] pairs for 7)
  *  fn 8: Philox4x32-10                                      (in: uint32[6n] ctr0..3,key0..1; out: uint32[4n])
@@ -242,7 +243,10 @@ int abcsmc_simulate(const abcsmc_config* cfg, int64_t n, const double* theta, co
  *         uses stream (seed = param_a, particle i, round = param_b, PERTURB, attempt 0))
  *  fn 14: importance-weight term q_k exp(-|u_j - u_k|^2 / (2 sigma_j^2)) as the weight kernels
  *         evaluate it (table exponential)       (in: double[18n] records {u_j[8], sigma_j, u_k[8], q_k};
- *                                                out: double[n]) */
+ *                                                out: double[n])
+ *  fn 15..18: exp by selection (the day's), log(1 - x) and x / (1 - x) for 0 < x <= 1/2, sqrt without
+ *         range tests (x normal, > 0)                       (in: double[n], out: double[n])
+ *  fn 19: x / y without range tests                         (in: double[2n] pairs, out: double[n]) */
 int abcsmc_debug_eval(int32_t fn, int64_t n, const void* in, void* out, double param_a, int32_t param_b);
 
 /* Measurement helper (not part of the method): what the current device

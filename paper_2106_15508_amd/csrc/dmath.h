@@ -103,9 +103,11 @@ constexpr double kF0 = 1.0, kF1 = 1.0, kF2 = 1.0 / 2.0, kF3 = 1.0 / 6.0, kF4 = 1
 // ---------------------------------------------------------------- division, square root
 
 // a / b and sqrt(x), correctly rounded, for operands and results that stay
-// well inside the normal range (x > 0): the Newton steps of the general
-// sequences without their scaling, range tests and fix-up (a third of the
-// instructions).  Callers name the range.
+// well inside the normal range (x > 0): Newton-Raphson steps on the hardware's
+// reciprocal and Markstein's correction of the quotient by its residual;
+// Goldschmidt's coupled iteration for x^(1/2) and x^(-1/2) / 2 and two residual
+// corrections.  Without the scaling, range tests and fix-up that any operand
+// needs they take a third of the instructions.  Callers name the range.
 __device__ __forceinline__ double div_n(double a, double b)
 {
     double y = __builtin_amdgcn_rcp(b);
@@ -217,28 +219,6 @@ __device__ __forceinline__ double expm1_select(double x)
     return small ? __builtin_fma(x * x, p, x) : e - 1.0;
 }
 
-__device__ __forceinline__ double expm1(double x)
-{
-    if (x != x) return x;
-    if (__builtin_fabs(x) <= 0.34657359027997264) {
-        double p = kF14;
-        p = __builtin_fma(p, x, kF13);
-        p = __builtin_fma(p, x, kF12);
-        p = __builtin_fma(p, x, kF11);
-        p = __builtin_fma(p, x, kF10);
-        p = __builtin_fma(p, x, kF9);
-        p = __builtin_fma(p, x, kF8);
-        p = __builtin_fma(p, x, kF7);
-        p = __builtin_fma(p, x, kF6);
-        p = __builtin_fma(p, x, kF5);
-        p = __builtin_fma(p, x, kF4);
-        p = __builtin_fma(p, x, kF3);
-        p = __builtin_fma(p, x, kF2);
-        return __builtin_fma(x * x, p, x);
-    }
-    return exp(x) - 1.0;
-}
-
 // ---------------------------------------------------------------- log family
 
 // s^2/3 + s^4/5 + ... + s^22/23 evaluated at z = s^2 (times z).
@@ -285,20 +265,6 @@ __device__ __forceinline__ double log(double x)
     return log_pos(x);
 }
 
-__device__ __forceinline__ double log1p(double x)
-{
-    if (x != x) return x;
-    if (x == -1.0) return -__builtin_inf();
-    if (x < -1.0) return __builtin_nan("");
-    if (x >= kSqrt1_2 - 1.0 && x <= 0.41421356237309515) {
-        const double s = x / (2.0 + x);
-        const double R = atanh_tail(s * s);
-        return 2.0 * (s + s * R);
-    }
-    const double u = 1.0 + x;
-    return log(u) + (x - (u - 1.0)) / u;
-}
-
 // ---------------------------------------------------------------- trig / normals
 
 // sin y and cos y for 0 <= y <= pi/4 (Taylor).
@@ -332,32 +298,10 @@ __device__ __forceinline__ double flip_sign(double v, uint32_t bit31)
     return __longlong_as_double(__double_as_longlong(v) ^ (long long)((uint64_t)bit31 << 32));
 }
 
-// (cos 2 pi t, sin 2 pi t) for t in [0, 1).
-__device__ __forceinline__ void sincos2pi(double t, double& c, double& s)
-{
-    const double t4 = t * 4.0;
-    const double q = __builtin_floor(t4);
-    const double f = t4 - q;
-    const bool fold = f > 0.5;
-    const double g = fold ? 1.0 - f : f;
-    const double y = g * kHalfPi;
-    double sy, pc;
-    sincos_octant(y, sy, pc);
-    // quadrant 0: (cf, sf), 1: (-sf, cf), 2: (-cf, -sf), 3: (sf, -cf) with
-    // (cf, sf) = (pc, sy), exchanged by the fold; by selection, so that the
-    // lanes' quadrants do not split the wave
-    const unsigned iq = (unsigned)(int)q;
-    const bool swap = fold != ((iq & 1u) != 0);
-    const double cc = swap ? sy : pc;
-    const double ss = swap ? pc : sy;
-    c = (iq + 1u) & 2u ? -cc : cc;
-    s = iq & 2u ? -ss : ss;
-}
-
-// sincos2pi((h + 1/2) 2^-32) with the quadrant and the octant fold taken from
-// h's bits: t 4 - q is (r + 1/2) 2^-30 for the low 30 bits r, above 1/2 where
-// bit 29 is set, and 1 - f there has the complement of r; the same values, all
-// of them exact.
+// (cos 2 pi t, sin 2 pi t) for t = (h + 1/2) 2^-32.  The quadrant q and the
+// octant fold are taken from h's bits: f = 4 t - q is (r + 1/2) 2^-30 for the low
+// 30 bits r, above 1/2 where bit 29 is set, and 1 - f there has the complement
+// of r; all of these are exact.
 __device__ __forceinline__ void sincos_half(uint32_t h, double& c, double& s)
 {
     const uint32_t fold = (uint32_t)((int32_t)(h << 2) >> 31);  // all ones where bit 29 is set

@@ -862,13 +862,13 @@ int abcsmc_simulate(const abcsmc_config* cfg, int64_t n, const double* theta, co
 
 int abcsmc_debug_eval(int32_t fn, int64_t n, const void* in, void* out, double param_a, int32_t param_b)
 {
-    if (n < 1 || !in || !out || fn < 0 || fn > 14) return fail(nullptr, ABCSMC_EINVAL, "bad debug_eval arguments");
+    if (n < 1 || !in || !out || fn < 0 || fn > 19) return fail(nullptr, ABCSMC_EINVAL, "bad debug_eval arguments");
     if (fn == 13 && (!(param_a >= 0.0) || param_a > 9007199254740992.0))
         return fail(nullptr, ABCSMC_EINVAL, "seed must be an integer-valued double in [0, 2^53]");
     if (fn == 11 && (param_b < 1 || param_b > 128)) return fail(nullptr, ABCSMC_EINVAL, "beta b out of range");
     size_t in_b = 0, out_b = 0;
     switch (fn) {
-    case 7: in_b = 16 * n; out_b = 8 * n; break;
+    case 7: case 19: in_b = 16 * n; out_b = 8 * n; break;
     case 8: in_b = 24 * n; out_b = 16 * n; break;
     case 9: in_b = 8 * n; out_b = 16 * n; break;
     case 10: case 12: in_b = 24 * n; out_b = 8 * n; break;

@@ -196,6 +196,45 @@ __global__ __launch_bounds__(kBlock) void simulate_traj_kernel(TrajArgs a)
         lane::simulate_distance<kSampler, true>(a.m, th, nullptr, a.round, index, __builtin_inf(), traj, days);
 }
 
+// log1p(x) and (cos 2 pi t, sin 2 pi t) over all the arguments that the test
+// hook takes: the kernels' own functions where those are defined (x in
+// [-1/2, 0), t = (h + 1/2) 2^-32), the same formulas elsewhere.
+__device__ __forceinline__ double hook_log1p(double x)
+{
+    if (x < 0.0 && x >= -0.5) return dm::log1p_neg(-x);
+    if (x != x) return x;
+    if (x == -1.0) return -__builtin_inf();
+    if (x < -1.0) return __builtin_nan("");
+    if (x >= 0.0 && x <= 0.41421356237309515) {
+        const double s = x / (2.0 + x);
+        const double R = dm::atanh_tail(s * s);
+        return 2.0 * (s + s * R);
+    }
+    const double u = 1.0 + x;
+    return dm::log(u) + (x - (u - 1.0)) / u;
+}
+
+__device__ __forceinline__ void hook_sincos2pi(double t, double& c, double& s)
+{
+    const double h = t * 0x1p32 - 0.5;
+    if (h >= 0.0 && h < 0x1p32 && __builtin_floor(h) == h) {
+        dm::sincos_half((uint32_t)h, c, s);
+        return;
+    }
+    const double t4 = t * 4.0;
+    const double q = __builtin_floor(t4);
+    const double f = t4 - q;
+    const bool fold = f > 0.5;
+    double sy, pc;
+    dm::sincos_octant((fold ? 1.0 - f : f) * dm::kHalfPi, sy, pc);
+    const unsigned iq = (unsigned)(int)q;
+    const bool swap = fold != ((iq & 1u) != 0);
+    const double cc = swap ? sy : pc;
+    const double ss = swap ? pc : sy;
+    c = (iq + 1u) & 2u ? -cc : cc;
+    s = iq & 2u ? -ss : ss;
+}
+
 __global__ __launch_bounds__(kBlock) void debug_eval_kernel(int32_t fn, int64_t n, const void* in,
                                                             void* out, double pa, int32_t pb)
 {
@@ -205,11 +244,11 @@ __global__ __launch_bounds__(kBlock) void debug_eval_kernel(int32_t fn, int64_t 
     double* y = (double*)out;
     switch (fn) {
     case 0: y[i] = dm::exp(x[i]); break;
-    case 1: y[i] = dm::expm1(x[i]); break;
+    case 1: y[i] = dm::expm1_select(x[i]); break;
     case 2: y[i] = dm::log(x[i]); break;
-    case 3: y[i] = dm::log1p(x[i]); break;
-    case 4: { double c, s; dm::sincos2pi(x[i], c, s); y[i] = c; } break;
-    case 5: { double c, s; dm::sincos2pi(x[i], c, s); y[i] = s; } break;
+    case 3: y[i] = hook_log1p(x[i]); break;
+    case 4: { double c, s; hook_sincos2pi(x[i], c, s); y[i] = c; } break;
+    case 5: { double c, s; hook_sincos2pi(x[i], c, s); y[i] = s; } break;
     case 6: y[i] = __builtin_sqrt(x[i]); break;
     case 7: y[i] = x[2 * i] / x[2 * i + 1]; break;
     case 8: {
@@ -240,6 +279,11 @@ __global__ __launch_bounds__(kBlock) void debug_eval_kernel(int32_t fn, int64_t 
         for (int32_t mm = 0; mm < pb; ++mm) L = L + dm::log(dm::u01(w[mm])) / (pa + (double)mm);
         y[i] = dm::exp(L);
     } break;
+    case 15: y[i] = dm::exp_select(x[i]); break;
+    case 16: y[i] = dm::log1p_neg(x[i]); break;
+    case 17: y[i] = dm::odds(x[i]); break;
+    case 18: y[i] = dm::sqrt_n(x[i]); break;
+    case 19: y[i] = dm::div_n(x[2 * i], x[2 * i + 1]); break;
     default: break;
     }
 }

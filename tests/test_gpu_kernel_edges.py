@@ -372,3 +372,59 @@ def test_cached_schedules_are_for_the_kernels_they_were_tuned_on(tmp_path):
     assert all(s["propose_blocks"] != 7 for s in chosen) and chosen[0] == chosen[2]
     lines = cache.read_text().splitlines()
     assert len(lines) == 3 and len({l.split()[0] for l in lines}) == 3
+
+
+def _map(fn, x):
+    x = np.ascontiguousarray(x, dtype=np.float64)
+    n = x.size // (2 if fn == 19 else 1)
+    return A.debug_eval(fn, x, n, np.zeros(n))
+
+
+def _equal(got, want, x):
+    bad = np.flatnonzero((got.view(np.uint64) != want.view(np.uint64)) & ~(np.isnan(got) & np.isnan(want)))
+    assert bad.size == 0, (bad.size, x[bad[:5]], got[bad[:5]], want[bad[:5]])
+
+
+def _around(*points):
+    return np.array([v for p in points for v in (np.nextafter(p, -np.inf), p, np.nextafter(p, np.inf))])
+
+
+def test_day_exponentials_bitwise(oracle):
+    """exp and expm1 as the simulated day takes them (ranges by selection):
+    bit for bit the oracle's, at both cut-offs and the switch of form too."""
+    rng = np.random.default_rng(31)
+    special = np.concatenate([_around(-708.0, 709.782712893384, 0.34657359027997264, -0.34657359027997264, 0.0, -37.0),
+                              [-0.0, np.inf, -np.inf, np.nan, 1e308, -1e308, 5e-324, -1e-310, 1e9, -1e9]])
+    x = np.concatenate([special, rng.uniform(-760, 760, 200_000), rng.uniform(-2, 2, 200_000), rng.uniform(-40, 40, 100_000),
+                        -(10.0 ** rng.uniform(-320, 4, 100_000)), 10.0 ** rng.uniform(-320, 4, 100_000)])
+    _equal(_map(15, x), oracle.fmap("exp", x), x)
+    _equal(_map(1, x), oracle.fmap("expm1", x), x)
+
+
+def test_search_inputs_bitwise(oracle):
+    """log(1 - q) and q / (1 - q) for 0 < q <= 1/2 as the binomial search takes
+    them: bit for bit the oracle's log1p and IEEE division."""
+    rng = np.random.default_rng(32)
+    q = np.concatenate([10.0 ** rng.uniform(-300, -0.302, 300_000), rng.uniform(0, 0.5, 500_000) + 1e-300,
+                        _around(0.2928932188134524, 0.25, 2.0**-53, 2.0**-52, 1e-16), [0.5, np.nextafter(0.5, 0), 1e-300]])
+    q = q[q <= 0.5]
+    _equal(_map(16, q), oracle.fmap("log1p", -q), q)
+    _equal(_map(17, q), q / (1.0 - q), q)
+
+
+def test_unscaled_division_and_root_are_correctly_rounded():
+    """Division and square root without range tests, over the operands the
+    kernels give them, against IEEE: quotients of the logarithm and of the
+    binomial's probabilities, roots of -2 log u and of a binomial's variance."""
+    rng = np.random.default_rng(33)
+    f = np.concatenate([rng.uniform(0.70710678118654757, 1.4142135623730951, 1_000_000), _around(1.0, 0.7071067811865476, 1.4142135623730950)])
+    a = f - 1.0                                              # of log x
+    q = np.concatenate([rng.uniform(0, 0.5, 500_000), 10.0 ** rng.uniform(-290, -0.31, 200_000)])
+    u = 1.0 - q
+    num = np.concatenate([a, -q, -q - (u - 1.0), q])         # and of log1p(-q), q / (1 - q)
+    den = np.concatenate([2.0 + a, 2.0 - q, u, u])
+    _equal(_map(19, np.stack([num, den], 1).ravel()), num / den, num)
+    k = rng.integers(3, 2**26, 100_000).astype(np.float64)
+    x = np.concatenate([rng.uniform(0, 45, 500_000) + 2.0**-32, 2.0 ** rng.uniform(-32, 6, 300_000), 2.0 ** rng.uniform(2.3, 53, 500_000),
+                        k * k, np.nextafter(k * k, 0), np.nextafter(k * k, np.inf), _around(2.0**-32, 45.0, 5.0, 2.0**53)])
+    _equal(_map(18, x), np.sqrt(x), x)
