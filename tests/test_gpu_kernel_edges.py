@@ -428,3 +428,62 @@ def test_unscaled_division_and_root_are_correctly_rounded():
     x = np.concatenate([rng.uniform(0, 45, 500_000) + 2.0**-32, 2.0 ** rng.uniform(-32, 6, 300_000), 2.0 ** rng.uniform(2.3, 53, 500_000),
                         k * k, np.nextafter(k * k, 0), np.nextafter(k * k, np.inf), _around(2.0**-32, 45.0, 5.0, 2.0**53)])
     _equal(_map(18, x), np.sqrt(x), x)
+
+
+@pytest.mark.parametrize("sampler", [W.SAMPLER_BINOMIAL, W.SAMPLER_NORMAL_FLOOR])
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 63, 64, 65, 300])
+def test_every_quad_trajectory_at_extreme_rates(oracle, sampler, n):
+    """All n trajectories, the last partial wave and workgroup of quads
+    included, at the extreme rates that the four-lane form takes (below 2^1022)."""
+    rates = [r for r in EXTREME if max(map(abs, r)) < 2.0**1022]
+    assert len(rates) >= 6
+    w = W.tiny(sampler=sampler)
+    theta = np.array([rates[k % len(rates)] for k in range(n)])
+    got = A.simulate(w, theta, seed=3, rnd=2, index0=11)
+    for k in range(n):
+        want = oracle.simulate(w, theta[k], 3, 2, 11 + k)
+        days = int(np.argmax(np.append((want < 0).any(1), True)))   # up to the first undefined count
+        assert days >= 1
+        assert np.array_equal(got[k][:days], want[:days]), k
+
+
+@pytest.mark.parametrize("n,sampler", [(1025, W.SAMPLER_BINOMIAL), (8192, W.SAMPLER_BINOMIAL), (8193, W.SAMPLER_BINOMIAL),
+                                       (32_768, W.SAMPLER_BINOMIAL), (32_769, W.SAMPLER_NORMAL_FLOOR), (49_153, W.SAMPLER_BINOMIAL)])
+def test_predictive_bands_at_dispatch_edges(oracle, n, sampler):
+    """Bands of rows held in 8 and in 32 registers a thread and of rows read
+    from memory, and series made by four lanes and by one: the oracle's
+    trajectories and numpy's linear quantiles, equal."""
+    w = W.tiny(n_particles=n, n_days=3, n_rounds=1, sampler=sampler, seed=n)
+    obs = oracle.observations(w)
+    q = (0.0, 0.005, 0.5, 0.75, 0.999, 1.0)
+    with A.Context(w, obs) as ctx:
+        ctx.round()
+        u = ctx.population()["u"]
+        got = ctx.predict(2, seed=9, quantiles=q)
+    wp = w.with_(n_days=2)
+    lo, hi = np.asarray(w.lo), np.asarray(w.hi)
+    series = np.zeros((3, 3, n))
+    for j in range(n):
+        series[:, :, j] = oracle.simulate(wp, lo + u[j] * (hi - lo), 9, oracle.PREDICT_ROUND, j, obs0=obs[0])[:, 2:5]
+    want = np.quantile(series, q, axis=-1, method="linear").transpose(1, 2, 0)
+    assert np.array_equal(got, want)
+
+
+@pytest.mark.parametrize("n", [2**18, 300_001])
+def test_tolerance_of_crowded_distances(n):
+    """A handful of distinct distances: the rank's bin holds more values than
+    the multi-block percentile collects, which goes over all of them again."""
+    crowded = 0
+    obs = np.array([[1, 0, 0], [2, 0, 0]])
+    for ratio in (0.2, 0.5, 0.8):
+        w = W.C2.with_(n_particles=n, surv_ratio=ratio, population=3, n_days=1)
+        with A.Context(w, obs, flags=A.F_SKIP_WEIGHTS) as ctx:
+            info = ctx.round()
+            d = ctx.weights()[1]
+        assert info["eps_next"] == np.quantile(d, ratio), (ratio, np.unique(d))
+        bits = d.view(np.uint64)
+        top = int(bits.min() ^ bits.max()).bit_length() - 1
+        digit = bits >> np.uint64(max(top - 10, 0))
+        rank = int(np.floor((n - 1) * ratio))
+        crowded += int((digit == np.sort(digit)[rank]).sum()) > 65536
+    assert crowded >= 2
