@@ -284,7 +284,8 @@ typedef struct {
                                 2 largest/smallest interleaved */
     int32_t weight_cols;     /* target columns per weight-kernel workgroup, 256 to 2^20 (0 = 256); a run is
                                 split in 32 parts at most */
-    double issue_margin;     /* chunk budget N / (rate * 256) x margin before over-issue (0 = 1.1) */
+    double issue_margin;     /* work items issued before over-issue: N / (rate * proposals per item) x margin
+                                (0 = 1.1; 256 proposals per item, 64 where four lanes make each) */
 } abcsmc_schedule;
 
 int abcsmc_batch_workspace_size(const abcsmc_config* cfgs, int32_t n_runs, size_t* bytes);

@@ -289,8 +289,9 @@ bool propose_by_quads(int64_t n, int sampler, bool any_rates);
 void launch_compact(const CompactArgs& a, hipStream_t s);
 void launch_resample(const ResampleArgs& a, hipStream_t s);
 // The weight pass in three parts, so that the caller can time the sum kernel
-// alone: the window pass (coordinate pick, column and row sorts, windows),
-// the windowed sums, and the per-row merge of the chunk partial sums.
+// alone: the preparation (sort code from the columns' statistics, column and
+// row sorts, sorted operands), the windowed sums, and the per-row merge of the
+// chunk partial sums.
 void launch_weights_window(const WeightArgs& a, hipStream_t s);
 void launch_weights_sum(const WeightArgs& a, hipStream_t s);
 void launch_weights_finalize(const WeightArgs& a, hipStream_t s);

@@ -13,10 +13,11 @@ namespace {
 // Proposal kernel of one batch: lane p makes proposal j = base + p and
 // publishes the wave's acceptance ballot for the ordered compaction.
 // ---------------------------------------------------------------------------
-// Waves per SIMD the register allocation aims for.  The kernel needs 144
-// VGPRs, so three waves per SIMD are resident whether two or three are asked
-// for; asking for two gave a slightly different instruction schedule that ran
-// 1.8% faster, and asking for four (128 VGPRs) was 6% slower.
+// Waves per SIMD the register allocation aims for.  The binomial kernels take
+// 161 and 167 VGPRs, so three waves per SIMD are resident whether two or three
+// are asked for; two gave a slightly different schedule (10 stages of 131072
+// particles x 120 days 7.92 ms, three 7.97, four, with spills, 8.30; 2^20 x 60
+// without early exit 8.77, 8.76 and 8.62).
 #ifndef ABCSMC_PROPOSE_WAVES
 #define ABCSMC_PROPOSE_WAVES 2
 #endif

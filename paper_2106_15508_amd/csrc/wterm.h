@@ -12,7 +12,8 @@ namespace wterm {
 // Scalar-column form used by the weight kernels.  Columns (u_k[8] and q_k, in
 // two arrays: a 64-byte line holds one column's u) are the same for every
 // lane of a wave, so they are read through wave-uniform pointers in the
-// constant address space (scalar loads into SGPRs, no LDS staging).  The exponential uses a 1024-entry table of 2^(i/1024):
+// constant address space (scalar loads into SGPRs, no LDS staging).  The
+// exponential uses a 1024-entry table of 2^(i/1024):
 //   t = D c_j with c_j = -1024 / (2 sigma_j^2 ln 2)  (the exponent in units
 //   of ln2/1024), k = rint(t), r = (t - k) ln2/1024, |r| <= 3.4e-4,
 //   exp = 2^(k >> 10) 2^((k & 1023)/1024) (1 + r + r^2/2 + r^3/6)
@@ -23,8 +24,8 @@ namespace wterm {
 // table entry (whose own i << 10 is taken off beforehand; entries carry 2^64,
 // the sum's scale, so that exponents down to the widest window's -710 stay
 // normal).  Far columns of a wave's list may give anything and are left out
-// by the execution mask.  27 vector instructions where rint, conversion,
-// ldexp and the column's number from LDS took 31.
+// by the execution mask.  28 vector instructions (25 FP64) where rint,
+// conversion, ldexp and the column's number from LDS took 31.
 constexpr int kTabBits = 10;
 constexpr int kTab = 1 << kTabBits;
 
@@ -46,9 +47,7 @@ __device__ __forceinline__ Col load_col(const_col_ptr cu, const_col_ptr cq, uint
     return c;
 }
 
-// exp of the term (without q): with f = t - k in [-1/2, 1/2] and L = ln2/1024,
-// e^(f L) = 1 + f (L + f (L^2/2 + f L^3/6)); ex[0..2] = L, L^2/2, L^3/6
-// (kernel arguments: SGPRs).
+// |u_j - u_k|^2
 __device__ __forceinline__ double dist2(const double* uj, const Col& c)
 {
     double D = 0.0;
@@ -60,7 +59,10 @@ __device__ __forceinline__ double dist2(const double* uj, const Col& c)
     return D;
 }
 
-// times 2^64, for |D c_j| < 2^20.
+// exp of the term (without q) times 2^64: with f = t - k in [-1/2, 1/2] and
+// L = ln2/1024, e^(f L) = 1 + f (L + f (L^2/2 + f L^3/6)); ex[0..2] = L, L^2/2,
+// L^3/6 (kernel arguments: SGPRs).  For |D c_j| < 1086 * 1024, where the scaled
+// result is still a normal number (the widest window reaches 1.0499e6).
 __device__ __forceinline__ double term_exp(double D, double cj, const double* T, const double* ex, double ex1)
 {
     constexpr double kMagic = 0x1.8p52;
@@ -112,13 +114,14 @@ __device__ __forceinline__ void load_table(double* T, const double* g)
 }
 
 // Widest window of a row (the cap of window_radius): a column more than
-// kWindow sigma_j away gives an exponent below -710, where both exponentials
-// are exactly 0.
+// kWindow sigma_j away has an exponent below -710, where exp is 0 by the
+// definition used throughout (dm::exp's cut-off); the table form has no cut-off
+// of its own.
 constexpr double kWindow = 37.7;
 
 // Narrower per-row window with a bound on what it leaves out.  Every column
-// with |u_k - u_j| > W sigma_j has a term at most q_k e^{-W^2/2}, so all of them together are at most Q e^{-W^2/2}
-// (Q = sum_k q_k).  The row sum holds the parent's own term
+// with |u_k - u_j| > W sigma_j has a term at most q_k e^{-W^2/2}, so all of them
+// together are at most Q e^{-W^2/2} (Q = sum_k q_k).  The row sum holds the parent's own term
 // L_par = q_par e^{-|u_j - u_par|^2 / (2 sigma_j^2)}, so with
 //   W^2 = 2 (ln Q - ln L_par + 53 ln 2)
 // the omitted mass is at most 2^-53 of the row sum: one unit roundoff of the
