@@ -151,9 +151,7 @@ typedef struct abcsmc_ctx abcsmc_ctx;
  * at least this large, 256-byte aligned, and left to the context until
  * abcsmc_free: it holds the populations between stages and tables written
  * once at abcsmc_init).  Ask the library that is loaded: the size may differ
- * between versions.  With cfg.batch = 0 it is never above that of ABI version
- * 4's first libraries; with a small cfg.batch of one's own it can be (by up to
- * 37% between 10000 and 33000 particles, 9% above 2^18). */
+ * between versions.  It is never above that of ABI version 4's first libraries. */
 int abcsmc_workspace_size(const abcsmc_config* cfg, size_t* bytes);
 
 /* Create a context.  obs: (T+1) x 3 int64, row t = (A, R, D) on day t, row 0

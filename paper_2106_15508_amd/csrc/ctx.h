@@ -31,7 +31,7 @@ struct DevPop {
 // Byte layout of the device workspace (every region 256-byte aligned).
 struct Layout {
     size_t obs, pop[2][8], q, cdf, cols, st_u, st_d, st_sigma, st_parent, st_att, wave_mask, wave_off,
-        ctr, theta, red[5], hist, sel, sellist, sellist_cap, wpart, rowkeys, colkeys, scu, scq, scop, scbox, sru, srscale,
+        ctr, theta, red[5], hist, sel, sellist, sellist_cap, wslots, wpart, rowkeys, colkeys, scu, scq, scop, scbox, sru, srscale,
         srr2, srop, srbox, dimpart, geom, wcounts, rank[2], rwin, wtab, total;
 };
 

@@ -194,7 +194,7 @@ struct WeightArgs {
     int32_t N;
     int32_t chunks;         // column chunks (second grid dimension)
     const unsigned long long* M;  // device scalar: survivors
-    double* partial;        // chunks x N row sums per column chunk
+    double* partial;        // slots x N row sums per column chunk
     double* logw;           // N
     unsigned long long* rowkeys;  // Npad sort keys (row index in the low 32 bits)
     unsigned long long* colkeys;  // Npad sort keys (column index in the low 32 bits)
@@ -206,6 +206,9 @@ struct WeightArgs {
     WeightGeom* geom;       // device: the sort code
     size_t npad;            // padded sort length (power of two >= N)
     int32_t chunk_tiles;    // column tiles per chunk
+    int32_t slots;          // chunks that `partial` holds at once
+    int32_t first_chunk;    // of one pass over the chunks: its first one
+    int32_t first_slot;     // and that one's slot (1 after the first pass: slot 0 holds the sums so far)
     uint2* counts;          // chunks x groups: columns listed, pairs inside the rows' own windows
     unsigned long long* terms;  // device counter of evaluated terms
     unsigned long long* window_terms;  // device counter: pairs inside the rows' own windows
@@ -267,6 +270,9 @@ struct SelectArgs {
 // Column tiles per chunk (grid y) and chunks of the weight kernel for N rows.
 int weight_chunk_tiles(int64_t N);
 int weight_chunks(int64_t N);
+// Bytes the first versions' weight pass (and copied out parameters) took for N
+// rows beside the proposals' staging.
+size_t weight_first_bytes(int64_t N);
 constexpr int kDimBlocks = 64;  // blocks of the column statistics
 
 struct TrajArgs {
@@ -293,7 +299,8 @@ void launch_resample(const ResampleArgs& a, hipStream_t s);
 // row sorts, sorted operands), the windowed sums, and the per-row merge of the
 // chunk partial sums.
 void launch_weights_window(const WeightArgs& a, hipStream_t s);
-void launch_weights_sum(const WeightArgs& a, hipStream_t s);
+// (sum notes its last pass in a for finalize.)
+void launch_weights_sum(WeightArgs& a, hipStream_t s);
 void launch_weights_finalize(const WeightArgs& a, hipStream_t s);
 void launch_select(const SelectArgs& a, hipStream_t s);
 // Normalised (or uniform) weights and the next tolerance.

@@ -94,14 +94,20 @@ Layout make_layout(const abcsmc_config& c)
     L.srbox = take(rpad / kWave * 17 * sizeof(float));
     // the partial sums follow on the column keys and window radii, which the
     // gather of the sorted operands has read
-    const size_t colkeys = align_up(npad * 8);
-    L.wpart = take(std::max((size_t)weight_chunks((int64_t)N) * N * sizeof(double), colkeys + N * sizeof(double)));
-    L.colkeys = L.wpart;
-    L.rwin = L.wpart + colkeys;
+    const size_t colkeys = align_up(npad * 8), chunks = (size_t)weight_chunks((int64_t)N);
     L.rowkeys = take(npad * 8);
-    L.wcounts = take((size_t)weight_chunks((int64_t)N) * (rpad / kWave) * sizeof(uint2));
+    L.wcounts = take(chunks * (rpad / kWave) * sizeof(uint2));
     L.dimpart = take(kDimBlocks * 32 * sizeof(double));
     L.geom = take(sizeof(WeightGeom));
+    // as many of them at once as fit beside small batches of the caller's own
+    // without asking for more than the first versions did (there 16384 rows take
+    // 19 of 52, in three passes); all, or all but one past 3.6 million rows, where
+    // the library sizes the batches
+    const size_t room = staged + weight_first_bytes((int64_t)N);
+    L.wslots = std::min(chunks, std::max<size_t>(2, (room > o ? room - o : 0) / (N * sizeof(double))));
+    L.wpart = take(std::max(L.wslots * N * sizeof(double), colkeys + N * sizeof(double)));
+    L.colkeys = L.wpart;
+    L.rwin = L.wpart + colkeys;
     // used before the sorted operands are gathered, or after the weights: the
     // unsorted keys, the percentile's list, the copied out parameters
     L.rank[0] = L.scu;
@@ -540,6 +546,7 @@ int abcsmc_round(abcsmc_ctx* x, abcsmc_round_info* info)
             wa.N = N;
             wa.chunks = weight_chunks(N);
             wa.chunk_tiles = weight_chunk_tiles(N);
+            wa.slots = (int32_t)x->L.wslots;
             wa.terms = &ctr->terms;
             wa.window_terms = &ctr->window_terms;
             wa.M = &ctr->survivors;

@@ -565,9 +565,10 @@ __global__ __launch_bounds__(kGroups * kSplit * kWave) __attribute__((amdgpu_wav
     WeightArgs a)
 {
     __shared__ double T[wterm::kTab];
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) a.ctr->ts[kTsSum] = wall_clock64();
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0 && a.first_chunk == 0) a.ctr->ts[kTsSum] = wall_clock64();
     const int M = (int)*a.M;
-    const int t0 = (int)blockIdx.y * a.chunk_tiles;
+    const int chunk = a.first_chunk + (int)blockIdx.y;
+    const int t0 = chunk * a.chunk_tiles;
     const int t1 = min((M + kColTile - 1) / kColTile, t0 + a.chunk_tiles);
     if (t0 >= t1) return;  // past the columns: the finalize pass does not read this chunk
     const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x / kWave), lane = threadIdx.x & (kWave - 1);
@@ -599,10 +600,10 @@ __global__ __launch_bounds__(kGroups * kSplit * kWave) __attribute__((amdgpu_wav
         }
     }
     if (split != 0) return;
-    if (r < a.N) a.partial[(size_t)blockIdx.y * a.N + r] = total;
+    if (r < a.N) a.partial[(size_t)(a.first_slot + (int)blockIdx.y) * a.N + r] = total;
     // (counted per group and added up by the finalize pass: 130000 atomics on one
     // line took longer than the smaller stages' sums)
-    if (lane == 0) a.counts[(size_t)blockIdx.y * (a.sr.pad / kWave) + group] = c;
+    if (lane == 0) a.counts[(size_t)chunk * (a.sr.pad / kWave) + group] = c;
 }
 
 __global__ __launch_bounds__(kBlock) void wtable_kernel(double* tab)
@@ -635,12 +636,35 @@ __global__ __launch_bounds__(kBlock) void wterm_debug_kernel(int64_t n, const do
     out[i] = D <= R * R ? __builtin_fma(c.q, wterm::term_exp(D, cj, T, a.ex, a.ex[1]), 0.0) * wterm::kSumScale : 0.0;
 }
 
+// Chunks that hold columns.
+__device__ __forceinline__ int used_chunks(const WeightArgs& a)
+{
+    const int tiles = ((int)*a.M + kColTile - 1) / kColTile;
+    return min(a.chunks, (tiles + a.chunk_tiles - 1) / a.chunk_tiles);
+}
+
+// Sum of row r over the chunks before `end`, in order.
+__device__ __forceinline__ double row_total(const WeightArgs& a, int r, int end)
+{
+    const int n = a.first_slot + max(end - a.first_chunk, 0);
+    double L = 0.0;
+#pragma unroll 8
+    for (int c = 0; c < n; ++c) L += a.partial[(size_t)c * a.N + r];
+    return L;
+}
+
+// The sums so far to slot 0, for another pass (fewer slots than chunks).
+__global__ __launch_bounds__(kBlock) void weights_fold_kernel(WeightArgs a)
+{
+    const int r = blockIdx.x * kBlock + threadIdx.x;
+    if (r < a.N) a.partial[r] = row_total(a, r, min(used_chunks(a), a.first_chunk + a.slots - a.first_slot));
+}
+
 __global__ __launch_bounds__(kBlock) void weights_finalize_kernel(WeightArgs a)
 {
     const int r = blockIdx.x * kBlock + threadIdx.x;
     if (r == 0) a.ctr->ts[kTsSummed] = wall_clock64();
-    const int tiles = ((int)*a.M + kColTile - 1) / kColTile;
-    const int nch = min(a.chunks, (tiles + a.chunk_tiles - 1) / a.chunk_tiles);
+    const int nch = used_chunks(a);
     // a wave's group: its terms and window pairs
     const int group = r / kWave, lane = threadIdx.x & (kWave - 1);
     if (group * kWave < a.N) {
@@ -658,10 +682,7 @@ __global__ __launch_bounds__(kBlock) void weights_finalize_kernel(WeightArgs a)
         }
     }
     if (r >= a.N) return;
-    // the chunks that hold columns, in order
-    double L = 0.0;
-#pragma unroll 8
-    for (int c = 0; c < nch; ++c) L += a.partial[(size_t)c * a.N + r];
+    const double L = row_total(a, r, nch);
     const size_t j = (size_t)(a.rowkeys[r] & 0xFFFFFFFFull);
     a.logw[j] = 8.0 * dm::log(a.sigma[j]) - dm::log(L);
 }
@@ -1076,14 +1097,22 @@ constexpr int kWeightSplit = 4;
 // (559 ms for 565 in 4 stages of 2^20); 300000: 56.0 and 56.3.
 static bool weight_split(int64_t N) { return N >= 2048 && N < ((int64_t)1 << 18); }
 
-void launch_weights_sum(const WeightArgs& a, hipStream_t s)
+void launch_weights_sum(WeightArgs& a, hipStream_t s)
 {
-    if (weight_split(a.N))
-        hipLaunchKernelGGL((weights_kernel<1, kWeightSplit>), dim3(blocks_of(a.N, kWave), a.chunks), dim3(kWeightSplit * kWave),
-                           0, s, a);
-    else
-        hipLaunchKernelGGL((weights_kernel<kWeightRows / kWave, 1>), dim3(blocks_of(a.N, kWeightRows), a.chunks),
-                           dim3(kWeightRows), 0, s, a);
+    a.first_chunk = a.first_slot = 0;
+    for (;;) {
+        const int n = std::min(a.slots - a.first_slot, a.chunks - a.first_chunk);
+        if (weight_split(a.N))
+            hipLaunchKernelGGL((weights_kernel<1, kWeightSplit>), dim3(blocks_of(a.N, kWave), n), dim3(kWeightSplit * kWave), 0,
+                               s, a);
+        else
+            hipLaunchKernelGGL((weights_kernel<kWeightRows / kWave, 1>), dim3(blocks_of(a.N, kWeightRows), n),
+                               dim3(kWeightRows), 0, s, a);
+        if (a.first_chunk + n == a.chunks) return;
+        hipLaunchKernelGGL(weights_fold_kernel, dim3(blocks_of(a.N, kBlock)), dim3(kBlock), 0, s, a);
+        a.first_chunk += n;
+        a.first_slot = 1;
+    }
 }
 
 void launch_weights_finalize(const WeightArgs& a, hipStream_t s)
@@ -1117,6 +1146,17 @@ int weight_chunks(int64_t N)
 {
     const int64_t tiles = (N + kColTile - 1) / kColTile, t = weight_chunk_tiles(N);
     return (int)((tiles + t - 1) / t);
+}
+
+size_t weight_first_bytes(int64_t N)
+{
+    // partial sums of 1024 columns a chunk, doubled until 128 are enough, or of
+    // 2048 workgroups and 64 chunks; keys; columns, their keys, radii; parameters
+    int64_t cols = 1024;
+    while ((N + cols - 1) / cols > 128) cols *= 2;
+    const int64_t rows = (N + kBlock - 1) / kBlock;
+    const int64_t chunks = std::max<int64_t>((N + cols - 1) / cols, std::min<int64_t>(64, 2048 / rows));
+    return (size_t)N * 8 * (size_t)(chunks + 9 + 1 + 1 + kNP) + 2 * sort_padded_size((size_t)N) * 8;
 }
 
 void launch_stage_end(const NormArgs& a, const SelectArgs& q, hipStream_t s)

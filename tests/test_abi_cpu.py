@@ -156,3 +156,14 @@ def test_workspaces_of_the_first_versions_are_still_enough():
         assert A.workspace_size(W.C2.with_(n_particles=n)) <= first, n
     for sizes, first in FIRST_BATCH_SIZES.items():
         assert A.Batch.workspace_size([W.C1.with_(n_particles=n) for n in sizes]) <= first, sizes
+
+
+#: and with batches of the caller's own: (particles, batch)
+FIRST_OWN_BATCH_SIZES = {(12000, 256): 10208000, (16384, 256): 12176896, (16384, 4096): 12515584, (20011, 256): 14064384,
+                         (20011, 65536): 19821312, (24576, 4096): 17038080, (33000, 256): 25062656,
+                         (300000, 4096): 323395328, (500000, 256): 728669184}
+
+
+def test_workspaces_beside_batches_of_ones_own():
+    for (n, batch), first in FIRST_OWN_BATCH_SIZES.items():
+        assert A.workspace_size(W.C2.with_(n_particles=n), batch=batch) <= first, (n, batch)

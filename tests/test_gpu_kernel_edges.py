@@ -487,3 +487,23 @@ def test_tolerance_of_crowded_distances(n):
         rank = int(np.floor((n - 1) * ratio))
         crowded += int((digit == np.sort(digit)[rank]).sum()) > 65536
     assert crowded >= 2
+
+
+@pytest.mark.parametrize("n,batch,first", [(12_000, 256, 10205184), (16_384, 256, 12174080), (21_763, 256, 14878464),
+                                           (300_000, 16_384, 324476160)])
+def test_weight_sums_in_several_passes(n, batch, first):
+    """Beside the staging of a small batch the partial sums hold fewer chunks
+    than there are (31 of 47, 19 of 52, 11 of 38, 62 of 74): the run of
+    library-sized batches, bit for bit, in a buffer of the first versions' size."""
+    import torch
+    w = W.C2.with_(n_particles=n, n_days=2, seed=n)
+    obs = A.observations(w)
+    buf = torch.full((first + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    with A.Context(w, obs) as own, A.Context(w, obs, batch=batch, workspace=(buf.data_ptr(), first)) as ctx:
+        for i in range(3):
+            a, b = own.round(), ctx.round()
+            for k in ("eps_next", "ess", "weight_terms", "weight_window_terms"):
+                assert a[k] == b[k], (i, k)
+            assert all(np.array_equal(x, y) for x, y in zip(own.weights(), ctx.weights())), i
+    assert (buf[first:] == 0x5A).all()
