@@ -286,6 +286,9 @@ typedef struct {
                                 (0 = 1.1; 256 proposals per item, 64 where four lanes make each) */
 } abcsmc_schedule;
 
+/* With cfg.max_proposals = 0 never above that of ABI version 4's first
+ * libraries; with budgets below 2 N it can be (by up to 19%), or with runs of a
+ * few hundred particles and any budget of one's own (4%). */
 int abcsmc_batch_workspace_size(const abcsmc_config* cfgs, int32_t n_runs, size_t* bytes);
 /* obs[r]: (T_r+1) x 3 int64 of run r; copied.  1 <= n_runs <= 4096, N_r <= 2^20, sum of N_r <= 2^26. */
 int abcsmc_batch_init(const abcsmc_config* cfgs, int32_t n_runs, const int64_t* const* obs, abcsmc_batch** out);

@@ -15,6 +15,14 @@ namespace abcsmc {
 constexpr int kChunkP = kBlock;          // proposals per work item of the persistent kernel, one lane each
 constexpr int kChunkQuad = kBlock / 4;   // and with four lanes per proposal
 constexpr int kMaxWChunks = 32;  // column chunks per run in the weight kernel
+// A run's partial sums hold at least kMinWSlots chunks (they begin in the packed
+// columns, 9 doubles a row).  Where that is not all, the first pass takes as many
+// chunks as there are slots, their sums go to slot 0, and every further pass
+// takes one less.
+constexpr int kMinWSlots = 9;
+constexpr int kMaxWPasses = 1 + (kMaxWChunks - kMinWSlots + kMinWSlots - 2) / (kMinWSlots - 1);
+inline __host__ __device__ int weight_pass(int chunk, int slots) { return chunk < slots ? 0 : 1 + (chunk - slots) / (slots - 1); }
+inline __host__ __device__ int weight_slot(int chunk, int slots) { return chunk < slots ? chunk : 1 + (chunk - slots) % (slots - 1); }
 constexpr int kKeyUnit = 32;     // shortest region of a run's sort keys
 
 // slots of the sort keys of a run of N particles
@@ -37,6 +45,7 @@ struct BRun {
     int32_t max_attempts;
     int32_t early_exit;
     int32_t wchunks;           // column chunks of the weight kernel
+    int32_t wslots;            // chunks whose partial sums are held at once
     double beta_a_fixed;
     double surv_ratio;
     double* u[2];
@@ -50,7 +59,7 @@ struct BRun {
     uint64_t* q;
     uint64_t* cdf;
     double* cols;
-    double* wpart;             // wchunks x N
+    double* wpart;             // wslots x N
     uint2* wcounts;            // wchunks x groups of 64 rows (WeightArgs::counts)
     double* st_u;
     double* st_d;
@@ -98,12 +107,13 @@ struct BatchArgs {
     BGlobal* g;
     const int32_t* order;      // run visiting order of the persistent kernel
     const int2* res_tab;       // segmented resample grid: (run, local block)
-    const int4* w_tab;         // weight grid: (run, row block, chunk, -)
+    const int4* w_tab;         // weight grid: (run, row block, chunk, slot), pass by pass
     const int2* fin_tab;       // weight finalize grid: (run, row block)
     int32_t n_runs;
     int32_t chunk;             // proposals per work item: kChunkP or kChunkQuad
     int32_t max_cap_blocks;    // largest staging capacity of a run in blocks of kBlock proposals
-    int32_t n_res_blocks, n_w_blocks, n_fin_blocks;
+    int32_t n_res_blocks, n_fin_blocks;
+    int32_t w_pass[kMaxWPasses + 1];  // first entry of w_tab of each pass over the chunks (the rest: the end)
     int32_t propose_blocks;
     double ex[7];              // table-exp constants (as WeightArgs::ex)
     // sort keys: run r owns the region of sort_region(N_r) slots from koff_r on

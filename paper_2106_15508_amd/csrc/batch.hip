@@ -567,17 +567,17 @@ __global__ __launch_bounds__(kWeightRows) void bgather_kernel(BatchArgs a)
 // tiles, sorted rows.  (Five waves a SIMD as in the single run: 10% of the
 // launch against four; with 28 instructions a term for 31 a run of 48 fits with
 // 2048 to 65536 particles went from 94.6 to 90.7 ms.)
-__global__ __launch_bounds__(kWeightRows) __attribute__((amdgpu_waves_per_eu(5))) void bweights_kernel(BatchArgs a)
+__global__ __launch_bounds__(kWeightRows) __attribute__((amdgpu_waves_per_eu(5))) void bweights_kernel(BatchArgs a, int entry0)
 {
     __shared__ double T[wterm::kTab];
-    const int4 wb = a.w_tab[blockIdx.x];
+    const int4 wb = a.w_tab[entry0 + blockIdx.x];
     const BRun& R = a.runs[wb.x];
     const BState& S = a.st[wb.x];
     if (S.failed) return;  // uniform across the block
     const int M = (int)S.survivors, tiles = (M + kColTile - 1) / kColTile;
     const int t0 = (int)(((long long)tiles * wb.z) / R.wchunks), t1 = (int)(((long long)tiles * (wb.z + 1)) / R.wchunks);
     const int rr = wb.y * kWeightRows + threadIdx.x;
-    double* out = R.wpart + (size_t)wb.z * R.N;
+    double* out = R.wpart + (size_t)wb.w * R.N;
     const int w = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
     const int group = __builtin_amdgcn_readfirstlane(wb.y * (kWeightRows / kWave) + w);
     if (t0 >= t1) {
@@ -595,6 +595,24 @@ __global__ __launch_bounds__(kWeightRows) __attribute__((amdgpu_waves_per_eu(5))
     }
     if (rr < R.N) out[rr] = total;
     if (lane == 0) R.wcounts[(size_t)wb.z * (R.sr.pad / kWave) + group] = make_uint2(listed, window);
+}
+
+// Sum of row rr over the first `slots` slots, in the chunks' order.
+__device__ __forceinline__ double slot_total(const BRun& R, int rr, int slots)
+{
+    double L = 0.0;
+    for (int c = 0; c < slots; ++c) L += R.wpart[(size_t)c * R.N + rr];
+    return L;
+}
+
+// After pass `pass`, the sums of the runs that need another one to slot 0.
+__global__ __launch_bounds__(kWeightRows) void bfold_kernel(BatchArgs a, int pass)
+{
+    const int2 fb = a.fin_tab[blockIdx.x];
+    const BRun& R = a.runs[fb.x];
+    if (a.st[fb.x].failed || weight_pass(R.wchunks - 1, R.wslots) <= pass) return;
+    const int rr = fb.y * kWeightRows + threadIdx.x;
+    if (rr < R.N) R.wpart[rr] = slot_total(R, rr, R.wslots);
 }
 
 __global__ __launch_bounds__(kWeightRows) void bfinalize_kernel(BatchArgs a)
@@ -620,8 +638,7 @@ __global__ __launch_bounds__(kWeightRows) void bfinalize_kernel(BatchArgs a)
         }
     }
     if (rr >= R.N) return;
-    double L = 0.0;
-    for (int c = 0; c < R.wchunks; ++c) L += R.wpart[(size_t)c * R.N + rr];
+    const double L = slot_total(R, rr, weight_slot(R.wchunks - 1, R.wslots) + 1);
     const size_t j = (size_t)(a.rowkeys[R.koff + rr] & 0xFFFFFull);
     R.logw[S.nxt][j] = 8.0 * dm::log(R.sigma[S.nxt][j]) - dm::log(L);
 }
@@ -711,7 +728,10 @@ void batch_launch_stage(const BatchArgs& a, bool stage0, hipStream_t s)
         launch_sort_spans(a.colkeys, a.rowkeys, a.spans, s);
         const dim3 bw(kWeightRows);
         hipLaunchKernelGGL(bgather_kernel, dim3(a.n_fin_blocks, 2), bw, 0, s, a);
-        hipLaunchKernelGGL(bweights_kernel, dim3(a.n_w_blocks), bw, 0, s, a);
+        for (int p = 0; p < kMaxWPasses && a.w_pass[p + 1] > a.w_pass[p]; ++p) {
+            if (p > 0) hipLaunchKernelGGL(bfold_kernel, dim3(a.n_fin_blocks), bw, 0, s, a, p - 1);
+            hipLaunchKernelGGL(bweights_kernel, dim3(a.w_pass[p + 1] - a.w_pass[p]), bw, 0, s, a, a.w_pass[p]);
+        }
         hipLaunchKernelGGL(bfinalize_kernel, dim3(a.n_fin_blocks), bw, 0, s, a);
     }
     hipLaunchKernelGGL(bnormalise_kernel, dim3(a.n_runs), dim3(kNormThreads), 0, s, a, stage0 ? 1 : 0);

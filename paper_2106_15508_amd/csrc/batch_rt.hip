@@ -64,7 +64,7 @@ int wchunks_for(int64_t N, int weight_cols)
 
 struct RunLayout {
     size_t obs, u[2], d[2], sigma[2], logw[2], W[2], parent[2], index[2], att[2], q, cdf, cols, wpart, st_u, st_d,
-        st_sigma, st_parent, st_att, wmask, woff, red_u, red_d, scu, scq, scop, scbox, sru, srscale, srr2, srop, srbox, wcounts, end;
+        st_sigma, st_parent, st_att, wmask, woff, red_u, red_d, scu, scq, scop, scbox, sru, srscale, srr2, srop, srbox, wcounts, wslots, end;
 };
 
 RunLayout run_layout(const abcsmc_config& c, size_t o)
@@ -91,11 +91,15 @@ RunLayout run_layout(const abcsmc_config& c, size_t o)
     }
     L.q = take(N * 8);
     L.cdf = take(N * 8);
-    L.cols = take(N * 9 * 8);
     L.red_u = take(3 * nres * 8);
     L.red_d = take(nres * 8);
     // The proposals' staging is done with when a stage's weights are formed:
-    // one place for both.
+    // one place for both.  The partial sums begin in the packed columns, which
+    // the gather of the sorted ones has read, and hold as many chunks as fit
+    // beside a small staging (max_proposals) without asking for more than the
+    // first versions did (chunks of 2048 columns; sorted columns, their keys, two
+    // sort keys); all where max_proposals is left to the library.
+    L.cols = L.wpart = take(N * 9 * 8);
     const size_t shared = o;
     L.st_u = take(B * kNP * 8);
     L.st_d = take(B * 8);
@@ -105,19 +109,27 @@ RunLayout run_layout(const abcsmc_config& c, size_t o)
     L.wmask = take(B / kWave * 8);
     L.woff = take(B / kWave * 4);
     const size_t staged = o;
-    o = shared;
-    const size_t cpad = weight_col_pad(N), rpad = weight_row_pad(N);
-    L.wpart = take((size_t)wchunks_max((int64_t)N) * N * 8);
-    L.scu = take(cpad * kNP * 8);
-    L.scq = take(cpad * 8);
-    L.scop = take(3 * cpad * 16);
-    L.scbox = take(cpad / kColTile * 16 * 4);
-    L.sru = take(rpad * kNP * 8);
-    L.srscale = take(rpad * 8);
-    L.srr2 = take(rpad * 8);
-    L.srop = take(3 * rpad * 16);
-    L.srbox = take(rpad / kWave * 17 * 4);
-    L.wcounts = take((size_t)wchunks_max((int64_t)N) * (rpad / kWave) * sizeof(uint2));
+    const size_t cpad = weight_col_pad(N), rpad = weight_row_pad(N), chunks = (size_t)wchunks_max((int64_t)N);
+    auto operands = [&](size_t at) {
+        o = at;
+        L.scu = take(cpad * kNP * 8);
+        L.scq = take(cpad * 8);
+        L.scop = take(3 * cpad * 16);
+        L.scbox = take(cpad / kColTile * 16 * 4);
+        L.sru = take(rpad * kNP * 8);
+        L.srscale = take(rpad * 8);
+        L.srr2 = take(rpad * 8);
+        L.srop = take(3 * rpad * 16);
+        L.srbox = take(rpad / kWave * 17 * 4);
+        L.wcounts = take(chunks * (rpad / kWave) * sizeof(uint2));
+        return o;
+    };
+    const size_t first_chunks = std::min<size_t>(kMaxWChunks, std::max<size_t>(1, (N / 2 + 2047) / 2048));
+    const size_t first = staged + N * 8 * (first_chunks + 9 + 1 + 2);
+    const size_t beside = operands(L.wpart) + sort_region((int64_t)N) * (2 * 8 + 1) + rpad / kWeightRows * chunks * sizeof(int4);
+    L.wslots = first > beside ? (first - beside) / (N * 8) : 0;
+    L.wslots = std::min<size_t>(chunks, std::max<size_t>(kMinWSlots, L.wslots));
+    operands(std::max(shared, al(L.wpart + L.wslots * N * 8)));
     o = std::max(o, staged);
     L.end = o;
     return L;
@@ -275,8 +287,14 @@ int apply_schedule(abcsmc_batch* b)
         b->runs[r].wchunks = wchunks_for(b->cfgs[r].n_particles, s.weight_cols);
         const int rb = (int)((b->cfgs[r].n_particles + kWeightRows - 1) / kWeightRows);
         for (int y = 0; y < rb; ++y)
-            for (int c = 0; c < b->runs[r].wchunks; ++c) wt.push_back(make_int4(r, y, c, 0));
+            for (int c = 0; c < b->runs[r].wchunks; ++c)
+                wt.push_back(make_int4(r, y, c, weight_slot(c, b->runs[r].wslots)));
     }
+    auto pass_of = [&](const int4& e) { return weight_pass(e.z, b->runs[e.x].wslots); };
+    std::stable_sort(wt.begin(), wt.end(), [&](const int4& x, const int4& y) { return pass_of(x) < pass_of(y); });
+    for (int p = 0; p <= kMaxWPasses; ++p)
+        b->args.w_pass[p] = (int32_t)(std::partition_point(wt.begin(), wt.end(), [&](const int4& e) { return pass_of(e) < p; }) -
+                                      wt.begin());
     if ((int)wt.size() > b->max_w_blocks) return bfail(&b->err, ABCSMC_EINVAL, "weight table overflow");
     BCHK(b, hipMemcpyAsync(b->ws + b->off_runs, b->runs.data(), b->runs.size() * sizeof(BRun), hipMemcpyHostToDevice,
                            b->stream));
@@ -285,7 +303,6 @@ int apply_schedule(abcsmc_batch* b)
     BGlobal g{b->stage, b->R, s.issue_margin > 1.0 ? s.issue_margin : 1.0};
     BCHK(b, hipMemcpyAsync(b->ws + b->off_g, &g, sizeof g, hipMemcpyHostToDevice, b->stream));
     BCHK(b, hipStreamSynchronize(b->stream));
-    b->args.n_w_blocks = (int)wt.size();
     b->args.propose_blocks = s.propose_blocks > 0 ? s.propose_blocks : resident_blocks(b->args) * compute_units();
     b->args.g = reinterpret_cast<BGlobal*>(b->ws + b->off_g);
     return ABCSMC_OK;
@@ -521,6 +538,7 @@ int abcsmc_batch_init(const abcsmc_config* cfgs, int32_t n_runs, const int64_t* 
         R.cdf = (uint64_t*)(w + L.cdf);
         R.cols = (double*)(w + L.cols);
         R.wpart = (double*)(w + L.wpart);
+        R.wslots = (int32_t)L.wslots;
         R.wcounts = (uint2*)(w + L.wcounts);
         R.st_u = (double*)(w + L.st_u);
         R.st_d = (double*)(w + L.st_d);

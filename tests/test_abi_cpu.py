@@ -167,3 +167,13 @@ FIRST_OWN_BATCH_SIZES = {(12000, 256): 10208000, (16384, 256): 12176896, (16384,
 def test_workspaces_beside_batches_of_ones_own():
     for (n, batch), first in FIRST_OWN_BATCH_SIZES.items():
         assert A.workspace_size(W.C2.with_(n_particles=n), batch=batch) <= first, (n, batch)
+
+
+#: one batched run: (particles, max_proposals / particles)
+FIRST_ONE_RUN_SIZES = {(16384, 0): 13010432, (20011, 0): 16265984, (32768, 0): 27074304, (10000, 2): 6225664,
+                       (20011, 2): 12743936, (65536, 2): 46838784, (2**20, 2): 885574144}
+
+
+def test_workspaces_of_one_batched_run():
+    for (n, budget), first in FIRST_ONE_RUN_SIZES.items():
+        assert A.Batch.workspace_size([W.C1.with_(n_particles=n, max_proposals=budget * n)]) <= first, (n, budget)

@@ -507,3 +507,25 @@ def test_weight_sums_in_several_passes(n, batch, first):
                 assert a[k] == b[k], (i, k)
             assert all(np.array_equal(x, y) for x, y in zip(own.weights(), ctx.weights())), i
     assert (buf[first:] == 0x5A).all()
+
+
+@pytest.mark.parametrize("ns,first", [((20_011,), 12742912), ((16_384,), 10119680), ((20_011, 300, 10_000, 65_536), 66241024)])
+def test_batched_weight_sums_in_several_passes(ns, first):
+    """With a budget of 2 N proposals a run's partial sums hold 12 of 32 chunks
+    at 20011 particles (10 of 20 at 10000, 24 of 32 at 65536): every run as
+    without a budget, bit for bit, in a buffer of the first versions' size."""
+    import torch
+    ws = [W.tiny(n_particles=n, n_days=6, seed=n) for n in ns]
+    obs = [A.observations(w) for w in ws]
+    buf = torch.full((first + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    torch.cuda.synchronize()
+    tight = [w.with_(max_proposals=2 * w.n_particles) for w in ws]
+    with A.Batch(ws, obs) as own, A.Batch(tight, obs, workspace=(buf.data_ptr(), first)) as b:
+        for i in range(4):
+            for r, (x, y) in enumerate(zip(own.round(), b.round())):
+                for k in ("eps_next", "ess", "weight_terms", "weight_window_terms"):
+                    assert x[k] == y[k], (i, r, k)
+            for r in range(len(ws)):
+                p, q = own.population(r), b.population(r)
+                assert all(np.array_equal(p[k], q[k]) for k in p), (i, r)
+    assert (buf[first:] == 0x5A).all()
