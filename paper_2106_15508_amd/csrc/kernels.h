@@ -50,6 +50,7 @@ struct StageCounters {
     unsigned long long window_terms;  // sum over rows of the row's own window (terms the rows need)
     double eps_next;               // eq. 8 of the accepted distances
     double ess;                    // effective sample size
+    unsigned long long crowded;    // 1: eps_next is left to launch_select_crowded
     // the constant-rate clock when the first workgroup of a phase's first kernel
     // starts: the phases' times without an event record (a few us of idle GPU
     // each) between the kernels
@@ -114,7 +115,9 @@ struct CompactArgs {
 
 // Per-block partial results of the multi-block reductions and scans.
 constexpr int kRedMax = 4096;  // max blocks of a reduction (N <= 2^22 at 1024 per block)
-constexpr int kSelectList = 1 << 16;
+// Values of one bin that the percentile's last workgroup finishes (a bin of 2^22
+// distances of many days holds about that many at most); more are crowded.
+constexpr int kSelectList = 1 << 14;
 struct Scratch {
     unsigned long long* u0;  // kRedMax
     unsigned long long* u1;  // kRedMax
@@ -122,7 +125,8 @@ struct Scratch {
     double* d0;              // kRedMax
     double* d1;              // kRedMax
     unsigned int* hist;      // 2048 bins of the multi-block select
-    unsigned long long* sel; // its state: values collected, values below the bin, values in the bin
+    unsigned long long* sel; // its state: values collected, values below the bin, values in the bin;
+                             // crowded: prefix, its undecided low bits, rank in it, values of it
     double* list;            // collected values
     uint32_t list_cap;       // as many as it holds, kSelectList at most
 };
@@ -264,7 +268,7 @@ struct SelectArgs {
     double alpha;
     Scratch sc;
     double* out;            // device scalar: type-7 quantile
-    StageCounters* ctr;     // where its start is noted, or null
+    StageCounters* ctr;     // where its start and whether the values are crowded is noted, or null
 };
 
 // Column tiles per chunk (grid y) and chunks of the weight kernel for N rows.
@@ -303,6 +307,8 @@ void launch_weights_window(const WeightArgs& a, hipStream_t s);
 void launch_weights_sum(WeightArgs& a, hipStream_t s);
 void launch_weights_finalize(const WeightArgs& a, hipStream_t s);
 void launch_select(const SelectArgs& a, hipStream_t s);
+// The quantile where launch_select noted crowded values.
+void launch_select_crowded(const SelectArgs& a, hipStream_t s);
 // Normalised (or uniform) weights and the next tolerance.
 void launch_stage_end(const NormArgs& n, const SelectArgs& q, hipStream_t s);
 // The stage's counters to pinned host memory.

@@ -589,6 +589,11 @@ int abcsmc_round(abcsmc_ctx* x, abcsmc_round_info* info)
         HIPCHK(x, hipGetLastError());
         StageCounters h{};
         if (const int rc = read_counters(x, h)) return rc;
+        if (h.crowded) {
+            launch_select_crowded(sa, s);
+            HIPCHK(x, hipGetLastError());
+            if (const int rc = read_counters(x, h)) return rc;
+        }
         if (screened) h.accepted = hc.accepted;  // counted by the screen's own batches
         hc = h;
         if (pending) {

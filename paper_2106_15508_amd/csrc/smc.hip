@@ -945,7 +945,7 @@ __global__ __launch_bounds__(kBlock) void select_hist_kernel(SelectArgs a)
 }
 
 // Bin of the rank (every block finds it), its values collected into the list
-// (at most list_cap of them are kept), the block's smallest value above.
+// (unless they are more than it holds), the block's smallest value above.
 __global__ __launch_bounds__(kBlock) void select_collect_kernel(SelectArgs a)
 {
     __shared__ unsigned long long shu[kBlock];
@@ -974,15 +974,13 @@ __global__ __launch_bounds__(kBlock) void select_collect_kernel(SelectArgs a)
     __syncthreads();
     const unsigned long long want = g.base + s_bin;
     unsigned long long above = ~0ull;
+    if (s_count <= a.sc.list_cap) {
 #pragma unroll 4
-    for (int k = blockIdx.x * kBlock + threadIdx.x; k < a.N; k += gridDim.x * kBlock) {
-        const double x = a.x[k];
-        const unsigned long long b = bsel::bits_of(x), d = b >> g.sh;
-        if (d == want) {
-            const unsigned long long at = atomicAdd(&a.sc.sel[0], 1ull);
-            if (at < a.sc.list_cap) a.sc.list[at] = x;
-        } else if (d > want && b < above) {
-            above = b;
+        for (int k = blockIdx.x * kBlock + threadIdx.x; k < a.N; k += gridDim.x * kBlock) {
+            const double x = a.x[k];
+            const unsigned long long b = bsel::bits_of(x), d = b >> g.sh;
+            if (d == want) a.sc.list[atomicAdd(&a.sc.sel[0], 1ull)] = x;
+            else if (d > want && b < above) above = b;
         }
     }
     above = bsel::wave_min64(above);
@@ -994,6 +992,9 @@ __global__ __launch_bounds__(kBlock) void select_collect_kernel(SelectArgs a)
         if (blockIdx.x == 0) {
             a.sc.sel[1] = s_below;
             a.sc.sel[2] = s_count;
+            a.sc.sel[3] = want << g.sh;
+            a.sc.sel[4] = (unsigned long long)g.sh;
+            a.sc.sel[5] = (unsigned)r0 - s_below;
         }
     }
 }
@@ -1005,7 +1006,13 @@ __global__ __launch_bounds__(bsel::kThreads) void select_finish_kernel(SelectArg
     bsel::ranks7(a.N, a.alpha, r0, r1);
     const unsigned int count = (unsigned int)a.sc.sel[2], rank = (unsigned int)r0 - (unsigned int)a.sc.sel[1];
     unsigned long long xa, xb;
-    if (count > a.sc.list_cap) {  // values crowded into one of 2048 bins: all of them again
+    const bool crowded = count > a.sc.list_cap;  // into one of 2048 bins
+    if (a.ctr && threadIdx.x == 0) a.ctr->crowded = crowded ? 1ull : 0ull;
+    if (crowded && a.ctr) {  // the caller sees it with the results: launch_select_crowded
+        for (int b = threadIdx.x; b < kBins; b += bsel::kThreads) a.sc.hist[b] = 0u;
+        return;
+    }
+    if (crowded) {  // all of them again
         bsel::order_pair(bsel::FromMemory{a.x, a.N}, a.N, (unsigned int)r0, sh);
         xa = sh.xa;
         xb = sh.xb;
@@ -1019,6 +1026,105 @@ __global__ __launch_bounds__(bsel::kThreads) void select_finish_kernel(SelectArg
         }
     }
     if (threadIdx.x == 0) *a.out = bsel::interpolate7(a.N, a.alpha, xa, xb);
+}
+
+// Crowded values (few distinct ones, or a range stretched by outliers): digits
+// of 11 bits from the rank's bin down, by all of the chip, until the prefix is
+// the value.  The first launches of select have the 11 bits above; at most five
+// digits are left.  Few distinct values: 0.06 ms at 40000, 0.11 at 2^20 and 0.19 at
+// 2^22, where one workgroup over all of them took 0.19, 5.4 and 21.6; a third stage
+// of 2^22 particles x 20 days 0.18 for 5.2.
+constexpr int kCrowdDigits = 5;
+
+__global__ __launch_bounds__(kBlock) void crowd_hist_kernel(SelectArgs a)
+{
+    __shared__ unsigned int h[kBins];
+    const int left = (int)a.sc.sel[4];
+    if (left == 0) return;
+    const int sh = left > 11 ? left - 11 : 0;
+    const unsigned long long prefix = a.sc.sel[3] >> left, digits = (1ull << (left - sh)) - 1ull;
+    for (int b = threadIdx.x; b < kBins; b += kBlock) h[b] = 0u;
+    __syncthreads();
+    const int lane = threadIdx.x & (kWave - 1);
+    for (int k0 = blockIdx.x * kBlock; k0 < a.N; k0 += gridDim.x * kBlock) {
+        const int k = k0 + (int)threadIdx.x;
+        const unsigned long long b = k < a.N ? bsel::bits_of(a.x[k]) : 0ull;
+        bool mine = k < a.N && b >> left == prefix;
+        const unsigned int d = (unsigned int)((b >> sh) & digits);
+        // a few rounds of one addition for all lanes of a digit (the same LDS word
+        // takes one lane after the other)
+        for (int i = 0; i < 4; ++i) {
+            const unsigned long long todo = __ballot(mine);
+            if (!todo) break;
+            const unsigned int one = __shfl(d, __builtin_ctzll(todo), kWave);
+            const unsigned long long same = __ballot(mine && d == one);
+            if (lane == __builtin_ctzll(todo)) atomicAdd(&h[one], (unsigned int)__popcll(same));
+            if (d == one) mine = false;
+        }
+        if (mine) atomicAdd(&h[d], 1u);
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < kBins; b += kBlock)
+        if (h[b]) atomicAdd(&a.sc.hist[b], h[b]);
+}
+
+// The rank's digit; the histogram is cleared for the next one.
+__global__ __launch_bounds__(kBlock) void crowd_pick_kernel(SelectArgs a)
+{
+    __shared__ unsigned long long shu[kBlock];
+    const int left = (int)a.sc.sel[4];
+    const unsigned long long rank = a.sc.sel[5], prefix = a.sc.sel[3];
+    if (left == 0) return;
+    const int sh = left > 11 ? left - 11 : 0;
+    constexpr int per = kBins / kBlock;
+    unsigned int h[per];
+    unsigned long long s = 0, tot;
+#pragma unroll
+    for (int i = 0; i < per; ++i) {
+        h[i] = a.sc.hist[threadIdx.x * per + i];
+        a.sc.hist[threadIdx.x * per + i] = 0u;
+        s += h[i];
+    }
+    unsigned long long run = block_excl_scan_u64(s, shu, &tot);  // (all threads have read the state)
+#pragma unroll
+    for (int i = 0; i < per; ++i) {
+        if (run <= rank && rank < run + h[i]) {
+            a.sc.sel[2] = h[i];
+            a.sc.sel[3] = prefix | (unsigned long long)(threadIdx.x * per + i) << sh;
+            a.sc.sel[4] = (unsigned long long)sh;
+            a.sc.sel[5] = rank - run;
+        }
+        run += h[i];
+    }
+}
+
+// Per-block smallest value above the one found.
+__global__ __launch_bounds__(kBlock) void crowd_above_kernel(SelectArgs a)
+{
+    __shared__ unsigned long long sh[kBlock / kWave];
+    const unsigned long long xa = a.sc.sel[3];
+    unsigned long long above = ~0ull;
+#pragma unroll 4
+    for (int k = blockIdx.x * kBlock + threadIdx.x; k < a.N; k += gridDim.x * kBlock) {
+        const unsigned long long b = bsel::bits_of(a.x[k]);
+        if (b > xa && b < above) above = b;
+    }
+    above = bsel::wave_min64(above);
+    if ((threadIdx.x & (kWave - 1)) == 0) sh[threadIdx.x / kWave] = above;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kBlock / kWave; ++w) above = sh[w] < above ? sh[w] : above;
+        a.sc.u2[blockIdx.x] = above;
+    }
+}
+
+__global__ __launch_bounds__(kWave) void crowd_finish_kernel(SelectArgs a, int G)
+{
+    const unsigned long long count = a.sc.sel[2], xa = a.sc.sel[3], rank = a.sc.sel[5];
+    unsigned long long above = ~0ull;
+    for (int b = threadIdx.x; b < G; b += kWave) above = a.sc.u2[b] < above ? a.sc.u2[b] : above;
+    above = bsel::wave_min64(above);
+    if (threadIdx.x == 0) *a.out = bsel::interpolate7(a.N, a.alpha, xa, rank + 1 < count ? xa : above);
 }
 
 // theta_d = lo_d + u_d (hi_d - lo_d) for the copy-out of a population.
@@ -1182,17 +1288,30 @@ void launch_publish(StageCounters* ctr, StageCounters* host, hipStream_t s)
     hipLaunchKernelGGL(publish_kernel, dim3(1), dim3(kWave), 0, s, ctr, host);
 }
 
+static unsigned select_blocks(int64_t N) { return std::min(blocks_of(N, 4 * kBlock), 512u); }
+
 void launch_select(const SelectArgs& a, hipStream_t s)
 {
     if (a.N <= kSelectOne) {
         hipLaunchKernelGGL(select_one_kernel, dim3(1), dim3(bsel::kThreads), 0, s, a);
         return;
     }
-    const unsigned G = std::min(blocks_of(a.N, 4 * kBlock), 512u);
+    const unsigned G = select_blocks(a.N);
     hipLaunchKernelGGL(select_range_kernel, dim3(G), dim3(kBlock), 0, s, a);
     hipLaunchKernelGGL(select_hist_kernel, dim3(G), dim3(kBlock), 0, s, a);
     hipLaunchKernelGGL(select_collect_kernel, dim3(G), dim3(kBlock), 0, s, a);
     hipLaunchKernelGGL(select_finish_kernel, dim3(1), dim3(bsel::kThreads), 0, s, a, (int)G);
+}
+
+void launch_select_crowded(const SelectArgs& a, hipStream_t s)
+{
+    const unsigned G = select_blocks(a.N);
+    for (int i = 0; i < kCrowdDigits; ++i) {
+        hipLaunchKernelGGL(crowd_hist_kernel, dim3(G), dim3(kBlock), 0, s, a);
+        hipLaunchKernelGGL(crowd_pick_kernel, dim3(1), dim3(kBlock), 0, s, a);
+    }
+    hipLaunchKernelGGL(crowd_above_kernel, dim3(G), dim3(kBlock), 0, s, a);
+    hipLaunchKernelGGL(crowd_finish_kernel, dim3(1), dim3(kWave), 0, s, a, (int)G);
 }
 
 }  // namespace abcsmc

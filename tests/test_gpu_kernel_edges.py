@@ -529,3 +529,22 @@ def test_batched_weight_sums_in_several_passes(ns, first):
                 p, q = own.population(r), b.population(r)
                 assert all(np.array_equal(p[k], q[k]) for k in p), (i, r)
     assert (buf[first:] == 0x5A).all()
+
+
+@pytest.mark.parametrize("population,n_days,n", [(3, 1, 2**18), (3, 1, 2**22), (200, 5, 2**18 + 3), (200, 5, 2**20), (2, 1, 2**20)])
+def test_tolerance_of_crowded_distances_takes_the_whole_chip(population, n_days, n):
+    """Crowded distances (a few values, or hundreds with 0 among them, so that a
+    bin is an octave): numpy's quantile at ranks on, below and above ties, and
+    the percentile no slower than 1 ms (one workgroup over all values: up to 22 ms)."""
+    obs = np.zeros((n_days + 1, 3), np.int64)
+    obs[0, 0] = 1
+    for ratio in (1e-6, 0.3, 0.5, 0.999999):
+        w = W.C2.with_(n_particles=n, surv_ratio=ratio, population=population, n_days=n_days)
+        with A.Context(w, obs, flags=A.F_SKIP_WEIGHTS) as ctx:
+            for _ in range(2):
+                info = ctx.round()
+                d = ctx.weights()[1]
+                assert info["eps_next"] == np.quantile(d, ratio), (ratio, np.unique(d)[:9])
+                assert info["ms_select"] <= 1.0
+                if info["eps_next"] == 0.0:
+                    break
