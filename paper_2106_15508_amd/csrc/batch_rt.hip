@@ -282,19 +282,19 @@ int apply_schedule(abcsmc_batch* b)
     std::vector<int32_t> order = run_order(b, s.run_order);
     std::vector<int4> wt;
     wt.reserve((size_t)b->max_w_blocks);
-    for (int i = 0; i < b->R; ++i) {
-        const int r = order[i];
-        b->runs[r].wchunks = wchunks_for(b->cfgs[r].n_particles, s.weight_cols);
-        const int rb = (int)((b->cfgs[r].n_particles + kWeightRows - 1) / kWeightRows);
-        for (int y = 0; y < rb; ++y)
-            for (int c = 0; c < b->runs[r].wchunks; ++c)
-                wt.push_back(make_int4(r, y, c, weight_slot(c, b->runs[r].wslots)));
+    for (int p = 0; p < kMaxWPasses; ++p) {
+        b->args.w_pass[p] = (int32_t)wt.size();
+        for (const int32_t r : order) {
+            BRun& R = b->runs[r];
+            R.wchunks = wchunks_for(R.N, s.weight_cols);
+            const int first = p == 0 ? 0 : R.wslots + (p - 1) * (R.wslots - 1);
+            const int end = std::min(R.wchunks, R.wslots + p * (R.wslots - 1));
+            const int rb = (R.N + kWeightRows - 1) / kWeightRows;
+            for (int y = 0; first < end && y < rb; ++y)
+                for (int c = first; c < end; ++c) wt.push_back(make_int4(r, y, c, weight_slot(c, R.wslots)));
+        }
     }
-    auto pass_of = [&](const int4& e) { return weight_pass(e.z, b->runs[e.x].wslots); };
-    std::stable_sort(wt.begin(), wt.end(), [&](const int4& x, const int4& y) { return pass_of(x) < pass_of(y); });
-    for (int p = 0; p <= kMaxWPasses; ++p)
-        b->args.w_pass[p] = (int32_t)(std::partition_point(wt.begin(), wt.end(), [&](const int4& e) { return pass_of(e) < p; }) -
-                                      wt.begin());
+    b->args.w_pass[kMaxWPasses] = (int32_t)wt.size();
     if ((int)wt.size() > b->max_w_blocks) return bfail(&b->err, ABCSMC_EINVAL, "weight table overflow");
     BCHK(b, hipMemcpyAsync(b->ws + b->off_runs, b->runs.data(), b->runs.size() * sizeof(BRun), hipMemcpyHostToDevice,
                            b->stream));

@@ -115,8 +115,8 @@ struct CompactArgs {
 
 // Per-block partial results of the multi-block reductions and scans.
 constexpr int kRedMax = 4096;  // max blocks of a reduction (N <= 2^22 at 1024 per block)
-// Values of one bin that the percentile's last workgroup finishes (a bin of 2^22
-// distances of many days holds about that many at most); more are crowded.
+// Values of one bin that the percentile's last workgroup finishes (as many
+// crowded ones 90 us); more are left to the whole chip.
 constexpr int kSelectList = 1 << 14;
 struct Scratch {
     unsigned long long* u0;  // kRedMax
