@@ -126,7 +126,7 @@ struct Scratch {
     double* d1;              // kRedMax
     unsigned int* hist;      // 2048 bins of the multi-block select
     unsigned long long* sel; // its state: values collected, values below the bin, values in the bin;
-                             // crowded: prefix, its undecided low bits, rank in it, values of it
+                             // prefix of the bin, its undecided low bits, rank in it; whether crowded
     double* list;            // collected values
     uint32_t list_cap;       // as many as it holds, kSelectList at most
 };
@@ -307,7 +307,8 @@ void launch_weights_window(const WeightArgs& a, hipStream_t s);
 void launch_weights_sum(WeightArgs& a, hipStream_t s);
 void launch_weights_finalize(const WeightArgs& a, hipStream_t s);
 void launch_select(const SelectArgs& a, hipStream_t s);
-// The quantile where launch_select noted crowded values.
+// The quantile where launch_select noted crowded values (without a.ctr it has
+// done so itself).
 void launch_select_crowded(const SelectArgs& a, hipStream_t s);
 // Normalised (or uniform) weights and the next tolerance.
 void launch_stage_end(const NormArgs& n, const SelectArgs& q, hipStream_t s);

@@ -816,7 +816,8 @@ __device__ __forceinline__ void normalise_one(const NormArgs& a, double* sh)
 // compute unit's L2 rate, 25 us at 20011 values).  More take four launches of the same
 // method: the range of the values, a histogram of the 11 bits from the highest
 // one they differ in, the values of the rank's bin collected beside the
-// smallest value above it, and one workgroup that finishes among those.
+// smallest value above it, and one workgroup that finishes among those (more than
+// its list holds: crowd_hist_kernel).
 // 38-50 us at 2^17 and 54-78 at 2^18 (one workgroup: 88 and 165), where six
 // fixed digits in thirteen launches took 76 at 2^17.
 // ---------------------------------------------------------------------------
@@ -1007,23 +1008,20 @@ __global__ __launch_bounds__(bsel::kThreads) void select_finish_kernel(SelectArg
     const unsigned int count = (unsigned int)a.sc.sel[2], rank = (unsigned int)r0 - (unsigned int)a.sc.sel[1];
     unsigned long long xa, xb;
     const bool crowded = count > a.sc.list_cap;  // into one of 2048 bins
-    if (a.ctr && threadIdx.x == 0) a.ctr->crowded = crowded ? 1ull : 0ull;
-    if (crowded && a.ctr) {  // the caller sees it with the results: launch_select_crowded
+    if (threadIdx.x == 0) {
+        a.sc.sel[6] = crowded ? 1ull : 0ull;
+        if (a.ctr) a.ctr->crowded = a.sc.sel[6];
+    }
+    if (crowded) {  // launch_select_crowded
         for (int b = threadIdx.x; b < kBins; b += bsel::kThreads) a.sc.hist[b] = 0u;
         return;
     }
-    if (crowded) {  // all of them again
-        bsel::order_pair(bsel::FromMemory{a.x, a.N}, a.N, (unsigned int)r0, sh);
-        xa = sh.xa;
-        xb = sh.xb;
-    } else {
-        bsel::order_pair(bsel::FromMemory{a.sc.list, (int)count}, (int)count, rank, sh);
-        xa = sh.xa;
-        xb = sh.xb;
-        if (rank + 1 >= count) {
-            xb = ~0ull;
-            for (int b = 0; b < G; ++b) xb = a.sc.u2[b] < xb ? a.sc.u2[b] : xb;
-        }
+    bsel::order_pair(bsel::FromMemory{a.sc.list, (int)count}, (int)count, rank, sh);
+    xa = sh.xa;
+    xb = sh.xb;
+    if (rank + 1 >= count) {
+        xb = ~0ull;
+        for (int b = 0; b < G; ++b) xb = a.sc.u2[b] < xb ? a.sc.u2[b] : xb;
     }
     if (threadIdx.x == 0) *a.out = bsel::interpolate7(a.N, a.alpha, xa, xb);
 }
@@ -1033,14 +1031,15 @@ __global__ __launch_bounds__(bsel::kThreads) void select_finish_kernel(SelectArg
 // the value.  The first launches of select have the 11 bits above; at most five
 // digits are left.  Few distinct values: 0.06 ms at 40000, 0.11 at 2^20 and 0.19 at
 // 2^22, where one workgroup over all of them took 0.19, 5.4 and 21.6; a third stage
-// of 2^22 particles x 20 days 0.18 for 5.2.
+// of 2^22 particles x 20 days 0.18 for 5.2.  Where values are not crowded these
+// launches do nothing.
 constexpr int kCrowdDigits = 5;
 
 __global__ __launch_bounds__(kBlock) void crowd_hist_kernel(SelectArgs a)
 {
     __shared__ unsigned int h[kBins];
     const int left = (int)a.sc.sel[4];
-    if (left == 0) return;
+    if (!a.sc.sel[6] || left == 0) return;
     const int sh = left > 11 ? left - 11 : 0;
     const unsigned long long prefix = a.sc.sel[3] >> left, digits = (1ull << (left - sh)) - 1ull;
     for (int b = threadIdx.x; b < kBins; b += kBlock) h[b] = 0u;
@@ -1074,7 +1073,7 @@ __global__ __launch_bounds__(kBlock) void crowd_pick_kernel(SelectArgs a)
     __shared__ unsigned long long shu[kBlock];
     const int left = (int)a.sc.sel[4];
     const unsigned long long rank = a.sc.sel[5], prefix = a.sc.sel[3];
-    if (left == 0) return;
+    if (!a.sc.sel[6] || left == 0) return;
     const int sh = left > 11 ? left - 11 : 0;
     constexpr int per = kBins / kBlock;
     unsigned int h[per];
@@ -1102,6 +1101,7 @@ __global__ __launch_bounds__(kBlock) void crowd_pick_kernel(SelectArgs a)
 __global__ __launch_bounds__(kBlock) void crowd_above_kernel(SelectArgs a)
 {
     __shared__ unsigned long long sh[kBlock / kWave];
+    if (!a.sc.sel[6]) return;
     const unsigned long long xa = a.sc.sel[3];
     unsigned long long above = ~0ull;
 #pragma unroll 4
@@ -1120,6 +1120,7 @@ __global__ __launch_bounds__(kBlock) void crowd_above_kernel(SelectArgs a)
 
 __global__ __launch_bounds__(kWave) void crowd_finish_kernel(SelectArgs a, int G)
 {
+    if (!a.sc.sel[6]) return;
     const unsigned long long count = a.sc.sel[2], xa = a.sc.sel[3], rank = a.sc.sel[5];
     unsigned long long above = ~0ull;
     for (int b = threadIdx.x; b < G; b += kWave) above = a.sc.u2[b] < above ? a.sc.u2[b] : above;
@@ -1301,6 +1302,7 @@ void launch_select(const SelectArgs& a, hipStream_t s)
     hipLaunchKernelGGL(select_hist_kernel, dim3(G), dim3(kBlock), 0, s, a);
     hipLaunchKernelGGL(select_collect_kernel, dim3(G), dim3(kBlock), 0, s, a);
     hipLaunchKernelGGL(select_finish_kernel, dim3(1), dim3(bsel::kThreads), 0, s, a, (int)G);
+    if (!a.ctr) launch_select_crowded(a, s);  // nobody reads whether they are
 }
 
 void launch_select_crowded(const SelectArgs& a, hipStream_t s)
